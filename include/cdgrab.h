@@ -85,7 +85,7 @@ typedef struct cdgrab_plan {
     int64_t pairs;           /* m*n/2 flattened pair differences                      */
     int64_t blocks;          /* ceil(pairs / block_pairs)                             */
     int32_t block_pairs;     /* Bb                                                    */
-    int32_t vector_width;    /* fp32 elements per global load: 4, 2 or 1              */
+    int32_t vector_width;    /* fp32 elements every row start is aligned to: 4, 2 or 1  */
     int32_t tile_elems;      /* elements of d per LDS tile of the dot/Gram pass        */
     int32_t fused_apply;     /* 1: apply fused into the next block's dot/Gram launch (0 when
                                 gram_ahead is 1: that form applies inside its own launch)  */

@@ -106,6 +106,9 @@ int pick_vector_width(int64_t d, int64_t base_align) {
     return 1;
 }
 
+// How the kernels read the rows (kAligned / kAnyRow / kTiny), from the alignment the plan reports.
+int row_form(int vector_width, int64_t d) { return vector_width == 4 ? kAligned : d >= 4 ? kAnyRow : kTiny; }
+
 // 32 pairs per block keep the double-precision Gram tiles under the HBM time for
 // long rows; short rows are bound by launches, not bytes, and take 64.
 int pick_block_pairs(int64_t pairs, int64_t d, int32_t requested) {
@@ -339,9 +342,9 @@ int run_block_ahead(cdgrab_handle *h, const RowMap &rm, const PrevBlock &prev, c
     };
     auto by_width = [&](auto dense_tag, auto random_tag) {
         constexpr bool DENSE = decltype(dense_tag)::value, RANDOM = decltype(random_tag)::value;
-        switch (plan.vector_width) {
-            case 4: launch(resolve_dots_apply_split<BB, 4, DENSE, RANDOM>); break;
-            case 2: launch(resolve_dots_apply_split<BB, 2, DENSE, RANDOM>); break;
+        switch (row_form(plan.vector_width, rm.d)) {
+            case kAligned: launch(resolve_dots_apply_split<BB, 4, DENSE, RANDOM>); break;
+            case kAnyRow: launch(resolve_dots_apply_split<BB, 2, DENSE, RANDOM>); break;
             default: launch(resolve_dots_apply_split<BB, 1, DENSE, RANDOM>); break;
         }
     };
@@ -385,15 +388,15 @@ int run_grams_ahead(cdgrab_handle *h, int64_t d, const cdgrab_plan &plan, int64_
         hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, h->maps, h->r_sum, h->partials, ntiles, count);
     };
     if (plan.tile_elems == 128) {
-        switch (plan.vector_width) {
-            case 4: launch(gram_batched<BB, 4, 128>); break;
-            case 2: launch(gram_batched<BB, 2, 128>); break;
+        switch (row_form(plan.vector_width, d)) {
+            case kAligned: launch(gram_batched<BB, 4, 128>); break;
+            case kAnyRow: launch(gram_batched<BB, 2, 128>); break;
             default: launch(gram_batched<BB, 1, 128>); break;
         }
     } else {
-        switch (plan.vector_width) {
-            case 4: launch(gram_batched<BB, 4, 64>); break;
-            case 2: launch(gram_batched<BB, 2, 64>); break;
+        switch (row_form(plan.vector_width, d)) {
+            case kAligned: launch(gram_batched<BB, 4, 64>); break;
+            case kAnyRow: launch(gram_batched<BB, 2, 64>); break;
             default: launch(gram_batched<BB, 1, 64>); break;
         }
     }
@@ -412,9 +415,9 @@ int run_block_vw(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, bool
                  const cdgrab_plan &plan, int8_t *signs_out, double *dots_out) {
     const int part = PartLayout<BB>::PART;
     MARK(h, 2, kPass1);
-    switch (plan.vector_width) {
-        case 4: launch_pass1<BB, 4>(h, rm, prev, plan); break;
-        case 2: launch_pass1<BB, 2>(h, rm, prev, plan); break;
+    switch (row_form(plan.vector_width, rm.d)) {
+        case kAligned: launch_pass1<BB, 4>(h, rm, prev, plan); break;
+        case kAnyRow: launch_pass1<BB, 2>(h, rm, prev, plan); break;
         default: launch_pass1<BB, 1>(h, rm, prev, plan); break;
     }
     MARK(h, 2, kReduce);
@@ -425,9 +428,9 @@ int run_block_vw(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, bool
     launch_resolve<BB>(h, rm, signs_out, dots_out);
     if (apply_now) {
         MARK(h, 2, kPass2);
-        switch (plan.vector_width) {
-            case 4: launch_pass2<BB, 4>(h, rm, plan.pass2_groups); break;
-            case 2: launch_pass2<BB, 2>(h, rm, plan.pass2_groups); break;
+        switch (row_form(plan.vector_width, rm.d)) {
+            case kAligned: launch_pass2<BB, 4>(h, rm, plan.pass2_groups); break;
+            case kAnyRow: launch_pass2<BB, 2>(h, rm, plan.pass2_groups); break;
             default: launch_pass2<BB, 1>(h, rm, plan.pass2_groups); break;
         }
     }
@@ -438,9 +441,9 @@ int run_block_vw(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, bool
 template <int BB>
 int apply_block_vw(cdgrab_handle *h, const RowMap &rm, const cdgrab_plan &plan) {
     MARK(h, 2, kPass2);
-    switch (plan.vector_width) {
-        case 4: launch_pass2<BB, 4>(h, rm, plan.pass2_groups); break;
-        case 2: launch_pass2<BB, 2>(h, rm, plan.pass2_groups); break;
+    switch (row_form(plan.vector_width, rm.d)) {
+        case kAligned: launch_pass2<BB, 4>(h, rm, plan.pass2_groups); break;
+        case kAnyRow: launch_pass2<BB, 2>(h, rm, plan.pass2_groups); break;
         default: launch_pass2<BB, 1>(h, rm, plan.pass2_groups); break;
     }
     HIP_TRY(h, hipGetLastError());
@@ -1191,9 +1194,7 @@ int cdgrab_herding_bound(cdgrab_handle *h, int64_t m, int64_t n, int64_t d, cons
     const size_t ids_bytes = (size_t)(sh.seg_len * m) * sizeof(int32_t);
     const int lds_ids = (perm && sh.spw == 1 && ids_bytes <= 48 * 1024) ? 1 : 0;
     const size_t lds = lds_ids ? ids_bytes : 0;
-    // widest load every row start allows
-    const uintptr_t zb = reinterpret_cast<uintptr_t>(z);
-    const int vw = (d % 4 == 0 && zb % 16 == 0) ? 4 : (d % 2 == 0 && zb % 8 == 0) ? 2 : 1;
+    const int form = row_form((d % 4 == 0 && reinterpret_cast<uintptr_t>(z) % 16 == 0) ? 4 : 1, d);
     hipLaunchKernelGGL(herding_clear, dim3(1), dim3(1), 0, h->stream, bits);
     auto launch = [&](auto vw_tag) {
         constexpr int VW = decltype(vw_tag)::value;
@@ -1209,9 +1210,9 @@ int cdgrab_herding_bound(cdgrab_handle *h, int64_t m, int64_t n, int64_t d, cons
         hipLaunchKernelGGL((herding_prefix_max<VW>), grid, dim3(256), lds, h->stream, z, perm, sh, lds_ids, zbar,
                            start, bits);
     };
-    if (vw == 4) launch(std::integral_constant<int, 4>{});
-    else if (vw == 2) launch(std::integral_constant<int, 2>{});
-    else launch(std::integral_constant<int, 1>{});
+    if (form == kAligned) launch(std::integral_constant<int, kAligned>{});
+    else if (form == kAnyRow) launch(std::integral_constant<int, kAnyRow>{});
+    else launch(std::integral_constant<int, kTiny>{});
     HIP_TRY(h, hipGetLastError());
     return CDGRAB_OK;
 }

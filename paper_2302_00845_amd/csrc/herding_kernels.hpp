@@ -37,8 +37,8 @@ __device__ __forceinline__ bool herding_thread_role(const HerdingShape &sh, int6
     return sl < sh.spw && s < sh.segments;
 }
 
-// Sum over the workers of elements e .. e+3 of step j's vectors.  VW = widest
-// aligned load every row start allows (as in the balancing kernels).  ids: the m
+// Sum over the workers of elements e .. e+3 of step j's vectors.  VW = how
+// a row is read (as in the balancing kernels).  ids: the m
 // example ids of the step (LDS), or null: read perm (or take j) per worker.
 template <int VW>
 __device__ __forceinline__ void herding_step_sum(const float *__restrict__ z, const int32_t *__restrict__ perm,

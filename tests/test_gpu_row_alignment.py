@@ -1,0 +1,53 @@
+"""Rows of any length at any 4-byte aligned address: every launch form reads four elements
+with one load, whose last group must stop at the end of the row.  Small-integer rows, so the
+oracle must be matched bit for bit; the rows lie between guard values that would show."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from parity import check_epoch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2302_00845_amd as p
+    return p
+
+
+def shifted(z, shift):
+    """z on the GPU, `shift` floats after a 16-byte boundary, with huge values on either side."""
+    flat = torch.full((z.size + 16,), 1e30, dtype=torch.float32, device="cuda")
+    view = flat[4 + shift:4 + shift + z.size].view(z.shape)
+    view.copy_(torch.from_numpy(z))
+    return view
+
+
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+@pytest.mark.parametrize("m,n,d,kw", [
+    (2, 6, 1, {}), (2, 6, 2, {}), (2, 6, 3, {}), (2, 6, 4, {}), (2, 6, 5, {}), (3, 40, 6, {}), (3, 44, 63, {}),
+    (3, 44, 65, {}), (3, 44, 66, dict(gram_mode=1)), (3, 44, 127, dict(gram_mode=1, apply_mode=1)),
+    (2, 24, 16385, {}), (2, 24, 65535, {}), (2, 24, 65539, dict(apply_mode=1)), (2, 20, 70001, dict(apply_mode=3)),
+    (2, 20, 70002, dict(apply_mode=4)), (3, 24, 131073, {}),
+])
+def test_epoch_on_rows_of_any_alignment(lib, shift, m, n, d, kw):
+    z = workloads.integer_rows(d + shift, m, n, d, 3)
+    h = lib.Handle(**kw)
+    out = lib.cdgrab_balance_epoch(h, m, n, d, grads=shifted(z, shift), want_r64=True, want_dots=True)
+    torch.cuda.synchronize()
+    got = {k: v.cpu().numpy() for k, v in out.items()}
+    rep = check_epoch(z, got, expect_exact_signs=True)
+    assert rep["r64_rel_l2"] == 0.0 and rep["dots_max_abs_err"] == 0.0
+
+
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+@pytest.mark.parametrize("m,n,d", [(3, 8, 1), (3, 8, 3), (3, 8, 5), (2, 30, 63), (2, 30, 517), (2, 6, 4099)])
+def test_herding_bound_on_rows_of_any_alignment(lib, shift, m, n, d):
+    z = workloads.integer_rows(d, m, n, d, 5)
+    perm = workloads.random_perms(1, m, n)
+    got = float(lib.cdgrab_herding_bound(lib.Handle(), shifted(z, shift), torch.from_numpy(perm).cuda())[0])
+    # double sums in another order than the oracle's: rounding of about m n additions
+    assert got == pytest.approx(oracle.parallel_herding(z, perm), rel=1e-13, abs=1e-13)
