@@ -51,6 +51,8 @@ struct cdgrab_handle {
     double *reduced = nullptr;                            // kReduceSlices x PartLayout<64>::PART doubles
     int8_t *eps_blk = nullptr; int64_t eps_cap = 0;       // 64 signs of the current block per walk
     int32_t *flag = nullptr;                              // reorder's bad-sign flag
+    int32_t *reorder_counts = nullptr; int64_t reorder_cap = 0;  // reorder: +1 signs per chunk
+    double *mean_ws = nullptr; int64_t mean_cap = 0;      // column mean: sums per chunk of rows
     const float *uniforms = nullptr;                      // caller's draws while a randomized epoch runs
     int64_t walks = 1;                                    // independent walks per launch while such an epoch runs
     WalkStrides ws{};                                     // their strides (all zero for one walk)
@@ -450,6 +452,52 @@ int apply_block_vw(cdgrab_handle *h, const RowMap &rm, const cdgrab_plan &plan) 
     return CDGRAB_OK;
 }
 
+// Orders of m workers from their signs (flag already cleared).  A grid holds at most 2^23 chunks.
+int launch_reorder(cdgrab_handle *h, int64_t m, int64_t n, const int8_t *signs, const int32_t *perm_in,
+                   int32_t *perm_out) {
+    const int64_t chunks = (n + kReorderChunk - 1) / kReorderChunk;
+    const int64_t most = std::max<int64_t>(1, ((int64_t)1 << 23) / chunks);
+    if (chunks > 1) {
+        const int rc = ensure(h, h->reorder_counts, h->reorder_cap, std::min(m, most) * chunks);
+        if (rc) return rc;
+    }
+    for (int64_t i = 0; i < m; i += most) {
+        const dim3 grid((unsigned)(std::min(most, m - i) * chunks)), block(kReorderThreads);
+        if (chunks > 1)
+            hipLaunchKernelGGL(reorder_count, grid, block, 0, h->stream, signs + i * n, n, chunks, h->reorder_counts);
+        hipLaunchKernelGGL(reorder_from_signs, grid, block, 0, h->stream, signs + i * n,
+                           perm_in ? perm_in + i * n : nullptr, perm_out + i * n, n, chunks, h->reorder_counts,
+                           h->flag);
+    }
+    HIP_TRY(h, hipGetLastError());
+    return CDGRAB_OK;
+}
+
+// mean_out[d] of n rows: about four workgroups per CU, at least eight rows per thread.
+int launch_column_mean(cdgrab_handle *h, int64_t n, int64_t d, const float *rows, float *mean_out) {
+    const int64_t quads = (d + 3) / 4;
+    const int slots = quads <= 128 ? (int)(256 / quads) : 1;
+    const int64_t grid_x = slots > 1 ? 1 : (quads + 255) / 256;
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>((n + 8 * slots - 1) / (8 * slots),
+                                                                (4 * (int64_t)h->num_cu + grid_x - 1) / grid_x));
+    const int64_t chunk_rows = (n + want - 1) / want, chunks = (n + chunk_rows - 1) / chunk_rows;
+    const int rc = ensure(h, h->mean_ws, h->mean_cap, chunks * d);
+    if (rc) return rc;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid_x, (unsigned)chunks), dim3(256), 0, h->stream, rows, n, d, quads,
+                           slots, chunk_rows, h->mean_ws);
+    };
+    switch (row_form((d % 4 == 0 && reinterpret_cast<uintptr_t>(rows) % 16 == 0) ? 4 : 1, d)) {
+        case kAligned: launch(column_sums<kAligned>); break;
+        case kAnyRow: launch(column_sums<kAnyRow>); break;
+        default: launch(column_sums<kTiny>); break;
+    }
+    hipLaunchKernelGGL(column_mean_finish, dim3((unsigned)((d + 15) / 16)), dim3(256), 0, h->stream, h->mean_ws, chunks,
+                       n, d, mean_out);
+    HIP_TRY(h, hipGetLastError());
+    return CDGRAB_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -500,6 +548,8 @@ int cdgrab_destroy(cdgrab_handle *h) {
     if (h->reduced) (void)hipFree(h->reduced);
     if (h->eps_blk) (void)hipFree(h->eps_blk);
     if (h->flag) (void)hipFree(h->flag);
+    if (h->reorder_counts) (void)hipFree(h->reorder_counts);
+    if (h->mean_ws) (void)hipFree(h->mean_ws);
     if (h->herd_ws) (void)hipFree(h->herd_ws);
     if (h->train_delta) (void)hipFree(h->train_delta);
     if (h->train_perm) (void)hipFree(h->train_perm);
@@ -1002,13 +1052,8 @@ int cdgrab_balance_epoch_stale_mean(cdgrab_handle *h, int64_t n, int64_t d, cons
     if (rc) return rc;
     hipLaunchKernelGGL(negate_signs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, h->stream, signs_out, n);
     hipLaunchKernelGGL(fill_zero_b32, dim3(1), dim3(64), 0, h->stream, reinterpret_cast<uint32_t *>(h->flag), (int64_t)1);
-    hipLaunchKernelGGL(reorder_from_signs, dim3(1), dim3(kScanThreads), 0, h->stream, signs_out, perm_in,
-                       perm_out, n, h->flag);
-    if (mean_out)
-        hipLaunchKernelGGL(column_mean, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, h->stream, grads, n, d,
-                           mean_out);
-    HIP_TRY(h, hipGetLastError());
-    return CDGRAB_OK;
+    if ((rc = launch_reorder(h, 1, n, signs_out, perm_in, perm_out))) return rc;
+    return mean_out ? launch_column_mean(h, n, d, grads, mean_out) : CDGRAB_OK;
 }
 
 int cdgrab_balance_epoch_independent(cdgrab_handle *h, int64_t m, int64_t n, int64_t d,
@@ -1154,9 +1199,8 @@ int cdgrab_reorder(cdgrab_handle *h, int64_t m, int64_t n, const int8_t *signs,
     HIP_TRY(h, hipSetDevice(h->device));
     if (!h->flag) { int64_t cap = 0; int rc = ensure(h, h->flag, cap, (int64_t)1); if (rc) return rc; }
     hipLaunchKernelGGL(fill_zero_b32, dim3(1), dim3(64), 0, h->stream, reinterpret_cast<uint32_t *>(h->flag), (int64_t)1);
-    hipLaunchKernelGGL(reorder_from_signs, dim3((unsigned)m), dim3(kScanThreads), 0, h->stream, signs,
-                       perm_in, perm_out, n, h->flag);
-    HIP_TRY(h, hipGetLastError());
+    const int rc = launch_reorder(h, m, n, signs, perm_in, perm_out);
+    if (rc) return rc;
     int32_t bad = 0;
     HIP_TRY(h, hipMemcpyAsync(&bad, h->flag, sizeof bad, hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));

@@ -51,3 +51,27 @@ def test_herding_bound_on_rows_of_any_alignment(lib, shift, m, n, d):
     got = float(lib.cdgrab_herding_bound(lib.Handle(), shifted(z, shift), torch.from_numpy(perm).cuda())[0])
     # double sums in another order than the oracle's: rounding of about m n additions
     assert got == pytest.approx(oracle.parallel_herding(z, perm), rel=1e-13, abs=1e-13)
+
+
+@pytest.mark.parametrize("n,d", [(1, 1), (1, 7), (9, 3), (300, 4), (2049, 5), (4097, 16), (65, 508), (65, 512), (65, 513),
+                                 (30, 1030), (8193, 2)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_stale_mean_column_mean_and_order(lib, n, d, shift):
+    """The epoch's mean (chunks of rows added in double: exact on small integers up to the one
+    rounding of the quotient and the one to fp32) and the order its signs give."""
+    z = workloads.integer_rows(n + d, 1, n, d, 4)[0]
+    out = lib.cdgrab_balance_epoch_stale_mean(lib.Handle(), shifted(z, shift))
+    assert np.array_equal(out["mean"].cpu().numpy(), (z.astype(np.float64).sum(0) / n).astype(np.float32))
+    assert np.array_equal(out["perm"].cpu().numpy(), oracle.reorder(out["signs"].cpu().numpy(), None))
+
+
+@pytest.mark.parametrize("m,n", [(3, 4095), (3, 4096), (3, 4097), (2, 8192), (1, 8193), (70, 4100), (1, 1_000_003)])
+@pytest.mark.parametrize("with_perm", [False, True])
+def test_reorder_across_chunks(lib, m, n, with_perm):
+    signs = workloads.random_signs(n, m, n)
+    signs[0, :5000] = 1                                   # a chunk of one sign only
+    perm_in = workloads.random_perms(n, m, n) if with_perm else None
+    out = lib.cdgrab_reorder(lib.Handle(), torch.from_numpy(signs).cuda(),
+                             torch.from_numpy(perm_in).cuda() if with_perm else None).cpu().numpy()
+    for i in range(m):
+        assert np.array_equal(out[i], oracle.reorder(signs[i], perm_in[i] if with_perm else None))
