@@ -56,12 +56,13 @@ typedef struct cdgrab_options {
                             the flat kernel (one thread per four elements)                 */
     int32_t gram_mode;   /* dense input (and the staged rows of cdgrab_train_epoch_softmax).
                             1 = every block computes its Gram matrix in
-                            its own dot/Gram launch; 2 = the Gram matrices of up to 512
-                            blocks are computed ahead in one launch (they depend on the
-                            rows only) and a block then costs one launch (the previous
-                            block's resolver and apply, this block's dots); refused
-                            (EINVAL) for d > 131 072; 0 = choose (2 for rows up to 16 384
-                            elements when apply_mode is 0 as well)                        */
+                            its own dot/Gram launch; 2 = the Gram matrices of many
+                            pairs are computed ahead in one launch (they depend on the
+                            rows only) and the walk is a chain of steps of 64 .. 256 pairs
+                            (chosen by sizes, whatever the block size) at two launches each;
+                            refused (EINVAL) for d > 131 072; 0 = choose (2 for rows up to
+                            65 536 elements when apply_mode is 0 as well; staged rows: up to
+                            16 384)                                                       */
     int32_t apply_groups; /* cap on the workgroups of the resident apply kernel; 0 = two per CU */
 } cdgrab_options;
 
@@ -99,7 +100,7 @@ typedef struct cdgrab_plan {
     int64_t staging_bytes;   /* staging blocks [Bb][2][d] fp32 (two when fused), 0 for dense input */
     double bytes_per_example;/* algorithmic HBM bytes per example: each row twice, plus the
                                 double running sum per block: 8d + 12 d / Bb (read twice,
-                                written once) or 8d + 8 d / Bb when fused; 12d + 8 d / Bb
+                                written once) or 8d + 8 d / Bb when fused; at most 12d + 8 d / Bb
                                 with the Gram matrices computed ahead (rows read three times) */
 } cdgrab_plan;
 

@@ -41,19 +41,9 @@ struct RowMap {
     int32_t i0;     // worker of the block's first flattened pair
     int32_t m;
     int32_t nb;     // valid pairs in this block (<= Bb)
-    int32_t dense;  // 1: the rows are those of a dense input [m][n][d] in its own order
     int64_t off[2 * kMaxBlockPairs];  // off[2 j + which]
 
     __device__ __forceinline__ const float *row(int j, int which) const { return base + off[2 * j + which]; }
-    // Same address without the table, for dense input: pair j of the block is pair
-    // k0 + (i0 + j) / m of worker (i0 + j) % m.  A per-thread j costs a memory round trip
-    // through the table and a few integer instructions this way.
-    __device__ __forceinline__ const float *dense_row(int j, int which) const {
-        const uint32_t q = (uint32_t)(i0 + j);
-        const uint32_t dk = q / (uint32_t)m;
-        const int64_t i = (int64_t)(q - dk * (uint32_t)m), k = k0 + (int64_t)dk;
-        return base + (i * n + 2 * k + which) * d;
-    }
 };
 
 // How a kernel reads four consecutive elements of a row (template parameter VW):
@@ -103,18 +93,32 @@ __device__ __forceinline__ float4 load4(const float *row, int64_t e, int64_t d) 
 // out-of-range parts read another part of the row instead and are replaced by zero afterwards.
 // (A load inside an `if` ends in a wait for it before the next one is issued; with
 // straight-line code all loads of a thread are in flight together.)
-template <int VW>
+// NT: with the non-temporal hint (false where the next launch on the same XCD reads the row again).
+template <bool NT>
+__device__ __forceinline__ float load_one(const float *p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+template <bool NT>
+__device__ __forceinline__ float4_t load_four(const float *p) {  // 4-byte aligned
+    const float4_any *q = reinterpret_cast<const float4_any *>(p);
+    if constexpr (NT) return __builtin_nontemporal_load(q);
+    else return *q;
+}
+
+template <int VW, bool NT = true>
 __device__ __forceinline__ float4 load4_nb(const float *row, bool have, int64_t e, int64_t d) {
     float4 v;
     if constexpr (VW == kAligned) {
         const bool in = have && e < d;
-        const float4_t t = __builtin_nontemporal_load(reinterpret_cast<const float4_t *>(row + (in ? e : 0)));
+        const float4_t t = load_four<NT>(row + (in ? e : 0));
         v = make_float4(in ? t.x : 0.f, in ? t.y : 0.f, in ? t.z : 0.f, in ? t.w : 0.f);
     } else if constexpr (VW == kAnyRow) {
         // a group that reaches beyond the row reads the row's last four elements and moves them down
         const int64_t base = e <= d - 4 ? e : d - 4;
         const int sh = have && e - base < 4 ? (int)(e - base) : 4;
-        const float4_any t = __builtin_nontemporal_load(reinterpret_cast<const float4_any *>(row + base));
+        const float4_t t = load_four<NT>(row + base);
         // (in binary steps: a chain of comparisons on sh becomes branches)
         const bool s1 = sh & 1, s2 = sh & 2, s4 = sh & 4;
         const float x1 = s1 ? t.y : t.x, y1 = s1 ? t.z : t.y, z1 = s1 ? t.w : t.z, w1 = s1 ? 0.f : t.w;
@@ -125,7 +129,7 @@ __device__ __forceinline__ float4 load4_nb(const float *row, bool have, int64_t 
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const bool in = have && e + q < d;
-            const float t = __builtin_nontemporal_load(row + (in ? e + q : 0));
+            const float t = load_one<NT>(row + (in ? e + q : 0));
             o[q] = in ? t : 0.f;
         }
         v = make_float4(o[0], o[1], o[2], o[3]);
@@ -178,10 +182,9 @@ struct PrevBlock {
 struct WalkStrides {
     int64_t rows;   // floats from walk w's rows to walk w+1's
     int64_t r;      // doubles between running sums
-    int64_t gram;   // doubles between the walks' reduced Gram tiles
+    int64_t gram;   // doubles between the walks' Gram tiles
     int64_t dots;   // doubles between the walks' per-workgroup dots
     int64_t out;    // entries between the walks' slices of signs_out / dots_out
-    int64_t maps;   // row maps per walk
 };
 
 // `group` of `ngroups` workgroups share the tiles; the workgroup's result goes to `out`.
@@ -392,42 +395,6 @@ __global__ __launch_bounds__(kThreads) void pass1_dots_gram(RowMap rm, PrevBlock
                                             ntiles, (int)blockIdx.x, (int)gridDim.x);
 }
 
-// The Gram matrices of many blocks in one launch (they depend on the rows only, not on
-// the running sum or on earlier signs): blockIdx.y picks the block, whose row map is
-// read from device memory, and gridDim.x workgroups share its tiles.  The dots this
-// form also emits are taken against whatever the running sum holds and are not used.
-template <int BB, int VW, int TE>
-__global__ __launch_bounds__(kThreads) void gram_batched(const RowMap *__restrict__ maps,
-                                                         double *__restrict__ r_sum,
-                                                         double *__restrict__ partials, int64_t ntiles,
-                                                         int64_t maps_per_walk)
-{
-    // blockIdx.z: the walk (its maps follow the previous walk's)
-    const RowMap &rm = maps[(int64_t)blockIdx.z * maps_per_walk + blockIdx.y];
-    PrevBlock none;
-    none.rm.nb = 0;
-    none.eps = nullptr;
-    const int64_t slot = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    pass1_body<BB, VW, TE, false, false>(rm, none, r_sum, partials + slot * PartLayout<BB>::PART, ntiles,
-                                         (int)blockIdx.x, (int)gridDim.x);
-}
-
-// Sum over the `groups` workgroups of each block of the batched form, in group order:
-// gram_all[b][idx] = sum_g partials[(b * groups + g)][idx].
-__global__ __launch_bounds__(kThreads) void reduce_batched(const double *__restrict__ partials,
-                                                           double *__restrict__ gram_all, int part, int groups,
-                                                           int64_t walk_gram_stride)
-{
-    const int idx = blockIdx.x * kThreads + threadIdx.x;
-    if (idx >= part) return;
-    // blockIdx.y: block of the batch, blockIdx.z: walk
-    const double *src = partials + ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * groups * part + idx;
-    double sum = 0.0;
-#pragma unroll 8
-    for (int g = 0; g < groups; ++g) sum += src[(int64_t)g * part];
-    gram_all[(int64_t)blockIdx.z * walk_gram_stride + (int64_t)blockIdx.y * part + idx] = sum;
-}
-
 // ---------------------------------------------------------------------------
 // Fixed-order reduction of the per-workgroup partials, first level: the list of
 // workgroups is cut into kReduceSlices slices (blockIdx.y); each workgroup sums
@@ -476,21 +443,22 @@ __global__ __launch_bounds__(kThreads) void reduce_partials(const double *__rest
 // keeps 64 doubles of the Gram matrix per lane in registers.
 template <int BB> constexpr int kResolveThreads = BB > 32 ? 512 : 1024;
 
-// The resolver's body, run by all NT threads of a workgroup (the walk by its first
-// wavefront).  write_out: store the signs (and resolved dots) to global memory; eps_lds
-// (LDS, BB entries, or null): the block's signs for the rest of the workgroup, valid after
-// the barrier this function ends with.
-template <int BB, bool RANDOM, int SLICES, int NT>
-__device__ __forceinline__ void resolve_body(const double *__restrict__ gram_src, int64_t gram_stride,
-                                             const double *__restrict__ dot_src, int dot_groups,
-                                             int64_t dot_stride, int nb, int64_t k0, int32_t i0, int32_t m,
-                                             int64_t half_n, bool write_out, int8_t *__restrict__ eps_blk,
-                                             int8_t *__restrict__ signs_out, double *__restrict__ dots_out,
-                                             const float *__restrict__ uniforms, int8_t *eps_lds)
+// The walk is run by the workgroup's first wavefront.
+template <int BB, bool RANDOM, int SLICES>
+__global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const double *__restrict__ gram_src,
+                                                                     int64_t gram_stride,
+                                                                     const double *__restrict__ dot_src,
+                                                                     int dot_groups, int64_t dot_stride, int nb,
+                                                                     int64_t k0, int32_t i0, int32_t m, int64_t half_n,
+                                                                     int8_t *__restrict__ eps_blk,
+                                                                     int8_t *__restrict__ signs_out,
+                                                                     double *__restrict__ dots_out,
+                                                                     const float *__restrict__ uniforms)
 {
     // Gram tiles: sum of SLICES arrays gram_src[s * gram_stride + idx];
     // dots: sum of dot_groups arrays dot_src[g * dot_stride + k]; both in index order.
     using L = PartLayout<BB>;
+    constexpr int NT = kResolveThreads<BB>;
     constexpr int SUBS = (NT / BB < 16) ? NT / BB : 16;  // threads sharing one dot
     __shared__ double G[BB][BB + 1];
     __shared__ double P[BB];
@@ -602,34 +570,12 @@ __device__ __forceinline__ void resolve_body(const double *__restrict__ gram_src
         }
         const double my_t = t;
         const int my_eps = rule(t) ? 1 : -1;
-        if (eps_lds && lane < BB) eps_lds[lane] = (lane < nb) ? (int8_t)my_eps : (int8_t)0;
-        if (write_out && lane < nb) {
+        if (lane < nb) {
             eps_blk[lane] = (int8_t)my_eps;
             signs_out[slot] = (int8_t)my_eps;
             if (dots_out) dots_out[slot] = my_t;
         }
     }
-    __syncthreads();
-}
-
-template <int BB, bool RANDOM, int SLICES>
-__global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const double *__restrict__ gram_src,
-                                                                     int64_t gram_stride,
-                                                                     const double *__restrict__ dot_src,
-                                                                     int dot_groups, int64_t dot_stride, int nb,
-                                                                     int64_t k0, int32_t i0, int32_t m, int64_t half_n,
-                                                                     int8_t *__restrict__ eps_blk,
-                                                                     int8_t *__restrict__ signs_out,
-                                                                     double *__restrict__ dots_out,
-                                                                     const float *__restrict__ uniforms,
-                                                                     WalkStrides ws)
-{
-    const int64_t w = blockIdx.y;  // the walk
-    resolve_body<BB, RANDOM, SLICES, kResolveThreads<BB>>(gram_src + w * ws.gram, gram_stride, dot_src + w * ws.dots,
-                                                          dot_groups, dot_stride, nb, k0, i0, m, half_n, true,
-                                                          eps_blk + w * kMaxBlockPairs, signs_out + w * ws.out,
-                                                          dots_out ? dots_out + w * ws.out : nullptr, uniforms,
-                                                          nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -739,13 +685,10 @@ constexpr int kSplitElems = (kThreads / kSplitGroups) * 4;  // 64 elements per w
 
 template <int BB, int VW, bool FULL>
 __global__ __launch_bounds__(kThreads) void pass2_apply_split(RowMap rm, const int8_t *__restrict__ eps_blk,
-                                                              double *__restrict__ r_sum, WalkStrides ws)
+                                                              double *__restrict__ r_sum)
 {
     __shared__ double part[kSplitGroups][kSplitElems];
     const int64_t d = rm.d;
-    const int64_t woff = (int64_t)blockIdx.y * ws.rows;  // blockIdx.y: the walk
-    eps_blk += (int64_t)blockIdx.y * kMaxBlockPairs;
-    r_sum += (int64_t)blockIdx.y * ws.r;
     const int quad = threadIdx.x % (kThreads / kSplitGroups), grp = threadIdx.x / (kThreads / kSplitGroups);
     const int64_t e = (int64_t)blockIdx.x * kSplitElems + quad * 4;
     const int64_t mine = (int64_t)blockIdx.x * kSplitElems + threadIdx.x;
@@ -758,8 +701,8 @@ __global__ __launch_bounds__(kThreads) void pass2_apply_split(RowMap rm, const i
         const int j = grp * PER + q;
         // (offsets of missing pairs are readable rows: zero, or those of an earlier block)
         const bool have = FULL || j < rm.nb;
-        a[q] = load4_nb<VW>(rm.row(j, 0) + woff, have, e, d);
-        b[q] = load4_nb<VW>(rm.row(j, 1) + woff, have, e, d);
+        a[q] = load4_nb<VW>(rm.row(j, 0), have, e, d);
+        b[q] = load4_nb<VW>(rm.row(j, 1), have, e, d);
     }
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -783,99 +726,6 @@ __global__ __launch_bounds__(kThreads) void pass2_apply_split(RowMap rm, const i
 }
 
 // ---------------------------------------------------------------------------
-// Short rows with the Gram matrices computed ahead (gram_batched): the chain of a block
-// in ONE launch.  What is left on the chain is the resolver of the PREVIOUS block,
-// r += sum_k eps_k d_k over it, and the dots <r, d_k> of this block against the result.
-// Every workgroup resolves the previous block for itself (its reduced Gram tiles and the
-// per-workgroup dots the previous launch wrote: the resolver's body on 256 threads,
-// redundantly in each of the d/64 workgroups -- a few tens of KB from the L2 and a walk of
-// Bb steps, cheaper than a launch boundary).  Then, with the thread layout of
-// pass2_apply_split (a workgroup owns 64 elements, group g of 16 threads takes the pairs
-// g*PER .. g*PER+PER-1 of either block), it applies the previous block and writes its share
-// of this block's Bb dots to dots_out_part[blockIdx.x][BB], which must not be the array
-// being read.  Workgroup 0 also stores the previous block's signs.  DENSE: row addresses by
-// arithmetic (RowMap::dense_row) instead of through the offset table.
-template <int BB, int VW, bool DENSE, bool RANDOM>
-__global__ __launch_bounds__(kThreads) void resolve_dots_apply_split(
-    RowMap rm, PrevBlock prev, const double *__restrict__ prev_gram, const double *__restrict__ dots_in_part,
-    double *__restrict__ dots_out_part, int dot_groups, double *__restrict__ r_sum, int8_t *__restrict__ eps_blk,
-    int8_t *__restrict__ signs_out, double *__restrict__ dots_out, const float *__restrict__ uniforms,
-    WalkStrides ws)
-{
-    __shared__ double part[kSplitGroups][kSplitElems];
-    __shared__ double rnew[kSplitElems];
-    __shared__ int8_t eps_s[kMaxBlockPairs];
-    const int64_t d = rm.d;
-    // blockIdx.y: the walk; what it owns lies at a fixed stride from the first walk's
-    const int64_t w = blockIdx.y;
-    const int64_t woff = w * ws.rows;
-    prev_gram += w * ws.gram;
-    dots_in_part += w * ws.dots;
-    dots_out_part += w * ws.dots;
-    r_sum += w * ws.r;
-    eps_blk += w * kMaxBlockPairs;
-    signs_out += w * ws.out;
-    if (dots_out) dots_out += w * ws.out;
-    constexpr int QUADS = kThreads / kSplitGroups;  // 16 threads, four elements each
-    const int quad = threadIdx.x % QUADS, grp = threadIdx.x / QUADS;
-    const int64_t e = (int64_t)blockIdx.x * kSplitElems + quad * 4;
-    const int64_t mine = (int64_t)blockIdx.x * kSplitElems + threadIdx.x;
-    // the rows of both blocks are requested before the resolver's inputs
-    const double r_old = (threadIdx.x < kSplitElems) ? r_sum[mine] : 0.0;  // padded to a multiple of 128
-    constexpr int PER = BB / kSplitGroups;
-    float4 pa[PER], pb[PER], ca[PER], cb[PER];
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int j = grp * PER + q;
-        const int jp = j < prev.rm.nb ? j : 0, jc = j < rm.nb ? j : 0;
-        pa[q] = load4_nb<VW>((DENSE ? prev.rm.dense_row(jp, 0) : prev.rm.row(j, 0)) + woff, true, e, d);
-        pb[q] = load4_nb<VW>((DENSE ? prev.rm.dense_row(jp, 1) : prev.rm.row(j, 1)) + woff, true, e, d);
-        ca[q] = load4_nb<VW>((DENSE ? rm.dense_row(jc, 0) : rm.row(j, 0)) + woff, true, e, d);
-        cb[q] = load4_nb<VW>((DENSE ? rm.dense_row(jc, 1) : rm.row(j, 1)) + woff, true, e, d);
-    }
-    if (prev.rm.nb > 0) {  // uniform
-        resolve_body<BB, RANDOM, 1, kThreads>(prev_gram, 0, dots_in_part, dot_groups, BB, prev.rm.nb, prev.rm.k0,
-                                              prev.rm.i0, prev.rm.m, prev.rm.n / 2, blockIdx.x == 0, eps_blk,
-                                              signs_out, dots_out, uniforms, eps_s);
-    } else {
-        if (threadIdx.x < BB) eps_s[threadIdx.x] = 0;
-        __syncthreads();
-    }
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const double sg = (double)eps_s[grp * PER + q];  // 0 for a pair the previous block does not have
-        acc[0] = __builtin_fma(sg, (double)pb[q].x - (double)pa[q].x, acc[0]);
-        acc[1] = __builtin_fma(sg, (double)pb[q].y - (double)pa[q].y, acc[1]);
-        acc[2] = __builtin_fma(sg, (double)pb[q].z - (double)pa[q].z, acc[2]);
-        acc[3] = __builtin_fma(sg, (double)pb[q].w - (double)pa[q].w, acc[3]);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) part[grp][quad * 4 + q] = acc[q];
-    __syncthreads();
-    if (threadIdx.x < kSplitElems) {
-        double sum = 0.0;
-#pragma unroll
-        for (int g = 0; g < kSplitGroups; ++g) sum += part[g][threadIdx.x];
-        const double r = r_old + sum;  // elements beyond d load as zero, so the padding stays zero
-        r_sum[mine] = r;
-        rnew[threadIdx.x] = r;
-    }
-    __syncthreads();
-    const double r0 = rnew[quad * 4], r1 = rnew[quad * 4 + 1], r2 = rnew[quad * 4 + 2], r3 = rnew[quad * 4 + 3];
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        double p = r0 * ((double)cb[q].x - (double)ca[q].x);
-        p = __builtin_fma(r1, (double)cb[q].y - (double)ca[q].y, p);
-        p = __builtin_fma(r2, (double)cb[q].z - (double)ca[q].z, p);
-        p = __builtin_fma(r3, (double)cb[q].w - (double)ca[q].w, p);
-#pragma unroll
-        for (int off = 1; off < QUADS; off <<= 1) p += __shfl_xor(p, off, 64);
-        if (quad == 0) dots_out_part[(int64_t)blockIdx.x * BB + grp * PER + q] = p;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Clears `count` 32-bit words.  The library clears its flags and scratch with fill
 // kernels rather than memset nodes, so that a caller may capture its stream in a graph.
 __global__ void fill_zero_b32(uint32_t *p, int64_t count) {
@@ -888,53 +738,6 @@ __global__ void fill_zero_f64(double *p, int64_t count) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (; i < count; i += stride) p[i] = 0.0;
-}
-
-// Row maps of `count` consecutive blocks starting at flattened pair first_pair: block b
-// holds the pairs first_pair + b*bb .. (up to total_pairs).  One thread per (block, pair).
-__global__ __launch_bounds__(kMaxBlockPairs) void fill_row_maps(RowMap *__restrict__ maps, const float *base,
-                                                                int64_t m, int64_t n, int64_t d, int bb,
-                                                                int64_t first_pair, int64_t total_pairs,
-                                                                int64_t center_off, int layout,
-                                                                int64_t walk_rows_stride)
-{
-    // layout 0: dense [m][n][d];  1: single rows paired with the row at center_off;
-    // 2: a staging chunk [q][2][d] that starts at first_pair (base = the chunk)
-    // blockIdx.y: the walk (its rows start walk_rows_stride floats after the previous walk's)
-    const int use_center = layout == 1;
-    base += (int64_t)blockIdx.y * walk_rows_stride;
-    RowMap &rm = maps[(int64_t)blockIdx.y * gridDim.x + blockIdx.x];
-    const int j = threadIdx.x;
-    const int64_t p0 = first_pair + (int64_t)blockIdx.x * bb;
-    const int64_t left = total_pairs - p0;
-    const int nb = (int)(left < bb ? left : bb);
-    if (j == 0) {
-        rm.base = base;
-        rm.d = d;
-        rm.n = n;
-        rm.k0 = p0 / m;
-        rm.i0 = (int32_t)(p0 - (p0 / m) * m);
-        rm.m = (int32_t)m;
-        rm.nb = nb;
-        rm.dense = layout == 0 ? 1 : 0;
-    }
-    int64_t o0 = 0, o1 = 0;
-    if (j < nb) {
-        const int64_t p = p0 + j;
-        if (use_center) {
-            o0 = p * d;
-            o1 = center_off;
-        } else if (layout == 2) {
-            o0 = (p - first_pair) * 2 * d;
-            o1 = o0 + d;
-        } else {
-            const int64_t k = p / m, i = p - k * m;
-            o0 = (i * n + 2 * k) * d;
-            o1 = o0 + d;
-        }
-    }
-    rm.off[2 * j] = o0;
-    rm.off[2 * j + 1] = o1;
 }
 
 __global__ void export_running_sum(const double *__restrict__ r_sum, int64_t d, float *__restrict__ r32,

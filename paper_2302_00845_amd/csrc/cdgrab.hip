@@ -11,10 +11,12 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <string>
 #include <vector>
 
 #include "balance_kernels.hpp"
+#include "chain_kernels.hpp"
 #include "order_kernels.hpp"
 #include "herding_kernels.hpp"
 
@@ -49,7 +51,7 @@ struct cdgrab_handle {
     double *r_sum = nullptr;   int64_t r_cap = 0;         // doubles
     double *partials = nullptr; int64_t partials_cap = 0; // doubles
     double *reduced = nullptr;                            // kReduceSlices x PartLayout<64>::PART doubles
-    int8_t *eps_blk = nullptr; int64_t eps_cap = 0;       // 64 signs of the current block per walk
+    int8_t *eps_blk = nullptr; int64_t eps_cap = 0;       // signs of the current block (per walk: of the current step)
     int32_t *flag = nullptr;                              // reorder's bad-sign flag
     int32_t *reorder_counts = nullptr; int64_t reorder_cap = 0;  // reorder: +1 signs per chunk
     double *mean_ws = nullptr; int64_t mean_cap = 0;      // column mean: sums per chunk of rows
@@ -61,9 +63,9 @@ struct cdgrab_handle {
     int32_t *train_perm = nullptr; int64_t train_perm_cap = 0;  // spare [m][n] order of the multi-epoch driver
     int8_t *train_signs = nullptr; int64_t train_signs_cap = 0; // its [m][n/2] signs when the caller wants none
     double *herd_ws = nullptr; int64_t herd_cap = 0;      // herding evaluator: segment sums, starts, mean
-    double *gram_all = nullptr; int64_t gram_all_cap = 0; // Grams-ahead form: reduced tiles of up to kGramBatch blocks
-    double *dot_partials = nullptr; int64_t dot_partials_cap = 0;  // its per-workgroup dots of one block
-    RowMap *maps = nullptr; int64_t maps_cap = 0;         // its row maps (device)
+    double *gram_all = nullptr; int64_t gram_all_cap = 0; // Grams-ahead form: Gram tiles of a batch of steps
+    double *gram_parts = nullptr; int64_t gram_parts_cap = 0;      // shares of tiles whose elements are split
+    double *dot_partials = nullptr; int64_t dot_partials_cap = 0;  // its per-workgroup dots of one step
     float *staging = nullptr;  int64_t staging_cap = 0;   // floats: two staging chunks (the fused pass reads the previous block too)
     bool fixed_workspace = false;                         // the workspace pointers are borrowed: never grow or free them
 
@@ -127,15 +129,17 @@ int pick_block_pairs(int64_t pairs, int64_t d, int32_t requested) {
 // per 32-pair block, 2M: 213 against 198, 4M: 423 against 388).
 bool fuse_apply_by_default(int64_t d) { return d <= (int64_t)5 << 18; }
 
-// Dense input with short rows: a block is bound by its chain of launches, so the Gram
-// matrices (which depend on the rows only) are taken off the chain: one launch computes
-// them for up to kGramBatch blocks, and a block then costs one launch (resolver of the
-// previous block, its apply, this block's dots).  Measured on MI355X (m = 16, 64-pair blocks), time per block of the per-block
-// form -> this form: d = 256: 22.0 -> 8.9 us; 4096: 23.3 -> 11.2; 7850: 26.1 -> 15.8;
-// 16 384: 26.3 -> 19.3; 32 768: 35.9 -> 44.0; 65 536: 48.6 -> 132 (the rows are read three
-// times instead of twice, and every workgroup repeats the previous block's resolver).
-constexpr int64_t kGramBatch = 512;
-constexpr int64_t kGramAheadMaxD = 16384;     // chosen by default up to here
+// Short rows: a block is bound by its chain of launches, so the Gram matrices (which depend on
+// the rows only) are taken off the chain and the chain is cut into steps of 64 .. 256 pairs at
+// two launches each (chain_kernels.hpp).
+constexpr int64_t kGramBatch = 512;                  // a staging chunk holds at most this many blocks
+constexpr int64_t kGramBytes = (int64_t)256 << 20;   // Gram tiles held at a time
+// Measured on MI355X (m = 16), us per 64 pairs of the per-block form -> this form: d = 256: 20.4 -> 5.2;
+// 1024: 20.7 -> 5.6; 4096: 20.9 -> 7.7; 7850: 22.4 -> 10.0; 16 384: 24.2 -> 13.6; 32 768: 33.8 -> 21.0;
+// 65 536: 46.6 -> 35.8; 98 304: 46.1 -> 49.7; 131 072: 66.5 -> 66.8 (the rows are read three times
+// instead of twice).
+constexpr int64_t kGramAheadMaxD = 65536;     // chosen by default up to here
+constexpr int64_t kChunkAheadMaxD = 16384;    // and for staging chunks of several blocks up to here
 constexpr int64_t kGramAheadLimitD = 131072;  // refused beyond (gram_mode 2)
 bool gram_ahead_by_default(int64_t d, int64_t blocks, bool streamed) {
     return !streamed && blocks >= 2 && d <= kGramAheadMaxD;
@@ -143,6 +147,59 @@ bool gram_ahead_by_default(int64_t d, int64_t blocks, bool streamed) {
 
 int part_size(int bb) {
     return bb == 64 ? PartLayout<64>::PART : bb == 32 ? PartLayout<32>::PART : PartLayout<16>::PART;
+}
+
+// How the Grams-ahead form cuts an epoch (per walk: `walks` independent ones run side by side).
+struct ChainPlan {
+    int sp;             // pairs per step
+    int tiles;          // Gram tiles stored per step
+    int64_t steps;      // steps whose Gram tiles are computed in one launch
+    int ksplit;         // workgroups sharing the elements of a tile
+    int groups;         // workgroups of a step's wide launch
+    int64_t gram_len, parts_len, dots_len;  // doubles of workspace, all walks
+};
+
+// Time of one step of sp pairs, microseconds, fitted to measured epochs (30 000 pairs of 7850
+// elements: 11.7 / 15.9 / 27.9 us per step of 64 / 128 / 256 pairs and 0.35 / 0.95 / 1.8 ms of Gram
+// tiles; 500 000 pairs of 16 elements: 7.7 / 11.6 / 20.6 us; 64 walks of 468 pairs of 7850: 82 us per
+// 64-pair step).  Long chains of one walk want long steps, many walks or long rows short ones.
+double step_cost_us(int64_t sp, int64_t d, int64_t walks) {
+    const double blk = (double)(sp / kTilePairs), tiles = blk * (blk + 1) / 2;
+    const double launches = (d > 256 ? 5.7 : 3.7) + 0.066 * (double)sp;
+    const double rows = (double)walks * 16.0 * (double)sp * (double)d / 6.25e6;
+    const double gram = (double)walks * tiles * kTileEntries * 2.0 * (double)d / 40e6;
+    return launches + rows + gram;
+}
+
+ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pairs, int num_cu) {
+    ChainPlan c{};
+    const int64_t longest = chunk_pairs > 0 ? std::min(chunk_pairs, pairs) : pairs;
+    double best = 0.0;
+    for (int sp = kTilePairs; sp <= kMaxStepPairs; sp *= 2) {
+        if (sp > kTilePairs && sp / 2 >= longest) break;  // a shorter step holds them all
+        const double cost = (double)((pairs + sp - 1) / sp) * step_cost_us(sp, d, walks);
+        if (c.sp == 0 || cost < best) { c.sp = sp; best = cost; }
+    }
+    const int blk = c.sp / kTilePairs;
+    c.tiles = blk * (blk + 1) / 2;
+    const int64_t per_step = walks * c.tiles * kTileEntries;
+    const int64_t total = (longest + c.sp - 1) / c.sp;
+    c.steps = std::max<int64_t>(1, std::min<int64_t>(total, kGramBytes / 8 / per_step));
+    // Workgroups per tile: the launch takes whole rounds of two workgroups per CU, each as long as its
+    // share of a tile; shares cost a write and two reads of a tile each.  At least four k-tiles per share.
+    const int64_t ktiles = (d + kGramTE - 1) / kGramTE, wgs = c.steps * walks * c.tiles, slots = 2 * (int64_t)num_cu;
+    const double tile_us = 2.0 * kTileEntries * (double)d / (45e6 / (double)slots);
+    double least = 0.0;
+    for (int64_t ks = 1; ks <= std::max<int64_t>(1, std::min<int64_t>(ktiles / 4, 64)); ++ks) {
+        const double rounds = (double)((wgs * ks + slots - 1) / slots) / (double)ks;
+        const double us = rounds * tile_us + (ks > 1 ? 4.0 + (double)(wgs * (2 * ks + 1)) * kTileEntries * 8.0 / 4e6 : 0.0);
+        if (ks == 1 || us < 0.98 * least) { least = us; c.ksplit = (int)ks; }
+    }
+    c.groups = (int)((d + kStepElems - 1) / kStepElems);
+    c.gram_len = c.steps * per_step;
+    c.parts_len = c.ksplit > 1 ? c.gram_len * c.ksplit : 0;
+    c.dots_len = walks * c.groups * c.sp;
+    return c;
 }
 
 // The launch plan of one epoch.  `chunk_pairs` is the number of flattened pairs staged per
@@ -175,7 +232,7 @@ int plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t str
     const bool ahead_dense = !streamed && plan->blocks >= 2 &&
                              (gram_mode == 2 || (gram_mode == 0 && apply_mode == 0 &&
                                                  gram_ahead_by_default(d, plan->blocks, false)));
-    const bool ahead_streamed = streamed && gram_mode != 1 && apply_mode == 0 && d <= kGramAheadMaxD &&
+    const bool ahead_streamed = streamed && gram_mode != 1 && apply_mode == 0 && d <= kChunkAheadMaxD &&
                                 plan->pairs > bb && chunk_pairs >= 2 * bb && chunk_pairs % bb == 0 &&
                                 chunk_pairs / bb <= kGramBatch;
     const bool ahead = ahead_dense || ahead_streamed;
@@ -188,15 +245,11 @@ int plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t str
     // two staging chunks when a launch reads the previous block's rows as well
     plan->staging_bytes = streamed ? ((fused || ahead) ? 2 : 1) * chunk_pairs * 2 * d * 4 : 0;
     const int64_t part = part_size(plan->block_pairs);
-    int64_t partial_doubles = (int64_t)plan->pass1_groups * part;
+    const int64_t partial_doubles = (int64_t)plan->pass1_groups * part;
     int64_t ahead_bytes = 0;
     if (ahead) {
-        const int64_t batch = streamed ? chunk_pairs / bb : std::min<int64_t>(plan->blocks, kGramBatch);
-        const int64_t gg = std::max<int64_t>(1, std::min<int64_t>(ntiles, (4 * (int64_t)num_cu + batch - 1) / batch));
-        partial_doubles = std::max(partial_doubles, batch * gg * part);
-        ahead_bytes = (batch + 1) * part * 8                               // reduced Gram tiles
-                      + 2 * ((d + kSplitElems - 1) / kSplitElems * bb) * 8  // per-workgroup dots, two blocks
-                      + batch * (int64_t)sizeof(RowMap);                    // row maps
+        const ChainPlan c = plan_chain(plan->pairs, d, 1, streamed ? chunk_pairs : 0, num_cu);
+        ahead_bytes = (c.gram_len + c.parts_len + c.dots_len) * 8 + kMaxStepPairs;
     }
     plan->workspace_bytes = round_up(d, kPadE) * 8 + partial_doubles * 8 +
                             (int64_t)kReduceSlices * PartLayout<64>::PART * 8 + 64 + ahead_bytes +
@@ -276,15 +329,14 @@ constexpr int64_t kResidentMinD = (int64_t)1 << 20;
 template <int BB, int VW>
 void launch_pass2(cdgrab_handle *h, const RowMap &rm, int groups) {
     // short rows: too few flat workgroups to hide latency -> split the pairs over thread groups
-    // (several independent walks per launch exist for short rows only, in this form)
-    if ((groups < 2 * h->num_cu && h->apply_mode < 3) || h->walks > 1) {
-        const dim3 grid((unsigned)((rm.d + kSplitElems - 1) / kSplitElems), (unsigned)h->walks);
+    if (groups < 2 * h->num_cu && h->apply_mode < 3) {
+        const dim3 grid((unsigned)((rm.d + kSplitElems - 1) / kSplitElems));
         if (rm.nb == BB)
             hipLaunchKernelGGL((pass2_apply_split<BB, VW, true>), grid, dim3(kThreads), 0, h->stream, rm,
-                               h->eps_blk, h->r_sum, h->ws);
+                               h->eps_blk, h->r_sum);
         else
             hipLaunchKernelGGL((pass2_apply_split<BB, VW, false>), grid, dim3(kThreads), 0, h->stream, rm,
-                               h->eps_blk, h->r_sum, h->ws);
+                               h->eps_blk, h->r_sum);
         return;
     }
     if (h->apply_mode == 3 || (h->apply_mode != 4 && rm.d >= kResidentMinD)) {
@@ -322,89 +374,84 @@ void launch_resolve(cdgrab_handle *h, const RowMap &rm, int8_t *signs_out, doubl
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(1), dim3(kResolveThreads<BB>), 0, h->stream, h->reduced,
                            (int64_t)part, h->reduced + PartLayout<BB>::GRAM, kReduceSlices, (int64_t)part, rm.nb,
-                           rm.k0, rm.i0, rm.m, rm.n / 2, h->eps_blk, signs_out, dots_out, h->uniforms, WalkStrides{});
+                           rm.k0, rm.i0, rm.m, rm.n / 2, h->eps_blk, signs_out, dots_out, h->uniforms);
     };
     if (h->uniforms) launch(resolve_signs<BB, true, kReduceSlices>);
     else launch(resolve_signs<BB, false, kReduceSlices>);
 }
 
-// Grams-ahead form of one block, one launch: every workgroup resolves the previous block
-// (its Gram tiles at prev_gram, its per-workgroup dots in dots_in), applies it and takes
-// this block's dots (into dots_out).  The first block of an epoch has prev.rm.nb == 0.
-template <int BB>
-int run_block_ahead(cdgrab_handle *h, const RowMap &rm, const PrevBlock &prev, const cdgrab_plan &plan,
-                    const double *prev_gram, const double *dots_in, double *dots_out, int8_t *signs_out,
-                    double *dots_export) {
-    const unsigned groups = (unsigned)((rm.d + kSplitElems - 1) / kSplitElems);
+// Dispatch on how the rows are read, which is a template parameter of the kernels.
+template <typename F>
+void by_row_form(int form, F &&launch) {
+    switch (form) {
+        case kAligned: launch(std::integral_constant<int, kAligned>{}); break;
+        case kAnyRow: launch(std::integral_constant<int, kAnyRow>{}); break;
+        default: launch(std::integral_constant<int, kTiny>{}); break;
+    }
+}
+
+// Gram tiles of `steps` steps per walk, the first at rows, into h->gram_all.
+int run_gram_tiles(cdgrab_handle *h, const StepRows &rows, int64_t pairs, const ChainPlan &c, int form) {
+    GramBatch gb{};
+    gb.rows = rows;
+    gb.pairs = pairs;
+    gb.walk_floats = h->ws.rows;
+    gb.sp = c.sp;
+    gb.steps = (int32_t)((pairs + c.sp - 1) / c.sp);
+    gb.units = (int32_t)(gb.steps * h->walks);
+    gb.tiles = c.tiles;
+    gb.ksplit = c.ksplit;
+    gb.ktiles = (int32_t)((rows.d + kGramTE - 1) / kGramTE);
+    const int64_t padded = gb.units >= 8 ? round_up(gb.units, 8) : gb.units;
     MARK(h, 2, kPass1);
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(groups, (unsigned)h->walks), dim3(kThreads), 0, h->stream, rm, prev,
-                           prev_gram, dots_in, dots_out, (int)groups, h->r_sum, h->eps_blk, signs_out, dots_export,
-                           h->uniforms, h->ws);
-    };
-    auto by_width = [&](auto dense_tag, auto random_tag) {
-        constexpr bool DENSE = decltype(dense_tag)::value, RANDOM = decltype(random_tag)::value;
-        switch (row_form(plan.vector_width, rm.d)) {
-            case kAligned: launch(resolve_dots_apply_split<BB, 4, DENSE, RANDOM>); break;
-            case kAnyRow: launch(resolve_dots_apply_split<BB, 2, DENSE, RANDOM>); break;
-            default: launch(resolve_dots_apply_split<BB, 1, DENSE, RANDOM>); break;
-        }
-    };
-    if (rm.dense) {
-        if (h->uniforms) by_width(std::true_type{}, std::true_type{});
-        else by_width(std::true_type{}, std::false_type{});
-    } else {
-        if (h->uniforms) by_width(std::false_type{}, std::true_type{});
-        else by_width(std::false_type{}, std::false_type{});
+    by_row_form(form, [&](auto vw) {
+        hipLaunchKernelGGL((gram_tiles<decltype(vw)::value>), dim3((unsigned)(padded * c.tiles), (unsigned)c.ksplit),
+                           dim3(kThreads), 0, h->stream, gb, c.ksplit > 1 ? h->gram_parts : h->gram_all);
+    });
+    if (c.ksplit > 1) {
+        MARK(h, 2, kReduce);
+        hipLaunchKernelGGL(gram_reduce, dim3((unsigned)(gb.units * c.tiles), kTileEntries / 2 / kThreads), dim3(kThreads),
+                           0, h->stream, h->gram_parts, h->gram_all, c.ksplit);
     }
     HIP_TRY(h, hipGetLastError());
     return CDGRAB_OK;
 }
 
-// The resolver alone, for the epoch's last block in the Grams-ahead form.
-template <int BB>
-int run_resolve_ahead(cdgrab_handle *h, const RowMap &rm, const double *gram, const double *dots_in,
-                      int8_t *signs_out, double *dots_export) {
-    const int groups = (int)((rm.d + kSplitElems - 1) / kSplitElems);
+// Wide launch of a step: applies prev (if it has pairs), dots of cur (if it has pairs).
+int run_step_wide(cdgrab_handle *h, const StepRows &cur, const StepRows &prev, const ChainPlan &c, int form) {
+    MARK(h, 2, kPass1);
+    by_row_form(form, [&](auto vw) {
+        constexpr int VW = decltype(vw)::value;
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(c.groups >= 16 ? round_up(c.groups, 8) : c.groups), (unsigned)h->walks),
+                               dim3(kStepThreads), 0, h->stream, cur, prev, h->eps_blk, c.sp, c.groups, h->r_sum,
+                               h->dot_partials, h->ws);
+        };
+        if (c.sp > 128) launch(chain_apply_dots<8, VW>);
+        else if (c.sp > 64) launch(chain_apply_dots<4, VW>);
+        else launch(chain_apply_dots<2, VW>);
+    });
+    HIP_TRY(h, hipGetLastError());
+    return CDGRAB_OK;
+}
+
+// Serial launch of a step: the walk.  dot_groups 0: the running sum is still zero.
+int run_step_walk(cdgrab_handle *h, const StepRows &cur, const ChainPlan &c, const double *gram, int dot_groups,
+                  int64_t half_n, int8_t *signs_out, double *dots_out) {
     MARK(h, 2, kResolve);
-    auto resolve = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(1, (unsigned)h->walks), dim3(kResolveThreads<BB>), 0, h->stream, gram,
-                           (int64_t)0, dots_in, groups, (int64_t)BB, rm.nb, rm.k0, rm.i0, rm.m, rm.n / 2,
-                           h->eps_blk, signs_out, dots_export, h->uniforms, h->ws);
+    auto by_rule = [&](auto sb) {
+        constexpr int SB = decltype(sb)::value;
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)h->walks), dim3(kWalkThreads), 0, h->stream, gram,
+                               h->dot_partials, dot_groups, c.sp, cur, half_n, h->eps_blk, signs_out, dots_out,
+                               h->uniforms, h->ws);
+        };
+        if (h->uniforms) launch(chain_walk<SB, true>);
+        else launch(chain_walk<SB, false>);
     };
-    if (h->uniforms) resolve(resolve_signs<BB, true, 1>);
-    else resolve(resolve_signs<BB, false, 1>);
-    HIP_TRY(h, hipGetLastError());
-    return CDGRAB_OK;
-}
-
-// Gram tiles of `count` blocks (row maps already in h->maps) into gram_out[count][PART].
-template <int BB>
-int run_grams_ahead(cdgrab_handle *h, int64_t d, const cdgrab_plan &plan, int64_t count, int groups,
-                    double *gram_out) {
-    constexpr int part = PartLayout<BB>::PART;
-    const dim3 grid((unsigned)groups, (unsigned)count, (unsigned)h->walks), block(kThreads);
-    MARK(h, 2, kPass1);
-    const int64_t ntiles = (d + plan.tile_elems - 1) / plan.tile_elems;
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, h->maps, h->r_sum, h->partials, ntiles, count);
-    };
-    if (plan.tile_elems == 128) {
-        switch (row_form(plan.vector_width, d)) {
-            case kAligned: launch(gram_batched<BB, 4, 128>); break;
-            case kAnyRow: launch(gram_batched<BB, 2, 128>); break;
-            default: launch(gram_batched<BB, 1, 128>); break;
-        }
-    } else {
-        switch (row_form(plan.vector_width, d)) {
-            case kAligned: launch(gram_batched<BB, 4, 64>); break;
-            case kAnyRow: launch(gram_batched<BB, 2, 64>); break;
-            default: launch(gram_batched<BB, 1, 64>); break;
-        }
-    }
-    MARK(h, 2, kReduce);
-    hipLaunchKernelGGL(reduce_batched, dim3((part + kThreads - 1) / kThreads, (unsigned)count, (unsigned)h->walks),
-                       block, 0, h->stream, h->partials, gram_out, part, groups, h->ws.gram);
+    if (c.sp > 128) by_rule(std::integral_constant<int, 256>{});
+    else if (c.sp > 64) by_rule(std::integral_constant<int, 128>{});
+    else by_rule(std::integral_constant<int, 64>{});
     HIP_TRY(h, hipGetLastError());
     return CDGRAB_OK;
 }
@@ -558,7 +605,7 @@ int cdgrab_destroy(cdgrab_handle *h) {
     if (h->staging) (void)hipFree(h->staging);
     if (h->gram_all) (void)hipFree(h->gram_all);
     if (h->dot_partials) (void)hipFree(h->dot_partials);
-    if (h->maps) (void)hipFree(h->maps);
+    if (h->gram_parts) (void)hipFree(h->gram_parts);
     delete h;
     return CDGRAB_OK;
 }
@@ -633,8 +680,7 @@ struct Epoch {
     int bb = 0;
     bool fused = false;        // apply inside the next block's dot/Gram launch
     bool ahead = false;        // Gram matrices of a batch of blocks ahead, one launch per block
-    int64_t batch = 0;         // blocks per ahead-launch (a staging chunk's blocks when streaming)
-    int gram_groups = 1;       // workgroups per block of the ahead-launch
+    ChainPlan chain{};         // its steps
     int64_t staging_chunk = 0; // floats per staging chunk
     int64_t center_off = 0;    // element offset of center_row from grads
     int64_t walks = 1;         // independent walks of this shape run side by side (m == 1, dense, Grams ahead)
@@ -670,8 +716,8 @@ int Epoch::prepare() {
         align = (a % 16 == 0) ? 16 : (a % 8 == 0) ? 8 : 4;
         if (a % 4) return fail(h, CDGRAB_EINVAL, "cdgrab_balance_epoch: grads is not 4-byte aligned");
     }
-    // (Every one of the d/64 workgroups of a block's launch in the Grams-ahead form reads all
-    // d/64 x Bb partial dots of the previous block: quadratic in d, hence refused for long rows.)
+    // (One workgroup adds all d / kStepElems shares of a step's dots in the Grams-ahead form, and its
+    // Gram tiles are bound by double MFMA work, not bytes: hence refused for long rows.)
     if (h->gram_mode == 2 && !streamed && d > kGramAheadLimitD)
         return fail(h, CDGRAB_EINVAL, "cdgrab_balance_epoch: gram_mode 2 is for rows up to %lld elements (d=%lld)",
                     (long long)kGramAheadLimitD, (long long)d);
@@ -683,7 +729,7 @@ int Epoch::prepare() {
     staging_chunk = chunk_pairs * 2 * d;
     fused = plan.fused_apply != 0;
     ahead = plan.gram_ahead != 0;
-    batch = streamed ? chunk_pairs / bb : std::min<int64_t>(plan.blocks, kGramBatch);
+    if (ahead) chain = plan_chain(plan.pairs, d, walks, streamed ? chunk_pairs : 0, h->num_cu);
 
     // workspace (per walk when several independent walks run side by side)
     const int64_t r_pad = round_up(d, kPadE);
@@ -695,7 +741,7 @@ int Epoch::prepare() {
     rc = ensure(h, h->partials, h->partials_cap, (int64_t)plan.pass1_groups * part_size(bb));
     if (rc) return rc;
     if (!h->reduced) { fixed_cap = 0; rc = ensure(h, h->reduced, fixed_cap, (int64_t)kReduceSlices * PartLayout<64>::PART); if (rc) return rc; }
-    rc = ensure(h, h->eps_blk, h->eps_cap, walks * kMaxBlockPairs);
+    rc = ensure(h, h->eps_blk, h->eps_cap, ahead ? walks * kMaxStepPairs : (int64_t)kMaxBlockPairs);
     if (rc) return rc;
     if (streamed) {
         // two chunks when a launch reads the previous block's rows as well: they must outlive the next fill
@@ -704,26 +750,16 @@ int Epoch::prepare() {
     }
     h->ws = WalkStrides{};
     if (ahead) {
-        // enough workgroups to fill the chip, at least one tile each
-        const int64_t ntiles = (d + plan.tile_elems - 1) / plan.tile_elems;
-        const int64_t launches = batch * walks;
-        gram_groups = (int)std::max<int64_t>(1, std::min<int64_t>(ntiles, (4 * h->num_cu + launches - 1) / launches));
-        const int64_t dot_len = (d + kSplitElems - 1) / kSplitElems * bb;
-        rc = ensure(h, h->partials, h->partials_cap, walks * batch * gram_groups * part_size(bb));
+        rc = ensure(h, h->gram_all, h->gram_all_cap, chain.gram_len);
         if (rc) return rc;
-        rc = ensure(h, h->gram_all, h->gram_all_cap, walks * (batch + 1) * part_size(bb));
-        if (rc) return rc;
-        rc = ensure(h, h->dot_partials, h->dot_partials_cap, walks * 2 * dot_len);
-        if (rc) return rc;
-        rc = ensure(h, h->maps, h->maps_cap, walks * batch);
+        if (chain.parts_len > 0 && (rc = ensure(h, h->gram_parts, h->gram_parts_cap, chain.parts_len))) return rc;
+        rc = ensure(h, h->dot_partials, h->dot_partials_cap, chain.dots_len);
         if (rc) return rc;
         if (walks > 1) {
             h->ws.rows = n * d;
             h->ws.r = r_pad;
-            h->ws.gram = (batch + 1) * part_size(bb);
-            h->ws.dots = 2 * dot_len;
+            h->ws.dots = chain.groups * (int64_t)chain.sp;
             h->ws.out = n / 2;
-            h->ws.maps = batch;
         }
     }
     h->walks = walks;
@@ -731,7 +767,7 @@ int Epoch::prepare() {
     center_off = center_row ? (int64_t)((reinterpret_cast<intptr_t>(center_row) - reinterpret_cast<intptr_t>(grads)) /
                                         (intptr_t)sizeof(float))
                             : 0;
-    rm.d = d; rm.m = (int32_t)m; rm.n = n; rm.dense = (!streamed && !center_row) ? 1 : 0;
+    rm.d = d; rm.m = (int32_t)m; rm.n = n;
     rm.k0 = 0; rm.i0 = 0; rm.nb = 0;
     // (a copy of this map stands in for "no previous block": its rows must be readable)
     rm.base = streamed ? h->staging : grads;
@@ -776,56 +812,51 @@ int Epoch::generate(int64_t first, int64_t count, float *stage_buf) {
     return CDGRAB_OK;
 }
 
-// Gram matrices of a batch of blocks in one launch, then one launch per block.  Slot 0 of
-// gram_all carries the last block of the previous batch over; the per-workgroup dots
-// alternate between two arrays (a launch reads the previous block's while it writes its own).
+// Gram tiles of a batch of steps in one launch, then two launches per step; the step before is
+// applied in the first of them.
 int Epoch::chain_ahead() {
-    const int64_t part = part_size(bb);
-    const int64_t dot_len = (d + kSplitElems - 1) / kSplitElems * bb;
-    int64_t blk = 0, prev_slot = 0, batch_index = 0;
+    const int form = row_form(plan.vector_width, d);
+    const int64_t batch_pairs = streamed ? chunk_pairs : chain.steps * chain.sp;
+    StepRows prev_step{}, none{};
+    none.d = d;
+    int64_t batch_index = 0;
     int rc = CDGRAB_OK;
-    for (int64_t b0 = 0; b0 < plan.blocks; b0 += batch, ++batch_index) {
-        const int64_t count = std::min<int64_t>(batch, plan.blocks - b0);
-        const int64_t first = b0 * bb, cnt_pairs = std::min<int64_t>(count * bb, plan.pairs - first);
+    for (int64_t first = 0; first < plan.pairs; first += batch_pairs, ++batch_index) {
+        const int64_t pairs = std::min(batch_pairs, plan.pairs - first);
         float *stage_buf = streamed ? h->staging + (batch_index & 1) * staging_chunk : nullptr;
-        if (streamed && (rc = generate(first, cnt_pairs, stage_buf))) return rc;
+        if (streamed && (rc = generate(first, pairs, stage_buf))) return rc;
         MARK(h, 1, kBalance);
-        if (b0 > 0)
-            for (int64_t w = 0; w < walks; ++w)
-                HIP_TRY(h, hipMemcpyAsync(h->gram_all + w * h->ws.gram, h->gram_all + w * h->ws.gram + prev_slot * part,
-                                          (size_t)part * sizeof(double), hipMemcpyDeviceToDevice, h->stream));
-        hipLaunchKernelGGL(fill_row_maps, dim3((unsigned)count, (unsigned)walks), dim3(kMaxBlockPairs), 0, h->stream,
-                           h->maps, streamed ? stage_buf : grads, m, n, d, bb, first, plan.pairs, center_off,
-                           streamed ? 2 : (center_row ? 1 : 0), h->ws.rows);
-        double *gram_out = h->gram_all + part;
-        rc = BY_BLOCK_PAIRS(bb, run_grams_ahead<64>(h, d, plan, count, gram_groups, gram_out),
-                            run_grams_ahead<32>(h, d, plan, count, gram_groups, gram_out),
-                            run_grams_ahead<16>(h, d, plan, count, gram_groups, gram_out));
-        if (rc) return rc;
-        for (int64_t b = 0; b < count; ++b, ++blk) {
-            const int64_t p0 = (b0 + b) * bb;
-            set_block(p0, std::min<int64_t>(bb, plan.pairs - p0), streamed ? stage_buf + (p0 - first) * 2 * d : nullptr);
-            // block b of this batch sits in slot b + 1, its predecessor in slot b
-            const double *prev_gram = h->gram_all + b * part;
-            const double *dots_in = h->dot_partials + ((blk + 1) & 1) * dot_len;
-            double *dots_mine = h->dot_partials + (blk & 1) * dot_len;
-            rc = BY_BLOCK_PAIRS(bb,
-                                run_block_ahead<64>(h, rm, prev, plan, prev_gram, dots_in, dots_mine, signs_out, dots_out),
-                                run_block_ahead<32>(h, rm, prev, plan, prev_gram, dots_in, dots_mine, signs_out, dots_out),
-                                run_block_ahead<16>(h, rm, prev, plan, prev_gram, dots_in, dots_mine, signs_out, dots_out));
-            if (rc) return rc;
-            prev.rm = rm;
-            have_prev = true;
+        StepRows rows{};
+        rows.base = streamed ? stage_buf : center_row ? grads + first * d : grads;
+        rows.centre = center_row;
+        rows.d = d;
+        rows.n = n;
+        rows.k0 = first / m;
+        rows.i0 = (int32_t)(first % m);
+        rows.m = (int32_t)m;
+        rows.layout = streamed ? kStaged : center_row ? kCentred : kDense;
+        // (a chunk of streamed pairs may hold more steps than one launch of Gram tiles)
+        for (int64_t at = 0; at < pairs; at += chain.steps * chain.sp) {
+            const int64_t count = std::min<int64_t>(chain.steps * chain.sp, pairs - at);
+            const StepRows part = step_at(rows, at, 0);
+            if ((rc = run_gram_tiles(h, part, count, chain, form))) return rc;
+            const int64_t steps = (count + chain.sp - 1) / chain.sp;
+            h->ws.gram = walks > 1 ? steps * chain.tiles * kTileEntries : 0;
+            for (int64_t s = 0; s < steps; ++s) {
+                StepRows cur = step_at(part, s * chain.sp, (int)std::min<int64_t>(chain.sp, count - s * chain.sp));
+                const bool has_prev = prev_step.nb > 0;
+                if (has_prev && (rc = run_step_wide(h, cur, prev_step, chain, form))) return rc;
+                // (output slots are counted from the flattened pair, whatever the layout)
+                cur.k0 = (first + at + s * chain.sp) / m;
+                cur.i0 = (int32_t)((first + at + s * chain.sp) % m);
+                if ((rc = run_step_walk(h, cur, chain, h->gram_all + s * chain.tiles * kTileEntries,
+                                        has_prev ? chain.groups : 0, n / 2, signs_out, dots_out))) return rc;
+                prev_step = cur;
+            }
         }
-        prev_slot = count;
     }
-    // the last block: the resolver alone (its apply follows)
-    const double *gram = h->gram_all + prev_slot * part;
-    const double *dots_in = h->dot_partials + ((blk + 1) & 1) * dot_len;
     MARK(h, 1, kBalance);
-    return BY_BLOCK_PAIRS(bb, run_resolve_ahead<64>(h, prev.rm, gram, dots_in, signs_out, dots_out),
-                          run_resolve_ahead<32>(h, prev.rm, gram, dots_in, signs_out, dots_out),
-                          run_resolve_ahead<16>(h, prev.rm, gram, dots_in, signs_out, dots_out));
+    return run_step_wide(h, none, prev_step, chain, form);
 }
 
 // Block by block: dot/Gram launch (with the previous block's apply inside it when
@@ -861,7 +892,7 @@ int Epoch::chain_blocks() {
 
 // The epoch's last block has no successor to apply it.
 int Epoch::apply_last() {
-    if (!(fused || ahead) || !have_prev) return CDGRAB_OK;
+    if (!fused || !have_prev) return CDGRAB_OK;
     MARK(h, 1, kBalance);
     return BY_BLOCK_PAIRS(bb, apply_block_vw<64>(h, prev.rm, plan), apply_block_vw<32>(h, prev.rm, plan),
                           apply_block_vw<16>(h, prev.rm, plan));
@@ -1150,15 +1181,18 @@ int cdgrab_train_epoch_softmax(cdgrab_handle *h, int64_t m, int64_t n, int64_t i
     TrainCtx ctx{h, m, n, in_dim, classes, (in_dim + 1) * classes, X, y, perm_in, W, velocity,
                  grads_out, loss_out, lr, momentum};
     // a chunk is a whole number of step pairs: about one block's worth of pairs, at least one step pair;
-    // for short rows eight blocks' worth (or as many as make it whole blocks), so that the Gram
-    // matrices of a chunk are computed in one launch and a block costs a single one
+    // for short rows a few hundred pairs and whole steps of the chain (whole blocks where the rows are
+    // too long for that), so that the Gram matrices of a chunk are computed in one launch
     const int64_t step_pairs = std::max<int64_t>(1, 64 / m);
     int64_t chunk = step_pairs * m;
-    if (ctx.d <= kGramAheadMaxD && h->gram_mode != 1 && h->apply_mode == 0) {
-        const int64_t bb = pick_block_pairs(m * (n / 2), ctx.d, h->block_pairs_opt);
-        int64_t k = 8;
-        if ((chunk * k) % bb != 0) k = bb;  // chunk * bb is a multiple of bb
-        if (chunk * k / bb <= kGramBatch && chunk * k * 2 * ctx.d * 4 * 2 <= ((int64_t)1 << 30)) chunk *= k;
+    if (ctx.d <= kChunkAheadMaxD && h->gram_mode != 1 && h->apply_mode == 0) {
+        const int64_t pairs = m * (n / 2), bb = pick_block_pairs(pairs, ctx.d, h->block_pairs_opt);
+        const int64_t sp = plan_chain(pairs, ctx.d, 1, 0, h->num_cu).sp;
+        const int64_t bytes = chunk * 2 * ctx.d * 4 * 2;  // of both staging chunks, per multiple
+        int64_t k = sp / std::gcd(chunk, sp);             // whole steps ...
+        k *= std::max<int64_t>(1, 512 / (chunk * k));     // ... and at least about 512 pairs
+        if (bytes * k > ((int64_t)1 << 30) || chunk * k / bb > kGramBatch) k = bb / std::gcd(chunk, bb);
+        if (chunk * k / bb <= kGramBatch && bytes * k <= ((int64_t)1 << 30)) chunk *= k;
     }
     return balance_epoch_impl(h, m, n, ctx.d, nullptr, train_generate, &ctx, chunk, perm_in,
                               signs_out, perm_out, nullptr, nullptr, nullptr);
