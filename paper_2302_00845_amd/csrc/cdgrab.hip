@@ -19,6 +19,7 @@
 #include "chain_kernels.hpp"
 #include "order_kernels.hpp"
 #include "herding_kernels.hpp"
+#include "narrow_kernels.hpp"
 
 using namespace cdgrab;
 
@@ -173,6 +174,10 @@ double step_cost_us(int64_t sp, int64_t d, int64_t walks) {
 
 ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pairs, int num_cu) {
     ChainPlan c{};
+    if (d <= kNarrowMaxD) {  // a walk is one workgroup: no workspace, blocks of one tile
+        c.sp = kTilePairs;
+        return c;
+    }
     const int64_t longest = chunk_pairs > 0 ? std::min(chunk_pairs, pairs) : pairs;
     double best = 0.0;
     for (int sp = kTilePairs; sp <= kMaxStepPairs; sp *= 2) {
@@ -388,6 +393,34 @@ void by_row_form(int form, F &&launch) {
         case kAnyRow: launch(std::integral_constant<int, kAnyRow>{}); break;
         default: launch(std::integral_constant<int, kTiny>{}); break;
     }
+}
+
+// All of `pairs` consecutive pairs of rows of at most kNarrowMaxD elements.
+int run_narrow(cdgrab_handle *h, const StepRows &rows, int64_t first, int64_t pairs, int64_t half_n,
+               int8_t *signs_out, double *dots_out) {
+    MARK(h, 2, kPass1);
+    for (int64_t at = 0; at < pairs; at += kNarrowMaxPairs) {
+        StepRows part = step_at(rows, at, 0);
+        part.k0 = (first + at) / rows.m;  // (output slots are counted from the flattened pair, whatever the layout)
+        part.i0 = (int32_t)((first + at) % rows.m);
+        const int count = (int)std::min<int64_t>(kNarrowMaxPairs, pairs - at);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)h->walks), dim3(kNarrowThreads), 0, h->stream, part, count, half_n,
+                               h->r_sum, signs_out, dots_out, h->uniforms, h->ws);
+        };
+        auto by_rule = [&](auto dp, auto vw) {
+            constexpr int DP = decltype(dp)::value, VW = decltype(vw)::value;
+            if (h->uniforms) launch(narrow_walk<DP, VW, true>);
+            else launch(narrow_walk<DP, VW, false>);
+        };
+        const std::integral_constant<int, kAnyRow> any{};
+        if (rows.d < 4) by_rule(std::integral_constant<int, 16>{}, std::integral_constant<int, kTiny>{});
+        else if (rows.d <= 16) by_rule(std::integral_constant<int, 16>{}, any);
+        else if (rows.d <= 32) by_rule(std::integral_constant<int, 32>{}, any);
+        else by_rule(std::integral_constant<int, 64>{}, any);
+    }
+    HIP_TRY(h, hipGetLastError());
+    return CDGRAB_OK;
 }
 
 // Gram tiles of `steps` steps per walk, the first at rows, into h->gram_all.
@@ -750,11 +783,9 @@ int Epoch::prepare() {
     }
     h->ws = WalkStrides{};
     if (ahead) {
-        rc = ensure(h, h->gram_all, h->gram_all_cap, chain.gram_len);
-        if (rc) return rc;
+        if (chain.gram_len > 0 && (rc = ensure(h, h->gram_all, h->gram_all_cap, chain.gram_len))) return rc;
         if (chain.parts_len > 0 && (rc = ensure(h, h->gram_parts, h->gram_parts_cap, chain.parts_len))) return rc;
-        rc = ensure(h, h->dot_partials, h->dot_partials_cap, chain.dots_len);
-        if (rc) return rc;
+        if (chain.dots_len > 0 && (rc = ensure(h, h->dot_partials, h->dot_partials_cap, chain.dots_len))) return rc;
         if (walks > 1) {
             h->ws.rows = n * d;
             h->ws.r = r_pad;
@@ -816,7 +847,8 @@ int Epoch::generate(int64_t first, int64_t count, float *stage_buf) {
 // applied in the first of them.
 int Epoch::chain_ahead() {
     const int form = row_form(plan.vector_width, d);
-    const int64_t batch_pairs = streamed ? chunk_pairs : chain.steps * chain.sp;
+    const bool narrow = d <= kNarrowMaxD;
+    const int64_t batch_pairs = streamed ? chunk_pairs : narrow ? plan.pairs : chain.steps * chain.sp;
     StepRows prev_step{}, none{};
     none.d = d;
     int64_t batch_index = 0;
@@ -835,6 +867,10 @@ int Epoch::chain_ahead() {
         rows.i0 = (int32_t)(first % m);
         rows.m = (int32_t)m;
         rows.layout = streamed ? kStaged : center_row ? kCentred : kDense;
+        if (narrow) {
+            if ((rc = run_narrow(h, rows, first, pairs, n / 2, signs_out, dots_out))) return rc;
+            continue;
+        }
         // (a chunk of streamed pairs may hold more steps than one launch of Gram tiles)
         for (int64_t at = 0; at < pairs; at += chain.steps * chain.sp) {
             const int64_t count = std::min<int64_t>(chain.steps * chain.sp, pairs - at);
@@ -855,6 +891,7 @@ int Epoch::chain_ahead() {
             }
         }
     }
+    if (narrow) return CDGRAB_OK;
     MARK(h, 1, kBalance);
     return run_step_wide(h, none, prev_step, chain, form);
 }

@@ -34,6 +34,16 @@ def test_dense_steps_match_oracle(lib, m, n, d):
     assert rep["r64_rel_l2"] == 0.0 and rep["dots_max_abs_err"] == 0.0
 
 
+@pytest.mark.parametrize("m,n,d", [
+    (1, 34, 1), (1, 126, 2), (1, 128, 3), (1, 130, 4), (2, 128, 5), (3, 86, 15), (5, 52, 17), (1, 382, 31), (1, 384, 32),
+    (1, 386, 33), (7, 74, 63), (11, 48, 64), (300, 4, 64),
+])
+def test_narrow_rows_match_oracle(lib, m, n, d):
+    """Rows of at most 64 elements: the whole walk in one workgroup, blocks of 64 pairs, the padded
+    row lengths 16, 32 and 64."""
+    test_dense_steps_match_oracle(lib, m, n, d)
+
+
 @pytest.mark.parametrize("n,d", [(64, 17), (65, 16), (129, 40), (300, 16), (513, 5), (300, 12_000)])
 def test_centred_steps_match_oracle(lib, n, d):
     g = workloads.integer_rows(n, 1, n, d, 3)[0]
