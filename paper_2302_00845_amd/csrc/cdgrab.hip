@@ -20,6 +20,7 @@
 #include "order_kernels.hpp"
 #include "herding_kernels.hpp"
 #include "narrow_kernels.hpp"
+#include "train_kernels.hpp"
 
 using namespace cdgrab;
 
@@ -60,7 +61,10 @@ struct cdgrab_handle {
     int64_t walks = 1;                                    // independent walks per launch while such an epoch runs
     WalkStrides ws{};                                     // their strides (all zero for one walk)
     float *zero_row = nullptr; int64_t zero_row_cap = 0;  // a zero vector standing in for a missing stale mean
-    float *train_delta = nullptr; int64_t train_delta_cap = 0;  // [m][classes] softmax deltas of one step
+    float *train_delta = nullptr; int64_t train_delta_cap = 0;  // [m][classes] softmax deltas of one step (of a block of steps)
+    int64_t *train_order = nullptr; int64_t train_order_cap = 0;  // rows of the examples in visiting order
+    double *train_base = nullptr; int64_t train_base_cap = 0;     // logits of a block's examples at its first weights
+    double *train_gram = nullptr; int64_t train_gram_cap = 0;     // Gram tiles of a chunk's features
     int32_t *train_perm = nullptr; int64_t train_perm_cap = 0;  // spare [m][n] order of the multi-epoch driver
     int8_t *train_signs = nullptr; int64_t train_signs_cap = 0; // its [m][n/2] signs when the caller wants none
     double *herd_ws = nullptr; int64_t herd_cap = 0;      // herding evaluator: segment sums, starts, mean
@@ -172,6 +176,21 @@ double step_cost_us(int64_t sp, int64_t d, int64_t walks) {
     return launches + rows + gram;
 }
 
+// Workgroups per Gram tile: the launch takes whole rounds of two workgroups per CU, each as long as its
+// share of a tile; shares cost a write and two reads of a tile each.  At least four k-tiles per share.
+int pick_ksplit(int64_t tiles, int64_t d, int num_cu) {
+    const int64_t ktiles = (d + kGramTE - 1) / kGramTE, slots = 2 * (int64_t)num_cu;
+    const double tile_us = 2.0 * kTileEntries * (double)d / (45e6 / (double)slots);
+    double least = 0.0;
+    int best = 1;
+    for (int64_t ks = 1; ks <= std::max<int64_t>(1, std::min<int64_t>(ktiles / 4, 64)); ++ks) {
+        const double rounds = (double)((tiles * ks + slots - 1) / slots) / (double)ks;
+        const double us = rounds * tile_us + (ks > 1 ? 4.0 + (double)(tiles * (2 * ks + 1)) * kTileEntries * 8.0 / 4e6 : 0.0);
+        if (ks == 1 || us < 0.98 * least) { least = us; best = (int)ks; }
+    }
+    return best;
+}
+
 ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pairs, int num_cu) {
     ChainPlan c{};
     if (d <= kNarrowMaxD) {  // a walk is one workgroup: no workspace, blocks of one tile
@@ -190,16 +209,7 @@ ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pair
     const int64_t per_step = walks * c.tiles * kTileEntries;
     const int64_t total = (longest + c.sp - 1) / c.sp;
     c.steps = std::max<int64_t>(1, std::min<int64_t>(total, kGramBytes / 8 / per_step));
-    // Workgroups per tile: the launch takes whole rounds of two workgroups per CU, each as long as its
-    // share of a tile; shares cost a write and two reads of a tile each.  At least four k-tiles per share.
-    const int64_t ktiles = (d + kGramTE - 1) / kGramTE, wgs = c.steps * walks * c.tiles, slots = 2 * (int64_t)num_cu;
-    const double tile_us = 2.0 * kTileEntries * (double)d / (45e6 / (double)slots);
-    double least = 0.0;
-    for (int64_t ks = 1; ks <= std::max<int64_t>(1, std::min<int64_t>(ktiles / 4, 64)); ++ks) {
-        const double rounds = (double)((wgs * ks + slots - 1) / slots) / (double)ks;
-        const double us = rounds * tile_us + (ks > 1 ? 4.0 + (double)(wgs * (2 * ks + 1)) * kTileEntries * 8.0 / 4e6 : 0.0);
-        if (ks == 1 || us < 0.98 * least) { least = us; c.ksplit = (int)ks; }
-    }
+    c.ksplit = pick_ksplit(c.steps * walks * c.tiles, d, num_cu);
     c.groups = (int)((d + kStepElems - 1) / kStepElems);
     c.gram_len = c.steps * per_step;
     c.parts_len = c.ksplit > 1 ? c.gram_len * c.ksplit : 0;
@@ -423,8 +433,24 @@ int run_narrow(cdgrab_handle *h, const StepRows &rows, int64_t first, int64_t pa
     return CDGRAB_OK;
 }
 
-// Gram tiles of `steps` steps per walk, the first at rows, into h->gram_all.
-int run_gram_tiles(cdgrab_handle *h, const StepRows &rows, int64_t pairs, const ChainPlan &c, int form) {
+// Gram tiles of `gb.units` units into out (through parts when the elements of a tile are shared).
+template <bool SINGLE>
+int run_gram_tiles(cdgrab_handle *h, const GramBatch &gb, double *out, double *parts, int form) {
+    const int64_t padded = gb.units >= 8 ? round_up(gb.units, 8) : gb.units;
+    by_row_form(form, [&](auto vw) {
+        hipLaunchKernelGGL((gram_tiles<decltype(vw)::value, SINGLE>),
+                           dim3((unsigned)(padded * gb.tiles), (unsigned)gb.ksplit), dim3(kThreads), 0, h->stream, gb,
+                           gb.ksplit > 1 ? parts : out);
+    });
+    if (gb.ksplit > 1)
+        hipLaunchKernelGGL(gram_reduce, dim3((unsigned)(gb.units * gb.tiles), kTileEntries / 2 / kThreads),
+                           dim3(kThreads), 0, h->stream, parts, out, gb.ksplit);
+    HIP_TRY(h, hipGetLastError());
+    return CDGRAB_OK;
+}
+
+// Those of the steps of `pairs` pairs per walk, the first at rows, into h->gram_all.
+int run_step_grams(cdgrab_handle *h, const StepRows &rows, int64_t pairs, const ChainPlan &c, int form) {
     GramBatch gb{};
     gb.rows = rows;
     gb.pairs = pairs;
@@ -435,19 +461,8 @@ int run_gram_tiles(cdgrab_handle *h, const StepRows &rows, int64_t pairs, const 
     gb.tiles = c.tiles;
     gb.ksplit = c.ksplit;
     gb.ktiles = (int32_t)((rows.d + kGramTE - 1) / kGramTE);
-    const int64_t padded = gb.units >= 8 ? round_up(gb.units, 8) : gb.units;
     MARK(h, 2, kPass1);
-    by_row_form(form, [&](auto vw) {
-        hipLaunchKernelGGL((gram_tiles<decltype(vw)::value>), dim3((unsigned)(padded * c.tiles), (unsigned)c.ksplit),
-                           dim3(kThreads), 0, h->stream, gb, c.ksplit > 1 ? h->gram_parts : h->gram_all);
-    });
-    if (c.ksplit > 1) {
-        MARK(h, 2, kReduce);
-        hipLaunchKernelGGL(gram_reduce, dim3((unsigned)(gb.units * c.tiles), kTileEntries / 2 / kThreads), dim3(kThreads),
-                           0, h->stream, h->gram_parts, h->gram_all, c.ksplit);
-    }
-    HIP_TRY(h, hipGetLastError());
-    return CDGRAB_OK;
+    return run_gram_tiles<false>(h, gb, h->gram_all, h->gram_parts, form);
 }
 
 // Wide launch of a step: applies prev (if it has pairs), dots of cur (if it has pairs).
@@ -632,6 +647,9 @@ int cdgrab_destroy(cdgrab_handle *h) {
     if (h->mean_ws) (void)hipFree(h->mean_ws);
     if (h->herd_ws) (void)hipFree(h->herd_ws);
     if (h->train_delta) (void)hipFree(h->train_delta);
+    if (h->train_order) (void)hipFree(h->train_order);
+    if (h->train_base) (void)hipFree(h->train_base);
+    if (h->train_gram) (void)hipFree(h->train_gram);
     if (h->train_perm) (void)hipFree(h->train_perm);
     if (h->train_signs) (void)hipFree(h->train_signs);
     if (h->zero_row) (void)hipFree(h->zero_row);
@@ -875,7 +893,7 @@ int Epoch::chain_ahead() {
         for (int64_t at = 0; at < pairs; at += chain.steps * chain.sp) {
             const int64_t count = std::min<int64_t>(chain.steps * chain.sp, pairs - at);
             const StepRows part = step_at(rows, at, 0);
-            if ((rc = run_gram_tiles(h, part, count, chain, form))) return rc;
+            if ((rc = run_step_grams(h, part, count, chain, form))) return rc;
             const int64_t steps = (count + chain.sp - 1) / chain.sp;
             h->ws.gram = walks > 1 ? steps * chain.tiles * kTileEntries : 0;
             for (int64_t s = 0; s < steps; ++s) {
@@ -1171,13 +1189,63 @@ struct TrainCtx {
     const float *X; const int32_t *y; const int32_t *perm_in;
     float *W, *velocity, *grads_out, *loss_out;
     float lr, momentum;
+    int64_t block_steps;  // steps per block of train_kernels.hpp; 0: a launch pair per step
+    int tiles, ksplit;    // Gram tiles per block of steps, workgroups per tile
 };
+
+// Workers and classes that the blocks of steps are for: at least four steps per block and one MFMA column
+// tile of classes.  (16 workers, 784 -> 10: 2.1 us per step against 11.6 in a launch pair per step.)
+int64_t train_block_steps(int64_t m, int64_t n, int64_t classes) {
+    const bool fits = m <= kSolveWorkers && classes <= kSolveClasses && n <= INT32_MAX / m;
+    return fits ? std::min<int64_t>((kSolveExamples / m) & ~(int64_t)1, n) : 0;
+}
+
+// The steps j .. j_end - 1 of a chunk, a block at a time.
+int train_blocks(TrainCtx *c, int64_t j, int64_t j_end, int64_t k_first, float *staging) {
+    cdgrab_handle *h = c->h;
+    const int64_t S = c->block_steps, m = c->m, d = c->in_dim;
+    GramBatch gb{};
+    gb.rows.base = c->X;
+    gb.rows.d = d;
+    gb.rows.m = 1;
+    gb.rows.layout = kStaged;
+    gb.examples = h->train_order + j * m;
+    gb.pairs = (j_end - j) * m;
+    gb.sp = (int32_t)(S * m);
+    gb.steps = gb.units = (int32_t)((j_end - j + S - 1) / S);
+    gb.tiles = c->tiles;
+    gb.ksplit = c->ksplit;
+    gb.ktiles = (int32_t)((d + kGramTE - 1) / kGramTE);
+    const int form = row_form((d % 4 == 0 && reinterpret_cast<uintptr_t>(c->X) % 16 == 0) ? 4 : 1, d);
+    const int rc = run_gram_tiles<true>(h, gb, h->train_gram, h->gram_parts, form);
+    if (rc) return rc;
+    for (int64_t b = 0; b < gb.units; ++b, j += S) {
+        const int steps = (int)std::min(S, j_end - j), examples = (int)(steps * m);
+        const int64_t *order = h->train_order + j * m;
+        hipLaunchKernelGGL(train_base_logits, dim3((unsigned)((examples + 15) / 16)), dim3(1024), 0, h->stream, c->X, order,
+                           examples, c->W, c->velocity, (int)d, (int)c->classes, h->train_base);
+        auto solve = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(1), dim3(256), 0, h->stream, h->train_gram + b * gb.tiles * kTileEntries,
+                               h->train_base, c->y, order, h->train_delta, c->loss_out, (int)m, steps, c->n, j,
+                               (int)c->classes, (double)c->lr, (double)c->momentum);
+        };
+        if (m <= 4) solve(train_solve<1>);
+        else if (m <= 8) solve(train_solve<2>);
+        else solve(train_solve<4>);
+        hipLaunchKernelGGL(train_update_block, dim3((unsigned)((c->d + 63) / 64)), dim3(1024), 0, h->stream, c->X, order,
+                           h->train_delta, c->W, c->velocity, staging, c->grads_out, (int)m, steps, c->n, j, k_first,
+                           (int)d, (int)c->classes, c->lr, c->momentum);
+    }
+    HIP_TRY(h, hipGetLastError());
+    return CDGRAB_OK;
+}
 
 int train_generate(void *vctx, int64_t first_pair, int64_t count, float *staging, void *stream) {
     TrainCtx *c = static_cast<TrainCtx *>(vctx);
     cdgrab_handle *h = c->h;
     if (first_pair % c->m != 0 || count % c->m != 0) return 1;  // chunks are whole step pairs
     const int64_t k_first = first_pair / c->m, k_count = count / c->m;
+    if (c->block_steps > 0) return train_blocks(c, 2 * k_first, 2 * (k_first + k_count), k_first, staging);
     const size_t lds = (size_t)c->classes * sizeof(float);
     for (int64_t j = 2 * k_first; j < 2 * (k_first + k_count); ++j) {
         hipLaunchKernelGGL(train_step_delta, dim3((unsigned)c->m), dim3(kDeltaWaves * 64), lds,
@@ -1213,10 +1281,11 @@ int cdgrab_train_epoch_softmax(cdgrab_handle *h, int64_t m, int64_t n, int64_t i
     if (momentum != 0.0f && !velocity)
         return fail(h, CDGRAB_EINVAL, "cdgrab_train_epoch_softmax: momentum needs a velocity buffer");
     HIP_TRY(h, hipSetDevice(h->device));
-    int rc = ensure(h, h->train_delta, h->train_delta_cap, m * classes);
+    const int64_t block_steps = train_block_steps(m, n, classes);
+    int rc = ensure(h, h->train_delta, h->train_delta_cap, block_steps > 0 ? block_steps * m * classes : m * classes);
     if (rc) return rc;
     TrainCtx ctx{h, m, n, in_dim, classes, (in_dim + 1) * classes, X, y, perm_in, W, velocity,
-                 grads_out, loss_out, lr, momentum};
+                 grads_out, loss_out, lr, momentum, block_steps, 0, 1};
     // a chunk is a whole number of step pairs: about one block's worth of pairs, at least one step pair;
     // for short rows a few hundred pairs and whole steps of the chain (whole blocks where the rows are
     // too long for that), so that the Gram matrices of a chunk are computed in one launch
@@ -1227,9 +1296,22 @@ int cdgrab_train_epoch_softmax(cdgrab_handle *h, int64_t m, int64_t n, int64_t i
         const int64_t sp = plan_chain(pairs, ctx.d, 1, 0, h->num_cu).sp;
         const int64_t bytes = chunk * 2 * ctx.d * 4 * 2;  // of both staging chunks, per multiple
         int64_t k = sp / std::gcd(chunk, sp);             // whole steps ...
-        k *= std::max<int64_t>(1, 512 / (chunk * k));     // ... and at least about 512 pairs
+        k *= std::max<int64_t>(1, 1024 / (chunk * k));    // ... and about 1024 pairs
         if (bytes * k > ((int64_t)1 << 30) || chunk * k / bb > kGramBatch) k = bb / std::gcd(chunk, bb);
         if (chunk * k / bb <= kGramBatch && bytes * k <= ((int64_t)1 << 30)) chunk *= k;
+    }
+    if (block_steps > 0) {
+        const int64_t blocks = (std::min(2 * (chunk / m), n) + block_steps - 1) / block_steps;  // of a chunk
+        const int64_t blk = (block_steps * m + kTilePairs - 1) / kTilePairs;
+        ctx.tiles = (int)(blk * (blk + 1) / 2);
+        ctx.ksplit = pick_ksplit(blocks * ctx.tiles, in_dim, h->num_cu);
+        const int64_t entries = blocks * ctx.tiles * kTileEntries;
+        if ((rc = ensure(h, h->train_gram, h->train_gram_cap, entries))) return rc;
+        if (ctx.ksplit > 1 && (rc = ensure(h, h->gram_parts, h->gram_parts_cap, entries * ctx.ksplit))) return rc;
+        if ((rc = ensure(h, h->train_order, h->train_order_cap, m * n))) return rc;
+        if ((rc = ensure(h, h->train_base, h->train_base_cap, (int64_t)kSolveExamples * 2 * kSolveClasses))) return rc;
+        hipLaunchKernelGGL(example_order, dim3((unsigned)((m * n + 255) / 256)), dim3(256), 0, h->stream, perm_in, m, n,
+                           h->train_order);
     }
     return balance_epoch_impl(h, m, n, ctx.d, nullptr, train_generate, &ctx, chunk, perm_in,
                               signs_out, perm_out, nullptr, nullptr, nullptr);

@@ -95,13 +95,14 @@ struct GramBatch {
     int32_t tiles;        // tiles stored per step
     int32_t ksplit;       // workgroups sharing the elements of a tile
     int32_t ktiles;       // kGramTE-element tiles of a row
+    const int64_t *examples;  // not null: the matrix of single rows base + examples[pair] * d instead of differences
 };
 constexpr int kGramTE = 32;
 
 // Position of tile (ti, tj), ti <= tj, in a step's list: (0,0) (0,1) (1,1) (0,2) (1,2) (2,2) ..
 __host__ __device__ constexpr int tile_index(int ti, int tj) { return tj * (tj + 1) / 2 + ti; }
 
-template <int VW>
+template <int VW, bool SINGLE>
 __global__ __launch_bounds__(kThreads, 2) void gram_tiles(GramBatch gb, double *__restrict__ out)
 {
     constexpr int STRIDE = kGramTE + 2;
@@ -135,6 +136,10 @@ __global__ __launch_bounds__(kThreads, 2) void gram_tiles(GramBatch gb, double *
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
         const int j = (s < 2 ? ti : tj) * kTilePairs + (s & 1) * 32 + prow;
+        if constexpr (SINGLE) {
+            src[s][0] = src[s][1] = gb.rows.base + gb.examples[(int64_t)step * gb.sp + (j < nb ? j : nb - 1)] * d;
+            continue;
+        }
         PairCursor(rows, j < nb ? j : nb - 1).rows(rows, src[s][0], src[s][1]);  // (a missing pair repeats the last one)
     }
     const int kt0 = (int)((int64_t)blockIdx.y * gb.ktiles / gb.ksplit);
@@ -148,7 +153,8 @@ __global__ __launch_bounds__(kThreads, 2) void gram_tiles(GramBatch gb, double *
 #pragma unroll
             for (int s = 0; s < 4; ++s)
                 if (s < sides) {
-                    const float4_t a = load_four<false>(src[s][0] + e), b = load_four<false>(src[s][1] + e);
+                    const float4_t b = load_four<false>(src[s][1] + e);
+                    const float4_t a = SINGLE ? (float4_t){0.f, 0.f, 0.f, 0.f} : load_four<false>(src[s][0] + e);
                     fa[s] = make_float4(a.x, a.y, a.z, a.w);
                     fb[s] = make_float4(b.x, b.y, b.z, b.w);
                 }
@@ -156,7 +162,7 @@ __global__ __launch_bounds__(kThreads, 2) void gram_tiles(GramBatch gb, double *
 #pragma unroll
             for (int s = 0; s < 4; ++s)
                 if (s < sides) {
-                    fa[s] = load4_nb<VW>(src[s][0], true, e, d);
+                    fa[s] = SINGLE ? make_float4(0.f, 0.f, 0.f, 0.f) : load4_nb<VW>(src[s][0], true, e, d);
                     fb[s] = load4_nb<VW>(src[s][1], true, e, d);
                 }
         }

@@ -1,0 +1,57 @@
+"""The training epoch in blocks of steps: numbers of steps around a block (256 examples), workers
+around its rounds of 4, 8 and 16, the most workers and classes it takes and one more of each."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from parity import check_epoch, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2302_00845_amd as p
+    return p
+
+
+@pytest.mark.parametrize("m,n,in_dim,classes,momentum", [
+    (1, 256, 6, 2, 0.9), (1, 258, 3, 3, 0.9), (1, 520, 1, 2, 0.0), (3, 84, 5, 4, 0.9), (3, 86, 33, 5, 0.9),
+    (4, 66, 8, 16, 0.5), (5, 52, 70, 7, 0.9), (8, 34, 9, 10, 0.9), (9, 60, 40, 10, 0.9), (16, 16, 31, 10, 0.9),
+    (16, 50, 130, 10, 0.9), (17, 30, 12, 3, 0.9), (33, 16, 12, 3, 0.0), (64, 4, 20, 16, 0.9), (64, 10, 20, 5, 0.9),
+    (65, 6, 20, 5, 0.9), (4, 20, 20, 17, 0.9), (16, 140, 2000, 10, 0.9), (7, 40, 3, 1, 0.9),
+])
+@pytest.mark.parametrize("with_perm", [True, False])
+def test_blocks_of_steps_match_oracle(lib, m, n, in_dim, classes, momentum, with_perm):
+    X, y, W0 = workloads.softmax_problem(m + n, m * n, in_dim, classes)
+    X, y, W0 = X.reshape(m, n, in_dim), y.reshape(m, n), (10 * W0).astype(np.float32)
+    perm = workloads.random_perms(3, m, n) if with_perm else None
+    lr = 0.2 / max(1.0, in_dim / 20)                      # contractive: rounding does not grow over the epoch
+    h = lib.Handle()
+    W = torch.from_numpy(W0.copy()).cuda()
+    v = torch.zeros(W.numel(), dtype=torch.float32, device="cuda") if momentum else None
+    out = lib.cdgrab_train_epoch_softmax(h, torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), W,
+                                         perm_in=torch.from_numpy(perm).cuda() if with_perm else None, velocity=v,
+                                         lr=lr, momentum=momentum, want_grads=True, want_loss=True)
+    torch.cuda.synchronize()
+    ref = oracle.train_epoch_softmax(X, y, perm if with_perm else np.tile(np.arange(n, dtype=np.int32), (m, 1)), W0,
+                                     None, lr, momentum)
+    rows = out["grads"].cpu().numpy()
+    # the 1e-5 relative L2 stated for per-example gradients; W after up to 520 fp32 updates of a
+    # contractive iteration: below 520 x 6e-8 = 3e-5 even if no rounding cancelled
+    if classes > 1:
+        assert rel_l2(W.cpu().numpy(), ref["W"]) <= 3e-5
+        # a row is [x; 1] delta^T, delta = p - onehot in fp32: where p is nearly 1 delta is a small difference,
+        # off by the rounding of p (6e-8) and by 1/2 of the logits' error (W's 3e-5 relative error, in
+        # practice 1e-6), so each row is held to 1e-5 of ||[x; 1]||, the bound for delta of order one
+        err = np.linalg.norm(rows - ref["rows"], axis=2)
+        xs = X if perm is None else np.take_along_axis(X, perm[:, :, None].astype(np.int64), 1)
+        assert np.all(err <= 1e-5 * np.sqrt(1.0 + (xs.astype(np.float64) ** 2).sum(2)))
+        if momentum:
+            assert rel_l2(v.cpu().numpy(), ref["v"]) <= 3e-5
+    else:
+        assert np.abs(rows).max() <= 1e-6
+    np.testing.assert_allclose(out["loss"].cpu().numpy(), ref["loss"], rtol=1e-4, atol=1e-5)
+    check_epoch(rows, {"signs": out["signs"].cpu().numpy(), "perm": out["perm"].cpu().numpy()}, perm)
