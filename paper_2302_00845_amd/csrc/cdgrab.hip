@@ -1194,7 +1194,7 @@ struct TrainCtx {
 };
 
 // Workers and classes that the blocks of steps are for: at least four steps per block and one MFMA column
-// tile of classes.  (16 workers, 784 -> 10: 2.1 us per step against 11.6 in a launch pair per step.)
+// tile of classes.  (16 workers, 784 -> 10: 2.6 us per step against 11.6 in a launch pair per step.)
 int64_t train_block_steps(int64_t m, int64_t n, int64_t classes) {
     const bool fits = m <= kSolveWorkers && classes <= kSolveClasses && n <= INT32_MAX / m;
     return fits ? std::min<int64_t>((kSolveExamples / m) & ~(int64_t)1, n) : 0;
@@ -1219,20 +1219,20 @@ int train_blocks(TrainCtx *c, int64_t j, int64_t j_end, int64_t k_first, float *
     const int form = row_form((d % 4 == 0 && reinterpret_cast<uintptr_t>(c->X) % 16 == 0) ? 4 : 1, d);
     const int rc = run_gram_tiles<true>(h, gb, h->train_gram, h->gram_parts, form);
     if (rc) return rc;
+    const int64_t update_blocks = (c->d + 63) / 64, update_groups = update_blocks >= 16 ? round_up(update_blocks, 8) : update_blocks;
     for (int64_t b = 0; b < gb.units; ++b, j += S) {
         const int steps = (int)std::min(S, j_end - j), examples = (int)(steps * m);
         const int64_t *order = h->train_order + j * m;
-        hipLaunchKernelGGL(train_base_logits, dim3((unsigned)((examples + 15) / 16)), dim3(1024), 0, h->stream, c->X, order,
-                           examples, c->W, c->velocity, (int)d, (int)c->classes, h->train_base);
+        hipLaunchKernelGGL(train_base_logits, dim3((unsigned)examples), dim3(512), 0, h->stream, c->X, order, c->W, c->velocity, (int)d, (int)c->classes, h->train_base);
         auto solve = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(1), dim3(256), 0, h->stream, h->train_gram + b * gb.tiles * kTileEntries,
+            hipLaunchKernelGGL(kernel, dim3(1), dim3(kSolveThreads), 0, h->stream, h->train_gram + b * gb.tiles * kTileEntries,
                                h->train_base, c->y, order, h->train_delta, c->loss_out, (int)m, steps, c->n, j,
                                (int)c->classes, (double)c->lr, (double)c->momentum);
         };
         if (m <= 4) solve(train_solve<1>);
         else if (m <= 8) solve(train_solve<2>);
         else solve(train_solve<4>);
-        hipLaunchKernelGGL(train_update_block, dim3((unsigned)((c->d + 63) / 64)), dim3(1024), 0, h->stream, c->X, order,
+        hipLaunchKernelGGL(train_update_block, dim3((unsigned)update_groups), dim3(1024), 0, h->stream, c->X, order,
                            h->train_delta, c->W, c->velocity, staging, c->grads_out, (int)m, steps, c->n, j, k_first,
                            (int)d, (int)c->classes, c->lr, c->momentum);
     }
