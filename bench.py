@@ -238,9 +238,9 @@ def measure_config(name, args, steps, warmup, cpu_seconds):
         _, tp = step(hp)
         avg_pairs = (N // 2) / blocks
         if ahead:
-            # per block: its share of the batched Gram launch (rows once) and the resolve + apply + dots
-            # launch (rows of this block and of the previous one, running sum read and written)
-            per_kernel = (("gram_batched+resolve_dots_apply", tp["pass1_ms"] + tp["pass2_ms"],
+            # per block: its share of the Gram tiles (rows once) and of a step's wide launch (rows of this
+            # step and of the previous one, running sum read and written); the walks are resolve_ms
+            per_kernel = (("gram_tiles+chain_apply_dots", tp["pass1_ms"] + tp["pass2_ms"],
                            24.0 * avg_pairs * d + 16.0 * d),)
         elif not fused:
             # algorithmic bytes per launch: both rows of every pair in the block (fp32) plus the
