@@ -407,16 +407,17 @@ void by_row_form(int form, F &&launch) {
 
 // All of `pairs` consecutive pairs of rows of at most kNarrowMaxD elements.
 int run_narrow(cdgrab_handle *h, const StepRows &rows, int64_t first, int64_t pairs, int64_t half_n,
-               int8_t *signs_out, double *dots_out) {
+               int8_t *signs_out, double *dots_out, float *r32, double *r64) {
     MARK(h, 2, kPass1);
     for (int64_t at = 0; at < pairs; at += kNarrowMaxPairs) {
+        const int fresh = first + at == 0;
         StepRows part = step_at(rows, at, 0);
         part.k0 = (first + at) / rows.m;  // (output slots are counted from the flattened pair, whatever the layout)
         part.i0 = (int32_t)((first + at) % rows.m);
         const int count = (int)std::min<int64_t>(kNarrowMaxPairs, pairs - at);
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)h->walks), dim3(kNarrowThreads), 0, h->stream, part, count, half_n,
-                               h->r_sum, signs_out, dots_out, h->uniforms, h->ws);
+                               fresh, h->r_sum, r32, r64, signs_out, dots_out, h->uniforms, h->ws);
         };
         auto by_rule = [&](auto dp, auto vw) {
             constexpr int DP = decltype(dp)::value, VW = decltype(vw)::value;
@@ -466,14 +467,15 @@ int run_step_grams(cdgrab_handle *h, const StepRows &rows, int64_t pairs, const 
 }
 
 // Wide launch of a step: applies prev (if it has pairs), dots of cur (if it has pairs).
-int run_step_wide(cdgrab_handle *h, const StepRows &cur, const StepRows &prev, const ChainPlan &c, int form) {
+int run_step_wide(cdgrab_handle *h, const StepRows &cur, const StepRows &prev, const ChainPlan &c, int form, bool fresh,
+                  float *r32, double *r64) {
     MARK(h, 2, kPass1);
     by_row_form(form, [&](auto vw) {
         constexpr int VW = decltype(vw)::value;
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)(c.groups >= 16 ? round_up(c.groups, 8) : c.groups), (unsigned)h->walks),
-                               dim3(kStepThreads), 0, h->stream, cur, prev, h->eps_blk, c.sp, c.groups, h->r_sum,
-                               h->dot_partials, h->ws);
+                               dim3(kStepThreads), 0, h->stream, cur, prev, h->eps_blk, c.sp, c.groups, fresh ? 1 : 0,
+                               h->r_sum, h->dot_partials, r32, r64, h->ws);
         };
         if (c.sp > 128) launch(chain_apply_dots<8, VW>);
         else if (c.sp > 64) launch(chain_apply_dots<4, VW>);
@@ -725,6 +727,8 @@ struct Epoch {
     const float *center_row;   // dense, m == 1: every row is paired with this one
     int8_t *signs_out;
     double *dots_out;
+    float *r_out;              // the running sum's exports, or null
+    double *r64_out;
 
     bool streamed = false;
     cdgrab_plan plan{};
@@ -870,6 +874,7 @@ int Epoch::chain_ahead() {
     StepRows prev_step{}, none{};
     none.d = d;
     int64_t batch_index = 0;
+    bool fresh = true;  // nothing has been applied yet
     int rc = CDGRAB_OK;
     for (int64_t first = 0; first < plan.pairs; first += batch_pairs, ++batch_index) {
         const int64_t pairs = std::min(batch_pairs, plan.pairs - first);
@@ -886,7 +891,8 @@ int Epoch::chain_ahead() {
         rows.m = (int32_t)m;
         rows.layout = streamed ? kStaged : center_row ? kCentred : kDense;
         if (narrow) {
-            if ((rc = run_narrow(h, rows, first, pairs, n / 2, signs_out, dots_out))) return rc;
+            // (every launch exports what it has: the last one's stays)
+            if ((rc = run_narrow(h, rows, first, pairs, n / 2, signs_out, dots_out, r_out, r64_out))) return rc;
             continue;
         }
         // (a chunk of streamed pairs may hold more steps than one launch of Gram tiles)
@@ -899,7 +905,10 @@ int Epoch::chain_ahead() {
             for (int64_t s = 0; s < steps; ++s) {
                 StepRows cur = step_at(part, s * chain.sp, (int)std::min<int64_t>(chain.sp, count - s * chain.sp));
                 const bool has_prev = prev_step.nb > 0;
-                if (has_prev && (rc = run_step_wide(h, cur, prev_step, chain, form))) return rc;
+                if (has_prev) {
+                    if ((rc = run_step_wide(h, cur, prev_step, chain, form, fresh, nullptr, nullptr))) return rc;
+                    fresh = false;
+                }
                 // (output slots are counted from the flattened pair, whatever the layout)
                 cur.k0 = (first + at + s * chain.sp) / m;
                 cur.i0 = (int32_t)((first + at + s * chain.sp) % m);
@@ -911,7 +920,7 @@ int Epoch::chain_ahead() {
     }
     if (narrow) return CDGRAB_OK;
     MARK(h, 1, kBalance);
-    return run_step_wide(h, none, prev_step, chain, form);
+    return run_step_wide(h, none, prev_step, chain, form, fresh, r_out, r64_out);
 }
 
 // Block by block: dot/Gram launch (with the previous block's apply inside it when
@@ -968,7 +977,7 @@ static int balance_epoch_impl(cdgrab_handle *h, int64_t m, int64_t n, int64_t d,
     if (!h) return CDGRAB_EINVAL;
     if (!signs_out || (!perm_out && !center_row))
         return fail(h, CDGRAB_EINVAL, "cdgrab_balance_epoch: signs_out and perm_out are required");
-    Epoch ep{h, m, n, d, grads, gen, gen_ctx, chunk_pairs, center_row, signs_out, dots_out};
+    Epoch ep{h, m, n, d, grads, gen, gen_ctx, chunk_pairs, center_row, signs_out, dots_out, r_out, r64_out};
     ep.walks = walks;
     int rc = ep.prepare();
     if (rc) return rc;
@@ -979,8 +988,9 @@ static int balance_epoch_impl(cdgrab_handle *h, int64_t m, int64_t n, int64_t d,
     h->marks.clear();
     h->events_used = 0;
     h->have_timing = false;
-    hipLaunchKernelGGL(fill_zero_f64, dim3(std::min<int64_t>(4096, (h->r_cap + 255) / 256)), dim3(256), 0,
-                       h->stream, h->r_sum, h->r_cap);
+    if (!ep.ahead)  // (the Grams-ahead form starts and exports the running sum in its own launches)
+        hipLaunchKernelGGL(fill_zero_f64, dim3(std::min<int64_t>(4096, (h->r_cap + 255) / 256)), dim3(256), 0,
+                           h->stream, h->r_sum, h->r_cap);
     rc = ep.ahead ? ep.chain_ahead() : ep.chain_blocks();
     if (rc) return rc;
     rc = ep.apply_last();
@@ -990,7 +1000,7 @@ static int balance_epoch_impl(cdgrab_handle *h, int64_t m, int64_t n, int64_t d,
     if (!center_row)  // (side-by-side walks are one-worker walks: `walks` rows of signs and orders)
         hipLaunchKernelGGL(build_pair_permutations, dim3((unsigned)((walks * m * (n / 2) + 255) / 256)), dim3(256),
                            0, h->stream, signs_out, perm_in, perm_out, walks * m, n);
-    if (r_out || r64_out)
+    if ((r_out || r64_out) && !ep.ahead)
         hipLaunchKernelGGL(export_running_sum, dim3((unsigned)std::min<int64_t>(8192, (d + 255) / 256)), dim3(256),
                            0, h->stream, h->r_sum, d, r_out, r64_out);
     MARK(h, 1, -1);

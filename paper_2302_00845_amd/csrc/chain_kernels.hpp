@@ -257,15 +257,19 @@ __global__ __launch_bounds__(kThreads) void gram_reduce(const double *__restrict
 // requested up front, so that the launch is one memory round trip long.  Neighbouring workgroups
 // share lines (rows need not start on one) and read at the next step what they read at this one, so
 // each XCD keeps a contiguous run of workgroups.  Either step may have
-// no pairs (the first step has no predecessor, the last apply no successor).
+// no pairs (the first step has no predecessor, the last apply no successor).  `fresh`: the running sum is
+// zero and r_sum holds nothing yet; r32 / r64 (or null): the running sum leaves here as well.  Both spare
+// a short epoch a launch of its own (4 x 64 x 1024: 28 us with a fill and an export launch, 25 now).
 constexpr int kStepElems = 64;
 constexpr int kStepThreads = 512;
 
 template <int PP, int VW>
 __global__ __launch_bounds__(kStepThreads, 2) void chain_apply_dots(StepRows cur, StepRows prev,
                                                                     const int8_t *__restrict__ eps, int sp, int groups,
-                                                                    double *__restrict__ r_sum,
-                                                                    double *__restrict__ dots_out, WalkStrides ws)
+                                                                    int fresh, double *__restrict__ r_sum,
+                                                                    double *__restrict__ dots_out,
+                                                                    float *__restrict__ r32, double *__restrict__ r64,
+                                                                    WalkStrides ws)
 {
     constexpr int QUADS = kStepElems / 4;              // 16
     constexpr int GROUPS = kStepThreads / QUADS;       // 32
@@ -313,7 +317,7 @@ __global__ __launch_bounds__(kStepThreads, 2) void chain_apply_dots(StepRows cur
             if (grp * PP + q + 1 < cur.nb) at.next(cur);
         }
     }
-    const double r_old = sub == 0 ? r_sum[mine] : 0.0;  // padded to a multiple of 128
+    const double r_old = sub == 0 && !fresh ? r_sum[mine] : 0.0;  // padded to a multiple of 128
     if (prev.nb > 0) {
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -341,6 +345,8 @@ __global__ __launch_bounds__(kStepThreads, 2) void chain_apply_dots(StepRows cur
             for (int g = 0; g < SUBS; ++g) s += part2[g][el];
             r += s;  // elements beyond d load as zero, so the padding stays zero
             r_sum[mine] = r;
+            if (r32 && mine < d) r32[mine] = (float)r;
+            if (r64 && mine < d) r64[mine] = r;
         }
         rnew[el] = r;
     }

@@ -46,10 +46,12 @@ __device__ __forceinline__ double sum_across_32(double x) {
 }
 
 // DP: padded row length (16, 32 or 64).  `pairs` consecutive pairs of every walk, the first at
-// rows; the running sum is read from and written back to r_sum.
+// rows; the running sum is read from (fresh: starts at zero) and written back to r_sum, and to r32 / r64
+// where they are not null.
 template <int DP, int VW, bool RANDOM>
-__global__ __launch_bounds__(kNarrowThreads) void narrow_walk(StepRows rows, int pairs, int64_t half_n,
-                                                              double *__restrict__ r_sum,
+__global__ __launch_bounds__(kNarrowThreads) void narrow_walk(StepRows rows, int pairs, int64_t half_n, int fresh,
+                                                              double *__restrict__ r_sum, float *__restrict__ r32,
+                                                              double *__restrict__ r64,
                                                               int8_t *__restrict__ signs_out,
                                                               double *__restrict__ dots_out,
                                                               const float *__restrict__ uniforms, WalkStrides ws)
@@ -266,7 +268,7 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_walk(StepRows rows, int
         load(odd, 1);
     }
     for (int q = h; q < kTilePairs * GS; q += kNarrowThreads - 128) G[q] = 0.0;
-    if (h < DP) r[h] = h < d ? r_sum[h] : 0.0;
+    if (h < DP) r[h] = h < d && !fresh ? r_sum[h] : 0.0;
     if (works) {
         store(even, 0);
         store(odd, 1);
@@ -282,7 +284,11 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_walk(StepRows rows, int
         block(b, even);
         if (b + 1 < blocks) block(b + 1, odd);
     }
-    if (h < d) r_sum[h] = r[h];
+    if (h < d) {
+        r_sum[h] = r[h];
+        if (r32) r32[h] = (float)r[h];
+        if (r64) r64[h] = r[h];
+    }
 }
 
 }  // namespace cdgrab
