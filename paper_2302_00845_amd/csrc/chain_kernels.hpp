@@ -297,11 +297,12 @@ __global__ __launch_bounds__(kStepThreads, 2) void chain_apply_dots(StepRows cur
     if (prev.nb > 0) {  // uniform
         PairCursor at(prev, grp * PP < prev.nb ? grp * PP : prev.nb - 1);
 #pragma unroll
-        for (int q = 0; q < PP; ++q) {  // (a missing pair repeats the last one, with sign 0)
+        for (int q = 0; q < PP; ++q) {  // (a missing pair enters as zero: 0 times a value that is not finite is not 0)
+            const bool have = grp * PP + q < prev.nb;
             const float *a, *b;
             at.rows(prev, a, b);
-            pa[q] = load4_nb<VW>(a, true, e, d);
-            pb[q] = load4_nb<VW>(b, true, e, d);
+            pa[q] = load4_nb<VW>(a, have, e, d);
+            pb[q] = load4_nb<VW>(b, have, e, d);
             if (grp * PP + q + 1 < prev.nb) at.next(prev);
         }
         __builtin_memcpy(sg, eps + grp * PP, PP);

@@ -79,3 +79,23 @@ def test_randomized_rule_over_steps(lib, m, n, d):
             assert int(out["signs"][i, k]) == eps, (k, i)
             r += eps * dv
     assert np.array_equal(out["r64"].cpu().numpy(), r)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("m,n,d", [
+    (3, 24, 20), (1, 130, 50),                    # rows of at most 64 elements
+    (1, 130, 66), (3, 86, 129), (1, 600, 1001),   # steps of 128 and 256 pairs, the last one ragged
+    (2, 130, 12_000), (1, 142, 40_003),           # of 128 and of 64 pairs
+    (2, 20, 70_001),                              # one launch per block of pairs
+])
+def test_value_that_is_not_finite_stays_where_it_is(lib, value, m, n, d):
+    """One element of the epoch's last pair is infinite or not a number: that element of the running
+    sum follows it, every other one is the exact sum under the signs the epoch reports."""
+    z = workloads.integer_rows(n + d, m, n, d, 3)
+    z[m - 1, n - 1, 5] = value
+    out = lib.cdgrab_balance_epoch(lib.Handle(), m, n, d, grads=torch.from_numpy(z).cuda(), want_r64=True)
+    eps = out["signs"].cpu().numpy().astype(np.float64)
+    diff = (z[:, 1::2].astype(np.float64) - z[:, 0::2])
+    want = np.einsum("ik,ikd->d", eps, diff)
+    assert np.array_equal(out["r64"].cpu().numpy(), want, equal_nan=True)
+    assert np.array_equal(out["r32"].cpu().numpy(), want.astype(np.float32), equal_nan=True)
