@@ -232,7 +232,8 @@ __global__ __launch_bounds__(kSolveThreads) void train_solve(const double *__res
     }
     __syncthreads();
     for (int q = tid; q < examples * classes; q += kSolveThreads) delta_out[q] = delta_all[q / classes][q % classes];
-    if (loss_out && tid < examples)
+    // (a label that names no class leaves its loss as it is)
+    if (loss_out && tid < examples && (uint32_t)label[tid] < (uint32_t)classes)
         loss_out[(int64_t)(tid % m) * n + j0 + tid / m] = -(margin[tid] - logf(sum_exp[tid]));
 }
 

@@ -55,3 +55,26 @@ def test_blocks_of_steps_match_oracle(lib, m, n, in_dim, classes, momentum, with
         assert np.abs(rows).max() <= 1e-6
     np.testing.assert_allclose(out["loss"].cpu().numpy(), ref["loss"], rtol=1e-4, atol=1e-5)
     check_epoch(rows, {"signs": out["signs"].cpu().numpy(), "perm": out["perm"].cpu().numpy()}, perm)
+
+
+@pytest.mark.parametrize("m", [8, 65])                    # blocks of steps, a launch pair per step
+def test_label_that_names_no_class_leaves_its_loss(lib, m):
+    """Such an example's delta is its softmax; nothing is written as its loss."""
+    n, in_dim, classes = 8, 12, 5
+    X, y, W0 = workloads.softmax_problem(3, m * n, in_dim, classes)
+    X, y = torch.from_numpy(X).cuda().view(m, n, in_dim), torch.from_numpy(y).cuda().view(m, n)
+    y[1, 2], y[m - 1, 5] = -1, classes
+    h, W = lib.Handle(), torch.from_numpy(W0.astype(np.float32)).cuda()
+    signs = torch.empty((m, n // 2), dtype=torch.int8, device="cuda")
+    perm = torch.empty((m, n), dtype=torch.int32, device="cuda")
+    rows = torch.empty((m, n, (in_dim + 1) * classes), device="cuda")
+    loss = torch.full((m, n), 123.0, device="cuda")
+    h._check(h._lib.cdgrab_train_epoch_softmax(
+        h._h, m, n, in_dim, classes, X.data_ptr(), y.data_ptr(), None, W.data_ptr(), None, 0.05, 0.0,
+        signs.data_ptr(), perm.data_ptr(), rows.data_ptr(), loss.data_ptr()))
+    ignored = torch.zeros((m, n), dtype=torch.bool, device="cuda")
+    ignored[1, 2] = ignored[m - 1, 5] = True
+    assert torch.all(loss[ignored] == 123.0) and torch.all(loss[~ignored] < 50.0)
+    # the bias row of a gradient is delta itself: it sums to 1 without a label, to 0 with one (5 roundings of 6e-8)
+    total = rows.view(m, n, in_dim + 1, classes)[:, :, in_dim].sum(2)
+    assert torch.all((total - ignored.float()).abs() <= 1e-6)
