@@ -217,6 +217,11 @@ ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pair
     return c;
 }
 
+// Two staging chunks when a launch reads the previous block's rows as well and there is a next chunk.
+int64_t staging_chunks(int64_t pairs, int64_t chunk_pairs, bool reads_previous) {
+    return reads_previous && pairs > chunk_pairs ? 2 : 1;
+}
+
 // The launch plan of one epoch.  `chunk_pairs` is the number of flattened pairs staged per
 // generator call (streamed input; 0 = one block).  Every decision an epoch takes is taken
 // here, so that cdgrab_plan_epoch reports exactly what a handle with the same options runs.
@@ -243,13 +248,12 @@ int plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t str
     if (chunk_pairs <= 0) chunk_pairs = bb;
 
     // Grams ahead: asked for, or chosen for short rows when the caller left both choices
-    // open; for streamed rows when a staging chunk holds several whole blocks.
+    // open; for streamed rows when a staging chunk holds more than one block's pairs.
     const bool ahead_dense = !streamed && plan->blocks >= 2 &&
                              (gram_mode == 2 || (gram_mode == 0 && apply_mode == 0 &&
                                                  gram_ahead_by_default(d, plan->blocks, false)));
     const bool ahead_streamed = streamed && gram_mode != 1 && apply_mode == 0 && d <= kChunkAheadMaxD &&
-                                plan->pairs > bb && chunk_pairs >= 2 * bb && chunk_pairs % bb == 0 &&
-                                chunk_pairs / bb <= kGramBatch;
+                                plan->pairs > bb && chunk_pairs > bb && chunk_pairs <= kGramBatch * bb;
     const bool ahead = ahead_dense || ahead_streamed;
     // the ahead form applies a block inside the next block's launch by construction
     const bool fused = !ahead && (apply_mode == 2 || (apply_mode == 0 && fuse_apply_by_default(d)));
@@ -257,8 +261,7 @@ int plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t str
     plan->fused_apply = fused ? 1 : 0;
     plan->reserved = 0;
 
-    // two staging chunks when a launch reads the previous block's rows as well
-    plan->staging_bytes = streamed ? ((fused || ahead) ? 2 : 1) * chunk_pairs * 2 * d * 4 : 0;
+    plan->staging_bytes = streamed ? staging_chunks(plan->pairs, chunk_pairs, fused || ahead) * chunk_pairs * 2 * d * 4 : 0;
     const int64_t part = part_size(plan->block_pairs);
     const int64_t partial_doubles = (int64_t)plan->pass1_groups * part;
     int64_t ahead_bytes = 0;
@@ -799,8 +802,8 @@ int Epoch::prepare() {
     rc = ensure(h, h->eps_blk, h->eps_cap, ahead ? walks * kMaxStepPairs : (int64_t)kMaxBlockPairs);
     if (rc) return rc;
     if (streamed) {
-        // two chunks when a launch reads the previous block's rows as well: they must outlive the next fill
-        rc = ensure(h, h->staging, h->staging_cap, ((fused || ahead) ? 2 : 1) * staging_chunk);
+        // (two chunks: the previous one's rows must outlive the next fill)
+        rc = ensure(h, h->staging, h->staging_cap, staging_chunks(plan.pairs, chunk_pairs, fused || ahead) * staging_chunk);
         if (rc) return rc;
     }
     h->ws = WalkStrides{};
@@ -1210,6 +1213,25 @@ int64_t train_block_steps(int64_t m, int64_t n, int64_t classes) {
     return fits ? std::min<int64_t>((kSolveExamples / m) & ~(int64_t)1, n) : 0;
 }
 
+// Flattened pairs staged at a time: whole step pairs, about 64 pairs; for short rows about 1024 pairs, so that
+// the Gram tiles of a chunk come from one launch.  There whole steps of the chain are preferred (a ragged
+// last one per chunk costs up to 6 %), but whole step pairs and whole steps at once can be many pairs
+// (14 080 for 11 workers), so a chunk is held to what the last-level cache holds, 256 MB, or to 1024 pairs,
+// and to the epoch.
+int64_t train_chunk_pairs(const cdgrab_handle *h, int64_t m, int64_t n, int64_t d) {
+    const int64_t pairs = m * (n / 2), bb = pick_block_pairs(pairs, d, h->block_pairs_opt);
+    const int64_t base = std::max<int64_t>(1, 64 / m) * m;
+    int64_t k = 1;
+    if (d <= kChunkAheadMaxD && h->gram_mode != 1 && h->apply_mode == 0) {
+        const int64_t sp = plan_chain(pairs, d, 1, 0, h->num_cu).sp;
+        k = sp / std::gcd(base, sp);
+        k *= std::max<int64_t>(1, 1024 / (base * k));
+        k = std::min(k, std::max<int64_t>(1024 / base, ((int64_t)1 << 28) / (base * 2 * d * 4)));
+        k = std::max<int64_t>(1, std::min(k, kGramBatch * bb / base));
+    }
+    return std::min(base * k, pairs);
+}
+
 // The steps j .. j_end - 1 of a chunk, a block at a time.
 int train_blocks(TrainCtx *c, int64_t j, int64_t j_end, int64_t k_first, float *staging) {
     cdgrab_handle *h = c->h;
@@ -1296,20 +1318,7 @@ int cdgrab_train_epoch_softmax(cdgrab_handle *h, int64_t m, int64_t n, int64_t i
     if (rc) return rc;
     TrainCtx ctx{h, m, n, in_dim, classes, (in_dim + 1) * classes, X, y, perm_in, W, velocity,
                  grads_out, loss_out, lr, momentum, block_steps, 0, 1};
-    // a chunk is a whole number of step pairs: about one block's worth of pairs, at least one step pair;
-    // for short rows a few hundred pairs and whole steps of the chain (whole blocks where the rows are
-    // too long for that), so that the Gram matrices of a chunk are computed in one launch
-    const int64_t step_pairs = std::max<int64_t>(1, 64 / m);
-    int64_t chunk = step_pairs * m;
-    if (ctx.d <= kChunkAheadMaxD && h->gram_mode != 1 && h->apply_mode == 0) {
-        const int64_t pairs = m * (n / 2), bb = pick_block_pairs(pairs, ctx.d, h->block_pairs_opt);
-        const int64_t sp = plan_chain(pairs, ctx.d, 1, 0, h->num_cu).sp;
-        const int64_t bytes = chunk * 2 * ctx.d * 4 * 2;  // of both staging chunks, per multiple
-        int64_t k = sp / std::gcd(chunk, sp);             // whole steps ...
-        k *= std::max<int64_t>(1, 1024 / (chunk * k));    // ... and about 1024 pairs
-        if (bytes * k > ((int64_t)1 << 30) || chunk * k / bb > kGramBatch) k = bb / std::gcd(chunk, bb);
-        if (chunk * k / bb <= kGramBatch && bytes * k <= ((int64_t)1 << 30)) chunk *= k;
-    }
+    const int64_t chunk = train_chunk_pairs(h, m, n, ctx.d);
     if (block_steps > 0) {
         const int64_t blocks = (std::min(2 * (chunk / m), n) + block_steps - 1) / block_steps;  // of a chunk
         const int64_t blk = (block_steps * m + kTilePairs - 1) / kTilePairs;

@@ -78,3 +78,26 @@ def test_label_that_names_no_class_leaves_its_loss(lib, m):
     # the bias row of a gradient is delta itself: it sums to 1 without a label, to 0 with one (5 roundings of 6e-8)
     total = rows.view(m, n, in_dim + 1, classes)[:, :, in_dim].sum(2)
     assert torch.all((total - ignored.float()).abs() <= 1e-6)
+
+
+@pytest.mark.parametrize("m,n,in_dim,classes", [(11, 900, 470, 10), (3, 86, 99, 10), (37, 120, 99, 10)])
+def test_staged_rows_are_a_bounded_chunk_of_the_epoch(lib, m, n, in_dim, classes):
+    """What an epoch allocates on a new handle: two chunks of 256 MB or 1024 pairs each, none longer than the
+    epoch, beside at most 64 MB of other workspace (Gram tiles of a chunk and their shares, for the most part)."""
+    d, pairs = (in_dim + 1) * classes, m * n // 2
+
+    def epoch(m, n):
+        X, y, W0 = workloads.softmax_problem(1, m * n, in_dim, classes)
+        args = (torch.from_numpy(X).cuda().view(m, n, in_dim), torch.from_numpy(y).cuda().view(m, n),
+                torch.from_numpy(W0.astype(np.float32)).cuda())
+        out = lib.cdgrab_train_epoch_softmax(lib.Handle(), *args, lr=0.01)  # (its outputs come from torch's pool)
+        torch.cuda.synchronize()
+        h = lib.Handle()
+        before = torch.cuda.mem_get_info()[0]
+        lib.cdgrab_train_epoch_softmax(h, *args, lr=0.01)
+        torch.cuda.synchronize()
+        del out
+        return before - torch.cuda.mem_get_info()[0]
+
+    taken = epoch(m, n)
+    assert taken <= 2 * min(max(1024 * 8 * d, 256 << 20), pairs * 8 * d) + (64 << 20), taken
