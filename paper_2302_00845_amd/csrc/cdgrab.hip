@@ -581,19 +581,23 @@ int launch_column_mean(cdgrab_handle *h, int64_t n, int64_t d, const float *rows
     const int64_t want = std::max<int64_t>(1, std::min<int64_t>((n + 8 * slots - 1) / (8 * slots),
                                                                 (4 * (int64_t)h->num_cu + grid_x - 1) / grid_x));
     const int64_t chunk_rows = (n + want - 1) / want, chunks = (n + chunk_rows - 1) / chunk_rows;
-    const int rc = ensure(h, h->mean_ws, h->mean_cap, chunks * d);
-    if (rc) return rc;
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)grid_x, (unsigned)chunks), dim3(256), 0, h->stream, rows, n, d, quads,
-                           slots, chunk_rows, h->mean_ws);
-    };
-    switch (row_form((d % 4 == 0 && reinterpret_cast<uintptr_t>(rows) % 16 == 0) ? 4 : 1, d)) {
-        case kAligned: launch(column_sums<kAligned>); break;
-        case kAnyRow: launch(column_sums<kAnyRow>); break;
-        default: launch(column_sums<kTiny>); break;
+    const int form = row_form((d % 4 == 0 && reinterpret_cast<uintptr_t>(rows) % 16 == 0) ? 4 : 1, d);
+    if (chunks > 1) {  // (a few times the elements that fill the chip; long rows are one chunk and need none)
+        const int rc = ensure(h, h->mean_ws, h->mean_cap, chunks * d);
+        if (rc) return rc;
     }
-    hipLaunchKernelGGL(column_mean_finish, dim3((unsigned)((d + 15) / 16)), dim3(256), 0, h->stream, h->mean_ws, chunks,
-                       n, d, mean_out);
+    by_row_form(form, [&](auto vw) {
+        constexpr int VW = decltype(vw)::value;
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)grid_x, (unsigned)chunks), dim3(256), 0, h->stream, rows, n, d,
+                               quads, slots, chunk_rows, h->mean_ws, mean_out);
+        };
+        if (chunks > 1) launch(column_sums<VW, false>);
+        else launch(column_sums<VW, true>);
+    });
+    if (chunks > 1)
+        hipLaunchKernelGGL(column_mean_finish, dim3((unsigned)((d + 15) / 16)), dim3(256), 0, h->stream, h->mean_ws,
+                           chunks, n, d, mean_out);
     HIP_TRY(h, hipGetLastError());
     return CDGRAB_OK;
 }

@@ -75,3 +75,19 @@ def test_reorder_across_chunks(lib, m, n, with_perm):
                              torch.from_numpy(perm_in).cuda() if with_perm else None).cpu().numpy()
     for i in range(m):
         assert np.array_equal(out[i], oracle.reorder(signs[i], perm_in[i] if with_perm else None))
+
+
+def test_mean_of_long_rows_takes_no_workspace(lib):
+    """Rows long enough to fill the GPU by themselves: the mean is written straight from the rows (exact on
+    small integers up to the two roundings), and the epoch allocates the running sum and partials only."""
+    n, d = 6, 30_000_001
+    z = torch.randint(-4, 5, (n, d), device="cuda", dtype=torch.int8).float()
+    lib.cdgrab_balance_epoch_stale_mean(lib.Handle(), z[:, :1000].contiguous(), z[0, :1000].contiguous())
+    lib.cdgrab_balance_epoch_stale_mean(lib.Handle(), z[:2], z[0])   # (torch's pool holds outputs of this size now)
+    torch.cuda.synchronize()
+    h = lib.Handle()
+    before = torch.cuda.mem_get_info()[0]
+    out = lib.cdgrab_balance_epoch_stale_mean(h, z, z[0])
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] <= 8 * d + (64 << 20)
+    assert torch.equal(out["mean"], (z.double().sum(0) / n).float())
