@@ -41,7 +41,10 @@ typedef struct cdgrab_handle cdgrab_handle;
 
 typedef struct cdgrab_options {
     int32_t device;      /* HIP device ordinal                                        */
-    int32_t block_pairs; /* Bb: pairs resolved per HBM pass; 0 = choose, else 16, 32 or 64 */
+    int32_t block_pairs; /* Bb: pairs resolved per HBM pass; 0 = choose, else 16, 32 or 64.
+                            The Grams-ahead form (gram_mode) cuts an epoch into steps of its
+                            own length instead and takes no notice of a choice made here, but for
+                            one: an epoch of one block does not take that form by default */
     void *stream;        /* hipStream_t to enqueue on; NULL = the null stream         */
     int32_t timing;      /* 0 off; 1 record events around generator / balancer work;
                             2 additionally around every balancer kernel               */
@@ -59,8 +62,9 @@ typedef struct cdgrab_options {
                             its own dot/Gram launch; 2 = the Gram matrices of many
                             pairs are computed ahead in one launch (they depend on the
                             rows only) and the walk is a chain of steps of 64 .. 256 pairs
-                            (chosen by sizes, whatever the block size) at two launches each;
-                            refused (EINVAL) for d > 131 072; 0 = choose (2 for rows up to
+                            (chosen by sizes, whatever the block size) at two launches each,
+                            or, for rows of at most 64 elements, one launch in which one
+                            workgroup per walk takes 64 pairs at a time; refused (EINVAL) for d > 131 072; 0 = choose (2 for rows up to
                             65 536 elements when apply_mode is 0 as well; staged rows: up to
                             16 384)                                                       */
     int32_t apply_groups; /* cap on the workgroups of the resident apply kernel; 0 = two per CU */
@@ -76,8 +80,8 @@ typedef struct cdgrab_timing {
     double resolve_ms;   /* sequential sign resolution                         */
     double pass2_ms;     /* stand-alone apply launches (only the last block's when fused) */
     double finish_ms;    /* permutation build + running-sum export             */
-    int64_t blocks;      /* number of blocks processed                         */
-    int32_t block_pairs; /* Bb used                                            */
+    int64_t blocks;      /* number of blocks processed (Grams-ahead form: of steps)  */
+    int32_t block_pairs; /* Bb used (Grams-ahead form: pairs per step)         */
     int32_t pass1_groups;/* workgroups used by the dot/Gram pass               */
 } cdgrab_timing;
 
@@ -85,7 +89,8 @@ typedef struct cdgrab_timing {
 typedef struct cdgrab_plan {
     int64_t pairs;           /* m*n/2 flattened pair differences                      */
     int64_t blocks;          /* ceil(pairs / block_pairs)                             */
-    int32_t block_pairs;     /* Bb                                                    */
+    int32_t block_pairs;     /* Bb: what is run block by block when gram_ahead is 0; else the
+                                unit that decided for that form (see step_pairs)       */
     int32_t vector_width;    /* fp32 elements every row start is aligned to: 4, 2 or 1  */
     int32_t tile_elems;      /* elements of d per LDS tile of the dot/Gram pass        */
     int32_t fused_apply;     /* 1: apply fused into the next block's dot/Gram launch (0 when
@@ -93,7 +98,8 @@ typedef struct cdgrab_plan {
     int32_t pass1_groups;    /* workgroups of the dot/Gram pass                       */
     int32_t pass2_groups;    /* workgroups of the apply pass                          */
     int32_t gram_ahead;      /* 1: Gram matrices of many blocks computed ahead in one launch */
-    int32_t reserved;
+    int32_t step_pairs;      /* pairs per step of the Grams-ahead form: 64, 128 or 256 (always
+                                64 for rows of at most 64 elements); 0 when gram_ahead is 0 */
     int64_t workspace_bytes; /* everything the handle allocates for this epoch: running sum,
                                 partials, slice sums, block signs, the buffers of the
                                 Grams-ahead form when gram_ahead is 1, and staging          */
@@ -101,7 +107,9 @@ typedef struct cdgrab_plan {
     double bytes_per_example;/* algorithmic HBM bytes per example: each row twice, plus the
                                 double running sum per block: 8d + 12 d / Bb (read twice,
                                 written once) or 8d + 8 d / Bb when fused; at most 12d + 8 d / Bb
-                                with the Gram matrices computed ahead (rows read three times) */
+                                with the Gram matrices computed ahead (rows read three times,
+                                Gram tiles of 256 MB at a time), 4d for rows of at most 64
+                                elements then (read once)                              */
 } cdgrab_plan;
 
 /* Generator callback for streamed input ("grads-or-generator").  It must enqueue,

@@ -51,7 +51,7 @@ class Plan(ctypes.Structure):
                 ("block_pairs", ctypes.c_int32), ("vector_width", ctypes.c_int32),
                 ("tile_elems", ctypes.c_int32), ("fused_apply", ctypes.c_int32),
                 ("pass1_groups", ctypes.c_int32), ("pass2_groups", ctypes.c_int32),
-                ("gram_ahead", ctypes.c_int32), ("reserved", ctypes.c_int32),
+                ("gram_ahead", ctypes.c_int32), ("step_pairs", ctypes.c_int32),
                 ("workspace_bytes", ctypes.c_int64), ("staging_bytes", ctypes.c_int64),
                 ("bytes_per_example", ctypes.c_double)]
 

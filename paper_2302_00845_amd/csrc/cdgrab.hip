@@ -259,7 +259,7 @@ int plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t str
     const bool fused = !ahead && (apply_mode == 2 || (apply_mode == 0 && fuse_apply_by_default(d)));
     plan->gram_ahead = ahead ? 1 : 0;
     plan->fused_apply = fused ? 1 : 0;
-    plan->reserved = 0;
+    plan->step_pairs = 0;
 
     plan->staging_bytes = streamed ? staging_chunks(plan->pairs, chunk_pairs, fused || ahead) * chunk_pairs * 2 * d * 4 : 0;
     const int64_t part = part_size(plan->block_pairs);
@@ -267,6 +267,7 @@ int plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t str
     int64_t ahead_bytes = 0;
     if (ahead) {
         const ChainPlan c = plan_chain(plan->pairs, d, 1, streamed ? chunk_pairs : 0, num_cu);
+        plan->step_pairs = c.sp;
         ahead_bytes = (c.gram_len + c.parts_len + c.dots_len) * 8 + kMaxStepPairs;
     }
     plan->workspace_bytes = round_up(d, kPadE) * 8 + partial_doubles * 8 +
@@ -274,8 +275,9 @@ int plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t str
                             plan->staging_bytes;
     // each row twice; the double running sum read twice and written once per block, or read
     // once and written once when the apply rides in the next block's launch; with the Gram
-    // matrices ahead the rows are read three times
-    plan->bytes_per_example = ahead ? 12.0 * (double)d + 8.0 * (double)d / (double)bb
+    // matrices ahead the rows are read three times (less: the first step takes no dots, and a step is
+    // at least a block), or once where the walk runs in one workgroup
+    plan->bytes_per_example = ahead ? (d <= kNarrowMaxD ? 4.0 * (double)d : 12.0 * (double)d + 8.0 * (double)d / (double)bb)
                                     : 8.0 * (double)d + (fused ? 8.0 : 12.0) * (double)d / (double)bb;
     return CDGRAB_OK;
 }
@@ -750,6 +752,7 @@ struct Epoch {
     RowMap rm;
     PrevBlock prev;
     bool have_prev = false;
+    int64_t steps_run = 0;     // of the Grams-ahead form
 
     int prepare();
     void set_block(int64_t p0, int64_t nb, const float *stage_base);
@@ -900,6 +903,7 @@ int Epoch::chain_ahead() {
         if (narrow) {
             // (every launch exports what it has: the last one's stays)
             if ((rc = run_narrow(h, rows, first, pairs, n / 2, signs_out, dots_out, r_out, r64_out))) return rc;
+            steps_run += (pairs + chain.sp - 1) / chain.sp;
             continue;
         }
         // (a chunk of streamed pairs may hold more steps than one launch of Gram tiles)
@@ -908,6 +912,7 @@ int Epoch::chain_ahead() {
             const StepRows part = step_at(rows, at, 0);
             if ((rc = run_step_grams(h, part, count, chain, form))) return rc;
             const int64_t steps = (count + chain.sp - 1) / chain.sp;
+            steps_run += steps;
             h->ws.gram = walks > 1 ? steps * chain.tiles * kTileEntries : 0;
             for (int64_t s = 0; s < steps; ++s) {
                 StepRows cur = step_at(part, s * chain.sp, (int)std::min<int64_t>(chain.sp, count - s * chain.sp));
@@ -1014,9 +1019,14 @@ static int balance_epoch_impl(cdgrab_handle *h, int64_t m, int64_t n, int64_t d,
     HIP_TRY(h, hipGetLastError());
     const int64_t cp = ep.chunk_pairs, bb = ep.bb;
     h->last = cdgrab_timing{};
-    h->last.blocks = ep.streamed ? ((ep.plan.pairs / cp) * ((cp + bb - 1) / bb) + ((ep.plan.pairs % cp) + bb - 1) / bb)
-                                 : ep.plan.blocks;
-    h->last.block_pairs = (int32_t)bb;
+    if (ep.ahead) {
+        h->last.blocks = ep.steps_run;
+        h->last.block_pairs = ep.chain.sp;
+    } else {
+        h->last.blocks = ep.streamed ? ((ep.plan.pairs / cp) * ((cp + bb - 1) / bb) + ((ep.plan.pairs % cp) + bb - 1) / bb)
+                                     : ep.plan.blocks;
+        h->last.block_pairs = (int32_t)bb;
+    }
     h->last.pass1_groups = ep.plan.pass1_groups;
     h->have_timing = h->timing >= 1;
     h->walks = 1;

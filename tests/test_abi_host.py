@@ -84,6 +84,19 @@ def test_plan_epoch_headline_shapes(p):
     assert p.cdgrab_plan_epoch(1, 66, 8, block_pairs=16)["blocks"] == 3
 
 
+@pytest.mark.parametrize("m,n,d,step,reads", [
+    (16, 3750, 7850, 128, None), (4, 64, 1024, 128, None), (1, 2050, 70, 256, None), (2, 130, 12_000, 64, None),
+    (1, 142, 40_003, 64, None),
+    (20, 50_000, 16, 64, 1), (1, 130, 64, 64, 1),          # one workgroup walks 64 pairs at a time, rows read once
+    (4, 16, 1024, 0, 2), (32, 64, 1_048_575, 0, 2),        # block by block
+])
+def test_plan_says_how_long_a_step_is(p, m, n, d, step, reads):
+    plan = p.cdgrab_plan_epoch(m, n, d)
+    assert plan["step_pairs"] == step and plan["gram_ahead"] == (step > 0)
+    if reads:  # the rows, and at most the running sum once per 16 pairs three times over
+        assert 4 * reads * d <= plan["bytes_per_example"] <= 4 * reads * d + (0 if step else 12 * d / 16)
+
+
 @pytest.mark.parametrize("args", [(0, 4, 4), (2, 3, 4), (2, 0, 4), (2, 4, 0), (2, -2, 4)])
 def test_plan_epoch_rejects_bad_sizes(p, args):
     with pytest.raises(p.CdgrabError) as ei:

@@ -85,7 +85,7 @@ def test_randomized_rule_over_steps(lib, m, n, d):
 @pytest.mark.parametrize("m,n,d", [
     (3, 24, 20), (1, 130, 50),                    # rows of at most 64 elements
     (1, 130, 66), (3, 86, 129), (1, 600, 1001),   # steps of 128 and 256 pairs, the last one ragged
-    (2, 130, 12_000), (1, 142, 40_003),           # of 128 and of 64 pairs
+    (2, 130, 12_000), (1, 142, 40_003),           # of 64 pairs
     (2, 20, 70_001),                              # one launch per block of pairs
 ])
 def test_value_that_is_not_finite_stays_where_it_is(lib, value, m, n, d):
@@ -99,3 +99,14 @@ def test_value_that_is_not_finite_stays_where_it_is(lib, value, m, n, d):
     want = np.einsum("ik,ikd->d", eps, diff)
     assert np.array_equal(out["r64"].cpu().numpy(), want, equal_nan=True)
     assert np.array_equal(out["r32"].cpu().numpy(), want.astype(np.float32), equal_nan=True)
+
+
+@pytest.mark.parametrize("m,n,d", [(1, 2050, 70), (16, 300, 7850), (3, 500, 16), (2, 130, 40_000), (3, 20, 300)])
+def test_timing_counts_what_the_plan_says(lib, m, n, d):
+    plan = lib.cdgrab_plan_epoch(m, n, d)
+    h = lib.Handle(timing=1)
+    z = torch.zeros((m, n, d), device="cuda")
+    lib.cdgrab_balance_epoch(h, m, n, d, grads=z)
+    unit = plan["step_pairs"] or plan["block_pairs"]
+    got = h.timing()
+    assert got["block_pairs"] == unit and got["blocks"] == -(-plan["pairs"] // unit)
