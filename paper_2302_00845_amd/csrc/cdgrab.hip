@@ -1221,10 +1221,22 @@ struct TrainCtx {
 };
 
 // Workers and classes that the blocks of steps are for: at least four steps per block and one MFMA column
-// tile of classes.  (16 workers, 784 -> 10: 2.6 us per step against 11.6 in a launch pair per step.)
+// tile of classes.  (16 workers, 784 -> 10: 2.6 us per step against 11.6 in a launch pair per step; 64
+// workers, whose blocks are four steps: 0.56 - 0.69 of the launch pairs' time at 784 .. 2000 -> 2 .. 8.)
 int64_t train_block_steps(int64_t m, int64_t n, int64_t classes) {
     const bool fits = m <= kSolveWorkers && classes <= kSolveClasses && n <= INT32_MAX / m;
     return fits ? std::min<int64_t>((kSolveExamples / m) & ~(int64_t)1, n) : 0;
+}
+
+// A block of fewer steps than this goes as launch pairs: its logits read all weights once per example, which
+// few steps do not repay.  Measured, time of an epoch of one block against its launch pairs (16 workers):
+// two steps 1.02 - 1.27 at 31 .. 784 features, 1.2 - 2.45 at 2000 .. 200 000; four steps 0.58 - 1.01 up to 2000
+// features and 0.8 - 0.97 beyond with more than eight classes, but 1.0 - 1.8 with 2 .. 8; six steps of those
+// 0.74 - 0.96, but 1.1 - 1.3 with four classes and 50 000 features or more; eight 0.58 - 0.95.  With more than
+// 32 workers a launch pair takes longer and four steps 0.72 - 0.84 (64 workers, 5000 -> 2).
+int64_t train_least_steps(int64_t m, int64_t in_dim, int64_t classes) {
+    if (m > 32 || in_dim <= 2048 || classes == 1 || classes > 8) return 4;
+    return in_dim > 32768 && classes <= 4 ? 8 : 6;
 }
 
 // Flattened pairs staged at a time: whole step pairs, about 64 pairs; for short rows about 1024 pairs, so that
@@ -1240,25 +1252,47 @@ int64_t train_chunk_pairs(const cdgrab_handle *h, int64_t m, int64_t n, int64_t 
         const int64_t sp = plan_chain(pairs, d, 1, 0, h->num_cu).sp;
         k = sp / std::gcd(base, sp);
         k *= std::max<int64_t>(1, 1024 / (base * k));
-        k = std::min(k, std::max<int64_t>(1024 / base, ((int64_t)1 << 28) / (base * 2 * d * 4)));
+        k = std::min(k, std::max<int64_t>(1024 / base, ((int64_t)1 << 28) / (2 * d * 4) / base));
         k = std::max<int64_t>(1, std::min(k, kGramBatch * bb / base));
     }
     return std::min(base * k, pairs);
 }
 
-// The steps j .. j_end - 1 of a chunk, a block at a time.
+// The steps j .. j_end - 1 of a chunk, a launch pair each.
+int train_step_launches(TrainCtx *c, int64_t j, int64_t j_end, int64_t k_first, float *staging) {
+    cdgrab_handle *h = c->h;
+    const size_t lds = (size_t)c->classes * sizeof(float);
+    for (; j < j_end; ++j) {
+        hipLaunchKernelGGL(train_step_delta, dim3((unsigned)c->m), dim3(kDeltaWaves * 64), lds, h->stream, c->X, c->y,
+                           c->perm_in, c->W, h->train_delta, c->loss_out, c->m, c->n, j, (int)c->in_dim,
+                           (int)c->classes);
+        auto update = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((c->d + 255) / 256)), dim3(256), 0, h->stream, c->X, c->perm_in,
+                               h->train_delta, c->W, c->velocity, staging, c->grads_out, c->m, c->n, j, k_first,
+                               (int)c->in_dim, (int)c->classes, c->lr, c->momentum);
+        };
+        if (c->perm_in) update(train_step_update<true>);
+        else update(train_step_update<false>);
+    }
+    HIP_TRY(h, hipGetLastError());
+    return CDGRAB_OK;
+}
+
+// The steps j .. j_end - 1 of a chunk, a block at a time; what is left for less than a shortest block, as above.
 int train_blocks(TrainCtx *c, int64_t j, int64_t j_end, int64_t k_first, float *staging) {
     cdgrab_handle *h = c->h;
-    const int64_t S = c->block_steps, m = c->m, d = c->in_dim;
+    const int64_t S = c->block_steps, m = c->m, d = c->in_dim, least = train_least_steps(c->m, c->in_dim, c->classes);
+    const int64_t rest = (j_end - j) % S, j_blocks = rest < least ? j_end - rest : j_end;
+    if (j == j_blocks) return train_step_launches(c, j, j_end, k_first, staging);
     GramBatch gb{};
     gb.rows.base = c->X;
     gb.rows.d = d;
     gb.rows.m = 1;
     gb.rows.layout = kStaged;
     gb.examples = h->train_order + j * m;
-    gb.pairs = (j_end - j) * m;
+    gb.pairs = (j_blocks - j) * m;
     gb.sp = (int32_t)(S * m);
-    gb.steps = gb.units = (int32_t)((j_end - j + S - 1) / S);
+    gb.steps = gb.units = (int32_t)((j_blocks - j + S - 1) / S);
     gb.tiles = c->tiles;
     gb.ksplit = c->ksplit;
     gb.ktiles = (int32_t)((d + kGramTE - 1) / kGramTE);
@@ -1267,7 +1301,7 @@ int train_blocks(TrainCtx *c, int64_t j, int64_t j_end, int64_t k_first, float *
     if (rc) return rc;
     const int64_t update_blocks = (c->d + 63) / 64, update_groups = update_blocks >= 16 ? round_up(update_blocks, 8) : update_blocks;
     for (int64_t b = 0; b < gb.units; ++b, j += S) {
-        const int steps = (int)std::min(S, j_end - j), examples = (int)(steps * m);
+        const int steps = (int)std::min(S, j_blocks - j), examples = (int)(steps * m);
         const int64_t *order = h->train_order + j * m;
         hipLaunchKernelGGL(train_base_logits, dim3((unsigned)examples), dim3(512), 0, h->stream, c->X, order, c->W, c->velocity, (int)d, (int)c->classes, h->train_base);
         auto solve = [&](auto kernel) {
@@ -1283,33 +1317,15 @@ int train_blocks(TrainCtx *c, int64_t j, int64_t j_end, int64_t k_first, float *
                            (int)d, (int)c->classes, c->lr, c->momentum);
     }
     HIP_TRY(h, hipGetLastError());
-    return CDGRAB_OK;
+    return train_step_launches(c, j_blocks, j_end, k_first, staging);
 }
 
-int train_generate(void *vctx, int64_t first_pair, int64_t count, float *staging, void *stream) {
+int train_generate(void *vctx, int64_t first_pair, int64_t count, float *staging, void *) {
     TrainCtx *c = static_cast<TrainCtx *>(vctx);
-    cdgrab_handle *h = c->h;
     if (first_pair % c->m != 0 || count % c->m != 0) return 1;  // chunks are whole step pairs
-    const int64_t k_first = first_pair / c->m, k_count = count / c->m;
-    if (c->block_steps > 0) return train_blocks(c, 2 * k_first, 2 * (k_first + k_count), k_first, staging);
-    const size_t lds = (size_t)c->classes * sizeof(float);
-    for (int64_t j = 2 * k_first; j < 2 * (k_first + k_count); ++j) {
-        hipLaunchKernelGGL(train_step_delta, dim3((unsigned)c->m), dim3(kDeltaWaves * 64), lds,
-                           static_cast<hipStream_t>(stream), c->X, c->y,
-                           c->perm_in, c->W, h->train_delta, c->loss_out, c->m, c->n, j, (int)c->in_dim,
-                           (int)c->classes);
-        if (c->perm_in)
-            hipLaunchKernelGGL(train_step_update<true>, dim3((unsigned)((c->d + 255) / 256)), dim3(256), 0,
-                               static_cast<hipStream_t>(stream), c->X, c->perm_in, h->train_delta, c->W,
-                               c->velocity, staging, c->grads_out, c->m, c->n, j, k_first, (int)c->in_dim,
-                               (int)c->classes, c->lr, c->momentum);
-        else
-            hipLaunchKernelGGL(train_step_update<false>, dim3((unsigned)((c->d + 255) / 256)), dim3(256), 0,
-                               static_cast<hipStream_t>(stream), c->X, c->perm_in, h->train_delta, c->W,
-                               c->velocity, staging, c->grads_out, c->m, c->n, j, k_first, (int)c->in_dim,
-                               (int)c->classes, c->lr, c->momentum);
-    }
-    return hipGetLastError() == hipSuccess ? 0 : 2;
+    const int64_t k_first = first_pair / c->m, j = 2 * k_first, j_end = j + 2 * (count / c->m);
+    return c->block_steps > 0 ? train_blocks(c, j, j_end, k_first, staging)
+                              : train_step_launches(c, j, j_end, k_first, staging);
 }
 }  // namespace
 
@@ -1327,12 +1343,13 @@ int cdgrab_train_epoch_softmax(cdgrab_handle *h, int64_t m, int64_t n, int64_t i
     if (momentum != 0.0f && !velocity)
         return fail(h, CDGRAB_EINVAL, "cdgrab_train_epoch_softmax: momentum needs a velocity buffer");
     HIP_TRY(h, hipSetDevice(h->device));
-    const int64_t block_steps = train_block_steps(m, n, classes);
+    const int64_t chunk = train_chunk_pairs(h, m, n, (in_dim + 1) * classes);
+    int64_t block_steps = std::min(train_block_steps(m, n, classes), 2 * (chunk / m));
+    if (block_steps < train_least_steps(m, in_dim, classes)) block_steps = 0;
     int rc = ensure(h, h->train_delta, h->train_delta_cap, block_steps > 0 ? block_steps * m * classes : m * classes);
     if (rc) return rc;
     TrainCtx ctx{h, m, n, in_dim, classes, (in_dim + 1) * classes, X, y, perm_in, W, velocity,
                  grads_out, loss_out, lr, momentum, block_steps, 0, 1};
-    const int64_t chunk = train_chunk_pairs(h, m, n, ctx.d);
     if (block_steps > 0) {
         const int64_t blocks = (std::min(2 * (chunk / m), n) + block_steps - 1) / block_steps;  // of a chunk
         const int64_t blk = (block_steps * m + kTilePairs - 1) / kTilePairs;

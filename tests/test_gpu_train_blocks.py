@@ -57,6 +57,18 @@ def test_blocks_of_steps_match_oracle(lib, m, n, in_dim, classes, momentum, with
     check_epoch(rows, {"signs": out["signs"].cpu().numpy(), "perm": out["perm"].cpu().numpy()}, perm)
 
 
+@pytest.mark.parametrize("m,n,in_dim,classes", [
+    (16, 2, 30, 10), (16, 18, 30, 10), (16, 20, 30, 10), (64, 6, 30, 10), (40, 14, 30, 4),   # 2 / 16 + 2 / 16 + 4 / 4 + 2 / 6 + 6 + 2
+    (16, 4, 2049, 4), (16, 20, 2049, 8), (16, 22, 2049, 2), (16, 4, 2049, 9), (33, 4, 2049, 4), (16, 4, 2048, 4),
+    (24, 12, 5500, 3), (40, 6, 5500, 3), (17, 12, 5500, 3), (16, 14, 32769, 4),              # rows of 16 503 and 131 080 elements
+])
+@pytest.mark.parametrize("with_perm", [True, False])
+def test_short_blocks_go_as_launch_pairs(lib, m, n, in_dim, classes, with_perm):
+    """Numbers of steps around the shortest block (4, 6 or 8 by features, classes and workers), which leave none,
+    some or all of a chunk's steps to a launch pair each."""
+    test_blocks_of_steps_match_oracle(lib, m, n, in_dim, classes, 0.9, with_perm)
+
+
 @pytest.mark.parametrize("m", [8, 65])                    # blocks of steps, a launch pair per step
 def test_label_that_names_no_class_leaves_its_loss(lib, m):
     """Such an example's delta is its softmax; nothing is written as its loss."""
