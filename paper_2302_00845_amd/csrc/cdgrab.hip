@@ -567,9 +567,14 @@ int launch_reorder(cdgrab_handle *h, int64_t m, int64_t n, const int8_t *signs, 
         const dim3 grid((unsigned)(std::min(most, m - i) * chunks)), block(kReorderThreads);
         if (chunks > 1)
             hipLaunchKernelGGL(reorder_count, grid, block, 0, h->stream, signs + i * n, n, chunks, h->reorder_counts);
-        hipLaunchKernelGGL(reorder_from_signs, grid, block, 0, h->stream, signs + i * n,
-                           perm_in ? perm_in + i * n : nullptr, perm_out + i * n, n, chunks, h->reorder_counts,
-                           h->flag);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, signs + i * n, perm_in ? perm_in + i * n : nullptr,
+                               perm_out + i * n, n, chunks, h->reorder_counts, h->flag);
+        };
+        if (n <= kReorderThreads) launch(reorder_from_signs<1>);
+        else if (n <= 4 * kReorderThreads) launch(reorder_from_signs<4>);
+        else if (n <= 8 * kReorderThreads) launch(reorder_from_signs<8>);
+        else launch(reorder_from_signs<kReorderPer>);
     }
     HIP_TRY(h, hipGetLastError());
     return CDGRAB_OK;

@@ -30,15 +30,16 @@ __global__ void build_pair_permutations(const int8_t *__restrict__ signs, const 
 
 // ---------------------------------------------------------------------------
 // General reorder from per-example signs (Sec. 2.1): a stable partition with the
-// negative part reversed.  A workgroup serves one chunk of kReorderChunk signs of one
+// negative part reversed.  A workgroup serves one chunk of 256 PER signs of one
 // worker: an exclusive prefix count of +1 signs gives each positive its slot from the
 // front and each negative its slot from the back.  Within a chunk the counts come from
-// wave votes (sixteen signs per thread, two barriers in all); the +1 signs of the earlier
+// wave votes (PER signs per thread, two barriers in all); the +1 signs of the earlier
 // chunks come from a count launch before it, which an order of one chunk does not need.
 // Bound by latency: n = 50 000 in one workgroup that walked 256 signs at a time 193 us,
-// these two launches 9 us.
+// these two launches 9 us.  Sixteen signs per thread, but no more than the order needs: threads that read
+// fifteen signs to drop them cost a call on 10 000 workers x 100 signs 62 us instead of 31.
 constexpr int kReorderThreads = 256;
-constexpr int kReorderPer = 16;  // signs per thread
+constexpr int kReorderPer = 16;  // signs per thread of an order of several chunks
 constexpr int kReorderChunk = kReorderThreads * kReorderPer;
 
 // counts[worker * chunks + chunk] = number of +1 signs
@@ -66,6 +67,7 @@ __global__ __launch_bounds__(kReorderThreads) void reorder_count(const int8_t *_
     }
 }
 
+template <int PER>
 __global__ __launch_bounds__(kReorderThreads) void reorder_from_signs(const int8_t *__restrict__ signs,
                                                                       const int32_t *__restrict__ perm_in,
                                                                       int32_t *__restrict__ perm_out, int64_t n,
@@ -73,20 +75,20 @@ __global__ __launch_bounds__(kReorderThreads) void reorder_from_signs(const int8
                                                                       const int32_t *__restrict__ counts,
                                                                       int32_t *__restrict__ bad_flag)
 {
-    constexpr int WAVES = kReorderThreads / 64;
-    __shared__ int group_tot[kReorderPer * WAVES];   // +1 signs of each 64 consecutive signs
+    constexpr int WAVES = kReorderThreads / 64, CHUNK = kReorderThreads * PER;
+    __shared__ int group_tot[PER * WAVES];   // +1 signs of each 64 consecutive signs
     __shared__ long long before_part[WAVES];
     const int64_t i = blockIdx.x / chunks, c = blockIdx.x - i * chunks;
     const int8_t *sg = signs + i * n;
     const int32_t *pin = perm_in ? perm_in + i * n : nullptr;
     int32_t *pout = perm_out + i * n;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int s[kReorderPer];
-    int32_t id[kReorderPer];
+    int s[PER];
+    int32_t id[PER];
     bool bad = false;
 #pragma unroll
-    for (int u = 0; u < kReorderPer; ++u) {
-        const int64_t j = c * kReorderChunk + u * kReorderThreads + threadIdx.x;
+    for (int u = 0; u < PER; ++u) {
+        const int64_t j = c * CHUNK + u * kReorderThreads + threadIdx.x;
         const int64_t jc = j < n ? j : n - 1;
         s[u] = sg[jc];
         id[u] = pin ? pin[jc] : (int32_t)jc;
@@ -95,38 +97,46 @@ __global__ __launch_bounds__(kReorderThreads) void reorder_from_signs(const int8
     }
     if (bad) atomicExch(bad_flag, 1);
     // +1 signs in the worker's earlier chunks
-    long long before = 0;
-    for (int64_t q = threadIdx.x; q < c; q += kReorderThreads) before += counts[i * chunks + q];
+    if (c > 0) {  // uniform
+        long long before = 0;
+        for (int64_t q = threadIdx.x; q < c; q += kReorderThreads) before += counts[i * chunks + q];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
-    if (lane == 0) before_part[wave] = before;
-    int rank[kReorderPer];  // +1 signs before this one within its 64
+        for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+        if (lane == 0) before_part[wave] = before;
+    }
+    int rank[PER];  // +1 signs before this one within its 64
 #pragma unroll
-    for (int u = 0; u < kReorderPer; ++u) {
+    for (int u = 0; u < PER; ++u) {
         const unsigned long long votes = __ballot(s[u] == 1);
         rank[u] = __popcll(votes & ((1ull << lane) - 1ull));
         if (lane == 0) group_tot[u * WAVES + wave] = __popcll(votes);
     }
     __syncthreads();
-    if (wave == 0) {  // exclusive scan over the 64 groups of the chunk
-        static_assert(kReorderPer * WAVES == 64, "one group per lane");
-        const int own = group_tot[lane];
-        int incl = own;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int up = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += up;
-        }
-        group_tot[lane] = incl - own;
-    }
-    __syncthreads();
     int64_t chunk_before = 0;
+    if constexpr (PER == 1) {  // four groups: each wavefront adds those before it
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) chunk_before += before_part[w];
+        for (int w = 0; w < WAVES; ++w) chunk_before += w < wave ? group_tot[w] : 0;
+    } else {
+        if (wave == 0) {  // exclusive scan over the groups of the chunk
+            static_assert(PER * WAVES <= 64, "one group per lane");
+            const int own = lane < PER * WAVES ? group_tot[lane] : 0;
+            int incl = own;
 #pragma unroll
-    for (int u = 0; u < kReorderPer; ++u) {
-        const int64_t j = c * kReorderChunk + u * kReorderThreads + threadIdx.x;
-        const int64_t pos_rank = chunk_before + group_tot[u * WAVES + wave] + rank[u];
+            for (int off = 1; off < 64; off <<= 1) {
+                const int up = __shfl_up(incl, off, 64);
+                if (lane >= off) incl += up;
+            }
+            if (lane < PER * WAVES) group_tot[lane] = incl - own;
+        }
+        __syncthreads();
+    }
+    if (c > 0)
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) chunk_before += before_part[w];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int64_t j = c * CHUNK + u * kReorderThreads + threadIdx.x;
+        const int64_t pos_rank = chunk_before + (PER == 1 ? 0 : group_tot[u * WAVES + wave]) + rank[u];
         if (s[u] == 1) pout[pos_rank] = id[u];
         else if (j < n) pout[n - 1 - (j - pos_rank)] = id[u];  // negatives fill from the back
     }

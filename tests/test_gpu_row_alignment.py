@@ -65,7 +65,8 @@ def test_stale_mean_column_mean_and_order(lib, n, d, shift):
     assert np.array_equal(out["perm"].cpu().numpy(), oracle.reorder(out["signs"].cpu().numpy(), None))
 
 
-@pytest.mark.parametrize("m,n", [(3, 4095), (3, 4096), (3, 4097), (2, 8192), (1, 8193), (70, 4100), (1, 1_000_003)])
+@pytest.mark.parametrize("m,n", [(5, 1), (5, 63), (5, 65), (300, 255), (3, 256), (3, 257), (3, 1023), (3, 1024),
+                                 (3, 1025), (3, 2047), (3, 2049), (3, 4095), (3, 4096), (3, 4097), (2, 8192), (1, 8193), (70, 4100), (1, 1_000_003)])
 @pytest.mark.parametrize("with_perm", [False, True])
 def test_reorder_across_chunks(lib, m, n, with_perm):
     signs = workloads.random_signs(n, m, n)
