@@ -143,11 +143,15 @@ constexpr int64_t kGramBytes = (int64_t)256 << 20;   // Gram tiles held at a tim
 // 1024: 20.7 -> 5.6; 4096: 20.9 -> 7.7; 7850: 22.4 -> 10.0; 16 384: 24.2 -> 13.6; 32 768: 33.8 -> 21.0;
 // 65 536: 46.6 -> 35.8; 98 304: 46.1 -> 49.7; 131 072: 66.5 -> 66.8 (the rows are read three times
 // instead of twice).
-constexpr int64_t kGramAheadMaxD = 65536;     // chosen by default up to here
+// That is for chains of many steps.  At 65 536 elements, where the per-block form changes to tiles of 128
+// elements, up to 128 pairs are faster in that form: 65 .. 128 pairs 87 against 103 us, 129 pairs 151 against
+// 139; at 57 344 elements 65 .. 128 pairs are equal.
+constexpr int64_t kGramAheadMaxD = 65536;     // chosen by default up to here ...
+constexpr int64_t kGramAheadEdgePairs = 128;  // ... where, at that length, there are more pairs than this
 constexpr int64_t kChunkAheadMaxD = 16384;    // and for staging chunks of several blocks up to here
 constexpr int64_t kGramAheadLimitD = 131072;  // refused beyond (gram_mode 2)
-bool gram_ahead_by_default(int64_t d, int64_t blocks, bool streamed) {
-    return !streamed && blocks >= 2 && d <= kGramAheadMaxD;
+bool gram_ahead_by_default(int64_t d, int64_t pairs) {
+    return d < kGramAheadMaxD || (d == kGramAheadMaxD && pairs > kGramAheadEdgePairs);
 }
 
 int part_size(int bb) {
@@ -223,11 +227,11 @@ int64_t staging_chunks(int64_t pairs, int64_t chunk_pairs, bool reads_previous) 
 }
 
 // The launch plan of one epoch.  `chunk_pairs` is the number of flattened pairs staged per
-// generator call (streamed input; 0 = one block).  Every decision an epoch takes is taken
+// generator call (streamed input; 0 = one block), `walks` the number of independent epochs side by side.  Every decision an epoch takes is taken
 // here, so that cdgrab_plan_epoch reports exactly what a handle with the same options runs.
 int plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t streamed,
                int64_t base_align, int num_cu, int32_t pass1_groups_opt, int apply_mode, int gram_mode,
-               int64_t chunk_pairs, cdgrab_plan *plan) {
+               int64_t chunk_pairs, int64_t walks, cdgrab_plan *plan) {
     if (m < 1 || n < 2 || (n & 1) || d < 1 || !plan) return CDGRAB_EINVAL;
     if (block_pairs != 0 && block_pairs != 16 && block_pairs != 32 && block_pairs != 64) return CDGRAB_EINVAL;
     if (base_align < 4 || (base_align & (base_align - 1))) return CDGRAB_EINVAL;
@@ -251,7 +255,7 @@ int plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t str
     // open; for streamed rows when a staging chunk holds more than one block's pairs.
     const bool ahead_dense = !streamed && plan->blocks >= 2 &&
                              (gram_mode == 2 || (gram_mode == 0 && apply_mode == 0 &&
-                                                 gram_ahead_by_default(d, plan->blocks, false)));
+                                                 gram_ahead_by_default(d, plan->pairs * walks)));
     const bool ahead_streamed = streamed && gram_mode != 1 && apply_mode == 0 && d <= kChunkAheadMaxD &&
                                 plan->pairs > bb && chunk_pairs > bb && chunk_pairs <= kGramBatch * bb;
     const bool ahead = ahead_dense || ahead_streamed;
@@ -683,7 +687,7 @@ const char *cdgrab_last_error(const cdgrab_handle *h) {
 
 int cdgrab_plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t streamed,
                       int64_t base_align, cdgrab_plan *plan) {
-    return plan_epoch(m, n, d, block_pairs, streamed, base_align, 256, 0, 0, 0, 0, plan);
+    return plan_epoch(m, n, d, block_pairs, streamed, base_align, 256, 0, 0, 0, 0, 1, plan);
 }
 
 int cdgrab_pergrad(cdgrab_handle *h, int64_t N, int64_t in_dim, int64_t classes, const float *X,
@@ -792,7 +796,7 @@ int Epoch::prepare() {
         return fail(h, CDGRAB_EINVAL, "cdgrab_balance_epoch: gram_mode 2 is for rows up to %lld elements (d=%lld)",
                     (long long)kGramAheadLimitD, (long long)d);
     int rc = plan_epoch(m, n, d, h->block_pairs_opt, streamed, align, h->num_cu, h->pass1_groups_opt,
-                        h->apply_mode, h->gram_mode, chunk_pairs, &plan);
+                        h->apply_mode, h->gram_mode, chunk_pairs, walks, &plan);
     if (rc != CDGRAB_OK) return fail(h, rc, "cdgrab_balance_epoch: sizes overflow or are invalid");
     bb = plan.block_pairs;
     if (chunk_pairs <= 0) chunk_pairs = bb;
@@ -1197,7 +1201,7 @@ int cdgrab_balance_epoch_independent(cdgrab_handle *h, int64_t m, int64_t n, int
         const uintptr_t a = reinterpret_cast<uintptr_t>(grads);
         cdgrab_plan one{};
         const int prc = plan_epoch(1, n, d, h->block_pairs_opt, 0, (a % 16 == 0) ? 16 : (a % 8 == 0) ? 8 : 4,
-                                   h->num_cu, h->pass1_groups_opt, h->apply_mode, h->gram_mode, 0, &one);
+                                   h->num_cu, h->pass1_groups_opt, h->apply_mode, h->gram_mode, 0, m, &one);
         if (prc == CDGRAB_OK && one.gram_ahead)
             return balance_epoch_impl(h, 1, n, d, grads, nullptr, nullptr, 0, perm_in, signs_out, perm_out,
                                       nullptr, nullptr, nullptr, nullptr, m);

@@ -88,6 +88,7 @@ def test_plan_epoch_headline_shapes(p):
     (16, 3750, 7850, 128, None), (4, 64, 1024, 128, None), (1, 2050, 70, 256, None), (2, 130, 12_000, 64, None),
     (1, 142, 40_003, 64, None),
     (20, 50_000, 16, 64, 1), (1, 130, 64, 64, 1),          # one workgroup walks 64 pairs at a time, rows read once
+    (1, 130, 65_532, 64, None), (1, 130, 65_536, 0, 2), (4, 64, 65_536, 0, 2), (1, 258, 65_536, 64, None),
     (4, 16, 1024, 0, 2), (32, 64, 1_048_575, 0, 2),        # block by block
 ])
 def test_plan_says_how_long_a_step_is(p, m, n, d, step, reads):

@@ -54,7 +54,7 @@ def test_centred_steps_match_oracle(lib, n, d):
     assert np.array_equal(out["r64"].cpu().numpy(), want["r"])
 
 
-@pytest.mark.parametrize("m,n,d", [(3, 128, 40), (9, 130, 40), (2, 600, 17), (40, 70, 1000), (5, 300, 9000)])
+@pytest.mark.parametrize("m,n,d", [(3, 128, 40), (9, 130, 40), (2, 600, 17), (40, 70, 1000), (5, 300, 9000), (2, 130, 65_536)])
 def test_walks_side_by_side_equal_single_walks(lib, m, n, d):
     z = workloads.integer_rows(m, m, n, d, 3)
     out = lib.cdgrab_balance_epoch_independent(lib.Handle(), torch.from_numpy(z).cuda())
