@@ -446,48 +446,36 @@ __global__ __launch_bounds__(kThreads) void reduce_partials(const double *__rest
 template <int BB> constexpr int kResolveThreads = BB > 32 ? 512 : 1024;
 
 // The walk is run by the workgroup's first wavefront.
-template <int BB, bool RANDOM, int SLICES>
-__global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const double *__restrict__ gram_src,
-                                                                     int64_t gram_stride,
-                                                                     const double *__restrict__ dot_src,
-                                                                     int dot_groups, int64_t dot_stride, int nb,
+template <int BB, bool RANDOM>
+__global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const double *__restrict__ sliced, int nb,
                                                                      int64_t k0, int32_t i0, int32_t m, int64_t half_n,
                                                                      int8_t *__restrict__ eps_blk,
                                                                      int8_t *__restrict__ signs_out,
                                                                      double *__restrict__ dots_out,
                                                                      const float *__restrict__ uniforms)
 {
-    // Gram tiles: sum of SLICES arrays gram_src[s * gram_stride + idx];
-    // dots: sum of dot_groups arrays dot_src[g * dot_stride + k]; both in index order.
+    // Gram tiles and dots: sums of the kReduceSlices arrays sliced[slice * PART], in order.
     using L = PartLayout<BB>;
     constexpr int NT = kResolveThreads<BB>;
-    constexpr int SUBS = (NT / BB < 16) ? NT / BB : 16;  // threads sharing one dot
     __shared__ double G[BB][BB + 1];
     __shared__ double P[BB];
-    __shared__ double psub[BB][SUBS + 1];
-    // The dots' first DV groups per thread are requested before anything else and
-    // consumed after the Gram tiles: indices beyond the last group re-read it and count
-    // as zero, so that no branch separates the loads.
-    constexpr int DV = (256 / SUBS < 32) ? 256 / SUBS : 32;  // loads per thread in the first batch
-    const int dk = (threadIdx.x / SUBS) % BB, dsub = threadIdx.x % SUBS;
-    double dv[DV];
-#pragma unroll
-    for (int u = 0; u < DV; ++u) {
-        const int g = dsub + u * SUBS;
-        dv[u] = dot_src[(int64_t)(g < dot_groups ? g : dot_groups - 1) * dot_stride + dk];
-    }
+    __shared__ double psub[BB][kReduceSlices + 1];
+    // A dot's slices are requested before anything else, one per thread, and consumed after the Gram tiles.
+    static_assert(BB * kReduceSlices <= NT, "a thread per dot and slice");
+    const int dk = (threadIdx.x / kReduceSlices) % BB, dsl = threadIdx.x % kReduceSlices;
+    const double dv = sliced[dsl * L::PART + L::GRAM + dk];
     // Two consecutive entries per thread and step (16 B loads; GRAM is even).  All loads
     // of a thread are issued before the first is used: entries beyond the end re-read
     // entry 0 and are dropped.
     constexpr int ITER = (L::GRAM + 2 * NT - 1) / (2 * NT);
-    double2 raw[ITER][SLICES];
+    double2 raw[ITER][kReduceSlices];
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
         const int idx = 2 * (int)threadIdx.x + it * 2 * NT;
         const int idc = idx < L::GRAM ? idx : 0;
 #pragma unroll
-        for (int sl = 0; sl < SLICES; ++sl)
-            raw[it][sl] = *reinterpret_cast<const double2 *>(gram_src + (int64_t)sl * gram_stride + idc);
+        for (int sl = 0; sl < kReduceSlices; ++sl)
+            raw[it][sl] = *reinterpret_cast<const double2 *>(sliced + sl * L::PART + idc);
     }
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
@@ -495,7 +483,7 @@ __global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const doubl
         if (idx >= L::GRAM) continue;
         double2 val = make_double2(0.0, 0.0);
 #pragma unroll
-        for (int sl = 0; sl < SLICES; ++sl) {
+        for (int sl = 0; sl < kReduceSlices; ++sl) {
             val.x += raw[it][sl].x;
             val.y += raw[it][sl].y;
         }
@@ -513,28 +501,12 @@ __global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const doubl
             if (th != tg) G[16 * th + j][16 * tg + i] = x;
         }
     }
-    if (threadIdx.x < BB * SUBS) {
-        double sum = 0.0;
-#pragma unroll
-        for (int u = 0; u < DV; ++u) sum += (dsub + u * SUBS < dot_groups) ? dv[u] : 0.0;
-        // (more than DV * SUBS groups: the rest in further batches of sixteen loads)
-        for (int g0 = dsub + DV * SUBS; g0 < dot_groups; g0 += 16 * SUBS) {
-            double v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int g = g0 + u * SUBS;
-                v[u] = dot_src[(int64_t)(g < dot_groups ? g : dot_groups - 1) * dot_stride + dk];
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) sum += (g0 + u * SUBS < dot_groups) ? v[u] : 0.0;
-        }
-        psub[dk][dsub] = sum;
-    }
+    if (threadIdx.x < BB * kReduceSlices) psub[dk][dsl] = dv;
     __syncthreads();
     if (threadIdx.x < BB) {
         double sum = 0.0;
 #pragma unroll
-        for (int q = 0; q < SUBS; ++q) sum += psub[threadIdx.x][q];
+        for (int q = 0; q < kReduceSlices; ++q) sum += psub[threadIdx.x][q];
         P[threadIdx.x] = sum;
     }
     __syncthreads();

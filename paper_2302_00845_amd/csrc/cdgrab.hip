@@ -393,15 +393,12 @@ void launch_pass2(cdgrab_handle *h, const RowMap &rm, int groups) {
 }
 template <int BB>
 void launch_resolve(cdgrab_handle *h, const RowMap &rm, int8_t *signs_out, double *dots_out) {
-    // Gram tiles and dots both come from the kReduceSlices slice sums
-    constexpr int part = PartLayout<BB>::PART;
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(1), dim3(kResolveThreads<BB>), 0, h->stream, h->reduced,
-                           (int64_t)part, h->reduced + PartLayout<BB>::GRAM, kReduceSlices, (int64_t)part, rm.nb,
-                           rm.k0, rm.i0, rm.m, rm.n / 2, h->eps_blk, signs_out, dots_out, h->uniforms);
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kResolveThreads<BB>), 0, h->stream, h->reduced, rm.nb, rm.k0, rm.i0,
+                           rm.m, rm.n / 2, h->eps_blk, signs_out, dots_out, h->uniforms);
     };
-    if (h->uniforms) launch(resolve_signs<BB, true, kReduceSlices>);
-    else launch(resolve_signs<BB, false, kReduceSlices>);
+    if (h->uniforms) launch(resolve_signs<BB, true>);
+    else launch(resolve_signs<BB, false>);
 }
 
 // Dispatch on how the rows are read, which is a template parameter of the kernels.
