@@ -6,7 +6,7 @@
 // sum, not on earlier signs -- and are taken off the chain: gram_tiles computes those of many
 // steps in one launch.  What stays on the chain is two launches per step:
 //   chain_apply_dots   r += sum eps_j d_j over the previous step, and this step's dots <r, d_k>,
-//                      every workgroup on 32 elements of d;
+//                      every workgroup on 64 elements of d;
 //   chain_walk         one workgroup adds the workgroups' shares of the dots and walks the step:
 //                      t_k = <r, d_k> + sum_{j<k} eps_j <d_j, d_k>, eps_k = +1 if t_k <= 0 else -1.
 // A longer step has fewer launches per pair and more Gram entries per pair (double MFMA work

@@ -67,11 +67,12 @@ def test_plan_epoch_headline_shapes(p):
     # inside its own launch, so it is not reported as the fused dot/Gram launch
     assert c2["gram_ahead"] == 1 and c2["bytes_per_example"] == 12 * 7850 + 8 * 7850 / 64
     assert c2["fused_apply"] == 0
-    # its workspace counts the buffers of that form: reduced Gram tiles of 469 blocks (+1 carried
-    # over), two blocks' per-workgroup dots, the row maps, and partials for all blocks' workgroups
+    # its workspace counts the buffers of that form: three 64 x 64 Gram tiles of each of 235 steps of 128
+    # pairs, perhaps in shares, and a step's dots of 123 workgroups; and the partials of the block form
+    assert c2["step_pairs"] == 128
     part = 10 * 256 + 64
-    groups = -(-4 * 256 // 469)
-    assert c2["workspace_bytes"] >= 469 * groups * part * 8 + 470 * part * 8 + 2 * 123 * 64 * 8
+    assert c2["workspace_bytes"] >= 235 * 3 * 64 * 64 * 8 + 123 * 128 * 8 + c2["pass1_groups"] * part * 8
+    assert c2["workspace_bytes"] < 65 * 235 * 3 * 64 * 64 * 8   # (at most 64 shares of a tile, and their sum)
     # long streamed rows: running sum + partials of 512 workgroups + one staging block
     assert c4["workspace_bytes"] >= 11_200_000 * 8 + 512 * (3 * 256 + 32) * 8 + c4["staging_bytes"]
     assert c4["workspace_bytes"] < 11_200_128 * 8 + 512 * (3 * 256 + 32) * 8 + c4["staging_bytes"] + (1 << 20)

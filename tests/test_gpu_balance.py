@@ -37,35 +37,38 @@ def run_epoch(p, z, perm_in=None, block_pairs=0, pass1_groups=0, apply_mode=0, g
 
 @pytest.mark.parametrize("case", HAND, ids=[c["name"] for c in HAND])
 @pytest.mark.parametrize("bb", [16, 32, 64])
-def test_hand_cases(lib, case, bb):
-    got = run_epoch(lib, case["rows"], block_pairs=bb)
+@pytest.mark.parametrize("gram_mode", [0, 1])             # (the steps of short rows take no notice of the block size)
+def test_hand_cases(lib, case, bb, gram_mode):
+    got = run_epoch(lib, case["rows"], block_pairs=bb, gram_mode=gram_mode)
     assert got["signs"].tolist() == case["eps"].tolist()
     assert got["r64"].tolist() == case["r"].tolist()
     assert got["perm"].tolist() == case["perm"].tolist()
 
 
+@pytest.mark.parametrize("gram_mode", [0, 1])
 @pytest.mark.parametrize("bb", [16, 32, 64])
 @pytest.mark.parametrize("seed,m,n,d,maxabs", [
     (0, 1, 2, 1, 3), (1, 1, 8, 3, 2), (2, 3, 6, 4, 2), (3, 4, 10, 7, 5), (4, 5, 4, 1, 1),
     (5, 2, 16, 2, 1), (6, 7, 12, 33, 9), (7, 4, 64, 1024, 8), (8, 3, 50, 777, 4),
     (9, 16, 8, 130, 2), (10, 33, 6, 258, 3), (11, 2, 70, 4100, 8), (12, 5, 60, 1500, 3),
 ])
-def test_exact_integer_inputs_bitwise(lib, bb, seed, m, n, d, maxabs):
+def test_exact_integer_inputs_bitwise(lib, gram_mode, bb, seed, m, n, d, maxabs):
     """Small-integer rows: all arithmetic is exact, so signs (ties included),
     running sum and permutations must equal the oracle bit for bit.  Shapes cover
     d < one tile, d not a multiple of 4 or 2, several tiles, ragged last block."""
     z = workloads.integer_rows(seed, m, n, d, maxabs)
     perm_in = workloads.random_perms(seed + 50, m, n)
-    got = run_epoch(lib, z, perm_in, block_pairs=bb)
+    got = run_epoch(lib, z, perm_in, block_pairs=bb, gram_mode=gram_mode)
     rep = check_epoch(z, got, perm_in, expect_exact_signs=True)
     assert rep["r64_rel_l2"] == 0.0
     assert rep["dots_max_abs_err"] == 0.0
 
 
 @pytest.mark.parametrize("bb", [16, 32, 64])
-def test_config1_tiny_epoch(lib, bb):
+@pytest.mark.parametrize("gram_mode", [0, 1])
+def test_config1_tiny_epoch(lib, bb, gram_mode):
     z = workloads.tiny_epoch(1234)                       # m=4, n=64, d=1024
-    got = run_epoch(lib, z, block_pairs=bb)
+    got = run_epoch(lib, z, block_pairs=bb, gram_mode=gram_mode)
     rep = check_epoch(z, got)
     assert rep["in_margin_flips"] == 0 or not rep["free_run_equal"]
 
@@ -98,7 +101,7 @@ def test_fused_and_separate_passes_agree(lib, m, n, d, bb):
 @pytest.mark.parametrize("m,n,d,bb,groups", [
     (4, 64, 1024, 16, 0), (3, 50, 777, 32, 0), (8, 40, 65536 + 12, 32, 0), (16, 30, 130, 64, 0),
     (2, 70, 30000, 0, 1),        # one workgroup: 30 groups per thread, two slabs of 15
-    (3, 22, 100001, 32, 2),      # odd row length (scalar loads), ragged last block, three slabs
+    (3, 22, 100001, 32, 2),      # odd row length, ragged last block, three slabs
     (2, 36, 262144 + 8, 16, 0),  # 65 538 groups on 257 workgroups: the last thread row is partly empty
     (1, 4, 1, 0, 0)])
 def test_resident_apply_matches_flat_apply(lib, m, n, d, bb, groups):
@@ -114,7 +117,7 @@ def test_resident_apply_matches_flat_apply(lib, m, n, d, bb, groups):
 
 
 def test_resident_apply_unaligned_rows(lib):
-    """Rows that start at an 8-byte (not 16-byte) boundary take the two-float loads."""
+    """Rows that start at an 8-byte (not 16-byte) boundary."""
     m, n, d = 2, 12, 20002
     z = workloads.heavy_rows(9, m, n, d)
     buf = torch.zeros(m * n * d + 2, dtype=torch.float32, device="cuda")
@@ -134,8 +137,8 @@ def test_resident_apply_unaligned_rows(lib):
 @pytest.mark.parametrize("m,n,d,bb", [(4, 64, 1024, 16), (3, 50, 777, 32), (8, 40, 65536 + 12, 32),
                                       (16, 30, 130, 64), (2, 70, 4100, 0), (5, 6, 3, 16), (1, 4, 1, 0)])
 def test_grams_ahead_and_per_block_agree(lib, m, n, d, bb):
-    """The Gram matrices do not depend on the running sum, so computing them for many
-    blocks ahead (one launch) and computing each inside its block's own launch are the
+    """The Gram matrices do not depend on the running sum, so computing them ahead for a
+    chain of steps (or for a one-workgroup walk) and computing each inside its block's own launch are the
     same computation: bit-identical on exact input, both within the oracle's tolerances on
     heavy-tailed rows.  (The long-row case forces the ahead form where it is not the default.)"""
     zi = workloads.integer_rows(m + n + 1, m, n, d, 6)
@@ -158,10 +161,11 @@ def test_grams_ahead_is_refused_for_long_rows(lib):
     assert ei.value.code == -1
 
 
-def test_grams_ahead_over_several_batches(lib):
-    """More blocks than one ahead-launch covers (512): the last block of a batch is the
-    previous block of the next batch's first."""
-    m, n, d = 3, 2 * 16 * 180, 37                     # 8640 pairs = 540 blocks of 16
+@pytest.mark.parametrize("d", [37, 71])                # one workgroup; 34 steps of the chain
+def test_grams_ahead_over_several_batches(lib, d):
+    """Many more pairs than a block or a step has, against 540 blocks of 16.  (More Gram tiles than are held at
+    a time: test_gpu_chain_steps.)"""
+    m, n = 3, 2 * 16 * 180                            # 8640 pairs
     zi = workloads.integer_rows(77, m, n, d, 3)
     a = run_epoch(lib, zi, block_pairs=16, gram_mode=2)
     b = run_epoch(lib, zi, block_pairs=16, gram_mode=1)
@@ -200,7 +204,7 @@ def test_seeded_random_shapes_exact(lib, m, n, d, bb, apply_mode, gram_mode):
 
 
 def test_unaligned_base_pointer(lib):
-    """A gradient array that starts 4 bytes into an allocation takes the scalar-load path."""
+    """A gradient array that starts 4 bytes into an allocation."""
     m, n, d = 3, 10, 1001
     z = workloads.integer_rows(21, m, n, d, 5)
     buf = torch.zeros(m * n * d + 1, dtype=torch.float32, device="cuda")

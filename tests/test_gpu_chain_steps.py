@@ -1,7 +1,7 @@
 """The chain of long steps that short rows are balanced with: numbers of pairs around its tiles of
-64 pairs and its steps of 64, 128 and 256 (rows of about 40 000, 12 000 and 50 elements choose
-those), in each layout the rows come in.  Small-integer rows, so every sum is exact and the
-oracle must be matched bit for bit, ties included."""
+64 pairs and its steps of 64, 128 and 256, in each layout the rows come in, more Gram tiles than
+are held at a time, and the one-workgroup walk of rows of at most 64 elements.  Small-integer rows, so
+every sum is exact and the oracle must be matched bit for bit, ties included."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +24,7 @@ def lib():
     (1, 512, 50), (1, 514, 50), (7, 220, 16), (100, 12, 16), (1, 2050, 3), (2, 126, 12_000), (3, 86, 12_001),
     (1, 600, 12_002), (2, 130, 40_000), (5, 56, 40_003), (3, 44, 65_536),
 ])
-def test_dense_steps_match_oracle(lib, m, n, d):
+def test_dense_epochs_match_oracle(lib, m, n, d):
     z = workloads.integer_rows(m + n, m, n, d, 3)
     perm = workloads.random_perms(2, m, n)
     out = lib.cdgrab_balance_epoch(lib.Handle(gram_mode=2), m, n, d, grads=torch.from_numpy(z).cuda(),
@@ -41,10 +41,55 @@ def test_dense_steps_match_oracle(lib, m, n, d):
 def test_narrow_rows_match_oracle(lib, m, n, d):
     """Rows of at most 64 elements: the whole walk in one workgroup, blocks of 64 pairs, the padded
     row lengths 16, 32 and 64."""
-    test_dense_steps_match_oracle(lib, m, n, d)
+    assert lib.cdgrab_plan_epoch(m, n, d)["step_pairs"] == (64 if m * n > 128 else 0)
+    test_dense_epochs_match_oracle(lib, m, n, d)
 
 
-@pytest.mark.parametrize("n,d", [(64, 17), (65, 16), (129, 40), (300, 16), (513, 5), (300, 12_000)])
+# the steps of these are what the plan says (asserted): full ones, a ragged last one, one or several
+@pytest.mark.parametrize("m,n,d,step", [
+    (1, 258, 66, 256), (1, 510, 66, 256), (1, 512, 66, 256), (1, 514, 66, 128), (1, 2050, 70, 256), (7, 220, 130, 256),
+    (5, 1000, 200, 256), (1, 2050, 1001, 256), (300, 10, 67, 256), (1, 130, 66, 128), (1, 600, 1001, 128),
+    (3, 256, 7850, 128), (16, 130, 2049, 256), (16, 130, 6001, 128), (1, 258, 12_000, 64), (3, 100, 30_001, 64),
+])
+def test_steps_of_every_length_match_oracle(lib, m, n, d, step):
+    assert lib.cdgrab_plan_epoch(m, n, d)["step_pairs"] == step
+    test_dense_epochs_match_oracle(lib, m, n, d)
+
+
+def steps_held(tiles_per_step):
+    """Steps whose Gram tiles (64 x 64 doubles each) are held at a time: 256 MB of them."""
+    return (256 << 20) // (tiles_per_step * 64 * 64 * 8)
+
+
+def test_more_steps_than_are_held_at_a_time(lib):
+    """220 000 pairs in steps of 256, ten tiles each: the last step of a batch of Gram tiles is applied
+    by the first step of the next."""
+    m, n, d = 1, 440_000, 66
+    plan = lib.cdgrab_plan_epoch(m, n, d)
+    assert plan["step_pairs"] == 256 and plan["pairs"] > steps_held(10) * 256
+    z = workloads.integer_rows(5, m, n, d, 3)
+    out = lib.cdgrab_balance_epoch(lib.Handle(), m, n, d, grads=torch.from_numpy(z).cuda(), want_r64=True)
+    want = oracle.server_epoch(z, None)
+    assert np.array_equal(out["signs"].cpu().numpy(), want["eps"])
+    assert np.array_equal(out["perm"].cpu().numpy(), want["perm"])
+    assert np.array_equal(out["r64"].cpu().numpy(), want["r"])
+
+
+def test_more_steps_of_many_walks_than_are_held_at_a_time(lib):
+    """1500 walks of 512 pairs side by side: whatever the steps' length, the walks' tiles (at least eight each)
+    do not fit at once.  Against the same walks one after the other, and three of them against the oracle."""
+    m, n, d = 1500, 1024, 66
+    assert m * (n // 2 // 64) > steps_held(1)
+    z = torch.randint(-3, 4, (m, n, d), device="cuda", dtype=torch.int8).float()
+    out = lib.cdgrab_balance_epoch_independent(lib.Handle(), z)
+    alone = lib.cdgrab_balance_epoch_independent(lib.Handle(gram_mode=1), z)
+    assert torch.equal(out["signs"], alone["signs"]) and torch.equal(out["perm"], alone["perm"])
+    for i in (0, 777, m - 1):
+        want = oracle.server_epoch(z[i:i + 1].cpu().numpy(), None)
+        assert np.array_equal(out["signs"][i].cpu().numpy(), want["eps"][0])
+
+
+@pytest.mark.parametrize("n,d", [(64, 17), (65, 16), (129, 40), (300, 16), (513, 5), (300, 12_000), (257, 66), (1100, 130)])
 def test_centred_steps_match_oracle(lib, n, d):
     g = workloads.integer_rows(n, 1, n, d, 3)[0]
     mean = np.rint(np.linspace(-2, 2, d)).astype(np.float32)
@@ -54,7 +99,7 @@ def test_centred_steps_match_oracle(lib, n, d):
     assert np.array_equal(out["r64"].cpu().numpy(), want["r"])
 
 
-@pytest.mark.parametrize("m,n,d", [(3, 128, 40), (9, 130, 40), (2, 600, 17), (40, 70, 1000), (5, 300, 9000), (2, 130, 65_536)])
+@pytest.mark.parametrize("m,n,d", [(3, 128, 40), (9, 130, 40), (2, 600, 17), (3, 1030, 70), (200, 140, 66), (40, 70, 1000), (5, 300, 9000), (2, 130, 65_536)])
 def test_walks_side_by_side_equal_single_walks(lib, m, n, d):
     z = workloads.integer_rows(m, m, n, d, 3)
     out = lib.cdgrab_balance_epoch_independent(lib.Handle(), torch.from_numpy(z).cuda())
@@ -64,7 +109,7 @@ def test_walks_side_by_side_equal_single_walks(lib, m, n, d):
         assert np.array_equal(out["perm"][i].cpu().numpy(), want["perm"][0])
 
 
-@pytest.mark.parametrize("m,n,d", [(3, 86, 30), (2, 300, 12_000), (1, 600, 20)])
+@pytest.mark.parametrize("m,n,d", [(3, 86, 30), (2, 300, 12_000), (1, 600, 20), (1, 1100, 70), (3, 86, 129)])
 def test_randomized_rule_over_steps(lib, m, n, d):
     """Rows scaled by a power of two (sums stay exact) so that many probabilities lie inside (0, 1)."""
     z = workloads.integer_rows(n, m, n, d, 2) * np.float32(2.0 ** -5)

@@ -48,11 +48,12 @@ def test_matches_oracle(lib, m, n, d, with_perm):
 
 @pytest.mark.parametrize("m,n,d,exact", [
     (5, 24, 300, False),        # one block per worker: m one-worker epochs back to back
-    (7, 200, 300, False),       # two blocks: the walks run side by side, the worker as a grid coordinate
-    (3, 2100, 40, True),        # seventeen blocks, a ragged last one, exact ties
-    (4, 300, 1001, True),       # odd row length: scalar loads, rows of later workers unaligned
+    (7, 200, 300, False),       # 100 pairs: the walks run side by side, the worker as a grid coordinate
+    (3, 2100, 40, True),        # rows of at most 64 elements: a workgroup per walk, 64 pairs at a time, exact ties
+    (4, 300, 1001, True),       # odd row length: rows of later workers unaligned
     (16, 468, 7850, False),     # config 2's row length
-    (2, 66000, 8, True),        # 516 blocks: more than one batch of Gram matrices, the last tile carried over
+    (2, 66000, 8, True),        # 33 000 pairs per worker
+    (2, 3000, 72, True),        # several steps of the chain per worker
     (70, 130, 16, False)])
 def test_independent_walks_match_oracle(lib, m, n, d, exact):
     """ID-GraB (PairBal): worker i's signs and order are those of a one-worker walk over its
