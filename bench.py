@@ -64,7 +64,7 @@ def parse_args():
                          "2: apply fused into the next block's dot/Gram launch")
     ap.add_argument("--gram-mode", type=int, default=0,
                     help="dense input: 0 library's choice; 1 every block computes its own Gram "
-                         "matrix; 2 Gram matrices of many blocks ahead in one launch")
+                         "matrix; 2 Gram matrices ahead of a chain of long steps")
     ap.add_argument("--n", type=int, default=0, help="override rows per worker (shorter epoch)")
     ap.add_argument("--seed", type=int, default=2302)
     ap.add_argument("--cpu-seconds", type=float, default=12.0,
@@ -210,8 +210,13 @@ def measure_config(name, args, steps, warmup, cpu_seconds):
     fused = fused and not ahead
     # whole balancer against the roofline: 8d + 12 d / Bb bytes per example with separate passes
     # (each row twice; double running sum read twice, written once per block), 8d + 8 d / Bb with the
-    # fused launch, 12d + 8 d / Bb with the Gram matrices ahead (rows read three times)
-    bytes_per_example = (12.0 * d + 8.0 * d / bb) if ahead else (8.0 * d + (8.0 if fused else 12.0) * d / bb)
+    # fused launch.  With the Gram matrices ahead the blocks reported are the chain's steps: rows are read three
+    # times, but for the first step's dots, the running sum read (but for the first step) and written once
+    # per step; rows of at most 64 elements are read once and the running sum stays on the chip.
+    in_one_launch = ahead and d <= 64
+    step_bytes = 8.0 * (N // 2) / blocks * d if in_one_launch else \
+        (24.0 * (N // 2) / blocks + 16.0) * d - (8.0 * min(bb, N // 2) + 8.0) / blocks * d
+    bytes_per_example = step_bytes * blocks / N if ahead else (8.0 * d + (8.0 if fused else 12.0) * d / bb)
     if w.kind == "softmax":
         bytes_per_example += 4.0 * d + 4.0 * 785              # the gradient kernel writes the row, reads x
     res = {
@@ -238,10 +243,10 @@ def measure_config(name, args, steps, warmup, cpu_seconds):
         _, tp = step(hp)
         avg_pairs = (N // 2) / blocks
         if ahead:
-            # per block: its share of the Gram tiles (rows once) and of a step's wide launch (rows of this
-            # step and of the previous one, running sum read and written); the walks are resolve_ms
-            per_kernel = (("gram_tiles+chain_apply_dots", tp["pass1_ms"] + tp["pass2_ms"],
-                           24.0 * avg_pairs * d + 16.0 * d),)
+            # per step of the chain: its share of the Gram tiles (rows once) and its wide launch (rows of this
+            # step and of the previous one, running sum); the walks are resolve_ms.  One launch: all of it
+            per_kernel = (("narrow_walk" if in_one_launch else "gram_tiles+chain_apply_dots",
+                           tp["pass1_ms"] + tp["pass2_ms"], step_bytes),)
         elif not fused:
             # algorithmic bytes per launch: both rows of every pair in the block (fp32) plus the
             # double running sum (read in pass 1; read and written in pass 2)
@@ -259,8 +264,12 @@ def measure_config(name, args, steps, warmup, cpu_seconds):
             avg_ms = ms / blocks
             kernels[kname] = {"avg_launch_ms": avg_ms, "algorithmic_bytes_per_launch": nbytes,
                               "achieved_GBs": nbytes / (avg_ms * 1e-3) / 1e9 if avg_ms > 0 else None}
-        kernels["reduce_partials"] = {"avg_launch_ms": tp["reduce_ms"] / blocks}
-        kernels["resolve_signs"] = {"avg_launch_ms": tp["resolve_ms"] / blocks}
+        if ahead:
+            kernels[per_kernel[0][0]]["averaged_over"] = "%d steps of %d pairs" % (blocks, bb)
+            kernels["chain_walk"] = {"avg_launch_ms": tp["resolve_ms"] / blocks}
+        else:
+            kernels["reduce_partials"] = {"avg_launch_ms": tp["reduce_ms"] / blocks}
+            kernels["resolve_signs"] = {"avg_launch_ms": tp["resolve_ms"] / blocks}
         dom = max((k[0] for k in per_kernel), key=lambda k: kernels[k]["avg_launch_ms"])
         traffic = read_traffic(name)
         res["roofline"] = {
@@ -403,7 +412,7 @@ def measure_next_row(name, args, steps, warmup):
         extra = {"steps_ms": float(np.mean([r[1]["generator_ms"] for r in runs])),
                  "balance_ms": float(np.mean([r[1]["balance_ms"] for r in runs])),
                  "mean_loss_by_epoch": [r[2] for r in runs],
-                 "note": "steps_ms = 2 launches per optimisation step (deltas; rows + mean + SGD update)"}
+                 "note": "steps_ms = blocks of 16 optimisation steps: Gram tiles of the features, logits, steps, rows + SGD updates"}
         metric, dtype = "training examples/sec (softmax regression under CD-GraB, one epoch)", "f32"
     else:
         G = pkg.cdgrab_pergrad(h, Xd, yd, torch.from_numpy(W0).to(dev)).view(m, n, d)

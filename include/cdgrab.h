@@ -65,8 +65,8 @@ typedef struct cdgrab_options {
                             (chosen by sizes, whatever the block size) at two launches each,
                             or, for rows of at most 64 elements, one launch in which one
                             workgroup per walk takes 64 pairs at a time; refused (EINVAL) for d > 131 072; 0 = choose (2 for rows up to
-                            65 536 elements when apply_mode is 0 as well; staged rows: up to
-                            16 384)                                                       */
+                            65 536 elements and more pairs than one block, at 65 536 than
+                            128, when apply_mode is 0 as well; staged rows: up to 16 384)  */
     int32_t apply_groups; /* cap on the workgroups of the resident apply kernel; 0 = two per CU */
 } cdgrab_options;
 

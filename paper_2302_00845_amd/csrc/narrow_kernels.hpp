@@ -6,10 +6,10 @@
 // wavefronts take turns walking a block, ten helpers meanwhile bring in the rows (two blocks
 // of loads in flight), form the differences in double and compute the next block's Gram matrix
 // by MFMA; then all helpers apply the decided block and take the next block's dots.
-// Bound by the serial chain of a block: the walk (15 ns per pair, four dependent instructions) and,
-// between two walks, apply + dots through LDS.  At 16 elements a block takes 1.9 us (walk 1.3,
-// apply 0.4, running sum 0.1, dots 0.2), 5.2 us in the steps of chain_kernels.hpp; at 64 elements
-// 3.2 us (the next block's Gram matrix, in MFMA time, outlasts the walk).  Longer rows would need
+// Bound by the serial chain of a block: the walk (20 ns per pair: four dependent instructions, 15 ns, and
+// a barrier on the way) and, between two walks, apply + dots through LDS.  At 16 elements a block takes 2.2 us
+// of an epoch (in-kernel clocks: walk 1.3, apply 0.4, running sum 0.1, dots 0.2), 5.2 us in the steps of
+// chain_kernels.hpp; at 33 .. 64 elements 3.8 us (the next block's Gram matrix, in MFMA time, outlasts the walk).  Longer rows would need
 // more LDS than a CU has for three blocks of differences and a Gram matrix.
 #pragma once
 #include "chain_kernels.hpp"
