@@ -170,7 +170,7 @@ struct ChainPlan {
 
 // Time of one step of sp pairs, microseconds, fitted to measured epochs, per step of 64 / 128 / 256 pairs:
 // 8192 pairs of 65 .. 256 elements 8.0 - 8.7 / 11.5 - 12.6 / 20.3 - 21.3 us, of 512 .. 2048 elements 9.7 - 10.0 /
-// 13.0 - 13.9 / 21.6 - 24.2; 30 000 pairs of 7850 elements 11.7 / 15.9 / 27.9 and 0.35 / 0.95 / 1.8 ms of Gram
+// 13.0 - 13.9 / 21.6 - 24.2; 30 000 pairs of 7850 elements 11.7 / 15.9 / 27.9 and 0.35 / 1.1 / 1.8 ms of Gram
 // tiles; 64 walks of 468 pairs of 7850: 82 us per 64-pair step.  Long chains of one walk want long steps, many walks
 // or long rows short ones.
 double step_cost_us(int64_t sp, int64_t d, int64_t walks) {

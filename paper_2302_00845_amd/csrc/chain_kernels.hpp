@@ -87,7 +87,7 @@ __host__ __device__ inline StepRows step_at(StepRows sr, int64_t first, int nb) 
 // enough steps, so that the rows they share come from its L2.
 // Bound by the matrix instructions and by what a diagonal tile leaves idle: three wavefronts compute
 // their quarters whole and the fourth has none, so ten 16 x 16 results are needed, twelve computed and the time
-// is that of sixteen.  Issued: 40 TFLOP/s on 235 steps of 128 pairs of 7850 elements (0.95 ms), 33 on 64 walks
+// is that of sixteen.  Issued: 35 TFLOP/s on 235 steps of 128 pairs of 7850 elements (1.08 ms), 33 on 64 walks
 // of 468 pairs, whose tiles are all diagonal (0.76 ms), of 48.9 in a loop of nothing else.
 struct GramBatch {
     StepRows rows;        // all pairs of the batch (nb unused)
