@@ -68,6 +68,7 @@ struct cdgrab_handle {
     int32_t *train_perm = nullptr; int64_t train_perm_cap = 0;  // spare [m][n] order of the multi-epoch driver
     int8_t *train_signs = nullptr; int64_t train_signs_cap = 0; // its [m][n/2] signs when the caller wants none
     double *herd_ws = nullptr; int64_t herd_cap = 0;      // herding evaluator: segment sums, starts, mean
+    double *herd_steps = nullptr; int64_t herd_steps_cap = 0;  // its steps' sums over the workers
     double *gram_all = nullptr; int64_t gram_all_cap = 0; // Grams-ahead form: Gram tiles of a batch of steps
     double *gram_parts = nullptr; int64_t gram_parts_cap = 0;      // shares of tiles whose elements are split
     double *dot_partials = nullptr; int64_t dot_partials_cap = 0;  // its per-workgroup dots of one step
@@ -664,6 +665,7 @@ int cdgrab_destroy(cdgrab_handle *h) {
     if (h->reorder_counts) (void)hipFree(h->reorder_counts);
     if (h->mean_ws) (void)hipFree(h->mean_ws);
     if (h->herd_ws) (void)hipFree(h->herd_ws);
+    if (h->herd_steps) (void)hipFree(h->herd_steps);
     if (h->train_delta) (void)hipFree(h->train_delta);
     if (h->train_order) (void)hipFree(h->train_order);
     if (h->train_base) (void)hipFree(h->train_base);
@@ -725,6 +727,15 @@ int cdgrab_pergrad(cdgrab_handle *h, int64_t N, int64_t in_dim, int64_t classes,
     HIP_TRY(h, hipGetLastError());
     return CDGRAB_OK;
 }
+
+// The herding evaluator keeps the steps' sums over the workers from this many workers on ... Measured, rows read
+// twice -> kept: four workers 363 -> 396 us (rows of 100 001 elements), 253 -> 225 (7850), 354 -> 380 (16 384); six
+// 362 -> 315, 344 -> 287, 354 -> 296; 32 workers 307 -> 219, 329 -> 226, 292 -> 210; rows of 8 .. 512 elements
+// equal up to twelve workers, 100 workers 147 -> 87 (16 elements).
+constexpr int64_t kHerdKeepMinWorkers = 6;
+constexpr int64_t kHerdKeepBytes = (int64_t)1 << 30;  // ... and up to this size
+
+constexpr int64_t kHerdScanMaxD = 128, kHerdManySegments = 160;  // of the prefix over the segments
 
 // Dispatch on the block size, which is a template parameter of the launch helpers.
 #define BY_BLOCK_PAIRS(bb, call64, call32, call16) ((bb) == 64 ? (call64) : (bb) == 32 ? (call32) : (call16))
@@ -1454,20 +1465,35 @@ int cdgrab_herding_bound(cdgrab_handle *h, int64_t m, int64_t n, int64_t d, cons
     const int lds_ids = (perm && sh.spw == 1 && ids_bytes <= 48 * 1024) ? 1 : 0;
     const size_t lds = lds_ids ? ids_bytes : 0;
     const int form = row_form((d % 4 == 0 && reinterpret_cast<uintptr_t>(z) % 16 == 0) ? 4 : 1, d);
+    // where the steps' sums are kept for the second pass (and fit), the rows are read once
+    const bool keep = m >= kHerdKeepMinWorkers && n <= kHerdKeepBytes / 32 / quads &&
+                      ensure(h, h->herd_steps, h->herd_steps_cap, n * quads * 4) == CDGRAB_OK;
     hipLaunchKernelGGL(herding_clear, dim3(1), dim3(1), 0, h->stream, bits);
     auto launch = [&](auto vw_tag) {
         constexpr int VW = decltype(vw_tag)::value;
-        hipLaunchKernelGGL((herding_segment_sums<VW>), grid, dim3(256), lds, h->stream, z, perm, sh, lds_ids, segsum);
-        // the prefix over segments: one thread per element for long rows, a workgroup scan per
-        // element for short ones (many segments, few elements)
-        if (sh.spw == 1)
-            hipLaunchKernelGGL(herding_segment_offsets, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, h->stream,
-                               segsum, sh, zbar, start);
+        auto sums = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(256), lds, h->stream, z, perm, sh, lds_ids, segsum, h->herd_steps);
+        };
+        if (keep) sums(herding_segment_sums<VW, true>);
+        else sums(herding_segment_sums<VW, false>);
+        // the prefix over segments: a workgroup per 16 elements, or per element where there are too few
+        // of them (m = 100, whole call: 100 elements 106 us by the scan, 113 otherwise; 512 elements 270 and 226)
+        if (d > kHerdScanMaxD)
+            if (sh.segments >= kHerdManySegments)
+                hipLaunchKernelGGL((herding_segment_offsets<16, 64>), dim3((unsigned)((d + 15) / 16)), dim3(1024), 0,
+                                   h->stream, segsum, sh, zbar, start);
+            else
+                hipLaunchKernelGGL((herding_segment_offsets<32, 8>), dim3((unsigned)((d + 31) / 32)), dim3(256), 0,
+                                   h->stream, segsum, sh, zbar, start);
         else
             hipLaunchKernelGGL(herding_segment_offsets_scan, dim3((unsigned)d), dim3(256), 0, h->stream,
                                segsum, sh, zbar, start);
-        hipLaunchKernelGGL((herding_prefix_max<VW>), grid, dim3(256), lds, h->stream, z, perm, sh, lds_ids, zbar,
-                           start, bits);
+        auto replay = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(256), keep ? 0 : lds, h->stream, z, perm, sh, lds_ids, zbar, start,
+                               h->herd_steps, bits);
+        };
+        if (keep) replay(herding_prefix_max<VW, true>);
+        else replay(herding_prefix_max<VW, false>);
     };
     if (form == kAligned) launch(std::integral_constant<int, kAligned>{});
     else if (form == kAnyRow) launch(std::integral_constant<int, kAnyRow>{});

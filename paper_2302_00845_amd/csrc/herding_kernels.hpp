@@ -6,6 +6,10 @@
 // pass C replays every segment from its starting prefix and keeps the largest
 // magnitude.  All sums are double; the result is a maximum, so the order in which
 // segments finish does not matter.
+// Bound by bytes.  Pass C needs only each step's sum over the workers, so with enough workers pass A
+// leaves those sums behind (8 bytes per step and element instead of 4 m read again):
+// 16 x 3750 rows of 7850 elements 711 -> 530 us (sums 446, of which about 100 for the 235 MB written
+// into the read stream; offsets 17; replay 54).  Non-temporal stores of the sums: 549.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -72,11 +76,13 @@ __device__ __forceinline__ const int32_t *herding_stage_ids(const int32_t *__res
 }
 
 // Pass A: segsum[s][e] = sum over the segment's steps and all workers.  One thread
-// per (segment = blockIdx.y, four consecutive elements).
-template <int VW>
+// per (segment = blockIdx.y, four consecutive elements).  STEPS: also steps[j][4 quads] = the sum of step j
+// over the workers (zero beyond d).
+template <int VW, bool STEPS>
 __global__ __launch_bounds__(256) void herding_segment_sums(const float *__restrict__ z,
                                                             const int32_t *__restrict__ perm, HerdingShape sh,
-                                                            int lds_ids, double *__restrict__ segsum)
+                                                            int lds_ids, double *__restrict__ segsum,
+                                                            double *__restrict__ steps)
 {
     extern __shared__ int32_t ids_lds[];
     int64_t s, qd;
@@ -91,6 +97,11 @@ __global__ __launch_bounds__(256) void herding_segment_sums(const float *__restr
     for (int64_t j = j0; j < j1; ++j) {
         double v[4];
         herding_step_sum<VW>(z, perm, ids ? ids + (j - j0) * sh.m : nullptr, sh, j, e, v);
+        if constexpr (STEPS) {
+            double2 *out = reinterpret_cast<double2 *>(steps + (j * sh.quads + qd) * 4);
+            out[0] = make_double2(v[0], v[1]);
+            out[1] = make_double2(v[2], v[3]);
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[q] += v[q];
     }
@@ -99,30 +110,48 @@ __global__ __launch_bounds__(256) void herding_segment_sums(const float *__restr
         if (e + q < sh.d) segsum[s * sh.d + e + q] = acc[q];
 }
 
-// Pass B (one thread per element): zbar[e] and start[s][e], the centred prefix
-// before segment s.
-__global__ __launch_bounds__(256) void herding_segment_offsets(const double *__restrict__ segsum, HerdingShape sh,
-                                                               double *__restrict__ zbar,
-                                                               double *__restrict__ start)
+// Pass B: zbar[e] and start[s][e], the centred prefix before segment s.  A workgroup serves ELEMS elements;
+// RUNS threads share an element, each taking a run of consecutive segments.  Bound by latency: one
+// thread per element walking all segments twice took 35 us for 268 segments of 7850 elements, now 17.
+// 64 runs, or 8 where there are few segments (21 segments of 100 001 elements, whole call: 438 us with 64, 378 with 8).
+template <int ELEMS, int RUNS>
+__global__ __launch_bounds__(ELEMS * RUNS) void herding_segment_offsets(const double *__restrict__ segsum,
+                                                                        HerdingShape sh, double *__restrict__ zbar,
+                                                                        double *__restrict__ start)
 {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= sh.d) return;
+    __shared__ double part[RUNS][ELEMS];
+    const int el = threadIdx.x % ELEMS, run = threadIdx.x / ELEMS;
+    const int64_t e = (int64_t)blockIdx.x * ELEMS + el;
+    const int64_t ec = e < sh.d ? e : sh.d - 1;
+    const int64_t s0 = run * sh.segments / RUNS, s1 = (run + 1) * sh.segments / RUNS;
+    double local = 0.0;
+#pragma unroll 8
+    for (int64_t s = s0; s < s1; ++s) local += segsum[s * sh.d + ec];
+    part[run][el] = local;
+    __syncthreads();
     double total = 0.0;
 #pragma unroll 8
-    for (int64_t s = 0; s < sh.segments; ++s) total += segsum[s * sh.d + e];
+    for (int q = 0; q < RUNS; ++q) total += part[q][el];
     const double mean = total / (double)(sh.m * sh.n);
-    zbar[e] = mean;
-    double run = 0.0;
+    if (e >= sh.d) return;
+    if (run == 0) zbar[e] = mean;
+    // (the runs before this one, each centred before it is added: their sums are small, the rows' are not; all
+    // their segments are full)
+    double at = 0.0;
+    for (int q = 0; q < run; ++q) {
+        const int64_t full = (q + 1) * sh.segments / RUNS - q * sh.segments / RUNS;
+        at += part[q][el] - (double)(full * sh.seg_len * sh.m) * mean;
+    }
 #pragma unroll 8
-    for (int64_t s = 0; s < sh.segments; ++s) {
-        start[s * sh.d + e] = run;
+    for (int64_t s = s0; s < s1; ++s) {
+        start[s * sh.d + e] = at;
         const int64_t j0 = s * sh.seg_len;
         const int64_t len = ((j0 + sh.seg_len < sh.n) ? sh.seg_len : sh.n - j0);
-        run += segsum[s * sh.d + e] - (double)(len * sh.m) * mean;
+        at += segsum[s * sh.d + e] - (double)(len * sh.m) * mean;
     }
 }
 
-// Pass B for short rows, where there are many segments and few elements: one workgroup per
+// Pass B for the shortest rows, where there are many segments and few elements: one workgroup per
 // element; thread t takes a run of consecutive segments, the workgroup adds the runs' sums
 // (mean), scans the centred run sums in thread order, and every thread then walks its run.
 __global__ __launch_bounds__(256) void herding_segment_offsets_scan(const double *__restrict__ segsum,
@@ -164,12 +193,13 @@ __global__ __launch_bounds__(256) void herding_segment_offsets_scan(const double
 
 // Pass C: replay each segment from its starting prefix; the largest |prefix| seen
 // anywhere is folded into *bound with an integer max on the bit pattern (valid
-// for non-negative doubles).
-template <int VW>
+// for non-negative doubles).  STEPS: the steps' sums over the workers come from pass A.
+template <int VW, bool STEPS>
 __global__ __launch_bounds__(256) void herding_prefix_max(const float *__restrict__ z,
                                                           const int32_t *__restrict__ perm, HerdingShape sh,
                                                           int lds_ids, const double *__restrict__ zbar,
                                                           const double *__restrict__ start,
+                                                          const double *__restrict__ steps,
                                                           unsigned long long *__restrict__ bound_bits)
 {
     __shared__ double wave_max[4];
@@ -178,7 +208,7 @@ __global__ __launch_bounds__(256) void herding_prefix_max(const float *__restric
     const bool active = herding_thread_role(sh, s, qd);
     const int64_t j0 = s * sh.seg_len;
     const int64_t j1 = (j0 + sh.seg_len < sh.n) ? j0 + sh.seg_len : sh.n;
-    const int32_t *ids = herding_stage_ids(perm, sh, j0, j1, sh.spw == 1 ? lds_ids : 0, ids_lds);
+    const int32_t *ids = STEPS ? nullptr : herding_stage_ids(perm, sh, j0, j1, sh.spw == 1 ? lds_ids : 0, ids_lds);
     double mx = 0.0;
     if (active) {
         const int64_t e = qd * 4;
@@ -189,13 +219,25 @@ __global__ __launch_bounds__(256) void herding_prefix_max(const float *__restric
             centre[q] = in ? (double)sh.m * zbar[e + q] : 0.0;
             acc[q] = in ? start[s * sh.d + e + q] : 0.0;
         }
-        for (int64_t j = j0; j < j1; ++j) {
-            double v[4];
-            herding_step_sum<VW>(z, perm, ids ? ids + (j - j0) * sh.m : nullptr, sh, j, e, v);
+        auto take = [&](const double (&v)[4]) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 acc[q] += v[q] - centre[q];
                 mx = fmax(mx, fabs(acc[q]));
+            }
+        };
+        if constexpr (STEPS) {
+            const double2 *in = reinterpret_cast<const double2 *>(steps + qd * 4);
+#pragma unroll 8
+            for (int64_t j = j0; j < j1; ++j) {
+                const double2 lo = in[j * sh.quads * 2], hi = in[j * sh.quads * 2 + 1];
+                take({lo.x, lo.y, hi.x, hi.y});
+            }
+        } else {
+            for (int64_t j = j0; j < j1; ++j) {
+                double v[4];
+                herding_step_sum<VW>(z, perm, ids ? ids + (j - j0) * sh.m : nullptr, sh, j, e, v);
+                take(v);
             }
         }
     }

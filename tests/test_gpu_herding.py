@@ -46,6 +46,20 @@ def test_matches_oracle(lib, m, n, d, with_perm):
     assert abs(got - want) <= 1e-9 * max(want, 1e-30)
 
 
+@pytest.mark.parametrize("m", [5, 6, 7])  # the steps' sums are kept from six workers on
+@pytest.mark.parametrize("n,d", [(1, 1), (257, 6), (40, 127), (300, 128), (300, 129), (65, 513), (700, 2049), (3, 100_003)])
+def test_steps_kept_or_read_again(lib, m, n, d):
+    """Both forms of the second pass and of the prefix over the segments, one handle for calls of growing
+    and shrinking size; sums of doubles, so only their order can differ from the oracle's."""
+    h = lib.Handle()
+    for steps in (n, 3 * n, max(1, n // 2)):
+        z = workloads.heavy_rows(m + steps, m, steps, d)
+        perm = workloads.random_perms(steps, m, steps)
+        want = oracle.parallel_herding(z, perm)
+        # m * steps double sums of rounding 1.1e-16 each, taken relative to the largest prefix
+        assert abs(gpu_bound(lib, h, z, perm) - want) <= 1e-12 * max(float(np.abs(z).sum((0, 1)).max()), 1e-30)
+
+
 @pytest.mark.parametrize("m,n,d,exact", [
     (5, 24, 300, False),        # one block per worker: m one-worker epochs back to back
     (7, 200, 300, False),       # 100 pairs: the walks run side by side, the worker as a grid coordinate
