@@ -79,16 +79,17 @@ __host__ __device__ inline StepRows step_at(StepRows sr, int64_t first, int nb) 
 // Gram tiles of many steps.  One workgroup computes one 64 x 64 tile (ti <= tj) of one step over
 // its share of d: tiles of kGramTE elements of the 64 + 64 pair differences are formed in double
 // on the way into LDS (an element is used by two wavefronts, so it is converted once instead of
-// twice), each of the four wavefronts owns a 32 x 32 quarter of the tile, and the next tile's
-// loads are in flight meanwhile.  LDS rows are 34 doubles: the sixteen rows a quarter of a
+// twice), and the next tile's loads are in flight meanwhile.  Off the diagonal each of the four wavefronts
+// owns a 32 x 32 quarter of the tile.  On it only the ten 16 x 16 results of the upper triangle
+// are needed, which four quarters cannot share evenly (three whole quarters and an idle wavefront took the
+// time of sixteen results), so there each wavefront takes a quarter of the elements and all ten.
+// LDS rows are 34 doubles: the sixteen rows a quarter of a
 // wavefront reads start four banks apart, so the 16-byte reads do not collide.  Element order
 // inside a tile: lane slot s of MFMA step 2q (2q + 1) takes element 8 q + 2 s (+ 1), the same for
 // both operands.  The tiles of one step are consecutive workgroups of one XCD where there are
 // enough steps, so that the rows they share come from its L2.
-// Bound by the matrix instructions and by what a diagonal tile leaves idle: three wavefronts compute
-// their quarters whole and the fourth has none, so ten 16 x 16 results are needed, twelve computed and the time
-// is that of sixteen.  Issued: 35 TFLOP/s on 235 steps of 128 pairs of 7850 elements (1.08 ms), 33 on 64 walks
-// of 468 pairs, whose tiles are all diagonal (0.76 ms), of 48.9 in a loop of nothing else.
+// Bound by the matrix instructions: 41 TFLOP/s on 235 steps of 128 pairs of 7850 elements (1.09 -> 0.82 ms),
+// 40 on 64 walks of 468 pairs, whose tiles are all diagonal (0.76 -> 0.51 ms), of 48.9 in a loop of nothing else.
 struct GramBatch {
     StepRows rows;        // all pairs of the batch (nb unused)
     int64_t pairs;        // pairs in the batch
@@ -105,6 +106,9 @@ constexpr int kGramTE = 32;
 
 // Position of tile (ti, tj), ti <= tj, in a step's list: (0,0) (0,1) (1,1) (0,2) (1,2) (2,2) ..
 __host__ __device__ constexpr int tile_index(int ti, int tj) { return tj * (tj + 1) / 2 + ti; }
+
+// A thread's share of a tile of elements, N rows of pairs: four elements of both rows each.
+template <int N> struct GramPieces { float4 a[N], b[N]; };
 
 template <int VW, bool SINGLE>
 __global__ __launch_bounds__(kThreads, 2) void gram_tiles(GramBatch gb, double *__restrict__ out)
@@ -131,7 +135,6 @@ __global__ __launch_bounds__(kThreads, 2) void gram_tiles(GramBatch gb, double *
     StepRows rows = gb.rows;
     rows.base += walk * gb.walk_floats;
     rows = step_at(rows, (int64_t)step * gb.sp, nb);
-    const bool diag = ti == tj;
     const int64_t d = rows.d;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -149,79 +152,144 @@ __global__ __launch_bounds__(kThreads, 2) void gram_tiles(GramBatch gb, double *
     const int kt0 = (int)((int64_t)blockIdx.y * gb.ktiles / gb.ksplit);
     const int kt1 = (int)((int64_t)(blockIdx.y + 1) * gb.ktiles / gb.ksplit);
 
-    float4 fa[4], fb[4];
-    const int sides = diag ? 2 : 4;
-    auto load = [&](int kt) {
+    double *dst = out + (((int64_t)unit * gb.tiles + tile) * gb.ksplit + blockIdx.y) * kTileEntries;
+    const int mrow = lane & 15, kslot = lane >> 4;
+    // N 32-row pieces of a tile of elements: the diagonal tile's two, or the four of both sides
+    auto load = [&](auto &x, int kt) {
+        constexpr int N = sizeof(x.a) / sizeof(x.a[0]);
         const int64_t e = (int64_t)kt * kGramTE + quad * 4;
         if ((int64_t)(kt + 1) * kGramTE <= d) {  // uniform
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                if (s < sides) {
-                    const float4_t b = load_four<false>(src[s][1] + e);
-                    const float4_t a = SINGLE ? (float4_t){0.f, 0.f, 0.f, 0.f} : load_four<false>(src[s][0] + e);
-                    fa[s] = make_float4(a.x, a.y, a.z, a.w);
-                    fb[s] = make_float4(b.x, b.y, b.z, b.w);
-                }
+            for (int s = 0; s < N; ++s) {
+                const float4_t b = load_four<false>(src[s][1] + e);
+                const float4_t a = SINGLE ? (float4_t){0.f, 0.f, 0.f, 0.f} : load_four<false>(src[s][0] + e);
+                x.a[s] = make_float4(a.x, a.y, a.z, a.w);
+                x.b[s] = make_float4(b.x, b.y, b.z, b.w);
+            }
         } else {
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                if (s < sides) {
-                    fa[s] = SINGLE ? make_float4(0.f, 0.f, 0.f, 0.f) : load4_nb<VW>(src[s][0], true, e, d);
-                    fb[s] = load4_nb<VW>(src[s][1], true, e, d);
-                }
+            for (int s = 0; s < N; ++s) {
+                x.a[s] = SINGLE ? make_float4(0.f, 0.f, 0.f, 0.f) : load4_nb<VW>(src[s][0], true, e, d);
+                x.b[s] = load4_nb<VW>(src[s][1], true, e, d);
+            }
         }
     };
-    auto store = [&](int stage) {
+    auto store = [&](const auto &x, int stage) {
+        constexpr int N = sizeof(x.a) / sizeof(x.a[0]);
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-            if (s < sides) {
-                double2 *p = reinterpret_cast<double2 *>(&lds[stage][s >> 1][((s & 1) * 32 + prow) * STRIDE + quad * 4]);
-                p[0] = make_double2((double)fb[s].x - (double)fa[s].x, (double)fb[s].y - (double)fa[s].y);
-                p[1] = make_double2((double)fb[s].z - (double)fa[s].z, (double)fb[s].w - (double)fa[s].w);
-            }
+        for (int s = 0; s < N; ++s) {
+            double2 *p = reinterpret_cast<double2 *>(&lds[stage][s >> 1][((s & 1) * 32 + prow) * STRIDE + quad * 4]);
+            p[0] = make_double2((double)x.b[s].x - (double)x.a[s].x, (double)x.b[s].y - (double)x.a[s].y);
+            p[1] = make_double2((double)x.b[s].z - (double)x.a[s].z, (double)x.b[s].w - (double)x.a[s].w);
+        }
     };
 
+    if (ti == tj) {  // uniform
+        // A wavefront takes a quarter of the elements of every tile and all ten results of the upper triangle,
+        // two tiles of loads in flight; the quarters' results are added in order through LDS.
+        GramPieces<2> even, odd;
+        double4_t acc[10];
+#pragma unroll
+        for (int q = 0; q < 10; ++q) acc[q] = (double4_t){0.0, 0.0, 0.0, 0.0};
+        if (kt0 < kt1) {
+            load(even, kt0);
+            if (kt0 + 1 < kt1) load(odd, kt0 + 1);
+            store(even, 0);
+            if (kt0 + 2 < kt1) load(even, kt0 + 2);
+        }
+        __syncthreads();
+        auto tile_of = [&](int kt, GramPieces<2> &next) {
+            const int stage = (kt - kt0) & 1;
+            const double *A = lds[stage][0] + mrow * STRIDE + 8 * wave + 2 * kslot;
+            double2 a[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) a[g] = *reinterpret_cast<const double2 *>(A + g * 16 * STRIDE);
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+#pragma unroll
+                for (int g = 0; g <= h; ++g)
+                    acc[tile_index(g, h)] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g].x, a[h].x, acc[tile_index(g, h)], 0, 0, 0);
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+#pragma unroll
+                for (int g = 0; g <= h; ++g)
+                    acc[tile_index(g, h)] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g].y, a[h].y, acc[tile_index(g, h)], 0, 0, 0);
+            if (kt + 1 < kt1) store(next, stage ^ 1);
+            if (kt + 3 < kt1) load(next, kt + 3);
+            __syncthreads();
+        };
+        for (int kt = kt0; kt < kt1; kt += 2) {
+            tile_of(kt, odd);
+            if (kt + 1 < kt1) tile_of(kt + 1, even);
+        }
+        // result q is added by wavefront q % 4, the other three leave theirs in LDS
+        double4_t *red = reinterpret_cast<double4_t *>(&lds[0][0][0]);
+        static_assert(10 * 3 * 64 * sizeof(double4_t) <= sizeof(lds), "three wavefronts' results");
+#pragma unroll
+        for (int q = 0; q < 10; ++q)
+            if ((q & 3) != wave) red[(q * 3 + wave - (wave > (q & 3) ? 1 : 0)) * 64 + lane] = acc[q];
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                // (the walk's columns are zero at and above the diagonal)
+                const int q = g <= h ? tile_index(g, h) : g * 4 + h;
+                if ((q & 3) != wave) continue;
+                double4_t sum = (double4_t){0.0, 0.0, 0.0, 0.0};
+                if (g <= h) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w)
+                        sum += w == (q & 3) ? acc[g <= h ? q : 0] : red[(q * 3 + w - (w > (q & 3) ? 1 : 0)) * 64 + lane];
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    int i, j;
+                    mfma_f64_16x16_coord(lane, v, i, j);
+                    const int r = 16 * g + i, c = 16 * h + j;
+                    dst[r * kTilePairs + c] = r < c ? sum[v] : 0.0;
+                }
+            }
+        return;
+    }
+
+    GramPieces<4> x;
     double4_t acc[2][2];
 #pragma unroll
     for (int g = 0; g < 2; ++g)
 #pragma unroll
         for (int h = 0; h < 2; ++h) acc[g][h] = (double4_t){0.0, 0.0, 0.0, 0.0};
     const int wi = wave >> 1, wj = wave & 1;
-    const int mrow = lane & 15, kslot = lane >> 4;
-    const bool idle = diag && wi > wj;  // the lower quarter of a symmetric tile
 
     if (kt0 < kt1) {
-        load(kt0);
-        store(0);
+        load(x, kt0);
+        store(x, 0);
     }
     __syncthreads();
     for (int kt = kt0; kt < kt1; ++kt) {
         const int stage = (kt - kt0) & 1;
-        if (kt + 1 < kt1) load(kt + 1);
-        if (!idle) {
-            const double *A = lds[stage][0] + (32 * wi + mrow) * STRIDE + 2 * kslot;
-            const double *B = lds[stage][diag ? 0 : 1] + (32 * wj + mrow) * STRIDE + 2 * kslot;
+        if (kt + 1 < kt1) load(x, kt + 1);
+        const double *A = lds[stage][0] + (32 * wi + mrow) * STRIDE + 2 * kslot;
+        const double *B = lds[stage][1] + (32 * wj + mrow) * STRIDE + 2 * kslot;
 #pragma unroll
-            for (int q = 0; q < kGramTE / 8; ++q) {
-                double2 a[2], b[2];
+        for (int q = 0; q < kGramTE / 8; ++q) {
+            double2 a[2], b[2];
 #pragma unroll
-                for (int g = 0; g < 2; ++g) {
-                    a[g] = *reinterpret_cast<const double2 *>(A + g * 16 * STRIDE + 8 * q);
-                    b[g] = *reinterpret_cast<const double2 *>(B + g * 16 * STRIDE + 8 * q);
-                }
-#pragma unroll
-                for (int g = 0; g < 2; ++g)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        acc[g][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g].x, b[h].x, acc[g][h], 0, 0, 0);
-                        acc[g][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g].y, b[h].y, acc[g][h], 0, 0, 0);
-                    }
+            for (int g = 0; g < 2; ++g) {
+                a[g] = *reinterpret_cast<const double2 *>(A + g * 16 * STRIDE + 8 * q);
+                b[g] = *reinterpret_cast<const double2 *>(B + g * 16 * STRIDE + 8 * q);
             }
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    acc[g][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g].x, b[h].x, acc[g][h], 0, 0, 0);
+                    acc[g][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g].y, b[h].y, acc[g][h], 0, 0, 0);
+                }
         }
-        if (kt + 1 < kt1) store(stage ^ 1);
+        if (kt + 1 < kt1) store(x, stage ^ 1);
         __syncthreads();
     }
-    double *dst = out + (((int64_t)unit * gb.tiles + tile) * gb.ksplit + blockIdx.y) * kTileEntries;
 #pragma unroll
     for (int g = 0; g < 2; ++g)
 #pragma unroll
@@ -230,9 +298,7 @@ __global__ __launch_bounds__(kThreads, 2) void gram_tiles(GramBatch gb, double *
             for (int v = 0; v < 4; ++v) {
                 int i, j;
                 mfma_f64_16x16_coord(lane, v, i, j);
-                const int r = 32 * wi + 16 * g + i, c = 32 * wj + 16 * h + j;
-                // (the walk's columns are zero at and above the diagonal)
-                dst[r * kTilePairs + c] = !diag || r < c ? acc[g][h][v] : 0.0;
+                dst[(32 * wi + 16 * g + i) * kTilePairs + 32 * wj + 16 * h + j] = acc[g][h][v];
             }
 }
 

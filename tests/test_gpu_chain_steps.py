@@ -56,6 +56,14 @@ def test_steps_of_every_length_match_oracle(lib, m, n, d, step):
     test_dense_epochs_match_oracle(lib, m, n, d)
 
 
+@pytest.mark.parametrize("d", [65, 96, 97, 128, 129, 160, 161, 225])
+@pytest.mark.parametrize("m,n", [(1, 130), (9, 128), (2, 258)])
+def test_tiles_of_few_elements_match_oracle(lib, m, n, d):
+    """Gram tiles shared by workgroups of one to a few tiles of 32 elements each (one walk), and whole (many)."""
+    test_dense_epochs_match_oracle(lib, m, n, d)
+    test_walks_side_by_side_equal_single_walks(lib, 40 * m, n, d)
+
+
 def steps_held(tiles_per_step):
     """Steps whose Gram tiles (64 x 64 doubles each) are held at a time: 256 MB of them."""
     return (256 << 20) // (tiles_per_step * 64 * 64 * 8)
