@@ -183,14 +183,15 @@ double step_cost_us(int64_t sp, int64_t d, int64_t walks) {
 }
 
 // Workgroups per Gram tile: the launch takes whole rounds of two workgroups per CU, each as long as its
-// share of a tile; shares cost a write and two reads of a tile each.  (128 pairs of 1024 elements: tiles and their
-// sums 15.3 us in 8 shares of four tiles of elements, 13.7 in 32 of one.)
+// share of a tile; shares cost a write and two reads of a tile each.  At least four tiles of elements per share (128
+// pairs of 1024 elements in 32 shares of one instead of 8 of four: 1.6 us less for the tiles, and 25 us more
+// for a workspace four times as large in a handle's first call).
 int pick_ksplit(int64_t tiles, int64_t d, int num_cu) {
     const int64_t ktiles = (d + kGramTE - 1) / kGramTE, slots = 2 * (int64_t)num_cu;
     const double tile_us = 2.0 * kTileEntries * (double)d / (45e6 / (double)slots);
     double least = 0.0;
     int best = 1;
-    for (int64_t ks = 1; ks <= std::max<int64_t>(1, std::min<int64_t>(ktiles, 64)); ++ks) {
+    for (int64_t ks = 1; ks <= std::max<int64_t>(1, std::min<int64_t>(ktiles / 4, 64)); ++ks) {
         const double rounds = (double)((tiles * ks + slots - 1) / slots) / (double)ks;
         const double us = rounds * tile_us + (ks > 1 ? 4.0 + (double)(tiles * (2 * ks + 1)) * kTileEntries * 8.0 / 4e6 : 0.0);
         if (ks == 1 || us < 0.98 * least) { least = us; best = (int)ks; }
