@@ -459,6 +459,21 @@ __device__ __forceinline__ double sign_of_bit(uint32_t word) {
     return __hiloint2double((int)hi, 0);
 }
 
+// A step of a walk whose lanes hold u = -t, never -0: u += c where lane LANE's u is not negative (its sign
+// is +1), else u -= c.  The whole decision is one sign bit: it reaches a scalar register by v_readlane (walk_sign),
+// flips the sign of c (sign_flipped_by), and c is added -- three dependent instructions, 22 cycles.  (Compare, vote,
+// scalar +-1 and FMA 37.8; sign bit by scalar AND and XOR 41; +-1 made first, read and multiplied 26.5; by DPP row
+// broadcast, which reaches sixteen lanes only, 25.3.)  Not for a u that is not a number.
+template <int LANE>
+__device__ __forceinline__ int walk_sign(double u) { return __builtin_amdgcn_readlane(__double2hiint(u), LANE); }
+
+// x, or -x if the sign bit of `decided` is set.
+__device__ __forceinline__ double sign_flipped_by(double x, uint32_t decided) {
+    // x ^ (decided & 0x80000000)
+    const int hi = (int)__builtin_amdgcn_bitop3_b32((uint32_t)__double2hiint(x), decided, 0x80000000u, 0x78);
+    return __hiloint2double(hi, __double2loint(x));
+}
+
 // f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
 template <int... I, typename F>
 __device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F &&f) {

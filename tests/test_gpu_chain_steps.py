@@ -154,6 +154,29 @@ def test_value_that_is_not_finite_stays_where_it_is(lib, value, m, n, d):
     assert np.array_equal(out["r32"].cpu().numpy(), want.astype(np.float32), equal_nan=True)
 
 
+@pytest.mark.parametrize("bits", [0x7fc00000, 0xffc00000])  # either sign of a value that is not a number
+@pytest.mark.parametrize("m,n,d", [
+    (3, 86, 5), (1, 700, 16), (5, 104, 30), (7, 74, 64),       # rows of at most 64 elements
+    (1, 130, 66), (3, 86, 129), (1, 600, 1001), (2, 130, 12_000),   # the chain of steps
+    (2, 20, 70_001),                                                # one launch per block of pairs
+])
+def test_dots_that_are_not_numbers(lib, bits, m, n, d):
+    """A value that is not a number in the middle of the epoch: pairs before it keep their signs; its own dot and all
+    later ones are not numbers, which the greedy rule answers with -1 and the randomized rule with +1."""
+    z = workloads.integer_rows(n + d, m, n, d, 3) * np.float32(2.0 ** -5)
+    pairs, at = m * n // 2, m * n // 4 + 1
+    clean = oracle.server_epoch(z, None)["eps"].T.ravel()  # in visiting order
+    z[at % m, 2 * (at // m) + 1, d // 2] = np.array(bits, np.uint32).view(np.float32)
+    zt = torch.from_numpy(z).cuda()
+    out = lib.cdgrab_balance_epoch(lib.Handle(), m, n, d, grads=zt, want_dots=True)
+    eps, dots = (out[key].cpu().numpy().T.ravel() for key in ("signs", "dots"))
+    assert np.array_equal(eps[:at], clean[:at]) and (eps[at:] == -1).all()
+    assert np.isfinite(dots[:at]).all() and np.isnan(dots[max(at, 1):]).all()
+    u = torch.rand((m, n // 2), device="cuda")
+    out = lib.cdgrab_balance_epoch_randomized(lib.Handle(), zt, u)
+    assert (out["signs"].cpu().numpy().T.ravel()[at:] == 1).all() and pairs > at
+
+
 @pytest.mark.parametrize("m,n,d", [(1, 2050, 70), (16, 300, 7850), (3, 500, 16), (2, 130, 40_000), (3, 20, 300)])
 def test_timing_counts_what_the_plan_says(lib, m, n, d):
     plan = lib.cdgrab_plan_epoch(m, n, d)
