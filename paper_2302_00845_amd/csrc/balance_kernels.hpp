@@ -19,6 +19,7 @@
 #include <stdint.h>
 
 #include <type_traits>
+#include <utility>
 
 namespace cdgrab {
 
@@ -436,11 +437,62 @@ __global__ __launch_bounds__(kThreads) void reduce_partials(const double *__rest
 }
 
 // ---------------------------------------------------------------------------
+// A step of a walk whose lanes hold u = -t, never -0: u loses c where lane LANE's u is not negative (its
+// sign is +1), else gains it.  The whole decision is one sign bit: it reaches a scalar register by v_readlane (walk_sign),
+// flips the sign of c (sign_flipped_by), and the sum is taken -- three dependent instructions, 22 cycles.  (Compare, vote,
+// scalar +-1 and FMA 37.8; sign bit by scalar AND and XOR 41; +-1 made first, read and multiplied 26.5; by DPP row
+// broadcast, which reaches sixteen lanes only, 25.3.)  Not for a u that is not a number.
+template <int LANE>
+__device__ __forceinline__ int walk_sign(double u) { return __builtin_amdgcn_readlane(__double2hiint(u), LANE); }
+
+// x, or -x if the sign bit of `decided` is set.
+__device__ __forceinline__ double sign_flipped_by(double x, uint32_t decided) {
+    // x ^ (decided & 0x80000000)
+    const int hi = (int)__builtin_amdgcn_bitop3_b32((uint32_t)__double2hiint(x), decided, 0x80000000u, 0x78);
+    return __hiloint2double(hi, __double2loint(x));
+}
+
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
+template <int... I, typename F>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F &&f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// One wavefront walks N pairs: lane k holds t of pair k before them and, in col, column k of their Gram matrix,
+// zero at and above the diagonal (so lane k changes at steps j < k only).  Returns the resolved dot; plus: the
+// pair's sign is +1.  Straight-line code, 22 cycles per pair by walk_sign; a vote per step instead of it (38) serves
+// where a dot is not a number, which has no sign to go by.
+// Randomized rule (PairBalance's RandomizedBalance subroutine, Sec. 3.2): with
+// c = z1 - z2 = -d, the first row gets +1 with probability p = (1 - <r,c>)/2 =
+// (1 + t)/2, so the exported sign (of the second row) is -1 when the draw is below p: the sign of their
+// difference (rounded once, so it is zero only where they are equal).
+template <int N, bool RANDOM>
+__device__ __forceinline__ double walk_pairs(const double (&col)[N], double t, float draw, bool &plus) {
+    auto rule = [&](double tv) { return RANDOM ? !((double)draw < 0.5 * (1.0 + tv)) : (tv <= 0.0); };
+    const double of = (double)draw;
+    double u = 0.0 - t;  // (a difference of equal numbers is +0)
+    static_for(std::make_integer_sequence<int, N>{}, [&](auto jj) {
+        constexpr int j = decltype(jj)::value;
+        u -= sign_flipped_by(col[j], (uint32_t)walk_sign<j>(RANDOM ? __builtin_fma(-0.5, 1.0 - u, of) : u));
+    });
+    if (__ballot(u != u)) {
+        u = 0.0 - t;
+        static_for(std::make_integer_sequence<int, N>{}, [&](auto jj) {
+            constexpr int j = decltype(jj)::value;
+            const bool vote = (__ballot(rule(0.0 - u)) >> j) & 1ull;
+            u -= vote ? col[j] : -col[j];
+        });
+    }
+    t = 0.0 - u;
+    plus = rule(t);
+    return t;
+}
+
+// ---------------------------------------------------------------------------
 // Sequential sign resolution.  All threads of the workgroup finish the reduction and unpack
 // the Gram tiles into LDS; then one wavefront walks the block: lane k carries
-// t_k = <r, d_k> + sum_{j<k, decided} eps_j G[j][k]; step j broadcasts t_j,
-// fixes eps_j = +1 if t_j <= 0 else -1 (or, given uniform draws, the randomized
-// rule) and updates the later lanes.
+// t_k = <r, d_k> + sum_{j<k, decided} eps_j G[j][k]; step j fixes eps_j = +1 if t_j <= 0
+// else -1 (or, given uniform draws, by the randomized rule) and updates the later lanes (walk_pairs).
 // Threads of the resolver's load phase: 1024, but 512 for 64-pair blocks, whose walk
 // keeps 64 doubles of the Gram matrix per lane in registers.
 template <int BB> constexpr int kResolveThreads = BB > 32 ? 512 : 1024;
@@ -518,7 +570,7 @@ __global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const doubl
         double col[BB];
 #pragma unroll
         for (int j = 0; j < BB; ++j) col[j] = (lane < BB && lane > j) ? G[lane][j] : 0.0;
-        double t = (lane < nb) ? P[lane] : 0.0;
+        const double t = (lane < nb) ? P[lane] : 0.0;
         // flattened pair of this lane -> (worker, pair) slot of the [m][n/2] arrays
         int64_t slot = 0;
         if (lane < nb) {
@@ -526,24 +578,12 @@ __global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const doubl
             uint32_t dq = q / (uint32_t)m;
             slot = (int64_t)(q - dq * (uint32_t)m) * half_n + (k0 + dq);
         }
-        // randomized rule (PairBalance's RandomizedBalance subroutine, Sec. 3.2): with
-        // c = z1 - z2 = -d, the first row gets +1 with probability p = (1 - <r,c>)/2 =
-        // (1 + t)/2, so the exported sign (of the second row) is -1 when u < p.
         const float my_u = (RANDOM && lane < nb) ? uniforms[slot] : 0.f;
-        auto rule = [&](double tv) { return RANDOM ? !((double)my_u < 0.5 * (1.0 + tv)) : (tv <= 0.0); };
-        // Every lane applies the rule to its own t at every step; a wave-wide vote turns
-        // lane j's answer into a scalar.  Lane k is updated at steps j < k only, so after
-        // the loop its t is the resolved dot of pair k and the rule on it is pair k's sign.
         // (Steps j >= nb of a short last block run too: they only touch lanes above j, which
-        // hold no pair.  Straight-line code, five instructions per step.)
-#pragma unroll
-        for (int j = 0; j < BB; ++j) {
-            // +col[j] or -col[j]: the vote's bit j picks the sign bit to flip (a scalar)
-            const uint32_t flip = ((__ballot(rule(t)) >> j) & 1ull) ? 0u : 0x80000000u;
-            t += __hiloint2double(__double2hiint(col[j]) ^ (int)flip, __double2loint(col[j]));
-        }
-        const double my_t = t;
-        const int my_eps = rule(t) ? 1 : -1;
+        // hold no pair.)
+        bool plus;
+        const double my_t = walk_pairs<BB, RANDOM>(col, t, my_u, plus);
+        const int my_eps = plus ? 1 : -1;
         if (lane < nb) {
             eps_blk[lane] = (int8_t)my_eps;
             signs_out[slot] = (int8_t)my_eps;

@@ -443,41 +443,16 @@ __global__ __launch_bounds__(kStepThreads, 2) void chain_apply_dots(StepRows cur
 // wavefront below TILES holds the columns of one Gram tile in registers: the wavefront of a
 // diagonal tile (s, s) walks the pairs 64 s .. 64 s + 63, then those of the tiles (s, w) add the
 // decided signs' contributions to the t of the pairs of w.
-// The walk: every lane applies the rule to its own t at every step and
-// a wave-wide vote turns lane j's answer into a scalar; lane k is updated at steps j < k only
-// (its column is stored as zero at and above the diagonal), so after the loop its t is the resolved dot
-// of pair k.  Straight-line code: 15 ns per pair, the latency of its four dependent instructions (64 pairs with
-// what is around them 1.05 us).
-// +1.0 if bit BIT of the (uniform) word is set, else -1.0, in a scalar register pair: a step of the
-// walk is then a compare, two scalar instructions and one FMA (exact: +-1 times the entry), and
-// no sign-flipped copy of an entry ever needs a vector register.
+// 64 pairs with what is around them take 0.7 us, 1.05 with a vote per step (walk_pairs).
+//
+// +1.0 if bit BIT of the (uniform) word is set, else -1.0, in a scalar register pair: a decided sign is then applied
+// in two scalar instructions and one FMA (exact: +-1 times the entry).
 template <int BIT>
 __device__ __forceinline__ double sign_of_bit(uint32_t word) {
     uint32_t hi;
     asm("s_bitcmp1_b32 %1, %2\n\ts_cselect_b32 %0, %3, %4"
         : "=s"(hi) : "s"(word), "n"(BIT), "s"(0x3ff00000u), "s"(0xbff00000u) : "scc");
     return __hiloint2double((int)hi, 0);
-}
-
-// A step of a walk whose lanes hold u = -t, never -0: u += c where lane LANE's u is not negative (its sign
-// is +1), else u -= c.  The whole decision is one sign bit: it reaches a scalar register by v_readlane (walk_sign),
-// flips the sign of c (sign_flipped_by), and c is added -- three dependent instructions, 22 cycles.  (Compare, vote,
-// scalar +-1 and FMA 37.8; sign bit by scalar AND and XOR 41; +-1 made first, read and multiplied 26.5; by DPP row
-// broadcast, which reaches sixteen lanes only, 25.3.)  Not for a u that is not a number.
-template <int LANE>
-__device__ __forceinline__ int walk_sign(double u) { return __builtin_amdgcn_readlane(__double2hiint(u), LANE); }
-
-// x, or -x if the sign bit of `decided` is set.
-__device__ __forceinline__ double sign_flipped_by(double x, uint32_t decided) {
-    // x ^ (decided & 0x80000000)
-    const int hi = (int)__builtin_amdgcn_bitop3_b32((uint32_t)__double2hiint(x), decided, 0x80000000u, 0x78);
-    return __hiloint2double(hi, __double2loint(x));
-}
-
-// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
-template <int... I, typename F>
-__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F &&f) {
-    (f(std::integral_constant<int, I>{}), ...);
 }
 
 template <int SB> constexpr int kWalkTiles = (SB / 64) * (SB / 64 + 1) / 2;
@@ -562,19 +537,10 @@ __global__ __launch_bounds__(kWalkThreads) void chain_walk(const double *__restr
             const uint32_t dq = q / (uint32_t)cur.m;
             slot = (int64_t)(q - dq * (uint32_t)cur.m) * half_n + (cur.k0 + dq);
         }
-        // randomized rule (PairBalance's RandomizedBalance subroutine, Sec. 3.2): with
-        // c = z1 - z2 = -d, the first row gets +1 with probability p = (1 - <r,c>)/2 =
-        // (1 + t)/2, so the exported sign (of the second row) is -1 when u < p.
         const float my_u = (RANDOM && kk < nb) ? uniforms[slot] : 0.f;
-        auto rule = [&](double tv) { return RANDOM ? !((double)my_u < 0.5 * (1.0 + tv)) : (tv <= 0.0); };
         pass_to(2 + 2 * tj);
-        double t = tnow[kk];
-        static_for(std::make_integer_sequence<int, 64>{}, [&](auto jj) {
-            constexpr int j = decltype(jj)::value;
-            const unsigned long long vote = __ballot(rule(t));
-            t = __builtin_fma(sign_of_bit<j & 31>(j < 32 ? (uint32_t)vote : (uint32_t)(vote >> 32)), col[j], t);
-        });
-        const bool plus = rule(t);
+        bool plus;
+        const double t = walk_pairs<64, RANDOM>(col, tnow[kk], my_u, plus);
         const unsigned long long all = __ballot(plus);
         if (lane == 0) votes = all;
         pass_to(2 + 2 * tj + 1);
