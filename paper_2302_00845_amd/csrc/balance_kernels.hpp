@@ -198,8 +198,9 @@ struct WalkStrides {
 };
 
 // `group` of `ngroups` workgroups share the tiles; the workgroup's result goes to `out`.
+// `fresh`: the running sum is zero and r_sum holds nothing yet.
 template <int BB, int VW, int TE, bool APPLY, bool NB>
-__device__ __forceinline__ void pass1_body(const RowMap &rm, const PrevBlock &prev, double *__restrict__ r_sum,
+__device__ __forceinline__ void pass1_body(const RowMap &rm, const PrevBlock &prev, int fresh, double *__restrict__ r_sum,
                                            double *__restrict__ out, int64_t ntiles, int group, int ngroups)
 {
     using L = PartLayout<BB>;
@@ -279,7 +280,8 @@ __device__ __forceinline__ void pass1_body(const RowMap &rm, const PrevBlock &pr
 #pragma unroll
             for (int u = 0; u < LOADS; ++u) prev_regs[u] = tile_load(psrc[u], true, t * TE + chunk * 4);
         }
-        if (tid < TE / 2) stage_s = *reinterpret_cast<const double2 *>(r_sum + t * TE + tid * 2);
+        // (with APPLY the load stays unconditional and its result is dropped: a branch here cost 2 % at 1M elements)
+        if (tid < TE / 2 && (APPLY || !fresh)) stage_s = *reinterpret_cast<const double2 *>(r_sum + t * TE + tid * 2);
     };
     int64_t tile = group;
     if (tile < ntiles) load_tile(tile);
@@ -309,10 +311,14 @@ __device__ __forceinline__ void pass1_body(const RowMap &rm, const PrevBlock &pr
                 double s0 = 0.0, s1 = 0.0;
 #pragma unroll
                 for (int q = 0; q < RPI; ++q) { s0 += col[q * TE]; s1 += col[q * TE + 1]; }
-                stage_s.x += s0;
-                stage_s.y += s1;
+                stage_s.x = (fresh ? 0.0 : stage_s.x) + s0;
+                stage_s.y = (fresh ? 0.0 : stage_s.y) + s1;
                 *reinterpret_cast<double2 *>(r_sum + tile * TE + tid * 2) = stage_s;
             }
+        }
+        if (!APPLY && tile == ntiles - 1) {  // (the apply launches write no padding)
+            if (tile * TE + tid * 2 >= d) stage_s.x = 0.0;
+            if (tile * TE + tid * 2 + 1 >= d) stage_s.y = 0.0;
         }
         if (tid < TE / 2)
             *reinterpret_cast<double2 *>(stage + 2 * TILE_FLOATS * 4 + tid * 16) = stage_s;
@@ -390,11 +396,12 @@ __device__ __forceinline__ void pass1_body(const RowMap &rm, const PrevBlock &pr
 }
 
 template <int BB, int VW, int TE, bool APPLY>
-__global__ __launch_bounds__(kThreads) void pass1_dots_gram(RowMap rm, PrevBlock prev, double *__restrict__ r_sum,
+__global__ __launch_bounds__(kThreads) void pass1_dots_gram(RowMap rm, PrevBlock prev, int fresh,
+                                                            double *__restrict__ r_sum,
                                                             double *__restrict__ partials,
                                                             int64_t ntiles)
 {
-    pass1_body<BB, VW, TE, APPLY, TE == 64>(rm, prev, r_sum, partials + (int64_t)blockIdx.x * PartLayout<BB>::PART,
+    pass1_body<BB, VW, TE, APPLY, TE == 64>(rm, prev, fresh, r_sum, partials + (int64_t)blockIdx.x * PartLayout<BB>::PART,
                                             ntiles, (int)blockIdx.x, (int)gridDim.x);
 }
 
@@ -593,11 +600,56 @@ __global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const doubl
 }
 
 // ---------------------------------------------------------------------------
+// What an apply launch does besides, so that no launch of its own clears or exports the running sum: the epoch's first
+// block starts it (fresh: r_sum holds nothing and is not read), the last one's result leaves as fp32 and / or
+// double (r32, r64; last: it goes nowhere else).  Five passes over the running sum less per epoch: 40 pairs of
+// 124M elements 15.06 -> @@GPT@@ ms, 128 pairs of 11.2M 3918 -> @@RES@@ us.
+struct SumEnds {
+    int fresh, last;
+    float *r32;
+    double *r64;
+};
+
+typedef double double2_any __attribute__((ext_vector_type(2), aligned(8)));
+
+// r[e .. e + 3] += acc.  The running sum is padded to the tile, and the padding of these four stays zero because
+// elements beyond d load as zero.
+__device__ __forceinline__ void update_four(const SumEnds &ends, double *__restrict__ r_sum, int64_t e, int64_t d,
+                                            const double (&acc)[4]) {
+    double2 lo = make_double2(0.0, 0.0), hi = lo;
+    if (!ends.fresh) {
+        lo = *reinterpret_cast<double2 *>(r_sum + e);
+        hi = *reinterpret_cast<double2 *>(r_sum + e + 2);
+    }
+    lo.x += acc[0]; lo.y += acc[1]; hi.x += acc[2]; hi.y += acc[3];
+    if (!ends.last) {
+        *reinterpret_cast<double2 *>(r_sum + e) = lo;
+        *reinterpret_cast<double2 *>(r_sum + e + 2) = hi;
+        return;
+    }
+    const double v[4] = {lo.x, lo.y, hi.x, hi.y};
+    if (e + 4 <= d) {
+        if (ends.r32) *reinterpret_cast<float4_any *>(ends.r32 + e) = (float4_any){(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+        if (ends.r64) {
+            *reinterpret_cast<double2_any *>(ends.r64 + e) = (double2_any){v[0], v[1]};
+            *reinterpret_cast<double2_any *>(ends.r64 + e + 2) = (double2_any){v[2], v[3]};
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (e + q < d) {
+                if (ends.r32) ends.r32[e + q] = (float)v[q];
+                if (ends.r64) ends.r64[e + q] = v[q];
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Pass 2: r += sum_k eps_k d_k.  Each thread owns four consecutive elements and
 // streams the block's rows through registers.  FULL = the block holds all BB
 // pairs (no per-pair test inside the unrolled loop).
 template <int BB, int VW, bool FULL>
-__global__ __launch_bounds__(kThreads) void pass2_apply(RowMap rm, const int8_t *__restrict__ eps_blk,
+__global__ __launch_bounds__(kThreads) void pass2_apply(RowMap rm, const int8_t *__restrict__ eps_blk, SumEnds ends,
                                                         double *__restrict__ r_sum)
 {
     const int64_t d = rm.d;
@@ -620,13 +672,7 @@ __global__ __launch_bounds__(kThreads) void pass2_apply(RowMap rm, const int8_t 
     };
     if (VW == kAnyRow && e + 4 <= d) add_rows(std::true_type{});
     else add_rows(std::false_type{});
-    // the running sum is padded to a multiple of the tile; the padding stays zero
-    // because elements beyond d load as zero
-    double2 lo = *reinterpret_cast<double2 *>(r_sum + e);
-    double2 hi = *reinterpret_cast<double2 *>(r_sum + e + 2);
-    lo.x += acc[0]; lo.y += acc[1]; hi.x += acc[2]; hi.y += acc[3];
-    *reinterpret_cast<double2 *>(r_sum + e) = lo;
-    *reinterpret_cast<double2 *>(r_sum + e + 2) = hi;
+    update_four(ends, r_sum, e, d, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -649,8 +695,8 @@ constexpr int kResidentGroups = 22;
 
 template <int BB, int VW, bool FULL>
 __global__ __launch_bounds__(kThreads, 2) void pass2_apply_resident(RowMap rm, const int8_t *__restrict__ eps_blk,
-                                                                    double *__restrict__ r_sum, int kuse,
-                                                                    int64_t g0)
+                                                                    SumEnds ends, double *__restrict__ r_sum,
+                                                                    int kuse, int64_t g0)
 {
     // this launch: groups g0 .. g0 + kuse - 1 of every thread (one slab)
     constexpr int K = kResidentGroups;
@@ -681,18 +727,10 @@ __global__ __launch_bounds__(kThreads, 2) void pass2_apply_resident(RowMap rm, c
             else add_rows(std::false_type{});
         }
     }
-    // the running sum is padded to a multiple of the tile; the padding stays zero
-    // because elements beyond d load as zero
 #pragma unroll
     for (int g = 0; g < K; ++g) {
         const int64_t e = ((g0 + g) * T + t) * 4;
-        if (g < kuse && e < d) {
-            double2 lo = *reinterpret_cast<double2 *>(r_sum + e);
-            double2 hi = *reinterpret_cast<double2 *>(r_sum + e + 2);
-            lo.x += acc[g][0]; lo.y += acc[g][1]; hi.x += acc[g][2]; hi.y += acc[g][3];
-            *reinterpret_cast<double2 *>(r_sum + e) = lo;
-            *reinterpret_cast<double2 *>(r_sum + e + 2) = hi;
-        }
+        if (g < kuse && e < d) update_four(ends, r_sum, e, d, acc[g]);
     }
 }
 
@@ -707,7 +745,7 @@ constexpr int kSplitElems = (kThreads / kSplitGroups) * 4;  // 64 elements per w
 
 template <int BB, int VW, bool FULL>
 __global__ __launch_bounds__(kThreads) void pass2_apply_split(RowMap rm, const int8_t *__restrict__ eps_blk,
-                                                              double *__restrict__ r_sum)
+                                                              SumEnds ends, double *__restrict__ r_sum)
 {
     __shared__ double part[kSplitGroups][kSplitElems];
     const int64_t d = rm.d;
@@ -715,7 +753,7 @@ __global__ __launch_bounds__(kThreads) void pass2_apply_split(RowMap rm, const i
     const int64_t e = (int64_t)blockIdx.x * kSplitElems + quad * 4;
     const int64_t mine = (int64_t)blockIdx.x * kSplitElems + threadIdx.x;
     // the running-sum element is requested first so that its latency overlaps the row loads
-    const double r_old = (threadIdx.x < kSplitElems && mine < d) ? r_sum[mine] : 0.0;
+    const double r_old = (threadIdx.x < kSplitElems && mine < d && !ends.fresh) ? r_sum[mine] : 0.0;
     constexpr int PER = BB / kSplitGroups;
     float4 a[PER], b[PER];
 #pragma unroll
@@ -743,7 +781,12 @@ __global__ __launch_bounds__(kThreads) void pass2_apply_split(RowMap rm, const i
         double sum = 0.0;
 #pragma unroll
         for (int g = 0; g < kSplitGroups; ++g) sum += part[g][threadIdx.x];
-        r_sum[mine] = r_old + sum;
+        const double r = r_old + sum;
+        if (!ends.last) r_sum[mine] = r;
+        else {
+            if (ends.r32) ends.r32[mine] = (float)r;
+            if (ends.r64) ends.r64[mine] = r;
+        }
     }
 }
 
@@ -754,24 +797,6 @@ __global__ void fill_zero_b32(uint32_t *p, int64_t count) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (; i < count; i += stride) p[i] = 0u;
-}
-
-__global__ void fill_zero_f64(double *p, int64_t count) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < count; i += stride) p[i] = 0.0;
-}
-
-__global__ void export_running_sum(const double *__restrict__ r_sum, int64_t d, float *__restrict__ r32,
-                                   double *__restrict__ r64)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < d; i += stride) {
-        double v = r_sum[i];
-        if (r32) r32[i] = (float)v;
-        if (r64) r64[i] = v;
-    }
 }
 
 }  // namespace cdgrab

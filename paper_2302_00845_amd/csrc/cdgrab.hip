@@ -330,7 +330,7 @@ int ensure(cdgrab_handle *h, T *&ptr, int64_t &cap, int64_t want) {
 }
 
 template <int BB, int VW>
-void launch_pass1(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, const cdgrab_plan &plan) {
+void launch_pass1(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, bool fresh, const cdgrab_plan &plan) {
     PrevBlock none;
     none.rm = rm;
     none.rm.nb = 0;
@@ -338,7 +338,8 @@ void launch_pass1(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, con
     const dim3 grid(plan.pass1_groups), block(kThreads);
     const int64_t ntiles = (rm.d + plan.tile_elems - 1) / plan.tile_elems;
     auto launch = [&](auto kernel, const PrevBlock &pb) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, rm, pb, h->r_sum, h->partials, ntiles);
+        hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, rm, pb, fresh ? 1 : 0, h->r_sum, h->partials,
+                           ntiles);
     };
     if (plan.tile_elems == 128) {
         if (prev) launch(pass1_dots_gram<BB, VW, 128, true>, *prev);
@@ -355,16 +356,16 @@ void launch_pass1(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, con
 constexpr int64_t kResidentMinD = (int64_t)1 << 20;
 
 template <int BB, int VW>
-void launch_pass2(cdgrab_handle *h, const RowMap &rm, int groups) {
+void launch_pass2(cdgrab_handle *h, const RowMap &rm, const SumEnds &ends, int groups) {
     // short rows: too few flat workgroups to hide latency -> split the pairs over thread groups
     if (groups < 2 * h->num_cu && h->apply_mode < 3) {
         const dim3 grid((unsigned)((rm.d + kSplitElems - 1) / kSplitElems));
         if (rm.nb == BB)
             hipLaunchKernelGGL((pass2_apply_split<BB, VW, true>), grid, dim3(kThreads), 0, h->stream, rm,
-                               h->eps_blk, h->r_sum);
+                               h->eps_blk, ends, h->r_sum);
         else
             hipLaunchKernelGGL((pass2_apply_split<BB, VW, false>), grid, dim3(kThreads), 0, h->stream, rm,
-                               h->eps_blk, h->r_sum);
+                               h->eps_blk, ends, h->r_sum);
         return;
     }
     if (h->apply_mode == 3 || (h->apply_mode != 4 && rm.d >= kResidentMinD)) {
@@ -381,19 +382,19 @@ void launch_pass2(cdgrab_handle *h, const RowMap &rm, int groups) {
         for (int64_t sl = 0; sl < slabs; ++sl) {
             if (rm.nb == BB)
                 hipLaunchKernelGGL((pass2_apply_resident<BB, VW, true>), dim3((unsigned)grid), dim3(kThreads), 0,
-                                   h->stream, rm, h->eps_blk, h->r_sum, kuse, sl * kuse);
+                                   h->stream, rm, h->eps_blk, ends, h->r_sum, kuse, sl * kuse);
             else
                 hipLaunchKernelGGL((pass2_apply_resident<BB, VW, false>), dim3((unsigned)grid), dim3(kThreads), 0,
-                                   h->stream, rm, h->eps_blk, h->r_sum, kuse, sl * kuse);
+                                   h->stream, rm, h->eps_blk, ends, h->r_sum, kuse, sl * kuse);
         }
         return;
     }
     if (rm.nb == BB)
         hipLaunchKernelGGL((pass2_apply<BB, VW, true>), dim3(groups), dim3(kThreads), 0, h->stream, rm,
-                           h->eps_blk, h->r_sum);
+                           h->eps_blk, ends, h->r_sum);
     else
         hipLaunchKernelGGL((pass2_apply<BB, VW, false>), dim3(groups), dim3(kThreads), 0, h->stream, rm,
-                           h->eps_blk, h->r_sum);
+                           h->eps_blk, ends, h->r_sum);
 }
 template <int BB>
 void launch_resolve(cdgrab_handle *h, const RowMap &rm, int8_t *signs_out, double *dots_out) {
@@ -516,18 +517,31 @@ int run_step_walk(cdgrab_handle *h, const StepRows &cur, const ChainPlan &c, con
     return CDGRAB_OK;
 }
 
+template <int BB>
+int apply_block_vw(cdgrab_handle *h, const RowMap &rm, const SumEnds &ends, const cdgrab_plan &plan) {
+    if (ends.last && !ends.r32 && !ends.r64) return CDGRAB_OK;  // nobody asked for the epoch's running sum
+    MARK(h, 2, kPass2);
+    switch (row_form(plan.vector_width, rm.d)) {
+        case kAligned: launch_pass2<BB, 4>(h, rm, ends, plan.pass2_groups); break;
+        case kAnyRow: launch_pass2<BB, 2>(h, rm, ends, plan.pass2_groups); break;
+        default: launch_pass2<BB, 1>(h, rm, ends, plan.pass2_groups); break;
+    }
+    HIP_TRY(h, hipGetLastError());
+    return CDGRAB_OK;
+}
+
 // One block: dots + Gram (with the previous block applied in the same launch when
 // `prev` is given), reduction, sign resolution, and -- unless the apply is left to the
-// next block's launch -- the apply pass.
+// next block's launch -- the apply pass.  fresh: nothing has been applied before this launch.
 template <int BB>
-int run_block_vw(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, bool apply_now,
+int run_block_vw(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, bool fresh, const SumEnds *apply_now,
                  const cdgrab_plan &plan, int8_t *signs_out, double *dots_out) {
     const int part = PartLayout<BB>::PART;
     MARK(h, 2, kPass1);
     switch (row_form(plan.vector_width, rm.d)) {
-        case kAligned: launch_pass1<BB, 4>(h, rm, prev, plan); break;
-        case kAnyRow: launch_pass1<BB, 2>(h, rm, prev, plan); break;
-        default: launch_pass1<BB, 1>(h, rm, prev, plan); break;
+        case kAligned: launch_pass1<BB, 4>(h, rm, prev, fresh, plan); break;
+        case kAnyRow: launch_pass1<BB, 2>(h, rm, prev, fresh, plan); break;
+        default: launch_pass1<BB, 1>(h, rm, prev, fresh, plan); break;
     }
     MARK(h, 2, kReduce);
     hipLaunchKernelGGL(reduce_partials,
@@ -535,28 +549,8 @@ int run_block_vw(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, bool
                        dim3(kThreads), 0, h->stream, h->partials, h->reduced, part, plan.pass1_groups);
     MARK(h, 2, kResolve);
     launch_resolve<BB>(h, rm, signs_out, dots_out);
-    if (apply_now) {
-        MARK(h, 2, kPass2);
-        switch (row_form(plan.vector_width, rm.d)) {
-            case kAligned: launch_pass2<BB, 4>(h, rm, plan.pass2_groups); break;
-            case kAnyRow: launch_pass2<BB, 2>(h, rm, plan.pass2_groups); break;
-            default: launch_pass2<BB, 1>(h, rm, plan.pass2_groups); break;
-        }
-    }
     HIP_TRY(h, hipGetLastError());
-    return CDGRAB_OK;
-}
-
-template <int BB>
-int apply_block_vw(cdgrab_handle *h, const RowMap &rm, const cdgrab_plan &plan) {
-    MARK(h, 2, kPass2);
-    switch (row_form(plan.vector_width, rm.d)) {
-        case kAligned: launch_pass2<BB, 4>(h, rm, plan.pass2_groups); break;
-        case kAnyRow: launch_pass2<BB, 2>(h, rm, plan.pass2_groups); break;
-        default: launch_pass2<BB, 1>(h, rm, plan.pass2_groups); break;
-    }
-    HIP_TRY(h, hipGetLastError());
-    return CDGRAB_OK;
+    return apply_now ? apply_block_vw<BB>(h, rm, *apply_now, plan) : CDGRAB_OK;
 }
 
 // Orders of m workers from their signs (flag already cleared).  A grid holds at most 2^23 chunks.
@@ -773,6 +767,7 @@ struct Epoch {
     PrevBlock prev;
     bool have_prev = false;
     int64_t steps_run = 0;     // of the Grams-ahead form
+    int64_t blocks_run = 0;    // of the other one
 
     int prepare();
     void set_block(int64_t p0, int64_t nb, const float *stage_base);
@@ -951,6 +946,7 @@ int Epoch::chain_ahead() {
         }
     }
     if (narrow) return CDGRAB_OK;
+    if (!r_out && !r64_out) return CDGRAB_OK;  // the last step would be applied for nobody
     MARK(h, 1, kBalance);
     return run_step_wide(h, none, prev_step, chain, form, fresh, r_out, r64_out);
 }
@@ -975,10 +971,15 @@ int Epoch::chain_blocks() {
             // read (40 pairs at d = 124M, 8 of them in the last block: 17.8 against 15.1 ms per epoch).
             // Same sums in the same order.
             const int kb = (!fused && bb == 32 && rm.nb <= 16) ? 16 : bb;
-            rc = BY_BLOCK_PAIRS(kb, run_block_vw<64>(h, rm, pp, !fused, plan, signs_out, dots_out),
-                                run_block_vw<32>(h, rm, pp, !fused, plan, signs_out, dots_out),
-                                run_block_vw<16>(h, rm, pp, !fused, plan, signs_out, dots_out));
+            // (fused: the launch of the epoch's second block is the first to write the running sum)
+            const bool fresh = blocks_run < (fused ? 2 : 1);
+            const SumEnds ends{fresh ? 1 : 0, p0 + rm.nb == plan.pairs ? 1 : 0, r_out, r64_out};
+            const SumEnds *now = fused ? nullptr : &ends;
+            rc = BY_BLOCK_PAIRS(kb, run_block_vw<64>(h, rm, pp, fresh, now, plan, signs_out, dots_out),
+                                run_block_vw<32>(h, rm, pp, fresh, now, plan, signs_out, dots_out),
+                                run_block_vw<16>(h, rm, pp, fresh, now, plan, signs_out, dots_out));
             if (rc) return rc;
+            ++blocks_run;
             prev.rm = rm;
             have_prev = true;
         }
@@ -990,8 +991,9 @@ int Epoch::chain_blocks() {
 int Epoch::apply_last() {
     if (!fused || !have_prev) return CDGRAB_OK;
     MARK(h, 1, kBalance);
-    return BY_BLOCK_PAIRS(bb, apply_block_vw<64>(h, prev.rm, plan), apply_block_vw<32>(h, prev.rm, plan),
-                          apply_block_vw<16>(h, prev.rm, plan));
+    const SumEnds ends{blocks_run < 2 ? 1 : 0, 1, r_out, r64_out};
+    return BY_BLOCK_PAIRS(bb, apply_block_vw<64>(h, prev.rm, ends, plan), apply_block_vw<32>(h, prev.rm, ends, plan),
+                          apply_block_vw<16>(h, prev.rm, ends, plan));
 }
 
 }  // namespace
@@ -1020,9 +1022,6 @@ static int balance_epoch_impl(cdgrab_handle *h, int64_t m, int64_t n, int64_t d,
     h->marks.clear();
     h->events_used = 0;
     h->have_timing = false;
-    if (!ep.ahead)  // (the Grams-ahead form starts and exports the running sum in its own launches)
-        hipLaunchKernelGGL(fill_zero_f64, dim3(std::min<int64_t>(4096, (h->r_cap + 255) / 256)), dim3(256), 0,
-                           h->stream, h->r_sum, h->r_cap);
     rc = ep.ahead ? ep.chain_ahead() : ep.chain_blocks();
     if (rc) return rc;
     rc = ep.apply_last();
@@ -1032,9 +1031,6 @@ static int balance_epoch_impl(cdgrab_handle *h, int64_t m, int64_t n, int64_t d,
     if (!center_row)  // (side-by-side walks are one-worker walks: `walks` rows of signs and orders)
         hipLaunchKernelGGL(build_pair_permutations, dim3((unsigned)((walks * m * (n / 2) + 255) / 256)), dim3(256),
                            0, h->stream, signs_out, perm_in, perm_out, walks * m, n);
-    if ((r_out || r64_out) && !ep.ahead)
-        hipLaunchKernelGGL(export_running_sum, dim3((unsigned)std::min<int64_t>(8192, (d + 255) / 256)), dim3(256),
-                           0, h->stream, h->r_sum, d, r_out, r64_out);
     MARK(h, 1, -1);
     HIP_TRY(h, hipGetLastError());
     const int64_t cp = ep.chunk_pairs, bb = ep.bb;
