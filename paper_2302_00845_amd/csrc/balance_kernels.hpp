@@ -472,17 +472,18 @@ __device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F &
 // Randomized rule (PairBalance's RandomizedBalance subroutine, Sec. 3.2): with
 // c = z1 - z2 = -d, the first row gets +1 with probability p = (1 - <r,c>)/2 =
 // (1 + t)/2, so the exported sign (of the second row) is -1 when the draw is below p: the sign of their
-// difference (rounded once, so it is zero only where they are equal).
+// difference (rounded once, so it is zero only where they are equal, and then +0: a draw of -0 is taken as 0).
+// A draw that is not a finite number goes by comparison, as a dot that is not a number does.
 template <int N, bool RANDOM>
 __device__ __forceinline__ double walk_pairs(const double (&col)[N], double t, float draw, bool &plus) {
     auto rule = [&](double tv) { return RANDOM ? !((double)draw < 0.5 * (1.0 + tv)) : (tv <= 0.0); };
-    const double of = (double)draw;
+    const double of = (double)draw + 0.0;
     double u = 0.0 - t;  // (a difference of equal numbers is +0)
     static_for(std::make_integer_sequence<int, N>{}, [&](auto jj) {
         constexpr int j = decltype(jj)::value;
         u -= sign_flipped_by(col[j], (uint32_t)walk_sign<j>(RANDOM ? __builtin_fma(-0.5, 1.0 - u, of) : u));
     });
-    if (__ballot(u != u)) {
+    if (__ballot(u != u || (RANDOM && !isfinite(draw)))) {
         u = 0.0 - t;
         static_for(std::make_integer_sequence<int, N>{}, [&](auto jj) {
             constexpr int j = decltype(jj)::value;
@@ -603,7 +604,7 @@ __global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const doubl
 // What an apply launch does besides, so that no launch of its own clears or exports the running sum: the epoch's first
 // block starts it (fresh: r_sum holds nothing and is not read), the last one's result leaves as fp32 and / or
 // double (r32, r64; last: it goes nowhere else).  Five passes over the running sum less per epoch: 40 pairs of
-// 124M elements 15.06 -> @@GPT@@ ms, 128 pairs of 11.2M 3918 -> @@RES@@ us.
+// 124M elements 15.00 -> 14.19 ms, 128 pairs of 11.2M 3919 -> 3813 us.
 struct SumEnds {
     int fresh, last;
     float *r32;

@@ -152,11 +152,11 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_walk(StepRows rows, int
             // randomized rule (PairBalance's RandomizedBalance subroutine, Sec. 3.2): with
             // c = z1 - z2 = -d, the first row gets +1 with probability p = (1 - <r,c>)/2 =
             // (1 + t)/2, so the exported sign (of the second row) is -1 when the draw is below p:
-            // the sign of their difference (rounded once, so it is zero only where they are equal).
+            // the sign of their difference (as in walk_pairs, which says which draws have one).
             const float dr = RANDOM ? draw[b % RING][k] : 0.f;
             auto rule = [&](double tv) { return RANDOM ? !((double)dr < 0.5 * (1.0 + tv)) : (tv <= 0.0); };
             auto vote = [&](int j) { return ((__ballot(rule(0.0 - u)) >> j) & 1ull) ? 0u : 0x80000000u; };
-            const double u0 = u, r0 = r, draw_of = (double)dr;
+            const double u0 = u, r0 = r, draw_of = (double)dr + 0.0;
             const double *col = &G[(b + 1) % 3][k];  // (of a block that does not exist: slots of the rings, not used)
             const double *here = &diff[b % RING][e], *next = &diff[(b + 1) % RING][e];
             uint32_t before = 0;
@@ -193,8 +193,8 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_walk(StepRows rows, int
             });
             follow(std::integral_constant<int, NB - 1>{});
             replace(std::integral_constant<int, NB - 1>{});
-            // a t that is not a number has no sign to go by: walk again by comparison
-            if (__ballot(u != u)) {
+            // a t that is not a number, or such a draw, has no sign to go by: walk again by comparison
+            if (__ballot(u != u || (RANDOM && !isfinite(dr)))) {
                 u = u0;
                 r = r0;
                 for (int j = 0; j < NB; ++j) {

@@ -134,6 +134,32 @@ def test_randomized_rule_over_steps(lib, m, n, d):
     assert np.array_equal(out["r64"].cpu().numpy(), r)
 
 
+@pytest.mark.parametrize("odd_draw", [-0.0, np.inf, np.nan])
+@pytest.mark.parametrize("m,n,d", [(3, 86, 16), (3, 86, 30), (1, 300, 64), (2, 300, 12_000), (3, 86, 129), (2, 20, 70_001)])
+def test_randomized_rule_at_its_threshold(lib, m, n, d, odd_draw):
+    """Draws equal to their probability (such a pair gets +1), at probability zero too, and draws that are no
+    ordinary numbers among them; the sums are exact, so every sign is determined."""
+    z = workloads.integer_rows(n + 1, m, n, d, 2) * np.float32(2.0 ** -5)
+    u, want = np.zeros((m, n // 2), np.float32), np.zeros((m, n // 2), np.int8)
+    r, at_zero = np.zeros(d), 0
+    for k in range(n // 2):
+        for i in range(m):
+            power = np.flatnonzero((r != 0) & (np.abs(np.frexp(r)[0]) == 0.5))
+            if (k * m + i) % 7 == 3 and power.size:  # a pair whose dot is -1
+                z[i, 2 * k:2 * k + 2] = 0
+                z[i, 2 * k + 1, power[0]] = -1.0 / r[power[0]]
+            dv = z[i, 2 * k + 1].astype(np.float64) - z[i, 2 * k]
+            p = 0.5 * (1.0 + float(r @ dv))
+            at_zero += p == 0.0
+            u[i, k] = p if 0.0 < p < 1.0 else odd_draw
+            want[i, k] = -1 if float(u[i, k]) < p else 1
+            r += want[i, k] * dv
+    assert at_zero > 2
+    out = lib.cdgrab_balance_epoch_randomized(lib.Handle(), torch.from_numpy(z).cuda(), torch.from_numpy(u).cuda())
+    assert np.array_equal(out["signs"].cpu().numpy(), want)
+    assert np.array_equal(out["r64"].cpu().numpy(), r)
+
+
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
 @pytest.mark.parametrize("m,n,d", [
     (3, 24, 20), (1, 130, 50),                    # rows of at most 64 elements
