@@ -60,6 +60,31 @@ def test_steps_kept_or_read_again(lib, m, n, d):
         assert abs(gpu_bound(lib, h, z, perm) - want) <= 1e-12 * max(float(np.abs(z).sum((0, 1)).max()), 1e-30)
 
 
+def test_capture_without_room_for_the_steps(lib):
+    """A handle that has no workspace for the steps' sums yet allocates none under capture: the rows are read again."""
+    big, z = (workloads.heavy_rows(m, m, n, d) for m, n, d in ((5, 600, 700), (6, 300, 600)))
+    zt, bt, s = torch.from_numpy(z).cuda(), torch.from_numpy(big).cuda(), torch.cuda.Stream()
+    h = lib.Handle(stream=s)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        first = lib.cdgrab_herding_bound(h, bt)
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        out = lib.cdgrab_herding_bound(h, zt)
+    want = oracle.parallel_herding(z)
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        # m * n double sums of rounding 1.1e-16 each, taken relative to the largest prefix
+        assert abs(float(out.cpu()[0]) - want) <= 1e-12 * float(np.abs(z).sum((0, 1)).max())
+        with torch.cuda.stream(s):
+            assert torch.equal(lib.cdgrab_herding_bound(h, bt), first)
+        s.synchronize()
+
+
 @pytest.mark.parametrize("m,n,d,exact", [
     (5, 24, 300, False),        # one block per worker: m one-worker epochs back to back
     (7, 200, 300, False),       # 100 pairs: the walks run side by side, the worker as a grid coordinate
