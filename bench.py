@@ -358,13 +358,14 @@ def measure_synthetic_herding(args, steps, warmup):
         if it >= warmup:
             times.append(e0.elapsed_time(e1))
     ms = float(np.mean(times))
-    gbs = 2.0 * N * d * 4 / (ms * 1e-3) / 1e9          # every row is read twice
+    # every row is read once, every step's sum over the workers written and read (8 bytes)
+    gbs = (4.0 * N + 16.0 * n) * d / (ms * 1e-3) / 1e9
     res = {"workload": "syn_herding", "metric": "examples/sec through the parallel herding objective",
            "m": m, "n": n, "d": d, "examples": N, "steps": steps, "warmup": warmup, "value": N / (ms * 1e-3),
            "unit": "examples/s", "ms_per_step": ms, "dtype": "f64", "herding_bound": float(b.cpu()[0]),
            "roofline": {"kernel": "herding_segment_sums + herding_prefix_max", "bound": "hbm", "achieved": gbs,
                         "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "traffic": None},
-           "note": "128 MB of traffic in all: bound by the three dependent launches, not by bytes"}
+           "note": "67 MB of traffic in all: bound by the three dependent launches, not by bytes"}
     h.close()
     return res
 
@@ -424,7 +425,8 @@ def measure_next_row(name, args, steps, warmup):
                 torch.cuda.synchronize()
                 return e0.elapsed_time(e1), float(b.cpu()[0])
             metric = "examples/sec through the parallel herding objective"
-            nbytes = 2.0 * N * d * 4                  # every row is read in pass A and again in pass C
+            # every row is read once, every step's sum over the workers written and read (8 bytes)
+            nbytes = (4.0 * N + 16.0 * n) * d
             kname = "herding_segment_sums + herding_prefix_max"
         else:
             def step():
