@@ -198,9 +198,11 @@ struct WalkStrides {
 };
 
 // `group` of `ngroups` workgroups share the tiles; the workgroup's result goes to `out`.
-// `fresh`: the running sum is zero and r_sum holds nothing yet.
-template <int BB, int VW, int TE, bool APPLY, bool NB>
-__device__ __forceinline__ void pass1_body(const RowMap &rm, const PrevBlock &prev, int fresh, double *__restrict__ r_sum,
+// FRESH: the running sum is zero and r_sum holds nothing yet; the launch that takes dots only then clears r_sum beyond d,
+// where the apply launches write nothing.  (As a kernel argument, with the padding masked in every launch: the dots of
+// 124M elements 5.24 -> 5.31 ms, of 11.2M 0.478 -> 0.479.)
+template <int BB, int VW, int TE, bool APPLY, bool FRESH, bool NB>
+__device__ __forceinline__ void pass1_body(const RowMap &rm, const PrevBlock &prev, double *__restrict__ r_sum,
                                            double *__restrict__ out, int64_t ntiles, int group, int ngroups)
 {
     using L = PartLayout<BB>;
@@ -280,8 +282,7 @@ __device__ __forceinline__ void pass1_body(const RowMap &rm, const PrevBlock &pr
 #pragma unroll
             for (int u = 0; u < LOADS; ++u) prev_regs[u] = tile_load(psrc[u], true, t * TE + chunk * 4);
         }
-        // (with APPLY the load stays unconditional and its result is dropped: a branch here cost 2 % at 1M elements)
-        if (tid < TE / 2 && (APPLY || !fresh)) stage_s = *reinterpret_cast<const double2 *>(r_sum + t * TE + tid * 2);
+        if (!FRESH && tid < TE / 2) stage_s = *reinterpret_cast<const double2 *>(r_sum + t * TE + tid * 2);
     };
     int64_t tile = group;
     if (tile < ntiles) load_tile(tile);
@@ -311,14 +312,15 @@ __device__ __forceinline__ void pass1_body(const RowMap &rm, const PrevBlock &pr
                 double s0 = 0.0, s1 = 0.0;
 #pragma unroll
                 for (int q = 0; q < RPI; ++q) { s0 += col[q * TE]; s1 += col[q * TE + 1]; }
-                stage_s.x = (fresh ? 0.0 : stage_s.x) + s0;
-                stage_s.y = (fresh ? 0.0 : stage_s.y) + s1;
+                stage_s.x = (FRESH ? 0.0 : stage_s.x) + s0;
+                stage_s.y = (FRESH ? 0.0 : stage_s.y) + s1;
                 *reinterpret_cast<double2 *>(r_sum + tile * TE + tid * 2) = stage_s;
             }
         }
-        if (!APPLY && tile == ntiles - 1) {  // (the apply launches write no padding)
-            if (tile * TE + tid * 2 >= d) stage_s.x = 0.0;
-            if (tile * TE + tid * 2 + 1 >= d) stage_s.y = 0.0;
+        if (FRESH && !APPLY && tile == ntiles - 1 && tid < TE / 2) {
+            const int64_t e = tile * TE + tid * 2;
+            if (e >= d) r_sum[e] = 0.0;
+            if (e + 1 >= d) r_sum[e + 1] = 0.0;
         }
         if (tid < TE / 2)
             *reinterpret_cast<double2 *>(stage + 2 * TILE_FLOATS * 4 + tid * 16) = stage_s;
@@ -395,14 +397,15 @@ __device__ __forceinline__ void pass1_body(const RowMap &rm, const PrevBlock &pr
     }
 }
 
-template <int BB, int VW, int TE, bool APPLY>
-__global__ __launch_bounds__(kThreads) void pass1_dots_gram(RowMap rm, PrevBlock prev, int fresh,
+template <int BB, int VW, int TE, bool APPLY, bool FRESH>
+__global__ __launch_bounds__(kThreads) void pass1_dots_gram(RowMap rm, PrevBlock prev,
                                                             double *__restrict__ r_sum,
                                                             double *__restrict__ partials,
                                                             int64_t ntiles)
 {
-    pass1_body<BB, VW, TE, APPLY, TE == 64>(rm, prev, fresh, r_sum, partials + (int64_t)blockIdx.x * PartLayout<BB>::PART,
-                                            ntiles, (int)blockIdx.x, (int)gridDim.x);
+    pass1_body<BB, VW, TE, APPLY, FRESH, TE == 64>(rm, prev, r_sum,
+                                                   partials + (int64_t)blockIdx.x * PartLayout<BB>::PART, ntiles,
+                                                   (int)blockIdx.x, (int)gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -604,7 +607,7 @@ __global__ __launch_bounds__(kResolveThreads<BB>) void resolve_signs(const doubl
 // What an apply launch does besides, so that no launch of its own clears or exports the running sum: the epoch's first
 // block starts it (fresh: r_sum holds nothing and is not read), the last one's result leaves as fp32 and / or
 // double (r32, r64; last: it goes nowhere else).  Five passes over the running sum less per epoch: 40 pairs of
-// 124M elements 15.00 -> 14.19 ms, 128 pairs of 11.2M 3919 -> 3813 us.
+// 124M elements 15.03 -> 14.07 ms, 128 pairs of 11.2M 3913 -> 3805 us.
 struct SumEnds {
     int fresh, last;
     float *r32;

@@ -338,16 +338,17 @@ void launch_pass1(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, boo
     const dim3 grid(plan.pass1_groups), block(kThreads);
     const int64_t ntiles = (rm.d + plan.tile_elems - 1) / plan.tile_elems;
     auto launch = [&](auto kernel, const PrevBlock &pb) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, rm, pb, fresh ? 1 : 0, h->r_sum, h->partials,
-                           ntiles);
+        hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, rm, pb, h->r_sum, h->partials, ntiles);
     };
-    if (plan.tile_elems == 128) {
-        if (prev) launch(pass1_dots_gram<BB, VW, 128, true>, *prev);
-        else launch(pass1_dots_gram<BB, VW, 128, false>, none);
-    } else {
-        if (prev) launch(pass1_dots_gram<BB, VW, 64, true>, *prev);
-        else launch(pass1_dots_gram<BB, VW, 64, false>, none);
-    }
+    auto by_start = [&](auto tile) {
+        constexpr int TE = decltype(tile)::value;
+        if (prev && fresh) launch(pass1_dots_gram<BB, VW, TE, true, true>, *prev);
+        else if (prev) launch(pass1_dots_gram<BB, VW, TE, true, false>, *prev);
+        else if (fresh) launch(pass1_dots_gram<BB, VW, TE, false, true>, none);
+        else launch(pass1_dots_gram<BB, VW, TE, false, false>, none);
+    };
+    if (plan.tile_elems == 128) by_start(std::integral_constant<int, 128>{});
+    else by_start(std::integral_constant<int, 64>{});
 }
 // Rows from this length on take the resident form of the apply pass (the running-sum
 // traffic in one burst); shorter ones the flat form, whose launch ramps up faster
