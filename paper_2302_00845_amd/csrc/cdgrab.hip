@@ -732,7 +732,11 @@ int cdgrab_pergrad(cdgrab_handle *h, int64_t N, int64_t in_dim, int64_t classes,
 constexpr int64_t kHerdKeepMinWorkers = 6;
 constexpr int64_t kHerdKeepBytes = (int64_t)1 << 30;  // ... and up to this size
 
-constexpr int64_t kHerdScanMaxD = 128, kHerdManySegments = 160;  // of the prefix over the segments
+// Of the prefix over the segments.  A thread that shares an element needs a segment of its own, so eight
+// threads share one from this many segments on; below, one thread takes them all (eight threads -> one, whole call: 4 steps of
+// 30M elements 1558 -> 695 us, 6 workers x 7 steps of 100 000 32.7 -> 28.5, calls below 20 us equal).
+constexpr int64_t kHerdScanMaxD = 128, kHerdManySegments = 160;
+constexpr int kHerdFewSegments = 8;
 
 // Dispatch on the block size, which is a template parameter of the launch helpers.
 #define BY_BLOCK_PAIRS(bb, call64, call32, call16) ((bb) == 64 ? (call64) : (bb) == 32 ? (call32) : (call16))
@@ -1489,6 +1493,9 @@ int cdgrab_herding_bound(cdgrab_handle *h, int64_t m, int64_t n, int64_t d, cons
             if (sh.segments >= kHerdManySegments)
                 hipLaunchKernelGGL((herding_segment_offsets<16, 64>), dim3((unsigned)((d + 15) / 16)), dim3(1024), 0,
                                    h->stream, segsum, sh, zbar, start);
+            else if (sh.segments < kHerdFewSegments)
+                hipLaunchKernelGGL((herding_segment_offsets_few<kHerdFewSegments - 1>), dim3((unsigned)((d + 255) / 256)),
+                                   dim3(256), 0, h->stream, segsum, sh, zbar, start);
             else
                 hipLaunchKernelGGL((herding_segment_offsets<32, 8>), dim3((unsigned)((d + 31) / 32)), dim3(256), 0,
                                    h->stream, segsum, sh, zbar, start);

@@ -151,6 +151,35 @@ __global__ __launch_bounds__(ELEMS * RUNS) void herding_segment_offsets(const do
     }
 }
 
+// Pass B for at most MOST segments (long rows, or few steps), whose sums one thread per element requests together.  More
+// threads per element than segments would leave some of them a run of none, worth 0 - 0 * mean, which is not a number
+// where the mean is not finite, and rows of 2^29 elements more threads than a launch holds.
+template <int MOST>
+__global__ __launch_bounds__(256) void herding_segment_offsets_few(const double *__restrict__ segsum, HerdingShape sh,
+                                                                   double *__restrict__ zbar,
+                                                                   double *__restrict__ start)
+{
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= sh.d) return;
+    double sum[MOST];
+#pragma unroll
+    for (int s = 0; s < MOST; ++s) sum[s] = segsum[(s < sh.segments ? s : sh.segments - 1) * sh.d + e];
+    double total = 0.0;
+#pragma unroll
+    for (int s = 0; s < MOST; ++s) total += s < sh.segments ? sum[s] : 0.0;
+    const double mean = total / (double)(sh.m * sh.n);
+    zbar[e] = mean;
+    double at = 0.0;
+#pragma unroll
+    for (int s = 0; s < MOST; ++s) {
+        if (s >= sh.segments) break;
+        start[s * sh.d + e] = at;
+        const int64_t j0 = s * sh.seg_len;
+        const int64_t len = ((j0 + sh.seg_len < sh.n) ? sh.seg_len : sh.n - j0);
+        at += sum[s] - (double)(len * sh.m) * mean;
+    }
+}
+
 // Pass B for the shortest rows, where there are many segments and few elements: one workgroup per
 // element; thread t takes a run of consecutive segments, the workgroup adds the runs' sums
 // (mean), scans the centred run sums in thread order, and every thread then walks its run.

@@ -60,6 +60,34 @@ def test_steps_kept_or_read_again(lib, m, n, d):
         assert abs(gpu_bound(lib, h, z, perm) - want) <= 1e-12 * max(float(np.abs(z).sum((0, 1)).max()), 1e-30)
 
 
+@pytest.mark.parametrize("m", [2, 6])
+@pytest.mark.parametrize("n", [1, 2, 5, 7, 8, 9, 12])  # steps, and segments of the prefix
+@pytest.mark.parametrize("d", [100, 129, 1023])
+def test_few_segments(lib, m, n, d):
+    """Fewer segments than threads would share an element: small whole numbers against the oracle, and an element
+    whose mean is not finite, whose prefix after a finite first step is not finite either."""
+    h = lib.Handle()
+    z = workloads.integer_rows(n, m, n, d)
+    want = oracle.parallel_herding(z)
+    # m * n double sums of rounding 1.1e-16 each, taken relative to the largest prefix
+    assert abs(gpu_bound(lib, h, z) - want) <= 1e-12 * max(float(np.abs(z).sum((0, 1)).max()), 1.0)
+    if n > 1:
+        z[m - 1, n - 1, d - 1] = np.inf
+        assert gpu_bound(lib, h, z) == np.inf
+
+
+def test_longest_rows(lib):
+    """Rows of more than 2^29 elements: every element has its mean and its prefix."""
+    h, d = lib.Handle(), (1 << 29) + 5
+    z = torch.zeros((1, 2, d), device="cuda")
+    for e in (0, 1 << 28, d - 1):
+        z[0, 0, e] = 6.0
+        assert gpu_bound(lib, h, z) == 3.0
+        z[0, 0, e] = 0.0
+    assert gpu_bound(lib, h, z) == 0.0
+    h.close()
+
+
 def test_capture_without_room_for_the_steps(lib):
     """A handle that has no workspace for the steps' sums yet allocates none under capture: the rows are read again."""
     big, z = (workloads.heavy_rows(m, m, n, d) for m, n, d in ((5, 600, 700), (6, 300, 600)))
