@@ -732,10 +732,19 @@ int cdgrab_pergrad(cdgrab_handle *h, int64_t N, int64_t in_dim, int64_t classes,
 constexpr int64_t kHerdKeepMinWorkers = 6;
 constexpr int64_t kHerdKeepBytes = (int64_t)1 << 30;  // ... and up to this size
 
-// Of the prefix over the segments.  A thread that shares an element needs a segment of its own, so eight
-// threads share one from this many segments on; below, one thread takes them all (eight threads -> one, whole call: 4 steps of
+// The prefix over the segments.  By a workgroup per element where there are few elements: always up to 200 of them
+// (400 steps and more of 130 elements 16 - 38 % of the call less than by 64 threads per element, of 200 elements 1 - 23 %),
+// up to 512 while segments * elements is small (one worker, 400 steps of 300, 400 and 512 elements 19.8, 21.0 and 22.2 us
+// against 23.2, 24.3 and 24.4; 1000 steps 27.8, 32.6 and 39.1 against 31.3, 33.5 and 34.3; 3000 steps 59, 70 and 90 against
+// 53, 59 and 61).
+constexpr int64_t kHerdScanMaxD = 200, kHerdScanSomeD = 512, kHerdScanEntries = 300000;
+bool herding_by_scan(int64_t segments, int64_t d) {
+    return d <= kHerdScanMaxD || (d <= kHerdScanSomeD && segments * d <= kHerdScanEntries);
+}
+// Above, 64 threads share an element where there are many segments, else eight.  A thread that shares an element needs a
+// segment of its own, so one thread takes all of fewer than eight (eight threads -> one, whole call: 4 steps of
 // 30M elements 1558 -> 695 us, 6 workers x 7 steps of 100 000 32.7 -> 28.5, calls below 20 us equal).
-constexpr int64_t kHerdScanMaxD = 128, kHerdManySegments = 160;
+constexpr int64_t kHerdManySegments = 160;
 constexpr int kHerdFewSegments = 8;
 
 // Dispatch on the block size, which is a template parameter of the launch helpers.
@@ -1487,21 +1496,18 @@ int cdgrab_herding_bound(cdgrab_handle *h, int64_t m, int64_t n, int64_t d, cons
         };
         if (keep) sums(herding_segment_sums<VW, true>);
         else sums(herding_segment_sums<VW, false>);
-        // the prefix over segments: a workgroup per 16 elements, or per element where there are too few
-        // of them (m = 100, whole call: 100 elements 106 us by the scan, 113 otherwise; 512 elements 270 and 226)
-        if (d > kHerdScanMaxD)
-            if (sh.segments >= kHerdManySegments)
-                hipLaunchKernelGGL((herding_segment_offsets<16, 64>), dim3((unsigned)((d + 15) / 16)), dim3(1024), 0,
-                                   h->stream, segsum, sh, zbar, start);
-            else if (sh.segments < kHerdFewSegments)
-                hipLaunchKernelGGL((herding_segment_offsets_few<kHerdFewSegments - 1>), dim3((unsigned)((d + 255) / 256)),
-                                   dim3(256), 0, h->stream, segsum, sh, zbar, start);
-            else
-                hipLaunchKernelGGL((herding_segment_offsets<32, 8>), dim3((unsigned)((d + 31) / 32)), dim3(256), 0,
-                                   h->stream, segsum, sh, zbar, start);
-        else
+        if (herding_by_scan(sh.segments, d))
             hipLaunchKernelGGL(herding_segment_offsets_scan, dim3((unsigned)d), dim3(256), 0, h->stream,
                                segsum, sh, zbar, start);
+        else if (sh.segments >= kHerdManySegments)
+            hipLaunchKernelGGL((herding_segment_offsets<16, 64>), dim3((unsigned)((d + 15) / 16)), dim3(1024), 0,
+                               h->stream, segsum, sh, zbar, start);
+        else if (sh.segments < kHerdFewSegments)
+            hipLaunchKernelGGL((herding_segment_offsets_few<kHerdFewSegments - 1>), dim3((unsigned)((d + 255) / 256)),
+                               dim3(256), 0, h->stream, segsum, sh, zbar, start);
+        else
+            hipLaunchKernelGGL((herding_segment_offsets<32, 8>), dim3((unsigned)((d + 31) / 32)), dim3(256), 0,
+                               h->stream, segsum, sh, zbar, start);
         auto replay = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, dim3(256), keep ? 0 : lds, h->stream, z, perm, sh, lds_ids, zbar, start,
                                h->herd_steps, bits);

@@ -61,8 +61,8 @@ def test_steps_kept_or_read_again(lib, m, n, d):
 
 
 @pytest.mark.parametrize("m", [2, 6])
-@pytest.mark.parametrize("n", [1, 2, 5, 7, 8, 9, 12])  # steps, and segments of the prefix
-@pytest.mark.parametrize("d", [100, 129, 1023])
+@pytest.mark.parametrize("n", [1, 2, 5, 7, 8, 9, 16, 17])  # steps, and segments of the prefix
+@pytest.mark.parametrize("d", [100, 201, 513, 1023])
 def test_few_segments(lib, m, n, d):
     """Fewer segments than threads would share an element: small whole numbers against the oracle, and an element
     whose mean is not finite, whose prefix after a finite first step is not finite either."""
@@ -74,6 +74,17 @@ def test_few_segments(lib, m, n, d):
     if n > 1:
         z[m - 1, n - 1, d - 1] = np.inf
         assert gpu_bound(lib, h, z) == np.inf
+
+
+@pytest.mark.parametrize("m", [1, 7])
+@pytest.mark.parametrize("n,d", [(1501, 200), (1501, 201), (585, 512), (586, 512), (160, 513)])
+def test_rules_of_the_prefix(lib, m, n, d):
+    """Both sides of the lines between the forms of the prefix over the segments (here as many as steps)."""
+    h = lib.Handle()
+    z = workloads.heavy_rows(n + d, m, n, d)
+    want = oracle.parallel_herding(z)
+    # m * n double sums of rounding 1.1e-16 each, taken relative to the largest prefix
+    assert abs(gpu_bound(lib, h, z) - want) <= 1e-12 * float(np.abs(z).sum((0, 1)).max())
 
 
 def test_longest_rows(lib):
