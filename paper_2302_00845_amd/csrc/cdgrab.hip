@@ -743,9 +743,12 @@ bool herding_by_scan(int64_t segments, int64_t d) {
 }
 // Above, 64 threads share an element where there are many segments, else eight.  A thread that shares an element needs a
 // segment of its own, so one thread takes all of fewer than eight (eight threads -> one, whole call: 4 steps of
-// 30M elements 1558 -> 695 us, 6 workers x 7 steps of 100 000 32.7 -> 28.5, calls below 20 us equal).
+// 30M elements 1558 -> 695 us, 6 workers x 7 steps of 100 000 32.7 -> 28.5, calls below 20 us equal), and it is the faster
+// form up to 24 (one worker: 8 segments of 250 000 elements 57.5 -> 51.8 us, 16 of 150 000 43.5 -> 39.6, 17 of 65 536
+// 37.1 -> 34.8, 24 45.3 -> 45.2; 32 54.3 -> 55.6), in three sizes, since it requests all it has room for (10 of
+// 100 001 in room for 24 36.8 us, for 16 33.3).
 constexpr int64_t kHerdManySegments = 160;
-constexpr int kHerdFewSegments = 8;
+constexpr int kHerdFewSegments = 24;
 
 // Dispatch on the block size, which is a template parameter of the launch helpers.
 #define BY_BLOCK_PAIRS(bb, call64, call32, call16) ((bb) == 64 ? (call64) : (bb) == 32 ? (call32) : (call16))
@@ -1496,15 +1499,21 @@ int cdgrab_herding_bound(cdgrab_handle *h, int64_t m, int64_t n, int64_t d, cons
         };
         if (keep) sums(herding_segment_sums<VW, true>);
         else sums(herding_segment_sums<VW, false>);
+        auto few = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, h->stream, segsum, sh, zbar, start);
+        };
         if (herding_by_scan(sh.segments, d))
             hipLaunchKernelGGL(herding_segment_offsets_scan, dim3((unsigned)d), dim3(256), 0, h->stream,
                                segsum, sh, zbar, start);
         else if (sh.segments >= kHerdManySegments)
             hipLaunchKernelGGL((herding_segment_offsets<16, 64>), dim3((unsigned)((d + 15) / 16)), dim3(1024), 0,
                                h->stream, segsum, sh, zbar, start);
-        else if (sh.segments < kHerdFewSegments)
-            hipLaunchKernelGGL((herding_segment_offsets_few<kHerdFewSegments - 1>), dim3((unsigned)((d + 255) / 256)),
-                               dim3(256), 0, h->stream, segsum, sh, zbar, start);
+        else if (sh.segments <= 8)
+            few(herding_segment_offsets_few<8>);
+        else if (sh.segments <= 16)
+            few(herding_segment_offsets_few<16>);
+        else if (sh.segments <= kHerdFewSegments)
+            few(herding_segment_offsets_few<kHerdFewSegments>);
         else
             hipLaunchKernelGGL((herding_segment_offsets<32, 8>), dim3((unsigned)((d + 31) / 32)), dim3(256), 0,
                                h->stream, segsum, sh, zbar, start);

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void herding_segment_sums(const float *__restr
 // Pass B: zbar[e] and start[s][e], the centred prefix before segment s.  A workgroup serves ELEMS elements;
 // RUNS threads share an element, each taking a run of consecutive segments.  Bound by latency: one
 // thread per element walking all segments twice took 35 us for 268 segments of 7850 elements, now 17.
-// 64 runs, or 8 where there are few segments (21 segments of 100 001 elements, whole call: 438 us with 64, 378 with 8).
+// 64 runs, or 8 where there are fewer segments (21 segments of 100 001 elements, whole call: 438 us with 64, 378 with 8).
 template <int ELEMS, int RUNS>
 __global__ __launch_bounds__(ELEMS * RUNS) void herding_segment_offsets(const double *__restrict__ segsum,
                                                                         HerdingShape sh, double *__restrict__ zbar,

@@ -61,7 +61,7 @@ def test_steps_kept_or_read_again(lib, m, n, d):
 
 
 @pytest.mark.parametrize("m", [2, 6])
-@pytest.mark.parametrize("n", [1, 2, 5, 7, 8, 9, 16, 17])  # steps, and segments of the prefix
+@pytest.mark.parametrize("n", [1, 2, 5, 7, 8, 9, 16, 17, 24, 25])  # steps, and segments of the prefix
 @pytest.mark.parametrize("d", [100, 201, 513, 1023])
 def test_few_segments(lib, m, n, d):
     """Fewer segments than threads would share an element: small whole numbers against the oracle, and an element
