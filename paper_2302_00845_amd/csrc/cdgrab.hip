@@ -1480,16 +1480,15 @@ int cdgrab_herding_bound(cdgrab_handle *h, int64_t m, int64_t n, int64_t d, cons
     const int lds_ids = (perm && sh.spw == 1 && ids_bytes <= 48 * 1024) ? 1 : 0;
     const size_t lds = lds_ids ? ids_bytes : 0;
     const int form = row_form((d % 4 == 0 && reinterpret_cast<uintptr_t>(z) % 16 == 0) ? 4 : 1, d);
-    // where the steps' sums are kept for the second pass (and fit), the rows are read once; nothing is allocated
-    // for them while the stream is being captured
-    const auto may_allocate = [&] {
+    // where the steps' sums are kept for the second pass (and fit), the rows are read once; not in a launch that is
+    // recorded, because their buffer is replaced when a later call has more steps
+    const auto capturing = [&] {
         hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(h->stream, &status) == hipSuccess) return status == hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(h->stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
         (void)hipGetLastError();
-        return false;
+        return true;
     };
-    const bool keep = m >= kHerdKeepMinWorkers && n <= kHerdKeepBytes / 32 / quads &&
-                      (h->herd_steps_cap >= n * quads * 4 || may_allocate()) &&
+    const bool keep = m >= kHerdKeepMinWorkers && n <= kHerdKeepBytes / 32 / quads && !capturing() &&
                       ensure(h, h->herd_steps, h->herd_steps_cap, n * quads * 4) == CDGRAB_OK;
     hipLaunchKernelGGL(herding_clear, dim3(1), dim3(1), 0, h->stream, bits);
     auto launch = [&](auto vw_tag) {

@@ -124,6 +124,30 @@ def test_capture_without_room_for_the_steps(lib):
         s.synchronize()
 
 
+def test_capture_on_a_handle_with_room_for_the_steps(lib):
+    """A recorded call holds no address of the steps' sums, whose buffer a later call with more steps replaces."""
+    z, more = (torch.from_numpy(workloads.heavy_rows(n, 6, n, 600)).cuda() for n in (300, 700))
+    room, s = torch.from_numpy(workloads.heavy_rows(5, 5, 800, 600)).cuda(), torch.cuda.Stream()
+    h = lib.Handle(stream=s)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        lib.cdgrab_herding_bound(h, room)  # the workspace of everything that follows but the steps' sums
+        want = lib.cdgrab_herding_bound(h, z)
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        out = lib.cdgrab_herding_bound(h, z)
+    for _ in range(3):
+        with torch.cuda.stream(s):
+            lib.cdgrab_herding_bound(h, more)
+        s.synchronize()
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)  # (the same sums in the same order, kept or read again)
+
+
 @pytest.mark.parametrize("m,n,d,exact", [
     (5, 24, 300, False),        # one block per worker: m one-worker epochs back to back
     (7, 200, 300, False),       # 100 pairs: the walks run side by side, the worker as a grid coordinate

@@ -104,3 +104,15 @@ def test_longest_rows_are_not_refused(call, d):
     """A thread per element in the prefix over the segments, of which rows this long have one."""
     launches = call("mark('call')\nrc = bound(1, 2, %d)\nassert rc == 0, text()\n" % d)["call"]
     assert len(launches) == 4
+
+
+def test_steps_sums_stay_out_of_a_capture(call):
+    """The sums kept from the first pass lie in a buffer that a later call with more steps replaces, so a launch that
+    is recorded must not hold its address, whether the handle has the buffer or not."""
+    parts = call("bound(5, 4000, 600)\n"           # room for the segments of everything that follows
+                 "mark('eager')\nassert bound(6, 300, 600) == 0\n"
+                 "capture(1)\nbefore = mallocs()\n"
+                 "mark('captured')\nassert bound(6, 300, 600) == 0 and bound(6, 600, 600) == 0\n"
+                 "assert mallocs() == before\n")
+    kept = lambda part: [name for name, _, _ in parts[part] if "ELb1E" in name]  # the kernels' STEPS form
+    assert len(kept("eager")) == 2 and not kept("captured")
