@@ -1488,8 +1488,13 @@ int cdgrab_herding_bound(cdgrab_handle *h, int64_t m, int64_t n, int64_t d, cons
         (void)hipGetLastError();
         return true;
     };
-    const bool keep = m >= kHerdKeepMinWorkers && n <= kHerdKeepBytes / 32 / quads && !capturing() &&
-                      ensure(h, h->herd_steps, h->herd_steps_cap, n * quads * 4) == CDGRAB_OK;
+    const auto room = [&] {  // (no error of the call if there is none)
+        const std::string text = h->err;
+        const bool there = ensure(h, h->herd_steps, h->herd_steps_cap, n * quads * 4) == CDGRAB_OK;
+        if (!there) h->err = text;
+        return there;
+    };
+    const bool keep = m >= kHerdKeepMinWorkers && n <= kHerdKeepBytes / 32 / quads && !capturing() && room();
     hipLaunchKernelGGL(herding_clear, dim3(1), dim3(1), 0, h->stream, bits);
     auto launch = [&](auto vw_tag) {
         constexpr int VW = decltype(vw_tag)::value;

@@ -116,3 +116,11 @@ def test_steps_sums_stay_out_of_a_capture(call):
                  "assert mallocs() == before\n")
     kept = lambda part: [name for name, _, _ in parts[part] if "ELb1E" in name]  # the kernels' STEPS form
     assert len(kept("eager")) == 2 and not kept("captured")
+
+
+def test_no_error_text_after_a_call_that_succeeds(call):
+    """Where the steps' sums do not fit, the rows are read again: the call succeeds and says nothing."""
+    call("assert bound(5, 4000, 600) == 0 and bound(6, 300, 600) == 0\n"
+         "assert bound(0, 1, 1) != 0\nbefore = text()\nassert before\n"
+         "room(1 << 20)\nassert bound(6, 2000, 600) == 0, text()\nassert text() == before\n"
+         "assert bound(6, 2000, 700_000) != 0 and 'workspace' in text()\n")
