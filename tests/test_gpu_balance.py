@@ -98,6 +98,26 @@ def test_fused_and_separate_passes_agree(lib, m, n, d, bb):
     check_epoch(z, run_epoch(lib, z, block_pairs=bb, apply_mode=1))
 
 
+@pytest.mark.parametrize("d", [1001, 66_001])        # 64- and 128-element tiles, the last one partly beyond the row
+@pytest.mark.parametrize("apply_mode", [1, 2, 3, 4])
+@pytest.mark.parametrize("n", [8, 32, 34, 40])        # blocks of 16 pairs: one, two, two and a short one
+def test_running_sum_of_an_earlier_epoch(lib, d, apply_mode, n):
+    """An epoch of rows that are no numbers leaves such a running sum on the handle, over more elements; the next
+    epochs start from zero all the same, also beyond the row's end, whichever of the sum's exports are asked for."""
+    h = lib.Handle(block_pairs=16, apply_mode=apply_mode, gram_mode=1)
+    left = torch.full((2, 40, d + 300), float("nan"), device="cuda")
+    z = workloads.integer_rows(n + d, 2, n, d, 4)
+    zt = torch.from_numpy(z).cuda()
+    for r32, r64 in ((True, True), (True, False), (False, True), (False, False)):
+        lib.cdgrab_balance_epoch(h, 2, 40, d + 300, grads=left)
+        out = lib.cdgrab_balance_epoch(h, 2, n, d, grads=zt, want_r32=r32, want_r64=r64, want_dots=True)
+        torch.cuda.synchronize()
+        got = {k: v.cpu().numpy() for k, v in out.items() if v is not None}
+        assert ("r32" in got, "r64" in got) == (r32, r64)
+        rep = check_epoch(z, got, expect_exact_signs=True)
+        assert rep["dots_max_abs_err"] == 0.0 and (not r64 or rep["r64_rel_l2"] == 0.0)
+
+
 @pytest.mark.parametrize("m,n,d,bb,groups", [
     (4, 64, 1024, 16, 0), (3, 50, 777, 32, 0), (8, 40, 65536 + 12, 32, 0), (16, 30, 130, 64, 0),
     (2, 70, 30000, 0, 1),        # one workgroup: 30 groups per thread, two slabs of 15
