@@ -202,7 +202,8 @@ int cdgrab_balance_epoch(cdgrab_handle *h, int64_t m, int64_t n, int64_t d,
  * exactly representable input, otherwise equal to double rounding).
  * Arguments and outputs as cdgrab_balance_epoch with grads given (no generator).
  * All calls on one GPU share that GPU's array, whatever their handle: calls that overlap
- * in time on one GPU (two streams, two threads) race.  A call clears what it needs cleared.
+ * in time on one GPU (two streams, two threads) race.  A call reads nothing that an earlier one
+ * left there.
  * Errors: EINVAL (as cdgrab_balance_epoch; grads NULL; d > CDGRAB_STATIC_MAX_D), EHIP. */
 #define CDGRAB_STATIC_MAX_D 131072
 int cdgrab_balance_epoch_static(cdgrab_handle *h, int64_t m, int64_t n, int64_t d,
@@ -309,7 +310,11 @@ int cdgrab_reorder(cdgrab_handle *h, int64_t m, int64_t n, const int8_t *signs,
  *     zbar = mean of all m*n vectors.
  *   z [m][n][d] fp32 dev, indexed by example id (NOT by visiting position),
  *   perm [m][n] int32 dev or NULL (identity), bound_out: one double, dev.
- * Sums in double.  Errors: EINVAL (sizes, null), ENOMEM, EHIP. */
+ * Sums in double.  From six workers on the handle keeps the sum over the workers of every step for its
+ * second pass: 8 n d bytes (d rounded up to a multiple of four) if that is at most 1 GiB, held until the
+ * handle is destroyed, and replaced (which synchronises the stream) by a call that needs more.  Where
+ * these sums find no room, and while the stream is being captured, the rows are read twice instead,
+ * with the same result.  The call may be captured like those with dense input.  Errors: EINVAL (sizes, null), ENOMEM, EHIP. */
 int cdgrab_herding_bound(cdgrab_handle *h, int64_t m, int64_t n, int64_t d, const float *z,
                          const int32_t *perm, double *bound_out);
 

@@ -140,13 +140,15 @@ bool fuse_apply_by_default(int64_t d) { return d <= (int64_t)5 << 18; }
 // two launches each (chain_kernels.hpp).
 constexpr int64_t kGramBatch = 512;                  // a staging chunk holds at most this many blocks
 constexpr int64_t kGramBytes = (int64_t)256 << 20;   // Gram tiles held at a time
-// Measured on MI355X (m = 16), us per 64 pairs of the per-block form -> this form: d = 256: 20.4 -> 5.2;
-// 1024: 20.7 -> 5.6; 4096: 20.9 -> 7.7; 7850: 22.4 -> 10.0; 16 384: 24.2 -> 13.6; 32 768: 33.8 -> 21.0;
-// 65 536: 46.6 -> 35.8; 98 304: 46.1 -> 49.7; 131 072: 66.5 -> 66.8 (the rows are read three times
+// Measured on MI355X (m = 16, 4096 pairs), us per 64 pairs of the per-block form -> this form: d = 256: 16.6 -> 5.1;
+// 1024: 17.9 -> 5.5; 4096: 18.2 -> 6.8; 7850: 19.6 -> 8.6; 16 384: 20.7 -> 12.1; 32 768: 30.6 -> 18.3;
+// 65 536: 43.4 -> 29.9; 81 920: 43.3 -> 37.0; 98 304: 43.2 -> 42.6; 131 072: 60.7 -> 55.7 (the rows are read three times
 // instead of twice).
-// That is for chains of many steps.  At 65 536 elements, where the per-block form changes to tiles of 128
-// elements, up to 128 pairs are faster in that form: 65 .. 128 pairs 87 against 103 us, 129 pairs 151 against
-// 139; at 57 344 elements 65 .. 128 pairs are equal.
+// That is for chains of many steps.  Fewer pairs, us per epoch: 128 pairs of 57 344 elements 87 -> 65, of 65 536 (where the
+// per-block form changes to tiles of 128 elements) 78 -> 69, of 81 920 80 -> 80, of 98 304 82 -> 88; 70 pairs 84 -> 62,
+// 73 -> 66, 57 -> 76, 58 -> 83; 257 pairs of 81 920 183 -> 182, of 98 304 189 -> 214.  The two lines below were drawn when
+// diagonal Gram tiles took a third longer (98 304 elements: 49.7 per 64 pairs in this form against 46.1; up to 128 pairs of
+// 65 536: 103 against 87) and have not moved since: by these figures both could lie near 81 920 elements.
 constexpr int64_t kGramAheadMaxD = 65536;     // chosen by default up to here ...
 constexpr int64_t kGramAheadEdgePairs = 128;  // ... where, at that length, there are more pairs than this
 constexpr int64_t kChunkAheadMaxD = 16384;    // and for staging chunks of several blocks up to here
@@ -169,11 +171,13 @@ struct ChainPlan {
     int64_t gram_len, parts_len, dots_len;  // doubles of workspace, all walks
 };
 
-// Time of one step of sp pairs, microseconds, fitted to measured epochs, per step of 64 / 128 / 256 pairs:
-// 8192 pairs of 65 .. 256 elements 8.0 - 8.7 / 11.5 - 12.6 / 20.3 - 21.3 us, of 512 .. 2048 elements 9.7 - 10.0 /
-// 13.0 - 13.9 / 21.6 - 24.2; 30 000 pairs of 7850 elements 11.7 / 15.9 / 27.9 and 0.35 / 1.1 / 1.8 ms of Gram
-// tiles; 64 walks of 468 pairs of 7850: 82 us per 64-pair step.  Long chains of one walk want long steps, many walks
-// or long rows short ones.
+// Time of one step of sp pairs, microseconds, fitted to measured epochs of 64 / 128 / 256 pairs per step.  Those epochs,
+// Gram tiles included: 8192 pairs of 66 .. 256 elements 8.1 - 8.4 / 12.0 - 12.8 / 19.8 - 20.7 us per step, of 512 .. 2048
+// elements 9.5 - 9.6 / 13.1 - 13.9 / 20.9 - 23.5; 30 000 pairs of 7850 elements 5.54 / 4.35 / 4.83 ms; 64 walks of 468
+// pairs of 7850 1.07 / 1.52 / 2.03 ms.  Long chains of one walk want long steps, many walks or long rows short ones.
+// Short chains are the model's weak side, because it counts a wide launch for the first step too, which has none: 300 pairs of
+// 7850 elements 72.7 / 65.7 / 77.0 us, 71.2 as chosen; of 256 elements 54.0 / 46.2 / 43.1, 46.7 as chosen; 8 walks of 100
+// pairs of 7850 50.4 / 46.8 / 45.9, 50.7 as chosen.
 double step_cost_us(int64_t sp, int64_t d, int64_t walks) {
     const double blk = (double)(sp / kTilePairs), tiles = blk * (blk + 1) / 2;
     const double launches = (d > 256 ? 5.7 : 3.7) + 0.066 * (double)sp;
@@ -1139,7 +1143,7 @@ int cdgrab_balance_epoch_static(cdgrab_handle *h, int64_t m, int64_t n, int64_t 
     } sv{h->r_sum, h->partials, h->reduced, h->eps_blk, h->r_cap, h->partials_cap, h->eps_cap,
          h->timing, h->gram_mode, h->pass1_groups_opt, h->fixed_workspace};
     h->r_sum = base;
-    h->r_cap = d > 0 ? round_up(d, kPadE) : 0;  // only this much is cleared and used
+    h->r_cap = d > 0 ? round_up(d, kPadE) : 0;  // only this much is used
     h->partials = base + kStaticRsum;
     h->partials_cap = kStaticPartials;
     h->reduced = h->partials + kStaticPartials;

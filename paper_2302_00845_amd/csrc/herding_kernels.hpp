@@ -9,7 +9,7 @@
 // Bound by bytes.  Pass C needs only each step's sum over the workers, so with enough workers pass A
 // leaves those sums behind (8 bytes per step and element instead of 4 m read again):
 // 16 x 3750 rows of 7850 elements 711 -> 530 us (sums 446, of which about 100 for the 235 MB written
-// into the read stream; offsets 17; replay 54).  Non-temporal stores of the sums: 549.
+// into the read stream; offsets 24; replay 52).  Non-temporal stores of the sums: 549.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void herding_segment_sums(const float *__restr
 
 // Pass B: zbar[e] and start[s][e], the centred prefix before segment s.  A workgroup serves ELEMS elements;
 // RUNS threads share an element, each taking a run of consecutive segments.  Bound by latency: one
-// thread per element walking all segments twice took 35 us for 268 segments of 7850 elements, now 17.
+// thread per element walking all segments twice took 34 us for 268 segments of 7850 elements, now 24.
 // 64 runs, or 8 where there are fewer segments (21 segments of 100 001 elements, whole call: 438 us with 64, 378 with 8).
 template <int ELEMS, int RUNS>
 __global__ __launch_bounds__(ELEMS * RUNS) void herding_segment_offsets(const double *__restrict__ segsum,
