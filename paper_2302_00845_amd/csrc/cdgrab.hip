@@ -19,6 +19,7 @@
 #include "chain_kernels.hpp"
 #include "order_kernels.hpp"
 #include "herding_kernels.hpp"
+#include "band_kernels.hpp"
 #include "narrow_kernels.hpp"
 #include "train_kernels.hpp"
 
@@ -168,6 +169,7 @@ struct ChainPlan {
     int64_t steps;      // steps whose Gram tiles are computed in one launch
     int ksplit;         // workgroups sharing the elements of a tile
     int groups;         // workgroups of a step's wide launch
+    int64_t band_pairs; // rows of at most kNarrowMaxD elements: pairs of a walk whose Gram results are ahead at a time (0: none are)
     int64_t gram_len, parts_len, dots_len;  // doubles of workspace, all walks
 };
 
@@ -203,13 +205,31 @@ int pick_ksplit(int64_t tiles, int64_t d, int num_cu) {
     return best;
 }
 
+// Rows of at most kNarrowMaxD elements: Gram results beforehand (band_kernels.hpp) or inside the walk's workgroup
+// (narrow_kernels.hpp).  The first has one launch more and walks faster.  us per epoch of one walk, inside -> beforehand, rows of
+// 16 / 32 / 64 elements: 256 pairs 13.4 -> 16.8 / 13.6 -> 17.2 / 19.0 -> 21.7; 384 pairs 16.9 -> 17.0 / 17.2 -> 18.1 /
+// 23.9 -> 24.7; 512 pairs 19.7 -> 17.4 / 20.6 -> 19.6 / 29.9 -> 27.9; 4096 pairs 89 -> 72 / 108 -> 76 / 172 -> 104; 200 000
+// pairs 3846 -> 2943 / 4814 -> 3001 / 7939 -> 4273.  The results of all walks go through memory: of 10 walks of 1000 pairs
+// 30.1 -> 27.9 / - / 49.6 -> 43.5, of 100 30.6 -> 40.1 / - / 51 -> 95.
+constexpr int64_t kBandMinPairs = 512;  // per walk
+constexpr int64_t kBandMaxWalks = 16;
+constexpr int64_t kBandBytes = (int64_t)64 << 20;  // Gram results and differences held at a time
+int narrow_padded(int64_t d) { return d <= 16 ? 16 : d <= 32 ? 32 : 64; }
+
 ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pairs, int num_cu) {
     ChainPlan c{};
-    if (d <= kNarrowMaxD) {  // a walk is one workgroup: no workspace, blocks of one tile
+    const int64_t longest = chunk_pairs > 0 ? std::min(chunk_pairs, pairs) : pairs;
+    if (d <= kNarrowMaxD) {  // a walk is one workgroup
         c.sp = kTilePairs;
+        if (longest >= kBandMinPairs && walks <= kBandMaxWalks) {
+            const int64_t per_block = band_doubles(narrow_padded(d));
+            const int64_t held = std::max<int64_t>(1, kBandBytes / 8 / per_block / walks);
+            const int64_t blocks = round_up(std::min<int64_t>((longest + kBandBlock - 1) / kBandBlock, held), kBandStride);
+            c.band_pairs = blocks * kBandBlock;
+            c.gram_len = walks * blocks * per_block;
+        }
         return c;
     }
-    const int64_t longest = chunk_pairs > 0 ? std::min(chunk_pairs, pairs) : pairs;
     double best = 0.0;
     for (int sp = kTilePairs; sp <= kMaxStepPairs; sp *= 2) {
         if (sp > kTilePairs && sp / 2 >= longest) break;  // a shorter step holds them all
@@ -333,6 +353,23 @@ int ensure(cdgrab_handle *h, T *&ptr, int64_t &cap, int64_t want) {
     return CDGRAB_OK;
 }
 
+// The same where the call can do without: no error of the call if there is no room.
+template <typename T>
+bool room(cdgrab_handle *h, T *&ptr, int64_t &cap, int64_t want) {
+    const std::string text = h->err;
+    const bool there = ensure(h, ptr, cap, want) == CDGRAB_OK;
+    if (!there) h->err = text;
+    return there;
+}
+
+// Are the handle's launches being recorded?
+bool capturing(cdgrab_handle *h) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 template <int BB, int VW>
 void launch_pass1(cdgrab_handle *h, const RowMap &rm, const PrevBlock *prev, bool fresh, const cdgrab_plan &plan) {
     PrevBlock none;
@@ -423,22 +460,41 @@ void by_row_form(int form, F &&launch) {
 
 // All of `pairs` consecutive pairs of rows of at most kNarrowMaxD elements.
 int run_narrow(cdgrab_handle *h, const StepRows &rows, int64_t first, int64_t pairs, int64_t half_n,
-               int8_t *signs_out, double *dots_out, float *r32, double *r64) {
+               const ChainPlan &c, int8_t *signs_out, double *dots_out, float *r32, double *r64) {
     MARK(h, 2, kPass1);
-    for (int64_t at = 0; at < pairs; at += kNarrowMaxPairs) {
+    const int64_t most = c.band_pairs > 0 ? c.band_pairs : kNarrowMaxPairs;
+    for (int64_t at = 0; at < pairs; at += most) {
         const int fresh = first + at == 0;
-        StepRows part = step_at(rows, at, 0);
-        part.k0 = (first + at) / rows.m;  // (output slots are counted from the flattened pair, whatever the layout)
-        part.i0 = (int32_t)((first + at) % rows.m);
-        const int count = (int)std::min<int64_t>(kNarrowMaxPairs, pairs - at);
-        auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)h->walks), dim3(kNarrowThreads), 0, h->stream, part, count, half_n,
-                               fresh, h->r_sum, r32, r64, signs_out, dots_out, h->uniforms, h->ws);
-        };
+        const StepRows part = step_at(rows, at, 0);
+        // (output slots are counted from the flattened pair, whatever the layout)
+        const int64_t k0 = (first + at) / rows.m;
+        const int32_t i0 = (int32_t)((first + at) % rows.m);
+        const int count = (int)std::min<int64_t>(most, pairs - at);
+        const dim3 walks((unsigned)h->walks);
         auto by_rule = [&](auto dp, auto vw) {
             constexpr int DP = decltype(dp)::value, VW = decltype(vw)::value;
-            if (h->uniforms) launch(narrow_walk<DP, VW, true>);
-            else launch(narrow_walk<DP, VW, false>);
+            if (c.band_pairs > 0) {
+                const int blocks = (int)round_up((count + kBandBlock - 1) / kBandBlock, kBandStride);
+                const BandSpace space{h->gram_all, (int64_t)blocks * band_doubles(DP), blocks};
+                hipLaunchKernelGGL((narrow_bands<DP, VW>), dim3((unsigned)((blocks + kWaves - 1) / kWaves), walks.x),
+                                   dim3(kThreads), 0, h->stream, part, k0, i0, count, half_n, space, h->uniforms, h->ws);
+                auto chain = [&](auto kernel) {
+                    hipLaunchKernelGGL(kernel, walks, dim3(kNarrowThreads), 0, h->stream, count, k0, i0, rows.m, rows.d,
+                                       half_n, fresh, space, h->r_sum, r32, r64, signs_out, dots_out, h->ws);
+                };
+                if (h->uniforms) chain(narrow_chain<DP, true>);
+                else chain(narrow_chain<DP, false>);
+                return;
+            }
+            StepRows slots = part;
+            slots.k0 = k0;
+            slots.i0 = i0;
+            auto walk = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, walks, dim3(kNarrowThreads), 0, h->stream, slots, count, half_n,
+                                   fresh, h->r_sum, r32, r64, signs_out, dots_out, h->uniforms, h->ws);
+            };
+            if (h->uniforms) walk(narrow_walk<DP, VW, true>);
+            else walk(narrow_walk<DP, VW, false>);
         };
         const std::integral_constant<int, kAnyRow> any{};
         if (rows.d < 4) by_rule(std::integral_constant<int, 16>{}, std::integral_constant<int, kTiny>{});
@@ -851,6 +907,10 @@ int Epoch::prepare() {
     }
     h->ws = WalkStrides{};
     if (ahead) {
+        // (short rows have a form without workspace: where there is no room, and while the launches are recorded, because
+        // this buffer is replaced when a later call has more pairs)
+        if (chain.band_pairs > 0 && (capturing(h) || !room(h, h->gram_all, h->gram_all_cap, chain.gram_len)))
+            chain.band_pairs = chain.gram_len = 0;
         if (chain.gram_len > 0 && (rc = ensure(h, h->gram_all, h->gram_all_cap, chain.gram_len))) return rc;
         if (chain.parts_len > 0 && (rc = ensure(h, h->gram_parts, h->gram_parts_cap, chain.parts_len))) return rc;
         if (chain.dots_len > 0 && (rc = ensure(h, h->dot_partials, h->dot_partials_cap, chain.dots_len))) return rc;
@@ -938,7 +998,7 @@ int Epoch::chain_ahead() {
         rows.layout = streamed ? kStaged : center_row ? kCentred : kDense;
         if (narrow) {
             // (every launch exports what it has: the last one's stays)
-            if ((rc = run_narrow(h, rows, first, pairs, n / 2, signs_out, dots_out, r_out, r64_out))) return rc;
+            if ((rc = run_narrow(h, rows, first, pairs, n / 2, chain, signs_out, dots_out, r_out, r64_out))) return rc;
             steps_run += (pairs + chain.sp - 1) / chain.sp;
             continue;
         }
@@ -1486,19 +1546,8 @@ int cdgrab_herding_bound(cdgrab_handle *h, int64_t m, int64_t n, int64_t d, cons
     const int form = row_form((d % 4 == 0 && reinterpret_cast<uintptr_t>(z) % 16 == 0) ? 4 : 1, d);
     // where the steps' sums are kept for the second pass (and fit), the rows are read once; not in a launch that is
     // recorded, because their buffer is replaced when a later call has more steps
-    const auto capturing = [&] {
-        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(h->stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
-        (void)hipGetLastError();
-        return true;
-    };
-    const auto room = [&] {  // (no error of the call if there is none)
-        const std::string text = h->err;
-        const bool there = ensure(h, h->herd_steps, h->herd_steps_cap, n * quads * 4) == CDGRAB_OK;
-        if (!there) h->err = text;
-        return there;
-    };
-    const bool keep = m >= kHerdKeepMinWorkers && n <= kHerdKeepBytes / 32 / quads && !capturing() && room();
+    const bool keep = m >= kHerdKeepMinWorkers && n <= kHerdKeepBytes / 32 / quads && !capturing(h) &&
+                      room(h, h->herd_steps, h->herd_steps_cap, n * quads * 4);
     hipLaunchKernelGGL(herding_clear, dim3(1), dim3(1), 0, h->stream, bits);
     auto launch = [&](auto vw_tag) {
         constexpr int VW = decltype(vw_tag)::value;

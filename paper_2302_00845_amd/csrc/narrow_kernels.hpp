@@ -1,4 +1,4 @@
-// Rows of at most 64 elements: a whole walk inside one workgroup.
+// Rows of at most 64 elements: a whole walk inside one workgroup (short walks and many of them; long ones: band_kernels.hpp).
 //
 // With so few elements a block of pairs is a few KB, the running sum is a few hundred bytes, and what
 // a chain of launches spends between its steps is many times the work in them.  So one workgroup

@@ -45,6 +45,63 @@ def test_narrow_rows_match_oracle(lib, m, n, d):
     test_dense_epochs_match_oracle(lib, m, n, d)
 
 
+LONG_NARROW = [  # pairs around multiples of 16 and 128, padded row lengths 16, 32 and 64, rows too short for one load
+    (1, 1024, 1), (2, 514, 2), (1, 1026, 3), (1, 1054, 4), (5, 206, 15), (1, 1280, 16), (3, 342, 17), (1, 1282, 31),
+    (7, 300, 32), (1, 1278, 33), (16, 130, 63), (300, 8, 64),
+]
+
+
+@pytest.mark.parametrize("m,n,d", LONG_NARROW)
+def test_long_narrow_walks_match_oracle(lib, m, n, d):
+    """At least 512 pairs of rows of at most 64 elements: Gram results of sixteen pairs with the next 64 beforehand."""
+    small = lib.cdgrab_plan_epoch(1, 1022, d)["workspace_bytes"]
+    assert lib.cdgrab_plan_epoch(m, n, d)["workspace_bytes"] - small >= m * n // 2 * (512 + 8 * 16)
+    test_dense_epochs_match_oracle(lib, m, n, d)
+    z = torch.from_numpy(workloads.integer_rows(n, m, n, d, 3)).cuda()
+    whole, inside = (lib.cdgrab_balance_epoch(lib.Handle(gram_mode=g), m, n, d, grads=z, want_r64=True, want_dots=True)
+                     for g in (2, 1))
+    assert all(torch.equal(whole[k], inside[k]) for k in ("signs", "perm", "r64", "r32", "dots"))
+
+
+@pytest.mark.parametrize("d", [16, 24, 64])
+def test_more_narrow_pairs_than_are_held_at_a_time(lib, d):
+    """64 MB of results and differences are held: the running sum goes from launch to launch."""
+    m, n = 3, 2 * 36_000 if d < 64 else 2 * 24_000
+    assert m * n // 2 * (512 + 8 * (16 if d == 16 else 32 if d == 24 else 64)) > 64 << 20
+    z = workloads.integer_rows(5, m, n, d, 3)
+    out = lib.cdgrab_balance_epoch(lib.Handle(), m, n, d, grads=torch.from_numpy(z).cuda(), want_r64=True)
+    want = oracle.server_epoch(z, None)
+    assert np.array_equal(out["signs"].cpu().numpy(), want["eps"])
+    assert np.array_equal(out["r64"].cpu().numpy(), want["r"])
+
+
+def test_recorded_narrow_walk(lib):
+    """Recorded launches use none of the workspace that a later, longer epoch replaces."""
+    m, n, d = 2, 1200, 20
+    zi = workloads.integer_rows(3, m, n, d, 3)
+    z, longer = torch.from_numpy(zi).cuda(), torch.randn((m, 4 * n, d), device="cuda")
+    want = oracle.server_epoch(zi, None)
+    s = torch.cuda.Stream()
+    h = lib.Handle(stream=s)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        lib.cdgrab_balance_epoch(h, m, n, d, grads=z)
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        out = lib.cdgrab_balance_epoch(h, m, n, d, grads=z, want_r64=True)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        with torch.cuda.stream(s):
+            lib.cdgrab_balance_epoch(h, m, 4 * n, d, grads=longer)
+        for k in ("signs", "r64"):
+            out[k].zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out["signs"].cpu().numpy(), want["eps"]) and np.array_equal(out["r64"].cpu().numpy(), want["r"])
+
+
 # the steps of these are what the plan says (asserted): full ones, a ragged last one, one or several
 @pytest.mark.parametrize("m,n,d,step", [
     (1, 258, 66, 256), (1, 510, 66, 256), (1, 512, 66, 256), (1, 514, 66, 128), (1, 2050, 70, 256), (7, 220, 130, 256),
@@ -201,6 +258,19 @@ def test_dots_that_are_not_numbers(lib, bits, m, n, d):
     u = torch.rand((m, n // 2), device="cuda")
     out = lib.cdgrab_balance_epoch_randomized(lib.Handle(), zt, u)
     assert (out["signs"].cpu().numpy().T.ravel()[at:] == 1).all() and pairs > at
+
+
+@pytest.mark.parametrize("m,n,d", [(3, 400, 5), (1, 1300, 16), (5, 304, 30), (7, 174, 64)])
+def test_long_narrow_walks_with_values_that_are_not_finite(lib, m, n, d):
+    for bits in (0x7fc00000, 0xffc00000):
+        test_dots_that_are_not_numbers(lib, bits, m, n, d)
+    for value in (np.inf, -np.inf, np.nan):
+        test_value_that_is_not_finite_stays_where_it_is(lib, value, m, n, max(d, 6))
+    test_randomized_rule_over_steps(lib, m, n, d)
+    for draw in (-0.0, np.inf, np.nan):
+        test_randomized_rule_at_its_threshold(lib, m, n, max(d, 16), draw)
+    test_centred_steps_match_oracle(lib, n * m, d)
+    test_walks_side_by_side_equal_single_walks(lib, 16, 1024 + n % 50 // 2 * 2, d)
 
 
 @pytest.mark.parametrize("m,n,d", [(1, 2050, 70), (16, 300, 7850), (3, 500, 16), (2, 130, 40_000), (3, 20, 300)])
