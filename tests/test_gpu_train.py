@@ -208,3 +208,26 @@ def test_argument_errors(lib):
     perm = torch.from_numpy(workloads.random_perms(0, 2, 4)).cuda()
     with pytest.raises(lib.CdgrabError):
         lib.cdgrab_train_softmax(h, X, y, W, perm, 0)                    # no epochs
+
+
+@pytest.mark.parametrize("m,n,in_dim,classes", [(8, 900, 30, 4), (4, 1100, 7, 4), (3, 1500, 783, 3), (16, 260, 12, 5)])
+def test_chunks_balanced_beside_the_next_one(lib, m, n, in_dim, classes):
+    """Two to four chunks, balanced on a second stream while the next is generated (chain of steps, and rows of at most
+    64 elements), against the same epochs with every launch on one stream, which is what a timed handle runs."""
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        handles = [lib.Handle(stream=s), lib.Handle(stream=s, timing=1)]
+        for epoch in range(3):
+            X = torch.rand((m, n, in_dim), generator=g, device="cuda")
+            y = torch.randint(0, classes, (m, n), generator=g, device="cuda", dtype=torch.int32)
+            perm = torch.rand((m, n), generator=g, device="cuda").argsort(1).to(torch.int32)
+            got = []
+            for h in handles:
+                W = torch.zeros((in_dim + 1, classes), device="cuda")
+                v = torch.zeros(W.numel(), device="cuda")
+                out = lib.cdgrab_train_epoch_softmax(h, X, y, W, perm_in=perm, velocity=v, lr=0.05, momentum=0.9)
+                got.append([out["signs"], out["perm"], W, v])
+            del X, y, perm
+            assert all(torch.equal(a, b) for a, b in zip(*got))
+    s.synchronize()
