@@ -561,16 +561,24 @@ int run_step_wide(cdgrab_handle *h, const StepRows &cur, const StepRows &prev, c
     return CDGRAB_OK;
 }
 
-// Serial launch of a step: the walk.  dot_groups 0: the running sum is still zero.
-int run_step_walk(cdgrab_handle *h, const StepRows &cur, const ChainPlan &c, const double *gram, int dot_groups,
-                  int64_t half_n, int8_t *signs_out, double *dots_out) {
+// Workgroups that read the next step's rows beside a walk.  us per epoch without them, with 32, 64, 120: 30 000 pairs of 7850
+// elements 4343 / 4177 / 4198 / 4206; 8000 of 2048 747 / 744 / 745 / 749, of 4096 909 / 875 / 878 / 880; 4096 of 16 384
+// 782 / 824 / 731 / 737, of 32 768 1172 / 1388 / 1085 / 1080; 2048 of 65 536 987 / 1304 / 1023 / 963.
+constexpr int kTouchMinGroups = 16;  // (shorter rows have no fixed XCD per element)
+int touch_workgroups(int64_t d) { return d <= 32768 ? 64 : 120; }
+
+// Serial launch of a step: the walk; the rows of `next` (if it has pairs) are read beside it.  dot_groups 0: the running sum is still zero.
+int run_step_walk(cdgrab_handle *h, const StepRows &cur, const StepRows &next, const ChainPlan &c, const double *gram,
+                  int dot_groups, int64_t half_n, int8_t *signs_out, double *dots_out) {
     MARK(h, 2, kResolve);
+    const int touch = next.nb > 0 && h->walks == 1 && c.groups >= kTouchMinGroups ? touch_workgroups(cur.d) : 0;
+    const RowsAhead ahead{next, c.groups};
     auto by_rule = [&](auto sb) {
         constexpr int SB = decltype(sb)::value;
         auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)h->walks), dim3(kWalkThreads), 0, h->stream, gram,
-                               h->dot_partials, dot_groups, c.sp, cur, half_n, h->eps_blk, signs_out, dots_out,
-                               h->uniforms, h->ws);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)h->walks, touch ? 8u + (unsigned)touch : 1u), dim3(kWalkThreads), 0,
+                               h->stream, gram, h->dot_partials, dot_groups, c.sp, cur, half_n, h->eps_blk, signs_out,
+                               dots_out, h->uniforms, h->ws, ahead);
         };
         if (h->uniforms) launch(chain_walk<SB, true>);
         else launch(chain_walk<SB, false>);
@@ -1077,7 +1085,9 @@ int Epoch::chain_ahead() {
                 // (output slots are counted from the flattened pair, whatever the layout)
                 cur.k0 = (first + at + s * chain.sp) / m;
                 cur.i0 = (int32_t)((first + at + s * chain.sp) % m);
-                if ((rc = run_step_walk(h, cur, chain, h->gram_all + s * chain.tiles * kTileEntries,
+                const int64_t after = (s + 1) * chain.sp;
+                const StepRows next = after < count ? step_at(part, after, (int)std::min<int64_t>(chain.sp, count - after)) : none;
+                if ((rc = run_step_walk(h, cur, next, chain, h->gram_all + s * chain.tiles * kTileEntries,
                                         has_prev ? chain.groups : 0, n / 2, signs_out, dots_out))) return rc;
                 prev_step = cur;
             }
