@@ -245,7 +245,7 @@ def measure_config(name, args, steps, warmup, cpu_seconds):
         if ahead:
             # per step of the chain: its share of the Gram tiles (rows once) and its wide launch (rows of this
             # step and of the previous one, running sum); the walks are resolve_ms.  One launch: all of it
-            per_kernel = (("narrow_walk" if in_one_launch else "gram_tiles+chain_apply_dots",
+            per_kernel = (("narrow walk" if in_one_launch else "gram_tiles+chain_apply_dots",
                            tp["pass1_ms"] + tp["pass2_ms"], step_bytes),)
         elif not fused:
             # algorithmic bytes per launch: both rows of every pair in the block (fp32) plus the

@@ -63,8 +63,9 @@ typedef struct cdgrab_options {
                             pairs are computed ahead in one launch (they depend on the
                             rows only) and the walk is a chain of steps of 64 .. 256 pairs
                             (chosen by sizes, whatever the block size) at two launches each,
-                            or, for rows of at most 64 elements, one launch in which one
-                            workgroup per walk takes 64 pairs at a time; refused (EINVAL) for d > 131 072; 0 = choose (2 for rows up to
+                            or, for rows of at most 64 elements, one workgroup per walk
+                            in one launch (long walks: behind a launch that computes
+                            Gram results of up to 64 MB of pairs ahead); refused (EINVAL) for d > 131 072; 0 = choose (2 for rows up to
                             65 536 elements and more pairs than one block, at 65 536 than
                             128, when apply_mode is 0 as well; staged rows: up to 16 384)  */
     int32_t apply_groups; /* cap on the workgroups of the resident apply kernel; 0 = two per CU */
