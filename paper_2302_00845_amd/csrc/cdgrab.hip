@@ -213,9 +213,10 @@ int pick_ksplit(int64_t tiles, int64_t d, int num_cu) {
 // (narrow_kernels.hpp).  The first has one launch more and walks faster.  us per epoch of one walk, inside -> beforehand, rows of
 // 16 / 32 / 64 elements: 256 pairs 13.4 -> 16.8 / 13.6 -> 17.2 / 19.0 -> 21.7; 384 pairs 16.9 -> 17.0 / 17.2 -> 18.1 /
 // 23.9 -> 24.7; 512 pairs 19.7 -> 17.4 / 20.6 -> 19.6 / 29.9 -> 27.9; 4096 pairs 89 -> 72 / 108 -> 76 / 172 -> 104; 200 000
-// pairs 3846 -> 2943 / 4814 -> 3001 / 7939 -> 4273.  The results of all walks go through memory: of 10 walks of 1000 pairs
-// 30.1 -> 27.9 / - / 49.6 -> 43.5, of 100 30.6 -> 40.1 / - / 51 -> 95.
-constexpr int64_t kBandMinPairs = 512;  // per walk
+// pairs 3846 -> 2943 / 4814 -> 3001 / 7939 -> 4273.  The results of all walks go through memory: 16 walks of 512 pairs 19.7 -> 19.0 /
+// 20.5 -> 22.0 / 28.9 -> 30.4, of 768 24.8 -> 24.3 / 27.0 -> 27.4 / 39.9 -> 38.2, of 1024 29.8 -> 29.2 / 33.2 -> 32.6 / 49.7 ->
+// 45.0, of 4000 88 -> 82 / 107 -> 87 / 170 -> 128; 100 walks of 1000 30.6 -> 40.1 / - / 51 -> 95.
+constexpr int64_t kBandMinPairs = 512, kBandMinPairsMore = 32;  // of the only walk, per further walk
 constexpr int64_t kBandMaxWalks = 16;
 constexpr int64_t kBandBytes = (int64_t)64 << 20;  // Gram results and differences held at a time
 int narrow_padded(int64_t d) { return d <= 16 ? 16 : d <= 32 ? 32 : 64; }
@@ -225,7 +226,7 @@ ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pair
     const int64_t longest = chunk_pairs > 0 ? std::min(chunk_pairs, pairs) : pairs;
     if (d <= kNarrowMaxD) {  // a walk is one workgroup
         c.sp = kTilePairs;
-        if (longest >= kBandMinPairs && walks <= kBandMaxWalks) {
+        if (walks <= kBandMaxWalks && longest >= kBandMinPairs + kBandMinPairsMore * (walks - 1)) {
             const int64_t per_block = band_doubles(narrow_padded(d));
             const int64_t held = std::max<int64_t>(1, kBandBytes / 8 / per_block / walks);
             const int64_t blocks = round_up(std::min<int64_t>((longest + kBandBlock - 1) / kBandBlock, held), kBandStride);

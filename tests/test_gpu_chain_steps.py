@@ -270,7 +270,7 @@ def test_long_narrow_walks_with_values_that_are_not_finite(lib, m, n, d):
     for draw in (-0.0, np.inf, np.nan):
         test_randomized_rule_at_its_threshold(lib, m, n, max(d, 16), draw)
     test_centred_steps_match_oracle(lib, n * m, d)
-    test_walks_side_by_side_equal_single_walks(lib, 16, 1024 + n % 50 // 2 * 2, d)
+    test_walks_side_by_side_equal_single_walks(lib, 16, 1984 + n % 50 // 2 * 2, d)
 
 
 @pytest.mark.parametrize("m,n,d", [(1, 2050, 70), (16, 300, 7850), (3, 500, 16), (2, 130, 40_000), (3, 20, 300)])
