@@ -74,6 +74,8 @@ struct cdgrab_handle {
     double *gram_all = nullptr; int64_t gram_all_cap = 0; // Grams-ahead form: Gram tiles of a batch of steps
     double *gram_parts = nullptr; int64_t gram_parts_cap = 0;      // shares of tiles whose elements are split
     double *dot_partials = nullptr; int64_t dot_partials_cap = 0;  // its per-workgroup dots of one step
+    double *bands = nullptr; int64_t bands_cap = 0;       // rows of at most kNarrowMaxD elements: Gram results and differences
+                                                          // beforehand.  Not gram_all: that one's address is in recorded chains.
     float *staging = nullptr;  int64_t staging_cap = 0;   // floats: two staging chunks (the fused pass reads the previous block too)
     bool fixed_workspace = false;                         // the workspace pointers are borrowed: never grow or free them
 
@@ -174,7 +176,7 @@ struct ChainPlan {
     int ksplit;         // workgroups sharing the elements of a tile
     int groups;         // workgroups of a step's wide launch
     int64_t band_pairs; // rows of at most kNarrowMaxD elements: pairs of a walk whose Gram results are ahead at a time (0: none are)
-    int64_t gram_len, parts_len, dots_len;  // doubles of workspace, all walks
+    int64_t gram_len, parts_len, dots_len, bands_len;  // doubles of workspace, all walks
 };
 
 // Time of one step of sp pairs, microseconds, fitted to measured epochs of 64 / 128 / 256 pairs per step.  Those epochs,
@@ -231,7 +233,7 @@ ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pair
             const int64_t held = std::max<int64_t>(1, kBandBytes / 8 / per_block / walks);
             const int64_t blocks = round_up(std::min<int64_t>((longest + kBandBlock - 1) / kBandBlock, held), kBandStride);
             c.band_pairs = blocks * kBandBlock;
-            c.gram_len = walks * blocks * per_block;
+            c.bands_len = walks * blocks * per_block;
         }
         return c;
     }
@@ -305,7 +307,7 @@ int plan_epoch(int64_t m, int64_t n, int64_t d, int32_t block_pairs, int32_t str
     if (ahead) {
         const ChainPlan c = plan_chain(plan->pairs, d, 1, streamed ? chunk_pairs : 0, num_cu);
         plan->step_pairs = c.sp;
-        ahead_bytes = (c.gram_len + c.parts_len + c.dots_len) * 8 + kMaxStepPairs;
+        ahead_bytes = (c.gram_len + c.parts_len + c.dots_len + c.bands_len) * 8 + kMaxStepPairs;
     }
     plan->workspace_bytes = round_up(d, kPadE) * 8 + partial_doubles * 8 +
                             (int64_t)kReduceSlices * PartLayout<64>::PART * 8 + 64 + ahead_bytes +
@@ -480,7 +482,7 @@ int run_narrow(cdgrab_handle *h, const StepRows &rows, int64_t first, int64_t pa
             constexpr int DP = decltype(dp)::value, VW = decltype(vw)::value;
             if (c.band_pairs > 0) {
                 const int blocks = (int)round_up((count + kBandBlock - 1) / kBandBlock, kBandStride);
-                const BandSpace space{h->gram_all, (int64_t)blocks * band_doubles(DP), blocks};
+                const BandSpace space{h->bands, (int64_t)blocks * band_doubles(DP), blocks};
                 hipLaunchKernelGGL((narrow_bands<DP, VW>), dim3((unsigned)((blocks + kWaves - 1) / kWaves), walks.x),
                                    dim3(kThreads), 0, h->stream, part, k0, i0, count, half_n, space, h->uniforms, h->ws);
                 auto chain = [&](auto kernel) {
@@ -751,6 +753,7 @@ int cdgrab_destroy(cdgrab_handle *h) {
     if (h->gram_all) (void)hipFree(h->gram_all);
     if (h->dot_partials) (void)hipFree(h->dot_partials);
     if (h->gram_parts) (void)hipFree(h->gram_parts);
+    if (h->bands) (void)hipFree(h->bands);
     delete h;
     return CDGRAB_OK;
 }
@@ -926,8 +929,8 @@ int Epoch::prepare() {
     if (ahead) {
         // (short rows have a form without workspace: where there is no room, and while the launches are recorded, because
         // this buffer is replaced when a later call has more pairs)
-        if (chain.band_pairs > 0 && (capturing(h) || !room(h, h->gram_all, h->gram_all_cap, chain.gram_len)))
-            chain.band_pairs = chain.gram_len = 0;
+        if (chain.band_pairs > 0 && (capturing(h) || !room(h, h->bands, h->bands_cap, chain.bands_len)))
+            chain.band_pairs = 0;
         if (chain.gram_len > 0 && (rc = ensure(h, h->gram_all, h->gram_all_cap, chain.gram_len))) return rc;
         if (chain.parts_len > 0 && (rc = ensure(h, h->gram_parts, h->gram_parts_cap, chain.parts_len))) return rc;
         if (chain.dots_len > 0 && (rc = ensure(h, h->dot_partials, h->dot_partials_cap, chain.dots_len))) return rc;

@@ -1,0 +1,143 @@
+"""What the epochs allocate, free, launch and order, seen from the host without a GPU: the calls into the HIP runtime
+are answered by a stand-in, in a process of its own, that launches nothing and prints every call that matters."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+STAND_IN = r"""
+#include <dlfcn.h>
+#include <stdint.h>
+#include <stdio.h>
+typedef struct { uint32_t x, y, z; } dim3;
+typedef unsigned long long u64;
+size_t most_bytes = (size_t)1 << 60;  /* a larger allocation fails */
+int capturing = 0;
+int launches_left = 1 << 30;          /* the launch after these fails, and the following ones do not */
+static int last = 0;
+static uintptr_t next = 1 << 20, handles = 16;
+#define SAY(...) (printf(__VA_ARGS__), fflush(stdout))
+int hipGetDeviceCount(int *n) { *n = 1; return 0; }
+int hipSetDevice(int d) { return 0; }
+int hipGetDevicePropertiesR0600(void *p, int d) { return 101; }  /* the library then assumes 256 CUs */
+int hipMalloc(void **p, size_t bytes) {
+    if (bytes > most_bytes) return 2;
+    *p = (void *)next;
+    SAY("malloc %llx %llu\n", (u64)next, (u64)bytes);
+    next += (bytes + 255) & ~(size_t)255;
+    return 0;
+}
+int hipFree(void *p) { SAY("free %llx\n", (u64)(uintptr_t)p); return 0; }
+int hipStreamSynchronize(void *s) { SAY("sync %llx\n", (u64)(uintptr_t)s); return 0; }
+int hipStreamIsCapturing(void *s, int *status) { *status = capturing; return 0; }
+int hipStreamCreateWithFlags(void **s, unsigned flags) { *s = (void *)(handles += 16); return 0; }
+int hipStreamDestroy(void *s) { return 0; }
+int hipEventCreate(void **e) { *e = (void *)(handles += 16); return 0; }
+int hipEventCreateWithFlags(void **e, unsigned flags) { *e = (void *)(handles += 16); return 0; }
+int hipEventDestroy(void *e) { return 0; }
+int hipEventRecord(void *e, void *s) { SAY("record %llx %llx\n", (u64)(uintptr_t)e, (u64)(uintptr_t)s); return 0; }
+int hipStreamWaitEvent(void *s, void *e, unsigned flags) {
+    SAY("wait %llx %llx\n", (u64)(uintptr_t)e, (u64)(uintptr_t)s);
+    return 0;
+}
+int hipMemcpyAsync(void *to, const void *from, size_t bytes, int kind, void *s) { return 0; }
+int hipGetLastError(void) { int e = last; last = 0; return e; }
+const char *hipGetErrorString(int e) { return "refused"; }
+static struct { dim3 grid, block; size_t lds; void *stream; } config;  /* of the launch in between */
+int __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, void *stream) {
+    config.grid = grid; config.block = block; config.lds = lds; config.stream = stream;
+    return 0;
+}
+int __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, void **stream) {
+    *grid = config.grid; *block = config.block; *lds = config.lds; *stream = config.stream;
+    return 0;
+}
+int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, void *stream) {
+    Dl_info info;
+    if (launches_left-- == 0) { last = 9; return 9; }
+    SAY("launch %s %u %u %llx\n", dladdr(f, &info) && info.dli_sname ? info.dli_sname : "?", grid.x, grid.y,
+        (u64)(uintptr_t)stream);
+    return 0;
+}
+"""
+
+CALLER = r"""
+import ctypes, sys
+hip = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+lib.cdgrab_last_error.restype = ctypes.c_char_p
+i64, ptr, f32 = ctypes.c_int64, ctypes.c_void_p, ctypes.c_float
+class Options(ctypes.Structure):
+    _fields_ = [(k, ptr if k == "stream" else ctypes.c_int32) for k in
+                ("device", "block_pairs", "stream", "timing", "pass1_groups", "apply_mode", "gram_mode", "apply_groups")]
+def handle(**options):
+    h = ptr()
+    assert lib.cdgrab_create(ctypes.byref(h), ctypes.byref(Options(**options))) == 0
+    return h
+h = handle()
+IN, SIGNS, PERM, DOTS, W, V, LABELS = (ptr((1 << 50) + (i << 44)) for i in range(7))  # (no kernel runs)
+def epoch(m, n, d, h=h):
+    return lib.cdgrab_balance_epoch(h, i64(m), i64(n), i64(d), IN, None, None, None, SIGNS, PERM, None, None, DOTS)
+def train(m, n, in_dim, classes, h=h):
+    return lib.cdgrab_train_epoch_softmax(h, i64(m), i64(n), i64(in_dim), i64(classes), IN, LABELS, None, W, None,
+                                          f32(0.1), f32(0), SIGNS, PERM, None, None)
+def text(h=h):
+    return lib.cdgrab_last_error(h).decode()
+def capture(on):
+    ctypes.c_int.in_dll(hip, "capturing").value = on
+def room(nbytes):
+    ctypes.c_size_t.in_dll(hip, "most_bytes").value = nbytes
+def fail_launch(after):
+    ctypes.c_int.in_dll(hip, "launches_left").value = after
+def mark(name):
+    print("#", name, flush=True)
+"""
+
+
+@pytest.fixture(scope="module")
+def call(tmp_path_factory):
+    import paper_2302_00845_amd as pkg
+    if not os.path.exists(pkg.library_path()):
+        from paper_2302_00845_amd import build
+        build.build_library(verbose=False)
+    where = tmp_path_factory.mktemp("hip")
+    src, so = where / "hip.c", where / "hip.so"
+    src.write_text(STAND_IN)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-D_GNU_SOURCE", "-o", str(so), str(src), "-ldl"], check=True)
+
+    def run(code):
+        """The calls (what, arguments ..) of every part of `code` that a mark() opens."""
+        p = subprocess.run([sys.executable, "-c", CALLER + code, str(so), pkg.library_path()], text=True,
+                           capture_output=True, timeout=120)
+        assert p.returncode == 0, p.stderr
+        parts, now = {}, None
+        for line in p.stdout.splitlines():
+            if line.startswith("# "):
+                now = parts.setdefault(line[2:], [])
+            elif now is not None:
+                now.append(tuple(line.split()))
+        return parts
+    return run
+
+
+def of(calls, what):
+    return [c[1:] for c in calls if c[0] == what]
+
+
+def kernels(calls):
+    return [c[0] for c in of(calls, "launch")]
+
+
+def test_long_narrow_epochs_leave_a_recorded_chain_its_buffers(call):
+    """Rows of at most 64 elements have a workspace of their own: a chain of steps that was recorded holds the addresses
+    of its Gram tiles, which an epoch of such rows must neither free nor replace."""
+    parts = call("mark('warm')\nassert epoch(4, 64, 1024) == 0\n"
+                 "capture(1)\nmark('recorded')\nassert epoch(4, 64, 1024) == 0\ncapture(0)\n"
+                 "mark('narrow')\nassert epoch(1, 100_000, 16) == 0\n"
+                 "mark('again')\nassert epoch(4, 64, 1024) == 0\n")
+    assert any("gram_tiles" in k for k in kernels(parts["recorded"])) and not of(parts["recorded"], "malloc")
+    assert any("narrow_chain" in k for k in kernels(parts["narrow"]))
+    had = {address for address, _ in of(parts["warm"], "malloc")}
+    assert had and not had & {address for address, in of(parts["narrow"], "free")}
+    assert not of(parts["again"], "malloc") and not of(parts["again"], "free")

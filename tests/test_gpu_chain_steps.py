@@ -102,6 +102,44 @@ def test_recorded_narrow_walk(lib):
         assert np.array_equal(out["signs"].cpu().numpy(), want["eps"]) and np.array_equal(out["r64"].cpu().numpy(), want["r"])
 
 
+def _recorded(lib, h, s, m, n, d, z):
+    """A graph of one epoch on handle h (which has run that shape before), and the outputs it writes."""
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        out = lib.cdgrab_balance_epoch(h, m, n, d, grads=z, want_r64=True, want_dots=True)
+    torch.cuda.synchronize()
+    return graph, out
+
+
+def _replays_equal(graph, out, want, between):
+    for _ in range(3):
+        between()
+        for k in want:
+            out[k].zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(out[k], want[k]) for k in want)
+
+
+def test_recorded_chain_after_long_narrow_epochs(lib):
+    """Long epochs of rows of at most 64 elements take none of the buffers that a recorded chain of steps holds."""
+    m, n, d = 4, 64, 1024
+    g = torch.Generator(device="cuda").manual_seed(5)
+    z, narrow = torch.randn((m, n, d), generator=g, device="cuda"), torch.randn((1, 100_000, 16), generator=g, device="cuda")
+    s = torch.cuda.Stream()
+    h = lib.Handle(stream=s)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        want = {k: v.clone() for k, v in lib.cdgrab_balance_epoch(h, m, n, d, grads=z, want_r64=True, want_dots=True).items()}
+    graph, out = _recorded(lib, h, s, m, n, d, z)
+
+    def between():
+        with torch.cuda.stream(s):
+            lib.cdgrab_balance_epoch(h, 1, 100_000, 16, grads=narrow)
+    _replays_equal(graph, out, want, between)
+
+
 # the steps of these are what the plan says (asserted): full ones, a ragged last one, one or several
 @pytest.mark.parametrize("m,n,d,step", [
     (1, 258, 66, 256), (1, 510, 66, 256), (1, 512, 66, 256), (1, 514, 66, 128), (1, 2050, 70, 256), (7, 220, 130, 256),
