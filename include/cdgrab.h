@@ -17,7 +17,11 @@
  *     call with a given shape allocates workspace (and may synchronise the stream
  *     to free a smaller one); later calls of cdgrab_pergrad and the balancing
  *     entry points with dense input enqueue kernels and device-to-device copies
- *     only, so they may be captured in a HIP graph.
+ *     only, so they may be captured in a HIP graph.  A captured call takes its sums in the
+ *     order of the eager one; rows of at most 64 elements and 512 pairs or more, if an epoch of that
+ *     shape has run on the handle before (else, and where up to 64 MB of workspace
+ *     find no room, in another order: the same result on exactly representable input, otherwise equal to
+ *     double rounding).
  *   - Return value: CDGRAB_OK (0) or a negative error code.  After an error the
  *     contents of the outputs are undefined; cdgrab_last_error() gives a text.
  *   - Sizes are int64_t counts of elements, never bytes.

@@ -76,6 +76,8 @@ struct cdgrab_handle {
     double *dot_partials = nullptr; int64_t dot_partials_cap = 0;  // its per-workgroup dots of one step
     double *bands = nullptr; int64_t bands_cap = 0;       // rows of at most kNarrowMaxD elements: Gram results and differences
                                                           // beforehand.  Not gram_all: that one's address is in recorded chains.
+    bool bands_in_graphs = false;                         // recorded launches hold its address ...
+    double *bands_kept = nullptr;                         // ... or that of this one, which it has replaced
     float *staging = nullptr;  int64_t staging_cap = 0;   // floats: two staging chunks (the fused pass reads the previous block too)
     bool fixed_workspace = false;                         // the workspace pointers are borrowed: never grow or free them
 
@@ -220,7 +222,8 @@ int pick_ksplit(int64_t tiles, int64_t d, int num_cu) {
 // 45.0, of 4000 88 -> 82 / 107 -> 87 / 170 -> 128; 100 walks of 1000 30.6 -> 40.1 / - / 51 -> 95.
 constexpr int64_t kBandMinPairs = 512, kBandMinPairsMore = 32;  // of the only walk, per further walk
 constexpr int64_t kBandMaxWalks = 16;
-constexpr int64_t kBandBytes = (int64_t)64 << 20;  // Gram results and differences held at a time
+constexpr int64_t kBandBytes = (int64_t)64 << 20;  // Gram results and differences held at a time ...
+constexpr int64_t kBandMost = kBandBytes / 8 + kBandMaxWalks * kBandStride * band_doubles(kNarrowMaxD);  // ... at most, in doubles
 int narrow_padded(int64_t d) { return d <= 16 ? 16 : d <= 32 ? 32 : 64; }
 
 ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pairs, int num_cu) {
@@ -374,6 +377,25 @@ bool capturing(cdgrab_handle *h) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(h->stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
     (void)hipGetLastError();
+    return true;
+}
+
+// `want` doubles for the Gram results of long narrow walks, or false: then they go without.  A recorded call allocates nothing
+// and takes the buffer that an eager one has left.  That buffer is not given back before the handle is; the one that takes its
+// place has room for any epoch, so that there is one such buffer.
+bool bands_room(cdgrab_handle *h, int64_t want) {
+    if (capturing(h)) {
+        if (h->bands_cap < want) return false;
+        h->bands_in_graphs = true;
+        return true;
+    }
+    if (h->bands_cap >= want || !h->bands_in_graphs) return room(h, h->bands, h->bands_cap, want);
+    double *all = nullptr;
+    int64_t cap = 0;
+    if (!room(h, all, cap, kBandMost)) return false;
+    h->bands_kept = h->bands;
+    h->bands = all;
+    h->bands_cap = cap;
     return true;
 }
 
@@ -754,6 +776,7 @@ int cdgrab_destroy(cdgrab_handle *h) {
     if (h->dot_partials) (void)hipFree(h->dot_partials);
     if (h->gram_parts) (void)hipFree(h->gram_parts);
     if (h->bands) (void)hipFree(h->bands);
+    if (h->bands_kept) (void)hipFree(h->bands_kept);
     delete h;
     return CDGRAB_OK;
 }
@@ -927,10 +950,7 @@ int Epoch::prepare() {
     }
     h->ws = WalkStrides{};
     if (ahead) {
-        // (short rows have a form without workspace: where there is no room, and while the launches are recorded, because
-        // this buffer is replaced when a later call has more pairs)
-        if (chain.band_pairs > 0 && (capturing(h) || !room(h, h->bands, h->bands_cap, chain.bands_len)))
-            chain.band_pairs = 0;
+        if (chain.band_pairs > 0 && !bands_room(h, chain.bands_len)) chain.band_pairs = 0;
         if (chain.gram_len > 0 && (rc = ensure(h, h->gram_all, h->gram_all_cap, chain.gram_len))) return rc;
         if (chain.parts_len > 0 && (rc = ensure(h, h->gram_parts, h->gram_parts_cap, chain.parts_len))) return rc;
         if (chain.dots_len > 0 && (rc = ensure(h, h->dot_partials, h->dot_partials_cap, chain.dots_len))) return rc;

@@ -141,3 +141,40 @@ def test_long_narrow_epochs_leave_a_recorded_chain_its_buffers(call):
     had = {address for address, _ in of(parts["warm"], "malloc")}
     assert had and not had & {address for address, in of(parts["narrow"], "free")}
     assert not of(parts["again"], "malloc") and not of(parts["again"], "free")
+
+
+def test_recorded_narrow_epochs_are_those_that_run_eagerly(call):
+    """Same launches, so the same sums in the same order; nothing is allocated, and no buffer that a recorded call was
+    given is freed by a longer epoch, however often those follow."""
+    parts = call("mark('eager')\nassert epoch(2, 1200, 20) == 0\n"
+                 "capture(1)\nmark('recorded')\nassert epoch(2, 1200, 20) == 0\ncapture(0)\n"
+                 "mark('longer')\nassert epoch(2, 4800, 20) == 0\n"
+                 "capture(1)\nmark('recorded longer')\nassert epoch(2, 4800, 20) == 0\ncapture(0)\n"
+                 "mark('longest')\nassert epoch(3, 100_000, 64) == 0 and epoch(1, 400_000, 16) == 0\n"
+                 "mark('destroyed')\nlib.cdgrab_destroy(h)\n")
+    assert kernels(parts["eager"]) == kernels(parts["recorded"])
+    assert kernels(parts["longer"]) == kernels(parts["recorded longer"])
+    assert all(any("narrow_chain" in k for k in kernels(parts[p])) for p in ("recorded", "recorded longer", "longest"))
+    assert not of(parts["recorded"], "malloc") and not of(parts["recorded longer"], "malloc")
+    had = {address for p in ("eager", "longer") for address, _ in of(parts[p], "malloc")}
+    freed = {address for p in ("longer", "recorded longer", "longest") for address, in of(parts[p], "free")}
+    assert had and not had & freed
+    # two buffers at most: the first, and one that holds what any epoch takes
+    big = [int(size) for p in ("longer", "longest") for _, size in of(parts[p], "malloc") if int(size) > 1 << 20]
+    assert len(big) == 1 and big[0] < 68 << 20
+    assert had <= {address for address, in of(parts["destroyed"], "free")}
+
+
+def test_narrow_epochs_where_there_is_no_room(call):
+    """Recorded before the handle has run such a shape, or with no memory for the Gram results: the form without workspace,
+    and no error text."""
+    parts = call("assert epoch(4, 64, 16) == 0\nassert epoch(1, 3, 16) != 0\nbefore = text()\nassert before\n"
+                 "capture(1)\nmark('recorded')\nassert epoch(1, 4000, 16) == 0\ncapture(0)\n"
+                 "room(1 << 20)\nmark('no room')\nassert epoch(1, 4000, 16) == 0\nassert text() == before\n"
+                 "room(1 << 40)\nmark('room')\nassert epoch(1, 4000, 16) == 0\n"
+                 "room(1 << 20)\nmark('no more room')\nassert epoch(1, 40_000, 16) == 0\nassert text() == before\n")
+    form = {p: [k for k in kernels(parts[p]) if "narrow" in k] for p in parts}
+    for p in ("recorded", "no room", "no more room"):
+        assert len(form[p]) == 1 and "narrow_walk" in form[p][0]
+    assert not of(parts["recorded"], "malloc")
+    assert len(form["room"]) == 2 and "narrow_bands" in form["room"][0] and "narrow_chain" in form["room"][1]

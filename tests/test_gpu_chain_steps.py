@@ -140,6 +140,25 @@ def test_recorded_chain_after_long_narrow_epochs(lib):
     _replays_equal(graph, out, want, between)
 
 
+@pytest.mark.parametrize("m,n,d", [(1, 3000, 16), (2, 1200, 20), (1, 2050, 64)])
+def test_recorded_narrow_walk_equals_the_eager_one(lib, m, n, d):
+    """Bit for bit where sums are rounded: a recorded call runs the launches of the eager one, also when longer epochs
+    have come between."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    z, longer = (torch.randn((m, k * n, d), generator=g, device="cuda") for k in (1, 5))
+    s = torch.cuda.Stream()
+    h = lib.Handle(stream=s)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        want = {k: v.clone() for k, v in lib.cdgrab_balance_epoch(h, m, n, d, grads=z, want_r64=True, want_dots=True).items()}
+    graph, out = _recorded(lib, h, s, m, n, d, z)
+
+    def between():
+        with torch.cuda.stream(s):
+            lib.cdgrab_balance_epoch(h, m, 5 * n, d, grads=longer)
+    _replays_equal(graph, out, want, between)
+
+
 # the steps of these are what the plan says (asserted): full ones, a ragged last one, one or several
 @pytest.mark.parametrize("m,n,d,step", [
     (1, 258, 66, 256), (1, 510, 66, 256), (1, 512, 66, 256), (1, 514, 66, 128), (1, 2050, 70, 256), (7, 220, 130, 256),
