@@ -2,28 +2,31 @@
 // whole chip, and a walk streams it in.
 //
 // narrow_bands   for every block of sixteen pairs, minus its Gram results with itself and with the next three blocks, and its
-//                differences in double, into a workspace;
-// narrow_chain   one workgroup per walk, which reads them (the Gram results straight into a ring in LDS):
+//                differences in double, into a workspace, and whether all of its values are finite;
+// walk_window    one workgroup per walk, which reads them (the Gram results straight into a ring in LDS):
 //   wavefront 0     walks.  Its lanes are a window of 64 pairs, a row of sixteen lanes per block: while block b is
 //                   walked, the dots of blocks b + 1 .. b + 3 take its signs too, so that no dot waits for the running
 //                   sum.  Little but a step's three instructions and an LDS read per two steps is issued;
-//   wavefront 1     (and 6, for rows of more than 32) applies block b - 1 to the running sum while b is walked; from the first t on that is not finite (or
-//                   such a draw) it walks the rest itself, pair by pair, after all others are done (without dots once an element of the
-//                   running sum is not a number: 25 000 pairs, the first not a number, 1469 us inside one workgroup, 765 now);
+//   wavefront 1     (and 6, for rows of more than 32) applies block b - 1 to the running sum while b is walked;
 //   wavefront 2     takes the dots of block b + 2 with the running sum that ends before block b - 1;
 //   wavefront 5     writes signs and dots, four blocks at a time;
-//   wavefronts 3, 7 bring in the Gram results.
+//   wavefronts 3, 7 bring in the Gram results;
+//   wavefront 4     looks, before the first block, whether a value of the launch or of the running sum is not finite.  If so, all go
+//                   on in narrow_walk, where only the blocks without a sign to go by are walked twice: an infinity in the
+//                   first of 25 000 pairs of 16 / 32 / 64 elements 521 / 620 / 1031 us, a draw that is no number 614 / 717 /
+//                   1285 (walked pair by pair from there on by wavefront 1: 3819 / 4217 / 4682 and 5727 / 6049 / 6512).
+//                   Finite values have finite dots: 64 products of a sum of 2^63 numbers below 2^129 and such a number.
 // One barrier per block, half way into its walk: what the block before has left in LDS is there by then, so that nothing of
 // it is waited for on the chain.
 //
 // Bound by the serial chain of wavefront 0: a step is 24.6 cycles of its own (three dependent instructions and the wait states
-// between them), 4 more for its share of an LDS read, and a block 2 per step more.  Per 64 pairs of a long epoch 0.94 us at 16
-// elements, 0.96 at 32, 1.37 at 64, where 24 KB per block pass through one CU; 1.23, 1.54 and 2.54 with everything in one
-// workgroup (narrow_kernels.hpp): 500 000 pairs of 16 elements 9657 -> 7411 us.  A check for dots that are not finite in the
-// walk itself cost 40 cycles per block, which is why wavefront 1 has it; a window of 64 pairs is three blocks of slack, one for
+// between them) and 4 more for its share of an LDS read; what a block adds around its barrier is 5 to 6 per step.  Per 64
+// pairs of a long epoch 0.91 us at 16 elements, 0.93 at 32, 1.36 at 64, where 24 KB per block pass through one CU; 1.23, 1.54 and
+// 2.54 with everything in one workgroup (narrow_kernels.hpp): 500 000 pairs of 16 elements 9657 -> 7228 us.  A check for dots
+// that are not finite in the walk itself cost 40 cycles per block; a window of 64 pairs is three blocks of slack, one for
 // each wavefront a sign passes through.
 #pragma once
-#include "narrow_kernels.hpp"
+#include "narrow_common.hpp"
 
 namespace cdgrab {
 
@@ -45,7 +48,13 @@ struct BandSpace {
     template <int DP> __device__ __forceinline__ float *draws(int64_t w) const {
         return reinterpret_cast<float *>(diff(w) + (int64_t)blocks * kBandBlock * DP);
     }
+    // per block: 0 where all of its differences and draws are finite, else 1
+    template <int DP> __device__ __forceinline__ uint8_t *strange(int64_t w) const {
+        return reinterpret_cast<uint8_t *>(draws<DP>(w) + (int64_t)blocks * kBandBlock);
+    }
 };
+// A walk's, in doubles (a multiple of 256 bytes).
+constexpr int64_t band_walk_doubles(int dp, int64_t blocks) { return blocks * band_doubles(dp) + (blocks + 255) / 256 * 32; }
 
 // A wavefront per block.  (k0, i0): where the first pair's outputs and draws are.
 template <int DP, int VW>
@@ -84,11 +93,18 @@ __global__ __launch_bounds__(kThreads) void narrow_bands(StepRows rows, int64_t 
     double *diff = space.diff(w) + (int64_t)c * kBandBlock * DP + ((mrow >> 1) * DP + kslot * PER) * 2 + (mrow & 1);
 #pragma unroll
     for (int q = 0; q < PER; ++q) diff[2 * q] = B[0][q];
+    double rest = 0.0;  // stays zero if all values are finite
+#pragma unroll
+    for (int q = 0; q < PER; ++q) rest = __builtin_fma(B[0][q], 0.0, rest);
     if (uniforms && kslot == 0) {
         const int pair = c * kBandBlock + mrow;
         const uint32_t q = (uint32_t)i0 + (uint32_t)(pair < pairs ? pair : 0), dq = q / (uint32_t)rows.m;
-        space.draws<DP>(w)[pair] = uniforms[(int64_t)(q - dq * (uint32_t)rows.m) * half_n + (k0 + dq)];
+        const float draw = uniforms[(int64_t)(q - dq * (uint32_t)rows.m) * half_n + (k0 + dq)];
+        space.draws<DP>(w)[pair] = draw;
+        rest = __builtin_fma((double)draw, 0.0, rest);
     }
+    const unsigned long long strange = __ballot(rest != 0.0);
+    if (lane == 0) space.strange<DP>(w)[c] = strange ? 1 : 0;
     double *band = space.band(w) + (int64_t)c * kBandDoubles;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -104,40 +120,49 @@ __global__ __launch_bounds__(kThreads) void narrow_bands(StepRows rows, int64_t 
     }
 }
 
-// As narrow_walk: `pairs` consecutive pairs of every walk; the running sum is read from (fresh: starts at zero) and
-// written back to r_sum, and to r32 / r64 where they are not null.
+constexpr int kBandFlight = 8;                  // blocks of Gram results on their way from memory ...
+constexpr int kBandRing = kBandFlight + 4;      // ... of those held
+
 template <int DP, bool RANDOM>
-__global__ __launch_bounds__(kNarrowThreads) void narrow_chain(int pairs, int64_t k0, int32_t i0, int32_t m, int64_t d,
-                                                               int64_t half_n, int fresh, BandSpace space,
-                                                               double *__restrict__ r_sum, float *__restrict__ r32,
-                                                               double *__restrict__ r64, int8_t *__restrict__ signs_out,
-                                                               double *__restrict__ dots_out, WalkStrides ws)
+struct BandArrays {
+    __attribute__((aligned(16))) double ring[kBandRing][kBandDoubles];
+    __attribute__((aligned(16))) double running[4][DP];  // the running sum before block b
+    // of the last blocks, in their own lanes: sign bit: the pair's sign is -1; minus the dot, unless RANDOM
+    __attribute__((aligned(16))) double verdict[2][4][64];
+    double walked[RANDOM ? 2 : 1][4][64];  // RANDOM: minus the dot
+    double start[4][64];      // minus the dots with the running sum three blocks back, in the block's lanes, else 0
+    double draw[4][kBandBlock];
+    int strange;              // not all values of the launch are finite
+};
+
+// Arguments as of narrow_walk, behind its arrays in LDS.  False, and nothing done, if a value of the launch is not finite.
+template <int DP, bool RANDOM>
+__device__ __forceinline__ bool walk_window(double (*ring)[kBandDoubles], double (*running)[DP], double (*verdict)[4][64],
+                                            double (*walked)[4][64], double (*start)[64], double (*draw)[kBandBlock], int *strange,
+                                            const StepRows &rows, int pairs, int64_t half_n, int fresh, const BandSpace &space,
+                                            double *__restrict__ r_sum, float *__restrict__ r32, double *__restrict__ r64,
+                                            int8_t *__restrict__ signs_out, double *__restrict__ dots_out)
 {
     constexpr int NB = kBandBlock;
-    constexpr int FLIGHT = 8;          // blocks of Gram results on their way from memory ...
-    constexpr int RING = FLIGHT + 4;   // ... of those held
+    constexpr int FLIGHT = kBandFlight, RING = kBandRing;
     constexpr int AHEAD = 8, AHEAD_DOTS = DP == 64 ? 4 : 8;  // blocks of differences on their way
     constexpr int SE = DP < 32 ? DP : 32;    // elements of the running sum per wavefront: rows of 64 take two
     static_assert(kBandStride % AHEAD == 0 && kBandStride % AHEAD_DOTS == 0 && kBandStride % 4 == 0, "whole rounds");
     static_assert(RING % 4 == 0, "the window's four blocks have fixed places");
-    __shared__ __attribute__((aligned(16))) double ring[RING][kBandDoubles];
-    __shared__ __attribute__((aligned(16))) double running[4][DP];  // the running sum before block b
-    // of the last blocks, in their own lanes: sign bit: the pair's sign is -1; minus the dot, unless RANDOM
-    __shared__ __attribute__((aligned(16))) double verdict[2][4][64];
-    __shared__ double walked[RANDOM ? 2 : 1][4][64];  // RANDOM: minus the dot
-    __shared__ double start[4][64];      // minus the dots with the running sum three blocks back, in the block's lanes, else 0
-    __shared__ double draw[4][NB];
-    const int64_t w = blockIdx.x;
+    const int64_t w = blockIdx.x, d = rows.d;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int blocks = space.blocks;
-    r_sum += w * ws.r;
-    signs_out += w * ws.out;
-    if (dots_out) dots_out += w * ws.out;
     auto slot_of = [&](int pair) {  // its place in the [m][n/2] arrays
-        const uint32_t q = (uint32_t)i0 + (uint32_t)pair, dq = q / (uint32_t)m;
-        return (int64_t)(q - dq * (uint32_t)m) * half_n + (k0 + dq);
+        const uint32_t q = (uint32_t)rows.i0 + (uint32_t)pair, dq = q / (uint32_t)rows.m;
+        return (int64_t)(q - dq * (uint32_t)rows.m) * half_n + (rows.k0 + dq);
     };
+    auto finite = [&] { return __builtin_amdgcn_readfirstlane(*strange) == 0; };  // (from the first barrier on)
+
+    // LDS reads right after a barrier meet the walker's.  25 000 pairs of 16 / 32 / 64 elements, without -> with these sixteen cycles in
+    // wavefronts 1 and 2: 390 -> 374, 388 -> 380, 548 -> 549 us, randomized 484 -> 471, 486 -> 479, 566 -> 576 (hence not
+    // in 2 there); 64 cycles in wavefront 1, which then comes late to the next barrier, 401 at 16 elements.
+    auto step_aside = [] { asm volatile("s_nop 15"); };
 
     // Barriers of every wavefront: one before the first block, one in each, one after the last.
     if (wave == 0) {
@@ -146,6 +171,7 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_chain(int pairs, int64_
 #pragma unroll
         for (int R = 0; R < 4; ++R) keep[R] = (lane >> 4) == R ? 0.0 : 1.0;
         narrow_barrier();
+        if (!finite()) return false;
 #pragma unroll
         for (int j = 0; j < NB - 2; j += 2) {
             const double2 x = *reinterpret_cast<const double2 *>(&ring[0][j * 64 + 2 * lane]);
@@ -203,20 +229,19 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_chain(int pairs, int64_
             for (int i = 0; i < PP / 2; ++i) v[i] = p[i * DP];
         };
         double r = e < d && !fresh ? r_sum[e] : 0.0;
-        int good = blocks;  // blocks before the first one with a t that has no sign to go by
         if (lane < SE) running[0][e] = r;
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) load(x[i], i);
         narrow_barrier();
+        if (!finite()) return false;
         narrow_barrier();
         for (int b0 = 0; b0 < blocks; b0 += AHEAD)
 #pragma unroll
             for (int i = 0; i < AHEAD; ++i) {
                 const int b = b0 + i;
                 narrow_barrier();
-                const double *block = &verdict[(b >> 2) & 1][b & 3][16 * (b & 3)];
-                const uint32_t *signs = reinterpret_cast<const uint32_t *>(block + first);
-                const double any = block[lane & 15];
+                step_aside();
+                const uint32_t *signs = reinterpret_cast<const uint32_t *>(&verdict[(b >> 2) & 1][b & 3][16 * (b & 3)] + first);
                 double sum[2] = {0.0, 0.0};
 #pragma unroll
                 for (int q = 0; q < PP / 2; ++q) {
@@ -225,67 +250,15 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_chain(int pairs, int64_
                 }
                 double all = sum[0] + sum[1];
                 if (SE == 16) all = sum_across_16(all);
-                all = sum_across_32(all);
-                if (__ballot(!(__builtin_fabs(any) < __builtin_inf())) && b < good) good = b;
-                if (b < good) r += all;  // (uniform)
+                r += sum_across_32(all);
                 if (lane < SE) running[(b + 1) & 3][e] = r;
                 load(x[i], b + AHEAD);
             }
-        auto leave = [&](double sum, int at) {
-            if (at >= d) return;
-            r_sum[at] = sum;
-            if (r32) r32[at] = (float)sum;
-            if (r64) r64[at] = sum;
-        };
-        if (good == blocks) {
-            if (lane < SE) leave(r, e);
-            return;
+        if (lane < SE && e < d) {
+            r_sum[e] = r;
+            if (r32) r32[e] = (float)r;
+            if (r64) r64[e] = r;
         }
-        if (wave == 6) return;
-        // the rest pair by pair, by comparison; the running sum has stayed what it was before block `good`
-        double sum = running[(blocks - 1) & 3][lane % DP];
-        constexpr int HELD = 4;
-        double2 v[HELD][NB / 2];
-        auto fetch = [&](double2 (&to)[NB / 2], int b) {
-            const double2 *p = reinterpret_cast<const double2 *>(space.diff(w) + (int64_t)(b < blocks ? b : blocks - 1) * NB * DP);
-#pragma unroll
-            for (int i = 0; i < NB / 2; ++i) to[i] = p[i * DP + lane % DP];
-        };
-#pragma unroll
-        for (int q = 0; q < HELD; ++q) fetch(v[q], good / HELD * HELD + q);
-        for (int b0 = good / HELD * HELD; b0 < blocks; b0 += HELD)
-#pragma unroll
-            for (int q = 0; q < HELD; ++q) {
-                const int b = b0 + q;
-                auto difference = [&](int j) { return j & 1 ? v[q][j / 2].y : v[q][j / 2].x; };
-                if (b >= good && __ballot(sum != sum)) {  // every further dot is not a number: no rule to wait for
-                    const bool plus = RANDOM;
-#pragma unroll
-                    for (int j = 0; j < NB; ++j) sum += plus ? difference(j) : -difference(j);
-                    if (lane < NB && b * NB + lane < pairs) {
-                        const int64_t slot = slot_of(b * NB + lane);
-                        signs_out[slot] = plus ? 1 : -1;
-                        if (dots_out) dots_out[slot] = __builtin_nan("");
-                    }
-                } else if (b >= good) {
-#pragma unroll
-                    for (int j = 0; j < NB; ++j) {
-                        const double dv = difference(j);
-                        double t = dpp_add<0x140>(sum_of_eight(sum * dv));  // row_mirror: the other eight of sixteen
-                        if (DP >= 32) t = sum_across_16(t);
-                        if (DP == 64) t = sum_across_32(t);
-                        const bool plus = RANDOM ? !((double)space.draws<DP>(w)[b * NB + j] < 0.5 * (1.0 + t)) : t <= 0.0;
-                        sum += plus ? dv : -dv;
-                        if (lane == 0 && b * NB + j < pairs) {
-                            const int64_t slot = slot_of(b * NB + j);
-                            signs_out[slot] = plus ? 1 : -1;
-                            if (dots_out) dots_out[slot] = t;
-                        }
-                    }
-                }
-                fetch(v[q], b + HELD);
-            }
-        if (lane < DP) leave(sum, lane);
     } else if (wave == 2) {
         constexpr int PE = DP / 8;  // elements per lane: lane (two pairs, part of the elements)
         const int two = lane & 7, part = lane >> 3, pair = 2 * two + (part & 1);  // (the pair whose dot it ends with)
@@ -323,11 +296,13 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_chain(int pairs, int64_
         load(0, AHEAD_DOTS);
         load(1, AHEAD_DOTS + 1);
         narrow_barrier();
+        if (!finite()) return false;
         for (int b0 = 0; b0 < blocks; b0 += AHEAD_DOTS)
 #pragma unroll
             for (int i = 0; i < AHEAD_DOTS; ++i) {
                 const int b = b0 + i;
                 narrow_barrier();
+                if (DP < 64) step_aside();
                 const double2 *src = reinterpret_cast<const double2 *>(&running[b > 0 ? (b - 1) & 3 : 0][part * PE]);
 #pragma unroll
                 for (int q = 0; q < PE / 2; ++q) {
@@ -341,22 +316,19 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_chain(int pairs, int64_
         narrow_barrier();
     } else if (wave == 5) {
         narrow_barrier();
+        if (!finite()) return false;
         narrow_barrier();
-        bool good = true;
         for (int b = 0; b < blocks; ++b) {
             narrow_barrier();
             if ((b & 3) != 3) continue;
             const int group = (b >> 2) & 1, kk = (b - 3) * NB + lane;
-            const int64_t slot = slot_of(kk);
             const double v = verdict[group][lane >> 4][lane];
             const double u = RANDOM ? walked[RANDOM ? group : 0][lane >> 4][lane] : v;
-            // (from the first block on that has no sign to go by, wavefront 1 writes them)
-            const unsigned long long bad = __ballot(!(__builtin_fabs(v) < __builtin_inf()));
-            if (kk < pairs && good && (bad == 0 || (lane >> 4) < (__builtin_ctzll(bad) >> 4))) {
+            if (kk < pairs) {
+                const int64_t slot = slot_of(kk);
                 signs_out[slot] = __double2hiint(v) < 0 ? -1 : 1;
                 if (dots_out) dots_out[slot] = 0.0 - u;
             }
-            good = good && bad == 0;
         }
     } else if (wave == 3 || wave == 7) {
         constexpr int LOADS = kBandDoubles / 2 / 128;  // of 1 KB each, per block and wavefront
@@ -379,6 +351,7 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_chain(int pairs, int64_
         for (int b = 0; b < FLIGHT + 3; ++b) issue(b);
         arrived();
         narrow_barrier();
+        if (!finite()) return false;
         for (int b = 0; b < blocks; ++b) {
             narrow_barrier();
             issue(b + FLIGHT + 3);
@@ -386,7 +359,27 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_chain(int pairs, int64_
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         narrow_barrier();
+    } else {
+        if (wave == 4) {
+            const double sum = !fresh && lane < d ? r_sum[lane] : 0.0;
+            const uint64_t *flags = reinterpret_cast<const uint64_t *>(space.strange<DP>(w));  // of eight blocks each
+            static_assert(kBandStride % 8 == 0, "whole words");
+            constexpr int HELD = 8;
+            uint64_t any = !(__builtin_fabs(sum) < __builtin_inf()) ? 1 : 0;
+            for (int at = lane; at < blocks / 8; at += 64 * HELD) {
+                uint64_t x[HELD];
+#pragma unroll
+                for (int q = 0; q < HELD; ++q) x[q] = flags[at + 64 * q < blocks / 8 ? at + 64 * q : at];
+#pragma unroll
+                for (int q = 0; q < HELD; ++q) any |= x[q];
+            }
+            const unsigned long long found = __ballot(any != 0);
+            if (lane == 0) *strange = found ? 1 : 0;
+        }
+        narrow_barrier();
+        return finite();
     }
+    return true;
 }
 
 }  // namespace cdgrab

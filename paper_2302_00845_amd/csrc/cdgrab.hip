@@ -216,14 +216,15 @@ int pick_ksplit(int64_t tiles, int64_t d, int num_cu) {
 // Rows of at most kNarrowMaxD elements: Gram results beforehand (band_kernels.hpp) or inside the walk's workgroup
 // (narrow_kernels.hpp).  The first has one launch more and walks faster.  us per epoch of one walk, inside -> beforehand, rows of
 // 16 / 32 / 64 elements: 256 pairs 13.4 -> 16.8 / 13.6 -> 17.2 / 19.0 -> 21.7; 384 pairs 16.9 -> 17.0 / 17.2 -> 18.1 /
-// 23.9 -> 24.7; 512 pairs 19.7 -> 17.4 / 20.6 -> 19.6 / 29.9 -> 27.9; 4096 pairs 89 -> 72 / 108 -> 76 / 172 -> 104; 200 000
-// pairs 3846 -> 2943 / 4814 -> 3001 / 7939 -> 4273.  The results of all walks go through memory: 16 walks of 512 pairs 19.7 -> 19.0 /
+// 23.9 -> 24.7; 512 pairs 19.7 -> 17.4 / 20.6 -> 19.6 / 29.9 -> 27.9; 4096 pairs 89 -> 71 / 108 -> 75 / 172 -> 107; 200 000
+// pairs 3846 -> 2861 / 4814 -> 2925 / 7939 -> 4276.  The results of all walks go through memory: 16 walks of 512 pairs 19.7 -> 19.0 /
 // 20.5 -> 22.0 / 28.9 -> 30.4, of 768 24.8 -> 24.3 / 27.0 -> 27.4 / 39.9 -> 38.2, of 1024 29.8 -> 29.2 / 33.2 -> 32.6 / 49.7 ->
 // 45.0, of 4000 88 -> 82 / 107 -> 87 / 170 -> 128; 100 walks of 1000 30.6 -> 40.1 / - / 51 -> 95.
 constexpr int64_t kBandMinPairs = 512, kBandMinPairsMore = 32;  // of the only walk, per further walk
 constexpr int64_t kBandMaxWalks = 16;
 constexpr int64_t kBandBytes = (int64_t)64 << 20;  // Gram results and differences held at a time ...
-constexpr int64_t kBandMost = kBandBytes / 8 + kBandMaxWalks * kBandStride * band_doubles(kNarrowMaxD);  // ... at most, in doubles
+// ... at most, in doubles
+constexpr int64_t kBandMost = kBandBytes / 8 + kBandMaxWalks * (kBandStride + 1) * band_doubles(kNarrowMaxD);
 int narrow_padded(int64_t d) { return d <= 16 ? 16 : d <= 32 ? 32 : 64; }
 
 ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pairs, int num_cu) {
@@ -236,7 +237,7 @@ ChainPlan plan_chain(int64_t pairs, int64_t d, int64_t walks, int64_t chunk_pair
             const int64_t held = std::max<int64_t>(1, kBandBytes / 8 / per_block / walks);
             const int64_t blocks = round_up(std::min<int64_t>((longest + kBandBlock - 1) / kBandBlock, held), kBandStride);
             c.band_pairs = blocks * kBandBlock;
-            c.bands_len = walks * blocks * per_block;
+            c.bands_len = walks * band_walk_doubles(narrow_padded(d), blocks);
         }
         return c;
     }
@@ -495,35 +496,29 @@ int run_narrow(cdgrab_handle *h, const StepRows &rows, int64_t first, int64_t pa
     for (int64_t at = 0; at < pairs; at += most) {
         const int fresh = first + at == 0;
         const StepRows part = step_at(rows, at, 0);
-        // (output slots are counted from the flattened pair, whatever the layout)
-        const int64_t k0 = (first + at) / rows.m;
-        const int32_t i0 = (int32_t)((first + at) % rows.m);
+        StepRows slots = part;  // (output slots are counted from the flattened pair, whatever the layout)
+        slots.k0 = (first + at) / rows.m;
+        slots.i0 = (int32_t)((first + at) % rows.m);
         const int count = (int)std::min<int64_t>(most, pairs - at);
         const dim3 walks((unsigned)h->walks);
         auto by_rule = [&](auto dp, auto vw) {
             constexpr int DP = decltype(dp)::value, VW = decltype(vw)::value;
+            BandSpace space{};
+            auto walk = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, walks, dim3(kNarrowThreads), 0, h->stream, slots, count, half_n, fresh, space,
+                                   h->r_sum, r32, r64, signs_out, dots_out, h->uniforms, h->ws);
+            };
             if (c.band_pairs > 0) {
                 const int blocks = (int)round_up((count + kBandBlock - 1) / kBandBlock, kBandStride);
-                const BandSpace space{h->bands, (int64_t)blocks * band_doubles(DP), blocks};
+                space = BandSpace{h->bands, band_walk_doubles(DP, blocks), blocks};
                 hipLaunchKernelGGL((narrow_bands<DP, VW>), dim3((unsigned)((blocks + kWaves - 1) / kWaves), walks.x),
-                                   dim3(kThreads), 0, h->stream, part, k0, i0, count, half_n, space, h->uniforms, h->ws);
-                auto chain = [&](auto kernel) {
-                    hipLaunchKernelGGL(kernel, walks, dim3(kNarrowThreads), 0, h->stream, count, k0, i0, rows.m, rows.d,
-                                       half_n, fresh, space, h->r_sum, r32, r64, signs_out, dots_out, h->ws);
-                };
-                if (h->uniforms) chain(narrow_chain<DP, true>);
-                else chain(narrow_chain<DP, false>);
-                return;
+                                   dim3(kThreads), 0, h->stream, part, slots.k0, slots.i0, count, half_n, space, h->uniforms, h->ws);
+                if (h->uniforms) walk(narrow_walk<DP, VW, true, true>);
+                else walk(narrow_walk<DP, VW, false, true>);
+            } else {
+                if (h->uniforms) walk(narrow_walk<DP, VW, true, false>);
+                else walk(narrow_walk<DP, VW, false, false>);
             }
-            StepRows slots = part;
-            slots.k0 = k0;
-            slots.i0 = i0;
-            auto walk = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, walks, dim3(kNarrowThreads), 0, h->stream, slots, count, half_n,
-                                   fresh, h->r_sum, r32, r64, signs_out, dots_out, h->uniforms, h->ws);
-            };
-            if (h->uniforms) walk(narrow_walk<DP, VW, true>);
-            else walk(narrow_walk<DP, VW, false>);
         };
         const std::integral_constant<int, kAnyRow> any{};
         if (rows.d < 4) by_rule(std::integral_constant<int, 16>{}, std::integral_constant<int, kTiny>{});

@@ -19,45 +19,9 @@
 // applies them, and two walking wavefronts taking turns: 1.16 us at 16 elements, but 1.9 at 32 and 3.0 at 64.
 // The next block's dots kept up to date by the walk itself, for which it needs twice the Gram results: 1.56 us at 16.
 #pragma once
-#include "chain_kernels.hpp"
+#include "band_kernels.hpp"
 
 namespace cdgrab {
-
-constexpr int kNarrowMaxD = 64;
-constexpr int kNarrowThreads = 512;
-constexpr int64_t kNarrowMaxPairs = (int64_t)1 << 30; // per launch and walk
-
-// Sums over lanes that differ in bit 0, 1 or 2 (DPP), or in bit 4 or 5 (row swaps), left in every
-// lane: a few cycles each, where a shuffle through LDS costs about a hundred.
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double x) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
-    return x + __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double sum_of_eight(double x) {
-    x = dpp_add<0xB1>(x);   // quad_perm 1 0 3 2
-    x = dpp_add<0x4E>(x);   // quad_perm 2 3 0 1
-    return dpp_add<0x141>(x);  // row_half_mirror: the other four of eight
-}
-__device__ __forceinline__ double sum_across_16(double x) {
-    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
-    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
-__device__ __forceinline__ double sum_across_32(double x) {
-    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
-    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
-
-// A barrier of the workgroup: what this wavefront has written to LDS is there, and what it has read from LDS is
-// in registers, before it passes; rows on their way from memory stay on their way.
-__device__ __forceinline__ void narrow_barrier() {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
 
 // p += x * (r of lane Q of the same row of sixteen lanes).  FIRST: r may be the result of the instruction before
 // (a DPP operand needs two wait states).
@@ -67,38 +31,67 @@ __device__ __forceinline__ void fma_row_lane(double &p, double r, double x, bool
     else asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+&v"(p) : "v"(r), "v"(x), "n"(Q));
 }
 
+constexpr int kNarrowAhead = 4;           // a block's differences come this many blocks before its walk
+
+template <int DP, bool RANDOM>
+struct NarrowArrays {
+    // Blocks of 64 pairs spend less between walks, of 32 fewer Gram results per pair: six 16 x 16 ones per 64 pairs
+    // instead of ten, of which three SIMDs take DP / 4 MFMAs each.
+    static constexpr int NB = DP == 16 ? 64 : 32;
+    static constexpr int DS = DP + 2;     // doubles per difference row in LDS (sixteen rows: distinct banks)
+    static constexpr int GS = NB + 2;
+    static constexpr int RING = kNarrowAhead + 1;  // blocks b .. b + kNarrowAhead are held
+    __attribute__((aligned(16))) double diff[RING][NB * DS];
+    double G[3][NB * GS];                 // minus the Gram matrices of blocks b .. b + 2; zero on and below the diagonal
+    double walked[2][NB];                 // minus the dots of the block just walked
+    float draw[RANDOM ? RING : 1][NB];
+    unsigned long long votes[2];          // ... and its signs
+};
+
 // DP: padded row length (16, 32 or 64).  `pairs` consecutive pairs of every walk, the first at
 // rows; the running sum is read from (fresh: starts at zero) and written back to r_sum, and to r32 / r64
-// where they are not null.
-template <int DP, int VW, bool RANDOM>
-__global__ __launch_bounds__(kNarrowThreads) void narrow_walk(StepRows rows, int pairs, int64_t half_n, int fresh,
+// where they are not null.  BANDS: narrow_bands has filled `space`, walk_window takes all of them, and this walk is for launches with
+// a value that is not finite.
+template <int DP, int VW, bool RANDOM, bool BANDS>
+__global__ __launch_bounds__(kNarrowThreads) void narrow_walk(StepRows rows, int pairs, int64_t half_n, int fresh, BandSpace space,
                                                               double *__restrict__ r_sum, float *__restrict__ r32,
                                                               double *__restrict__ r64,
                                                               int8_t *__restrict__ signs_out,
                                                               double *__restrict__ dots_out,
                                                               const float *__restrict__ uniforms, WalkStrides ws)
 {
-    // Blocks of 64 pairs spend less between walks, of 32 fewer Gram results per pair: six 16 x 16 ones per 64 pairs
-    // instead of ten, of which three SIMDs take DP / 4 MFMAs each.
-    constexpr int NB = DP == 16 ? 64 : 32;
-    constexpr int DS = DP + 2;            // doubles per difference row in LDS (sixteen rows: distinct banks)
-    constexpr int GS = NB + 2;
+    constexpr int NB = NarrowArrays<DP, RANDOM>::NB, DS = NarrowArrays<DP, RANDOM>::DS, GS = NarrowArrays<DP, RANDOM>::GS;
+    constexpr int AHEAD = kNarrowAhead, RING = NarrowArrays<DP, RANDOM>::RING;
     constexpr int QUADS = DP / 4;
     constexpr int LOADERS = 256;          // threads that bring in rows, PER items of (pair, four elements) each
     constexpr int PER = NB * QUADS / LOADERS;
-    constexpr int AHEAD = 4;              // a block's differences come this many blocks before its walk
-    constexpr int RING = AHEAD + 1;       // blocks b .. b + AHEAD are held
     constexpr int FLIGHT = 4;             // blocks of loads in flight
-    __shared__ __attribute__((aligned(16))) double diff[RING][NB * DS];
-    __shared__ double G[3][NB * GS];      // minus the Gram matrices of blocks b .. b + 2; zero on and below the diagonal
-    __shared__ double walked[2][NB];      // minus the dots of the block just walked
-    __shared__ float draw[RANDOM ? RING : 1][NB];
-    __shared__ unsigned long long votes[2];  // ... and its signs
+    using Arrays = NarrowArrays<DP, RANDOM>;
+    // (arrays of their own where there is no window: members of one variable could be each other's neighbours to the compiler, 2 - 4 %)
+    __shared__ __attribute__((aligned(16))) double own_diff[RING][NB * DS];
+    __shared__ double own_G[3][NB * GS];
+    __shared__ double own_walked[2][NB];
+    __shared__ float own_draw[RANDOM ? RING : 1][NB];
+    __shared__ unsigned long long own_votes[2];
+    __shared__ union { BandArrays<DP, RANDOM> window; Arrays inside; } shared;
+    auto &diff = *[&] { if constexpr (BANDS) return &shared.inside.diff; else return &own_diff; }();
+    auto &G = *[&] { if constexpr (BANDS) return &shared.inside.G; else return &own_G; }();
+    auto &walked = *[&] { if constexpr (BANDS) return &shared.inside.walked; else return &own_walked; }();
+    auto &draw = *[&] { if constexpr (BANDS) return &shared.inside.draw; else return &own_draw; }();
+    auto &votes = *[&] { if constexpr (BANDS) return &shared.inside.votes; else return &own_votes; }();
     const int64_t w = blockIdx.x;
     rows.base += w * ws.rows;
     r_sum += w * ws.r;
     signs_out += w * ws.out;
     if (dots_out) dots_out += w * ws.out;
+    if constexpr (BANDS) {
+        auto &s = shared.window;
+        if (walk_window<DP, RANDOM>(s.ring, s.running, s.verdict, s.walked, s.start, s.draw, &s.strange, rows, pairs, half_n,
+                                    fresh, space, r_sum, r32, r64, signs_out, dots_out)) return;
+        // what is on its way to LDS has to be there before the place is used again
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        narrow_barrier();
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t d = rows.d;
@@ -197,7 +190,11 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_walk(StepRows rows, int
             if (__ballot(u != u || (RANDOM && !isfinite(dr)))) {
                 u = u0;
                 r = r0;
-                for (int j = 0; j < NB; ++j) {
+                if (BANDS && __ballot(r != r)) {  // every dot from here on is not a number: no rule to wait for
+                    const uint32_t flip = RANDOM ? 0u : 0x80000000u;
+#pragma unroll 8
+                    for (int j = 0; j < NB; ++j) r += sign_flipped_by(here[j * DS], flip);
+                } else for (int j = 0; j < NB; ++j) {
                     const uint32_t flip = vote(j);
                     u += sign_flipped_by(G[b % 3][j * GS + k], flip);
                     r += sign_flipped_by(here[j * DS], flip);

@@ -1,6 +1,7 @@
 """What the epochs allocate, free, launch and order, seen from the host without a GPU: the calls into the HIP runtime
 are answered by a stand-in, in a process of its own, that launches nothing and prints every call that matters."""
 import os
+import re
 import subprocess
 import sys
 
@@ -129,6 +130,11 @@ def kernels(calls):
     return [c[0] for c in of(calls, "launch")]
 
 
+def walks_of(calls):
+    """Per launch that walks rows of at most 64 elements: are its Gram results beforehand (its last template argument)?"""
+    return [re.search(r"narrow_walkI(?:L[ib]\d+E)*Lb([01])EEE", k).group(1) == "1" for k in kernels(calls) if "narrow_walk" in k]
+
+
 def test_long_narrow_epochs_leave_a_recorded_chain_its_buffers(call):
     """Rows of at most 64 elements have a workspace of their own: a chain of steps that was recorded holds the addresses
     of its Gram tiles, which an epoch of such rows must neither free nor replace."""
@@ -137,7 +143,7 @@ def test_long_narrow_epochs_leave_a_recorded_chain_its_buffers(call):
                  "mark('narrow')\nassert epoch(1, 100_000, 16) == 0\n"
                  "mark('again')\nassert epoch(4, 64, 1024) == 0\n")
     assert any("gram_tiles" in k for k in kernels(parts["recorded"])) and not of(parts["recorded"], "malloc")
-    assert any("narrow_chain" in k for k in kernels(parts["narrow"]))
+    assert walks_of(parts["narrow"]) == [True]
     had = {address for address, _ in of(parts["warm"], "malloc")}
     assert had and not had & {address for address, in of(parts["narrow"], "free")}
     assert not of(parts["again"], "malloc") and not of(parts["again"], "free")
@@ -154,7 +160,7 @@ def test_recorded_narrow_epochs_are_those_that_run_eagerly(call):
                  "mark('destroyed')\nlib.cdgrab_destroy(h)\n")
     assert kernels(parts["eager"]) == kernels(parts["recorded"])
     assert kernels(parts["longer"]) == kernels(parts["recorded longer"])
-    assert all(any("narrow_chain" in k for k in kernels(parts[p])) for p in ("recorded", "recorded longer", "longest"))
+    assert all(walks_of(parts[p]) and all(walks_of(parts[p])) for p in ("recorded", "recorded longer", "longest"))
     assert not of(parts["recorded"], "malloc") and not of(parts["recorded longer"], "malloc")
     had = {address for p in ("eager", "longer") for address, _ in of(parts[p], "malloc")}
     freed = {address for p in ("longer", "recorded longer", "longest") for address, in of(parts[p], "free")}
@@ -173,8 +179,7 @@ def test_narrow_epochs_where_there_is_no_room(call):
                  "room(1 << 20)\nmark('no room')\nassert epoch(1, 4000, 16) == 0\nassert text() == before\n"
                  "room(1 << 40)\nmark('room')\nassert epoch(1, 4000, 16) == 0\n"
                  "room(1 << 20)\nmark('no more room')\nassert epoch(1, 40_000, 16) == 0\nassert text() == before\n")
-    form = {p: [k for k in kernels(parts[p]) if "narrow" in k] for p in parts}
     for p in ("recorded", "no room", "no more room"):
-        assert len(form[p]) == 1 and "narrow_walk" in form[p][0]
+        assert walks_of(parts[p]) == [False] and not any("narrow_bands" in k for k in kernels(parts[p]))
     assert not of(parts["recorded"], "malloc")
-    assert len(form["room"]) == 2 and "narrow_bands" in form["room"][0] and "narrow_chain" in form["room"][1]
+    assert walks_of(parts["room"]) == [True] and sum("narrow_bands" in k for k in kernels(parts["room"])) == 1
