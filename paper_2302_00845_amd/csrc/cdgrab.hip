@@ -581,22 +581,31 @@ int run_step_wide(cdgrab_handle *h, const StepRows &cur, const StepRows &prev, c
     return CDGRAB_OK;
 }
 
-// Workgroups that read the next step's rows beside a walk.  us per epoch without them, with 32, 64, 120: 30 000 pairs of 7850
-// elements 4343 / 4177 / 4198 / 4206; 8000 of 2048 747 / 744 / 745 / 749, of 4096 909 / 875 / 878 / 880; 4096 of 16 384
-// 782 / 824 / 731 / 737, of 32 768 1172 / 1388 / 1085 / 1080; 2048 of 65 536 987 / 1304 / 1023 / 963.
+// Workgroups that read the next step's rows beside a walk, if those are well below what the L2s hold (32 MB).  us per
+// epoch without them, with 32, 64, 120: 30 000 pairs of 7850 elements 4343 / 4177 / 4198 / 4206; 8000 of 2048 747 / 744 / 745 /
+// 749, of 4096 909 / 875 / 878 / 880; 4096 of 16 384 782 / 824 / 731 / 737, of 32 768 1172 / 1388 / 1085 / 1080.  Without,
+// with 64, 120 on both sides of the line, 300 and 2048 pairs: 32 768 elements (a step is 17 MB) 103.8 / 101.6 / 102.9 and
+// 580 / 543 / 543; 36 864 117.1 / 116.5 / 118.4 and 678 / 640 / 649; 20 000, where the 2048 pairs are in steps of 128,
+// 91.2 / 90.3 / 91.4 and 461 / 449 / 452; 40 960 118.0 / 119.2 / 121.0 and 696 / 669 / 680; 49 152
+// 125.6 / 129.8 / 130.2 and 743 / 791 / 739; 57 344 149.6 / 154.9 / 156.4 and 877 / 920 / 884; 65 533 160.1 / 169.3 / 170.4 and
+// 964 / 1020 / 967; 65 536 158.3 / 165.8 / 167.0 and 963 / 997 / 944; 131 072 with 120, 2048 pairs 1740 / - / 1750.
 constexpr int kTouchMinGroups = 16;  // (shorter rows have no fixed XCD per element)
-int touch_workgroups(int64_t d) { return d <= 32768 ? 64 : 120; }
+constexpr int64_t kTouchBytes = (int64_t)20 << 20;
+constexpr unsigned kTouchWorkgroups = 64;
+bool touch_next(const StepRows &next, const ChainPlan &c, int64_t walks) {
+    return next.nb > 0 && walks == 1 && c.groups >= kTouchMinGroups && 2 * c.sp * next.d * 4 < kTouchBytes;
+}
 
 // Serial launch of a step: the walk; the rows of `next` (if it has pairs) are read beside it.  dot_groups 0: the running sum is still zero.
 int run_step_walk(cdgrab_handle *h, const StepRows &cur, const StepRows &next, const ChainPlan &c, const double *gram,
                   int dot_groups, int64_t half_n, int8_t *signs_out, double *dots_out) {
     MARK(h, 2, kResolve);
-    const int touch = next.nb > 0 && h->walks == 1 && c.groups >= kTouchMinGroups ? touch_workgroups(cur.d) : 0;
+    const unsigned beside = touch_next(next, c, h->walks) ? 8 + kTouchWorkgroups : 1;
     const RowsAhead ahead{next, c.groups};
     auto by_rule = [&](auto sb) {
         constexpr int SB = decltype(sb)::value;
         auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)h->walks, touch ? 8u + (unsigned)touch : 1u), dim3(kWalkThreads), 0,
+            hipLaunchKernelGGL(kernel, dim3((unsigned)h->walks, beside), dim3(kWalkThreads), 0,
                                h->stream, gram, h->dot_partials, dot_groups, c.sp, cur, half_n, h->eps_blk, signs_out,
                                dots_out, h->uniforms, h->ws, ahead);
         };

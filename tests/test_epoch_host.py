@@ -183,3 +183,16 @@ def test_narrow_epochs_where_there_is_no_room(call):
         assert walks_of(parts[p]) == [False] and not any("narrow_bands" in k for k in kernels(parts[p]))
     assert not of(parts["recorded"], "malloc")
     assert walks_of(parts["room"]) == [True] and sum("narrow_bands" in k for k in kernels(parts["room"])) == 1
+
+
+@pytest.mark.parametrize("m,n,d,beside", [
+    (16, 300, 7850, True), (1, 600, 32_768, True), (1, 600, 40_959, True), (1, 600, 40_960, False),
+    (1, 4096, 20_000, True), (1, 600, 49_152, False),
+    (1, 4096, 65_536, False), (1, 600, 65_540, False), (1, 600, 131_072, False), (1, 600, 900, False),
+])
+def test_rows_read_beside_a_walk(call, m, n, d, beside):
+    """The next step's rows are read beside a walk where they fit the L2s; the last step has none after it."""
+    part = call("h = handle(gram_mode=2)\nmark('epoch')\nassert epoch(%d, %d, %d, h) == 0\n" % (m, n, d))["epoch"]
+    grids = [int(y) for name, _, y, _ in of(part, "launch") if "chain_walk" in name]
+    assert len(grids) > 1 and grids[-1] == 1
+    assert all((y > 8) == beside for y in grids[:-1])
