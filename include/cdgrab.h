@@ -12,16 +12,18 @@
  *     input and output buffer; inputs are never modified.  The handle owns its
  *     workspace (running sum, partial results, staging block).
  *   - Work is enqueued on the handle's HIP stream; a call returns once the work
- *     is enqueued unless stated otherwise.  The caller synchronises the stream
+ *     is enqueued unless stated otherwise.  (The training entry points also use a second
+ *     stream, which the handle owns: they order it behind what was enqueued before them
+ *     and before whatever is enqueued after them.)  The caller synchronises the stream
  *     before reading outputs.  Calls on one handle must not overlap.  The first
  *     call with a given shape allocates workspace (and may synchronise the stream
  *     to free a smaller one); later calls of cdgrab_pergrad and the balancing
  *     entry points with dense input enqueue kernels and device-to-device copies
  *     only, so they may be captured in a HIP graph.  A captured call takes its sums in the
- *     order of the eager one; rows of at most 64 elements and 512 pairs or more, if an epoch of that
- *     shape has run on the handle before (else, and where up to 64 MB of workspace
- *     find no room, in another order: the same result on exactly representable input, otherwise equal to
- *     double rounding).
+ *     order of the eager one.  (Rows of at most 64 elements, 512 pairs and more: if such an
+ *     epoch has run on the handle before.  Else, and where up to 64 MB of workspace find no
+ *     room, the order is another: the same result on exactly representable input, otherwise
+ *     equal to double rounding.)
  *   - Return value: CDGRAB_OK (0) or a negative error code.  After an error the
  *     contents of the outputs are undefined; cdgrab_last_error() gives a text.
  *   - Sizes are int64_t counts of elements, never bytes.
@@ -68,10 +70,12 @@ typedef struct cdgrab_options {
                             rows only) and the walk is a chain of steps of 64 .. 256 pairs
                             (chosen by sizes, whatever the block size) at two launches each,
                             or, for rows of at most 64 elements, one workgroup per walk
-                            in one launch (long walks: behind a launch that computes
-                            Gram results of up to 64 MB of pairs ahead); refused (EINVAL) for d > 131 072; 0 = choose (2 for rows up to
-                            65 536 elements and more pairs than one block, at 65 536 than
-                            128, when apply_mode is 0 as well; staged rows: up to 16 384)  */
+                            in one launch (up to sixteen walks, of at least 512 pairs and 32
+                            more per further walk: behind a launch that computes Gram results
+                            of up to 64 MB of pairs ahead); refused (EINVAL) for d > 131 072;
+                            0 = choose (2 for rows up to 65 536 elements and more pairs than
+                            one block, at 65 536 than 128, when apply_mode is 0 as well;
+                            staged rows: up to 16 384)  */
     int32_t apply_groups; /* cap on the workgroups of the resident apply kernel; 0 = two per CU */
 } cdgrab_options;
 
@@ -114,7 +118,8 @@ typedef struct cdgrab_plan {
                                 written once) or 8d + 8 d / Bb when fused; at most 12d + 8 d / Bb
                                 with the Gram matrices computed ahead (rows read three times,
                                 Gram tiles of 256 MB at a time), 4d for rows of at most 64
-                                elements then (read once)                              */
+                                elements then (read once; the 10 to 16 KB per 16 pairs of a long
+                                walk that the library writes and reads again are not counted) */
 } cdgrab_plan;
 
 /* Generator callback for streamed input ("grads-or-generator").  It must enqueue,
@@ -252,7 +257,10 @@ int cdgrab_balance_epoch_stale_mean(cdgrab_handle *h, int64_t n, int64_t d, cons
  * i.e. m separate runs of cdgrab_balance_epoch with m = 1.  For short rows (where such a
  * run is a chain of small dependent launches) the m walks run side by side, the worker as
  * a grid coordinate of every launch; for long rows one after the other.  Either way a
- * worker's result is that of its own one-worker epoch.  Same layouts as there:
+ * worker's result is that of its own one-worker epoch, but side by side the number of
+ * walks has a say in how launches are cut, so that sums may be taken in another order (the
+ * same result on exactly representable input; otherwise a dot that is zero to double
+ * rounding may decide otherwise).  Same layouts as there:
  *   grads [m][n][d] fp32 dev, perm_in [m][n] or NULL, signs_out [m][n/2], perm_out [m][n].
  * Errors: as cdgrab_balance_epoch. */
 int cdgrab_balance_epoch_independent(cdgrab_handle *h, int64_t m, int64_t n, int64_t d,
@@ -273,6 +281,9 @@ int cdgrab_balance_epoch_independent(cdgrab_handle *h, int64_t m, int64_t n, int
  *     visiting order (for verification; the epoch itself keeps only a few steps' rows),
  *   loss_out [m][n] fp32 dev or NULL: loss of each example when it was visited.
  *   perm_out must not overlap perm_in.
+ * Where the pairs are staged in several chunks of short rows, a chunk is balanced on the
+ * second stream while the next one's steps run.  With options.timing >= 1, and while the
+ * handle's stream is captured, everything runs on the one stream: same result, longer.
  * fp32 model arithmetic, double balancing arithmetic.
  * Errors: EINVAL (sizes, n odd, null, momentum without velocity, overlapping orders),
  * ENOMEM, EHIP. */

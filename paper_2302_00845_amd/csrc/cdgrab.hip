@@ -220,6 +220,11 @@ int pick_ksplit(int64_t tiles, int64_t d, int num_cu) {
 // pairs 3846 -> 2861 / 4814 -> 2925 / 7939 -> 4276.  The results of all walks go through memory: 16 walks of 512 pairs 19.7 -> 19.0 /
 // 20.5 -> 22.0 / 28.9 -> 30.4, of 768 24.8 -> 24.3 / 27.0 -> 27.4 / 39.9 -> 38.2, of 1024 29.8 -> 29.2 / 33.2 -> 32.6 / 49.7 ->
 // 45.0, of 4000 88 -> 82 / 107 -> 87 / 170 -> 128; 100 walks of 1000 30.6 -> 40.1 / - / 51 -> 95.
+// More than 16 walks, of 4000 and 25 000 pairs: 17 walks 88 -> 83 and 497 -> 473 / 107 -> 90 and 628 -> 525 / 169 -> 144 and 1016 ->
+// 826; 20 walks 88 -> 82 and 497 -> 484 / 107 -> 91 and 629 -> 555 / 170 -> 152 and 1015 -> 913; 24 walks 88 -> 84 and 498 -> 506 /
+// 107 -> 106 and 629 -> 586 / 170 -> 159 and 1018 -> 975; 32 walks 89 -> 99 and 500 -> 547 / 108 -> 114 and 629 -> 687 / 170 -> 167
+// and 1018 -> 1077; 64 walks 89 -> 122 and 501 -> 794 / 108 -> 151 and 632 -> 1031 / 172 -> 244 and 1025 -> 1610.  By these the line
+// could lie near 20 walks.
 constexpr int64_t kBandMinPairs = 512, kBandMinPairsMore = 32;  // of the only walk, per further walk
 constexpr int64_t kBandMaxWalks = 16;
 constexpr int64_t kBandBytes = (int64_t)64 << 20;  // Gram results and differences held at a time ...
@@ -1384,8 +1389,9 @@ int cdgrab_balance_epoch_independent(cdgrab_handle *h, int64_t m, int64_t n, int
         return fail(h, CDGRAB_EINVAL, "cdgrab_balance_epoch_independent: need even n >= 2, d >= 1");
     // Short rows (the Grams-ahead form): the m one-worker walks run side by side, the worker
     // as a grid coordinate, each on its own running sum -- every launch of the chain serves all
-    // workers.  Same kernels, same sums in the same order as a one-worker epoch.  (A worker's
-    // rows start n*d floats after the previous worker's: as aligned as the first worker's
+    // workers.  The sums are those of a one-worker epoch, perhaps in another order: the length of a step and the
+    // shares of a Gram tile go by the number of walks too, and with rows of at most kNarrowMaxD elements the form of
+    // the walk and the pairs of a launch.  (A worker's rows start n*d floats after the previous worker's: as aligned as the first worker's
     // whenever d suits the load width.)
     if (m > 1 && m <= 65535) {
         const uintptr_t a = reinterpret_cast<uintptr_t>(grads);
