@@ -196,3 +196,54 @@ def test_rows_read_beside_a_walk(call, m, n, d, beside):
     grids = [int(y) for name, _, y, _ in of(part, "launch") if "chain_walk" in name]
     assert len(grids) > 1 and grids[-1] == 1
     assert all((y > 8) == beside for y in grids[:-1])
+
+
+TRAIN = [(8, 900, 30, 4), (4, 1100, 7, 4), (4, 1500, 783, 3), (16, 260, 12, 5), (16, 1000, 784, 10)]
+
+
+def streams_of(calls):
+    return {s for name, _, _, s in of(calls, "launch")}
+
+
+def joined(calls, side):
+    """Does the first stream wait for an event behind the last launch on stream `side`?"""
+    last = max(i for i, c in enumerate(calls) if c[0] == "launch" and c[4] == side)
+    ends = [c[1] for c in calls[last:] if c[0] == "record" and c[2] == side]
+    return any(c[0] == "wait" and c[1] in ends and c[2] == "0" for c in calls[last:])
+
+
+@pytest.mark.parametrize("m,n,in_dim,classes", TRAIN)
+def test_training_chunks_go_to_a_second_stream(call, m, n, in_dim, classes):
+    """Several chunks, each balanced on the second stream behind its rows, its buffer filled again only behind that, and all
+    of it before what follows; with timing, or while launches are recorded, everything on the one stream."""
+    shape = "%d, %d, %d, %d" % (m, n, in_dim, classes)
+    parts = call("mark('beside')\nassert train(%s) == 0\n"
+                 "capture(1)\nmark('recorded')\nassert train(%s) == 0\ncapture(0)\n"
+                 "t = handle(timing=1)\nmark('timed')\nassert train(%s, t) == 0\n" % (shape, shape, shape))
+    assert streams_of(parts["recorded"]) == streams_of(parts["timed"]) == {"0"}
+    calls = parts["beside"]
+    side, = streams_of(calls) - {"0"}
+    walk = [c for c in calls if c[0] == "launch" and ("chain_walk" in c[1] or "narrow_walk" in c[1])]
+    assert all(c[4] == side for c in walk)
+    to_side, to_main = (sum(c[0] == "wait" and c[2] == s for c in calls) for s in (side, "0"))
+    assert to_side >= 2 and to_main == to_side - 2 + 1  # a wait per chunk; from the third chunk on for its buffer, and the end
+    assert joined(calls, side)
+
+
+@pytest.mark.parametrize("m,n,in_dim,classes", [(4, 1100, 7, 4), (16, 1000, 784, 10)])
+def test_streams_meet_again_where_a_launch_fails(call, m, n, in_dim, classes):
+    """Whichever launch fails: what has gone to the second stream is ordered before what follows the call on the first, and
+    the next call begins on the first."""
+    shape = "%d, %d, %d, %d" % (m, n, in_dim, classes)
+    total = sum(c[0] == "launch" for c in call("mark('all')\nassert train(%s) == 0\n" % shape)["all"])
+    tries = sorted({0, 1, total - 1, *range(0, total, max(1, total // 40))})
+    parts = call("".join("h%d = handle()\nmark('%d')\nfail_launch(%d)\nassert train(%s, h%d) in (-3, -4)\nmark('%d after')\n"
+                         "fail_launch(1 << 30)\nassert epoch(4, 64, 1024, h%d) == 0\n" % (k, k, k, shape, k, k, k) for k in tries))
+    on_side = 0
+    for k in tries:
+        calls = parts[str(k)]
+        for side in streams_of(calls) - {"0"}:
+            on_side += 1
+            assert joined(calls, side)
+        assert streams_of(parts["%d after" % k]) == {"0"}
+    assert on_side > 3

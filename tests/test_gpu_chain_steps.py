@@ -75,6 +75,70 @@ def test_more_narrow_pairs_than_are_held_at_a_time(lib, d):
     assert np.array_equal(out["r64"].cpu().numpy(), want["r"])
 
 
+def narrow_pairs_held(d, walks=1):
+    """Pairs of a walk per launch: 64 MB of Gram results, differences and draws, 16 pairs at a time, by eights."""
+    block = 8 * (16 * 64 + 16 * (16 if d <= 16 else 32 if d <= 32 else 64) + 8)
+    blocks = (64 << 20) // block // walks
+    return 16 * ((blocks + 7) // 8 * 8)
+
+
+def greedy_in_doubles(z):
+    """Signs, dots and running sum of one walk over pairs [m][n/2], by comparison: t <= 0 gives +1, no number -1."""
+    diff = (z[:, 1::2].astype(np.float64) - z[:, 0::2]).transpose(1, 0, 2).reshape(-1, z.shape[2])
+    r, eps, dots = np.zeros(z.shape[2]), np.empty(len(diff), np.int8), np.empty(len(diff))
+    with np.errstate(invalid="ignore"):
+        for q, dv in enumerate(diff):
+            dots[q] = r @ dv
+            eps[q] = 1 if dots[q] <= 0 else -1
+            r = r + eps[q] * dv
+    return eps, dots, r
+
+
+@pytest.mark.parametrize("d", [9, 30, 64])
+def test_narrow_launches_follow_each_other(lib, d):
+    """A launch begins at a pair of any worker: draws, signs and dots are where they belong, the running sum is handed on, also where
+    it holds what is not finite, and launches before that are not held up by it."""
+    m = 7
+    held = narrow_pairs_held(d)
+    n = 2 * (held // m + 300)
+    assert m * n // 2 > held and held % m
+    z = workloads.integer_rows(d, m, n, d, 2) * np.float32(2.0 ** -5)
+    zt = torch.from_numpy(z).cuda()
+    u = np.random.default_rng(d).random((m, n // 2), dtype=np.float32)
+    out = lib.cdgrab_balance_epoch_randomized(lib.Handle(), zt, torch.from_numpy(u).cuda())
+    want = oracle.randomized_epoch(z, u)
+    assert np.array_equal(out["signs"].cpu().numpy(), want["eps"]) and np.array_equal(out["dots"].cpu().numpy(), want["t"])
+    assert np.array_equal(out["r64"].cpu().numpy(), want["r"])
+    eps, dots, _ = greedy_in_doubles(z)
+    for at, value in ((held - 20, np.nan), (held - 20, np.inf), (held + 20, -np.inf), (held + 20, np.nan)):
+        w = z.copy()
+        w[at % m, 2 * (at // m) + 1, d // 2] = value
+        out = lib.cdgrab_balance_epoch(lib.Handle(), m, n, d, grads=torch.from_numpy(w).cuda(), want_r64=True, want_dots=True)
+        got, seen = (out[k].cpu().numpy().T.ravel() for k in ("signs", "dots"))
+        assert np.array_equal(got[:at], eps[:at]) and np.array_equal(seen[:at], dots[:at])
+        if np.isnan(value):
+            assert (got[at:] == -1).all() and np.isnan(seen[at:]).all()
+        # (an infinite pair's own dot may be infinite or no number: the shares of it that a block adds up are infinite already)
+        assert np.array_equal(got, np.where(seen <= 0, 1, -1))
+        diff = (w[:, 1::2].astype(np.float64) - w[:, 0::2]).transpose(1, 0, 2).reshape(-1, d)
+        assert np.array_equal(out["r64"].cpu().numpy(), (got[:, None] * diff).sum(0), equal_nan=True)
+    test_centred_steps_match_oracle(lib, held + 301, d)
+
+
+def test_narrow_launches_of_many_walks_follow_each_other(lib):
+    """Sixteen walks share the space; a value of one is no number in its first launch, of another in the second."""
+    m, d = 16, 50
+    held = narrow_pairs_held(d, m)
+    n = 2 * (held + 700)
+    z = workloads.integer_rows(4, m, n, d, 2)
+    want = [greedy_in_doubles(z[i:i + 1])[0] for i in range(m)]
+    z[3, 2 * 100, 7], z[12, 2 * held + 9, 20] = np.nan, np.nan
+    want[3][100:], want[12][held + 4:] = -1, -1
+    out = lib.cdgrab_balance_epoch_independent(lib.Handle(), torch.from_numpy(z).cuda())
+    for i in range(m):
+        assert np.array_equal(out["signs"][i].cpu().numpy(), want[i]), i
+
+
 def test_recorded_narrow_walk(lib):
     """Recorded launches use none of the workspace that a later, longer epoch replaces."""
     m, n, d = 2, 1200, 20
@@ -229,6 +293,17 @@ def test_walks_side_by_side_equal_single_walks(lib, m, n, d):
         want = oracle.server_epoch(z[i:i + 1], None)
         assert np.array_equal(out["signs"][i].cpu().numpy(), want["eps"][0])
         assert np.array_equal(out["perm"][i].cpu().numpy(), want["perm"][0])
+
+
+@pytest.mark.parametrize("m,n,d", [(3, 2000, 16), (16, 1200, 40), (20, 1200, 24), (5, 300, 200), (64, 200, 1000)])
+def test_walks_side_by_side_equal_single_walks_where_sums_are_rounded(lib, m, n, d):
+    """The order of the sums goes by the number of walks.  A sign would differ where a dot is zero to rounding, 1e-15 of its
+    size: none of these is."""
+    z = torch.randn((m, n, d), generator=torch.Generator(device="cuda").manual_seed(m + d), device="cuda")
+    out = lib.cdgrab_balance_epoch_independent(lib.Handle(), z)
+    for i in range(m):
+        one = lib.cdgrab_balance_epoch(lib.Handle(), 1, n, d, grads=z[i:i + 1].contiguous())
+        assert torch.equal(out["signs"][i], one["signs"][0]) and torch.equal(out["perm"][i], one["perm"][0])
 
 
 @pytest.mark.parametrize("m,n,d", [(3, 86, 30), (2, 300, 12_000), (1, 600, 20), (1, 1100, 70), (3, 86, 129)])

@@ -210,10 +210,11 @@ def test_argument_errors(lib):
         lib.cdgrab_train_softmax(h, X, y, W, perm, 0)                    # no epochs
 
 
-@pytest.mark.parametrize("m,n,in_dim,classes", [(8, 900, 30, 4), (4, 1100, 7, 4), (3, 1500, 783, 3), (16, 260, 12, 5)])
+@pytest.mark.parametrize("m,n,in_dim,classes", [(8, 900, 30, 4), (4, 1100, 7, 4), (3, 1500, 783, 3), (4, 1500, 783, 3), (16, 260, 12, 5)])
 def test_chunks_balanced_beside_the_next_one(lib, m, n, in_dim, classes):
-    """Two to four chunks, balanced on a second stream while the next is generated (chain of steps, and rows of at most
-    64 elements), against the same epochs with every launch on one stream, which is what a timed handle runs."""
+    """Two to four chunks (one with three workers), balanced on a second stream while the next is generated (chain of steps, and
+    rows of at most 64 elements), against the same epochs with every launch on one stream, which is what a timed handle runs.
+    tests/test_epoch_host.py counts the chunks."""
     g = torch.Generator(device="cuda").manual_seed(m + n)
     s = torch.cuda.Stream()
     with torch.cuda.stream(s):
