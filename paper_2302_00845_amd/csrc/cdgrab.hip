@@ -1022,7 +1022,7 @@ int Epoch::generate(int64_t first, int64_t count, float *stage_buf) {
 
 // A training epoch's chunks are generated by a chain of small launches (one workgroup solves the steps), and balanced by
 // another one, which needs the rows but not the other way round: while chunk k + 1 is generated, chunk k is balanced on a
-// second stream.  16 workers x 1000 steps of 784 -> 10: 3946 -> 3436 us (the training launches alone are
+// second stream.  16 workers x 1000 steps of 784 -> 10: 3948 -> 3462 us (the training launches alone are
 // 2750; the Gram launch of a chunk holds them up).  All of it is ordered before
 // whatever follows the call on the handle's stream, however the call ends.
 struct Beside {
