@@ -227,8 +227,8 @@ int pick_ksplit(int64_t tiles, int64_t d, int num_cu) {
 // could lie near 20 walks.
 constexpr int64_t kBandMinPairs = 512, kBandMinPairsMore = 32;  // of the only walk, per further walk
 constexpr int64_t kBandMaxWalks = 16;
-constexpr int64_t kBandBytes = (int64_t)64 << 20;  // Gram results and differences held at a time ...
-// ... at most, in doubles
+constexpr int64_t kBandBytes = (int64_t)64 << 20;  // Gram results and differences held at a time, but for whole strides of blocks
+// in doubles, with those: what no epoch exceeds
 constexpr int64_t kBandMost = kBandBytes / 8 + kBandMaxWalks * (kBandStride + 1) * band_doubles(kNarrowMaxD);
 int narrow_padded(int64_t d) { return d <= 16 ? 16 : d <= 32 ? 32 : 64; }
 
@@ -1391,8 +1391,8 @@ int cdgrab_balance_epoch_independent(cdgrab_handle *h, int64_t m, int64_t n, int
     // as a grid coordinate, each on its own running sum -- every launch of the chain serves all
     // workers.  The sums are those of a one-worker epoch, perhaps in another order: the length of a step and the
     // shares of a Gram tile go by the number of walks too, and with rows of at most kNarrowMaxD elements the form of
-    // the walk and the pairs of a launch.  (A worker's rows start n*d floats after the previous worker's: as aligned as the first worker's
-    // whenever d suits the load width.)
+    // the walk and the pairs of a launch.  (A worker's rows start n*d floats after the previous
+    // worker's: as aligned as the first worker's whenever d suits the load width.)
     if (m > 1 && m <= 65535) {
         const uintptr_t a = reinterpret_cast<uintptr_t>(grads);
         cdgrab_plan one{};
